@@ -3,7 +3,7 @@
 //   bf16: MFMA flash-style kernel, one workgroup per (block of query rows, kv head); the g = Hq/Hkv
 //         query heads that share a kv head are stacked into the same tile so K/V are streamed once
 //         for all of them.
-//   f32 : one wavefront per (row, head), online softmax (the small fp32 configuration).
+//   f32 : one workgroup per (row, head), online softmax (the small fp32 configuration).
 #include <hip/hip_runtime.h>
 
 #include "vlc_internal.h"
@@ -587,72 +587,108 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 }
 
 // ---------------------------------------------------------------------------------------------
-// f32 kernel: one wavefront per (row, head); lanes stride over keys with a private online softmax,
-// merged across lanes at the end.
+// f32 kernel: one workgroup per (row, head).  Keys in chunks of 512: a thread scores one key, the chunk's
+// probabilities meet in LDS, and the PV product runs with the lanes over d (whole value rows, coalesced), each
+// wavefront on its 64 keys of the chunk.  Bound by latency at the sizes of the fp32 configuration: 61 rows x 4 heads
+// over 304 keys take 8.5 us; one wavefront per (row, head) with the keys over its lanes, which walks five keys one
+// after the other and then adds 64 partial outputs by shuffles, took 23.5 us.
 // ---------------------------------------------------------------------------------------------
+constexpr int F32_WAVES = 8;        // 512 keys per chunk
+
 template <int D>
-__global__ __launch_bounds__(64) void attention_f32_kernel(const float* __restrict__ q, int64_t q_stride,
-                                                           const float* __restrict__ kc,
-                                                           const float* __restrict__ vc,
-                                                           const int32_t* __restrict__ row_kv_start,
-                                                           const int32_t* __restrict__ row_kv_len, int Hq,
-                                                           int Hkv, int g, float scale,
-                                                           float* __restrict__ out) {
-  __shared__ float sq[D];
-  const int row = blockIdx.x, head = blockIdx.y, lane = threadIdx.x;
+__global__ __launch_bounds__(64 * F32_WAVES) void attention_f32_kernel(const float* __restrict__ q, int64_t q_stride,
+                                                            const float* __restrict__ kc,
+                                                            const float* __restrict__ vc,
+                                                            const int32_t* __restrict__ row_kv_start,
+                                                            const int32_t* __restrict__ row_kv_len, int Hq,
+                                                            int Hkv, int g, float scale,
+                                                            float* __restrict__ out) {
+  constexpr int DL = D / 64;                       // output elements per lane
+  constexpr int UNROLL = 16;                       // value rows in flight
+  __shared__ __attribute__((aligned(16))) float sq[D];
+  __shared__ float sp[64 * F32_WAVES];                      // probabilities of the chunk
+  __shared__ float red_m[2][F32_WAVES];                  // chunk maxima of the wavefronts (two sets: one barrier per use)
+  __shared__ float red_l[F32_WAVES];
+  __shared__ float red_o[F32_WAVES][D];
+  const int row = blockIdx.x, head = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kvh = head / g;
   const float* qp = q + (int64_t)row * q_stride + (int64_t)head * D;
-  for (int d = lane; d < D; d += 64) sq[d] = qp[d] * scale;
-  __syncthreads();
+  if (tid < D) sq[tid] = qp[tid] * scale;
   const int len = row_kv_len[row];
   const int64_t start = row_kv_start[row];
   const int64_t kv_row = (int64_t)Hkv * D;
+  const float* kbase = kc + start * kv_row + (int64_t)kvh * D;
+  const float* vbase = vc + start * kv_row + (int64_t)kvh * D;
   float m = -INFINITY, l = 0.f;
-  float acc[D];
+  float acc[DL];
 #pragma unroll
-  for (int d = 0; d < D; ++d) acc[d] = 0.f;
-  for (int j = lane; j < len; j += 64) {
-    const float4* kp = reinterpret_cast<const float4*>(kc + (start + j) * kv_row + (int64_t)kvh * D);
-    float s = 0.f;
+  for (int e = 0; e < DL; ++e) acc[e] = 0.f;
+  __syncthreads();
+  for (int c0 = 0, it = 0; c0 < len; c0 += 64 * F32_WAVES, ++it) {
+    float s = -INFINITY;
+    if (c0 + tid < len) {
+      const float4* kp = reinterpret_cast<const float4*>(kbase + (int64_t)(c0 + tid) * kv_row);
+      s = 0.f;
 #pragma unroll
-    for (int c = 0; c < D / 4; ++c) {
-      const float4 kv = kp[c];
-      s = fmaf(kv.x, sq[4 * c], s);
-      s = fmaf(kv.y, sq[4 * c + 1], s);
-      s = fmaf(kv.z, sq[4 * c + 2], s);
-      s = fmaf(kv.w, sq[4 * c + 3], s);
+      for (int c = 0; c < D / 4; ++c) {
+        const float4 kv = kp[c];
+        const float4 qv = *reinterpret_cast<const float4*>(&sq[4 * c]);
+        s = fmaf(kv.x, qv.x, s);
+        s = fmaf(kv.y, qv.y, s);
+        s = fmaf(kv.z, qv.z, s);
+        s = fmaf(kv.w, qv.w, s);
+      }
     }
-    const float m_new = fmaxf(m, s);
-    const float alpha = expf(m - m_new);      // m = -inf on the first key -> 0
-    const float p = expf(s - m_new);
-    l = l * alpha + p;
-    const float4* vp = reinterpret_cast<const float4*>(vc + (start + j) * kv_row + (int64_t)kvh * D);
+    float mx = s;
 #pragma unroll
-    for (int c = 0; c < D / 4; ++c) {
-      const float4 vv = vp[c];
-      acc[4 * c] = acc[4 * c] * alpha + p * vv.x;
-      acc[4 * c + 1] = acc[4 * c + 1] * alpha + p * vv.y;
-      acc[4 * c + 2] = acc[4 * c + 2] * alpha + p * vv.z;
-      acc[4 * c + 3] = acc[4 * c + 3] * alpha + p * vv.w;
-    }
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    if (lane == 0) red_m[it & 1][wave] = mx;
+    __syncthreads();                               // also: the previous chunk's probabilities have been read
+    float m_new = m;
+#pragma unroll
+    for (int w = 0; w < F32_WAVES; ++w) m_new = fmaxf(m_new, red_m[it & 1][w]);
+    const float alpha = expf(m - m_new);           // m = -inf on the first chunk -> 0
+    const float p = expf(s - m_new);               // keys past the end: 0
     m = m_new;
+    l = l * alpha + p;
+    sp[tid] = p;
+#pragma unroll
+    for (int e = 0; e < DL; ++e) acc[e] *= alpha;
+    // a wavefront reads the probabilities it has written itself: no barrier, only the order of its LDS accesses
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int first = c0 + 64 * wave;
+    const int keys = min(64, len - first);
+    for (int j = 0; j < keys; j += UNROLL) {
+      float vv[UNROLL][DL];
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const float* vp = vbase + (int64_t)min(first + j + u, len - 1) * kv_row + DL * lane;
+#pragma unroll
+        for (int e = 0; e < DL; ++e) vv[u][e] = vp[e];
+      }
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const float pj = sp[64 * wave + j + u];    // 0 past the end
+#pragma unroll
+        for (int e = 0; e < DL; ++e) acc[e] = fmaf(pj, vv[u][e], acc[e]);
+      }
+    }
   }
-  // merge the 64 partial softmaxes
-  float m_all = m;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m_all = fmaxf(m_all, __shfl_xor(m_all, o));
-  const float w = (m == -INFINITY) ? 0.f : expf(m - m_all);
-  float l_all = l * w;
+  for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+  if (lane == 0) red_l[wave] = l;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) l_all += __shfl_xor(l_all, o);
-  const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;
-  float* op = out + ((int64_t)row * Hq + head) * D;
+  for (int e = 0; e < DL; ++e) red_o[wave][DL * lane + e] = acc[e];
+  __syncthreads();
+  if (tid < D) {
+    float lt = 0.f, o = 0.f;
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    float v = acc[d] * w;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (lane == (d & 63)) op[d] = v * inv;
+    for (int w = 0; w < F32_WAVES; ++w) {
+      lt += red_l[w];
+      o += red_o[w][tid];
+    }
+    out[((int64_t)row * Hq + head) * D + tid] = lt > 0.f ? o / lt : 0.f;
   }
 }
 
@@ -725,11 +761,11 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     if (n > 0x7fffffff || Hq > 65535) return fail(VLC_ERR_SHAPE, "attention(f32): grid too large");
     const dim3 grid((unsigned)n, (unsigned)Hq);
     if (D == 64)
-      hipLaunchKernelGGL(attention_f32_kernel<64>, grid, dim3(64), 0, st, (const float*)q, q_stride,
+      hipLaunchKernelGGL(attention_f32_kernel<64>, grid, dim3(64 * F32_WAVES), 0, st, (const float*)q, q_stride,
                          (const float*)k_cache, (const float*)v_cache, row_kv_start, row_kv_len, Hq, Hkv, g,
                          scale, (float*)out);
     else if (D == 128)
-      hipLaunchKernelGGL(attention_f32_kernel<128>, grid, dim3(64), 0, st, (const float*)q, q_stride,
+      hipLaunchKernelGGL(attention_f32_kernel<128>, grid, dim3(64 * F32_WAVES), 0, st, (const float*)q, q_stride,
                          (const float*)k_cache, (const float*)v_cache, row_kv_start, row_kv_len, Hq, Hkv, g,
                          scale, (float*)out);
     else

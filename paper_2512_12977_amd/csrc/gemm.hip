@@ -1,6 +1,6 @@
 // GEMMs of the recomputed rows: C[M,N] = epilogue(A[M,K] * W[N,K]^T), both operands K-contiguous.
 //   bf16: MFMA (v_mfma_f32_32x32x16_bf16), LDS-tiled, float accumulation.
-//   f32 : plain SIMT tile kernel (the small fp32 configuration).
+//   f32 : MFMA (v_mfma_f32_16x16x4_f32) from registers (the small fp32 configuration).
 // Epilogues: + bias, + residual (optionally gathered through a row map), SwiGLU of a gate|up pair.
 #include <hip/hip_runtime.h>
 
@@ -11,6 +11,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // a 16-byte chunk (native vector: stays in registers)
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
@@ -565,9 +566,19 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const float* __restric
 }
 
 // ---------------------------------------------------------------------------------------------
-// f32 SIMT kernel: 64 x 64 tile, 256 threads, 4 x 4 outputs per thread, k-tile 16
+// f32 kernel: v_mfma_f32_16x16x4_f32 (exact fp32 products and sums) on operands loaded straight into registers
 // ---------------------------------------------------------------------------------------------
-template <int EPI, bool GROUPED = false>
+// A wavefront owns MT x WT tiles of 16 x 16.  The W fragment is the MFMA "A" operand, so a lane ends up with four
+// consecutive output columns of one row.  Lane l loads 16 bytes of row l % 16 at k = 16 * step + 4 * (l / 16): element
+// e of all lanes is one k-slice of four for MFMA e (the order of k inside a step does not matter as long as both
+// operands use the same).  Nothing is staged through LDS: the fp32 configuration is small, its time is latency.
+//
+// KW = 4 (few output tiles): the four wavefronts of a workgroup share one 16 x 16 output tile (two W tiles for
+// SwiGLU) and take every fourth k-step each; their sums meet in LDS.  With 61 rows of the tiny decoder (K = 256 or
+// 512) a product is 64 ... 128 workgroups and 4 ... 5 us, one memory latency and the launch; 64 x 64 tiles on vector
+// instructions, 4 ... 8 workgroups walking k in 16-wide steps behind barriers, took 43 ... 98 us.
+// KW = 1 (enough tiles for the chip): 2 x 2 wavefronts, each with its own output tiles; up to 106 TFLOP/s (47 before).
+template <int MT, int NT, int WGM, int WGN, int KW, int EPI, bool GROUPED = false>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda,
                                                        const float* __restrict__ W, float* __restrict__ C,
                                                        int64_t ldc, int M, int N, int K,
@@ -577,70 +588,116 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
                                                        const GroupTile* __restrict__ gtab,
                                                        const int32_t* __restrict__ g_ntiles,
                                                        const int32_t* __restrict__ amap, int64_t w_stride) {
-  constexpr int T = 64, KB = 16;
-  constexpr int NW = (EPI == EPI_SWIGLU) ? 2 : 1;
-  __shared__ float As[KB][T + 1];
-  __shared__ float Ws[NW][KB][T + 1];
-  int m0 = blockIdx.y * T;
-  const int n0 = blockIdx.x * T;
-  if constexpr (GROUPED) {       // see gemm_bf16_kernel
-    if ((int)blockIdx.y >= *g_ntiles) return;
-    const GroupTile g = gtab[blockIdx.y];
-    m0 = g.m0;
-    M = g.m_end;
+  static_assert(WGM * WGN * KW == 4, "four wavefronts");
+  constexpr int WT = (EPI == EPI_SWIGLU) ? 2 * NT : NT;   // W tiles: gate tiles, then the up tiles of the same columns
+  constexpr int BM = WGM * MT * 16, BN = WGN * NT * 16;   // rows, output columns per workgroup
+  constexpr int U = KW > 1 ? 4 : 1;                       // k-steps loaded together
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, lk = lane >> 4;
+  const int kw = wave % KW, wm = wave / KW / WGN, wn = wave / KW % WGN;
+  int m0 = blockIdx.y * BM;
+  const int n0 = blockIdx.x * BN;
+  if constexpr (GROUPED) {       // see gemm_bf16_kernel; a 64-row entry of the table is 64 / BM workgroups here
+    constexpr int SUB = 64 / BM;
+    if ((int)blockIdx.y / SUB >= *g_ntiles) return;
+    const GroupTile g = gtab[blockIdx.y / SUB];
+    m0 = g.m0 + (int)(blockIdx.y % SUB) * BM;
+    M = min(g.m_end, g.m0 + 64);
+    if (m0 >= M) return;
     W += (int64_t)g.expert * w_stride;
   }
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[NW][4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += KB) {
-    for (int e = threadIdx.x; e < T * KB; e += 256) {
-      const int r = e / KB, kk = e % KB;
-      const int m = m0 + r, n = n0 + r, k = k0 + kk;
-      int64_t am = m;
-      if constexpr (GROUPED) {
-        if (amap && m < M) am = amap[m];
-      }
-      As[kk][r] = (m < M && k < K) ? A[am * lda + k] : 0.f;
-      Ws[0][kk][r] = (n < N && k < K) ? W[(int64_t)n * K + k] : 0.f;
-      if (EPI == EPI_SWIGLU) Ws[NW - 1][kk][r] = (n < N && k < K) ? W[(int64_t)(N + n) * K + k] : 0.f;
+  const float* ap[MT];
+  const float* wp[WT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int m = min(m0 + (wm * MT + i) * 16 + l16, M - 1);   // ragged edges: re-read the last row
+    int64_t row = m;
+    if constexpr (GROUPED) {
+      if (amap) row = amap[m];
     }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KB; ++kk) {
-      float a[4], w[NW][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int s = 0; s < NW; ++s)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) w[s][j] = Ws[s][kk][tx * 4 + j];
-#pragma unroll
-      for (int s = 0; s < NW; ++s)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[s][i][j] = fmaf(a[i], w[s][j], acc[s][i][j]);
-    }
-    __syncthreads();
+    ap[i] = A + row * lda + 4 * lk;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
+  for (int j = 0; j < WT; ++j) {
+    const int n = min(n0 + (wn * NT + j % NT) * 16 + l16, N - 1);
+    wp[j] = W + (int64_t)(j < NT ? n : N + n) * K + 4 * lk;
+  }
+  f32x4 acc[WT][MT];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float v = acc[0][i][j];
-      if (EPI == EPI_BIAS) {
-        if (bias) v += bias[n];
-      } else if (EPI == EPI_RESIDUAL) {
-        const int64_t rr = rmap ? (int64_t)rmap[m] : (int64_t)m;
-        v += resid[rr * ldr + n];
-      } else {
-        v = v / (1.0f + expf(-v)) * acc[NW - 1][i][j];
+  for (int j = 0; j < WT; ++j)
+#pragma unroll
+    for (int i = 0; i < MT; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int steps = K / 16;      // K is a multiple of 16
+  f32x4 ab[2][U][MT], wb[2][U][WT];
+  // a step past the end loads the last one again and is left out of the sum
+#define VLC_F32_LOAD(b_, s_)                                                                       \
+  _Pragma("unroll") for (int u = 0; u < U; ++u) {                                                   \
+    const int k_ = min((s_) + u * KW, steps - 1) * 16;                                              \
+    _Pragma("unroll") for (int i = 0; i < MT; ++i) ab[b_][u][i] = *reinterpret_cast<const f32x4*>(ap[i] + k_); \
+    _Pragma("unroll") for (int j = 0; j < WT; ++j) wb[b_][u][j] = *reinterpret_cast<const f32x4*>(wp[j] + k_); \
+  }
+#define VLC_F32_MULTIPLY(b_, s_)                                                                   \
+  _Pragma("unroll") for (int u = 0; u < U; ++u)                                                     \
+    if ((s_) + u * KW < steps) {                                                                    \
+      _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                 \
+        _Pragma("unroll") for (int j = 0; j < WT; ++j)                                              \
+          _Pragma("unroll") for (int i = 0; i < MT; ++i)                                            \
+            acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wb[b_][u][j][e], ab[b_][u][i][e], acc[j][i], 0, 0, 0); \
+    }
+  VLC_F32_LOAD(0, kw)
+  for (int s = kw; s < steps; s += 2 * U * KW) {
+    if (s + U * KW < steps) { VLC_F32_LOAD(1, s + U * KW) }
+    VLC_F32_MULTIPLY(0, s)
+    if (s + 2 * U * KW < steps) { VLC_F32_LOAD(0, s + 2 * U * KW) }
+    VLC_F32_MULTIPLY(1, s + U * KW)
+  }
+#undef VLC_F32_LOAD
+#undef VLC_F32_MULTIPLY
+
+  if constexpr (KW > 1) {        // the wavefronts' sums over their k-steps, added in wavefront order
+    __shared__ f32x4 part[KW - 1][WT * MT][64];
+    if (kw > 0) {
+#pragma unroll
+      for (int t = 0; t < WT * MT; ++t) part[kw - 1][t][lane] = acc[t / MT][t % MT];
+    }
+    __syncthreads();
+    if (kw > 0) return;
+#pragma unroll
+    for (int t = 0; t < WT * MT; ++t)
+#pragma unroll
+      for (int w = 0; w < KW - 1; ++w) acc[t / MT][t % MT] += part[w][t][lane];
+  }
+
+  const bool whole = N % 4 == 0 && ldc % 4 == 0;   // four columns of a row in one store
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int m = m0 + (wm * MT + i) * 16 + l16;
+    if (m >= M) continue;
+    const int64_t rr = (EPI == EPI_RESIDUAL && rmap) ? (int64_t)rmap[m] : (int64_t)m;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int n = n0 + (wn * NT + j) * 16 + 4 * lk;
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = acc[j][i][e];
+        if (EPI == EPI_BIAS) {
+          if (bias && n + e < N) v[e] += bias[n + e];
+        } else if (EPI == EPI_RESIDUAL) {
+          if (n + e < N) v[e] += resid[rr * ldr + n + e];
+        } else {
+          v[e] = v[e] / (1.0f + expf(-v[e])) * acc[(EPI == EPI_SWIGLU ? NT : 0) + j][i][e];
+        }
       }
-      C[(int64_t)m * ldc + n] = v;
+      float* c = C + (int64_t)m * ldc + n;
+      if (whole && n < N) {
+        *reinterpret_cast<float4*>(c) = make_float4(v[0], v[1], v[2], v[3]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n + e < N) c[e] = v[e];
+      }
     }
   }
 }
@@ -805,14 +862,28 @@ int dispatch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ld
   }
 }
 
+// Output tiles of 128 rows (grouped: 64) x 128 columns (SwiGLU: 64) from 96 of them on, else 16 x 16 tiles with the k
+// range shared by the workgroup's four wavefronts.  Large against small tiles, 128 rows: 64 tiles 38 / 34 us (K = 256)
+// and 161 / 131 us (K = 2048), 128 tiles 41 / 49 and 163 / 244 us (vector instructions: 67 and 407 us); with 2048 tiles
+// 106 against 37 TFLOP/s.
+constexpr int64_t kF32LargeTiles = 96;
+
 template <int EPI>
 int launch_f32(const void* A, int64_t lda, const void* W, void* C, int64_t ldc, int64_t M, int64_t N,
                int64_t K, const void* bias, const void* resid, int64_t ldr, const int32_t* rmap,
                hipStream_t st) {
-  const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-  hipLaunchKernelGGL(gemm_f32_kernel<EPI>, grid, dim3(256), 0, st, (const float*)A, lda, (const float*)W,
-                     (float*)C, ldc, (int)M, (int)N, (int)K, (const float*)bias, (const float*)resid, ldr,
-                     rmap, (const GroupTile*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr, (int64_t)0);
+  constexpr int NT = EPI == EPI_SWIGLU ? 2 : 4;
+  const int64_t lm = (M + 127) / 128, ln = (N + 32 * NT - 1) / (32 * NT);
+  const bool large = lm * ln >= kF32LargeTiles;
+  const int64_t gy = large ? lm : (M + 15) / 16;
+  const dim3 grid((unsigned)(large ? ln : (N + 15) / 16), (unsigned)gy);
+#define VLC_LAUNCH_F32(...)                                                                                        \
+  hipLaunchKernelGGL((gemm_f32_kernel<__VA_ARGS__, EPI>), grid, dim3(256), 0, st, (const float*)A, lda, (const float*)W, \
+                     (float*)C, ldc, (int)M, (int)N, (int)K, (const float*)bias, (const float*)resid, ldr, rmap,   \
+                     (const GroupTile*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr, (int64_t)0)
+  if (large) VLC_LAUNCH_F32(4, NT, 2, 2, 1);
+  else VLC_LAUNCH_F32(1, 1, 1, 1, 4);
+#undef VLC_LAUNCH_F32
   VLC_CHECK_LAUNCH("gemm_f32");
   return VLC_OK;
 }
@@ -840,10 +911,18 @@ template <int EPI>
 int launch_f32_grouped(const void* A, int64_t lda, const int32_t* amap, const void* W, int64_t w_stride, void* C,
                        int64_t ldc, int64_t N, int64_t K, const GroupTile* gtab, const int32_t* g_ntiles,
                        int max_tiles_m, hipStream_t st) {
-  const dim3 grid((unsigned)((N + 63) / 64), (unsigned)max_tiles_m);
-  hipLaunchKernelGGL((gemm_f32_kernel<EPI, true>), grid, dim3(256), 0, st, (const float*)A, lda, (const float*)W,
-                     (float*)C, ldc, 0, (int)N, (int)K, (const float*)nullptr, (const float*)nullptr, (int64_t)0,
-                     (const int32_t*)nullptr, gtab, g_ntiles, amap, w_stride);
+  constexpr int NT = EPI == EPI_SWIGLU ? 2 : 4;
+  const int64_t ln = (N + 32 * NT - 1) / (32 * NT);
+  const bool large = max_tiles_m * ln >= kF32LargeTiles;
+  const int64_t gy = large ? max_tiles_m : (int64_t)max_tiles_m * 4;
+  const dim3 grid((unsigned)(large ? ln : (N + 15) / 16), (unsigned)gy);
+#define VLC_LAUNCH_F32(...)                                                                                       \
+  hipLaunchKernelGGL((gemm_f32_kernel<__VA_ARGS__, EPI, true>), grid, dim3(256), 0, st, (const float*)A, lda,     \
+                     (const float*)W, (float*)C, ldc, 0, (int)N, (int)K, (const float*)nullptr,                  \
+                     (const float*)nullptr, (int64_t)0, (const int32_t*)nullptr, gtab, g_ntiles, amap, w_stride)
+  if (large) VLC_LAUNCH_F32(2, NT, 2, 2, 1);
+  else VLC_LAUNCH_F32(1, 1, 1, 1, 4);
+#undef VLC_LAUNCH_F32
   VLC_CHECK_LAUNCH("gemm_f32_grouped");
   return VLC_OK;
 }
@@ -902,6 +981,7 @@ int launch_gemm_grouped(const void* A, int64_t lda, const int32_t* amap, const v
     return launch_bf16_grouped<128, 128, 2, 2, 2, 2, EPI_BIAS>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
   }
   if (dtype == VLC_F32) {
+    if (K % 16) return fail(VLC_ERR_SHAPE, "grouped gemm(f32): K=%lld must be a multiple of 16", (long long)K);
     if (epilogue == EPI_SWIGLU)
       return launch_f32_grouped<EPI_SWIGLU>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
     return launch_f32_grouped<EPI_BIAS>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
@@ -933,6 +1013,7 @@ int launch_gemm(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
       case EPI_SWIGLU: return dispatch_bf16<EPI_SWIGLU>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, splitk_ws, splitk_ws_bytes, deferred, st);
     }
   } else if (dtype == VLC_F32) {
+    if (K % 16) return fail(VLC_ERR_SHAPE, "gemm(f32): K=%lld must be a multiple of 16", (long long)K);
     switch (epilogue) {
       case EPI_BIAS:
       case EPI_BIAS_F32: return launch_f32<EPI_BIAS>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, st);

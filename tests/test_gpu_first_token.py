@@ -122,3 +122,15 @@ def test_first_token_full_vocabulary_7b():
     rows = [39, 0, 7, 13, 21, 22, 30, 38]
     print("first-token head 7b: oracle in slabs of 16384 output rows", flush=True)
     check(h, rows, Wh, shape)
+
+
+@pytest.mark.parametrize("n_req,vocab,H", [(1, 4, 64), (15, 20, 64), (16, 16, 128), (17, 132, 320), (61, 512, 1024),
+                                           (128, 16384, 64), (128, 32768, 64), (129, 16388, 192), (255, 16384, 64)])
+def test_first_token_f32_around_the_tile_edges(n_req, vocab, H):
+    """fp32 products around the edges of both tilings: 16 x 16 outputs with the k range shared by four wavefronts (K from
+    one k-step per wavefront on) and, from 256 tiles of 128 x 128 on, wavefronts of 64 x 64."""
+    import dataclasses
+    shape = dataclasses.replace(syn.SHAPES["tiny"], H=H, vocab=vocab)
+    Wh = syn.head_weights(shape, 900 + n_req)
+    h = np.random.default_rng(901 + vocab).standard_normal((n_req, H)).astype(np.float32)
+    check(h, list(range(n_req)), Wh, shape)

@@ -279,6 +279,13 @@ def test_attention_unsorted_lengths_and_one_row(dtype):
     attention_case(dtype, 4, 2, D, [(65, [64])], seed=4)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_attention_f32_around_the_key_chunks(D):
+    """Key counts around a wavefront's 64 keys and the workgroup's chunk of 512, up to several chunks."""
+    slots = [-1, 0, 15, 16, 62, 63, 64, 126, 127, 128, 447, 448, 510, 511, 512, 513, 575, 576, 1022, 1023, 1024, 1299]
+    attention_case("f32", 6, 2, D, [(1300, slots)], seed=31 + D)
+
+
 def test_attention_long_context_bf16():
     """7B head layout, S = 4500: rows at the start of each 'image' and a trailing text run."""
     S = 4500

@@ -325,3 +325,14 @@ def test_q3_8b_shape_layer_stage_by_stage():
     wl = syn.make_workload("c2_q3")
     dev, floor = check_layer_stage_by_stage(wl, 0)
     print("c2_q3 layer 0: |gpu-oracle|/|oracle| = %.2e, bf16 noise floor %.2e" % (dev, floor))
+
+
+@pytest.mark.parametrize("rows,H,I", [(2049, 2048, 1024), (130, 320, 2048)])
+def test_f32_layer_with_enough_tiles_for_the_chip(rows, H, I):
+    """fp32 layers whose products fill the chip with 128-row tiles (residual and SwiGLU epilogues; the last row tile
+    holds one row) and one below that, stage by stage."""
+    import dataclasses
+    sh = dataclasses.replace(syn.SHAPES["tiny_bias"], L=1, H=H, I=I)
+    req = syn.Request([syn.Segment(0, rows - 16, False), syn.Segment(rows - 16, 16, True, 3, 0)], 0)
+    wl = syn.Workload("f32_rows_%d" % rows, sh, [req], 16, "static", static_k=500, seed=77)
+    check_against_oracle(wl, layers=1, teacher_forced=False)
