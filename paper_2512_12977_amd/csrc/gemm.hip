@@ -135,7 +135,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
   constexpr int KS = BK / 16;
   // columns of C covered by this tile: SwiGLU consumes a gate and an up row per output column
   constexpr int CN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
-  static_assert(STAGES >= 2 && STAGES <= 4, "ring depth");
+  static_assert(STAGES >= 2 && STAGES <= 6, "ring depth");
   // SwiGLU pairs a gate and an up column inside a lane.  Even NT: the wavefront's first NT/2 tiles are gate columns,
   // the others the up columns of the same outputs.  Odd NT (MIXED): FT = NT/2 such pairs of tiles, then one tile
   // whose columns 0-15 are gate and 16-31 up columns of 16 more outputs (registers j and j + 8 of a lane).
@@ -246,23 +246,18 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
         VLC_LDS_DST(stage_, i_))
 #define VLC_ISSUE(kt_, stage_) _Pragma("unroll") for (int i = 0; i < LOADS; ++i) VLC_DMA(kt_, i, stage_);
 
-  // fragment positions inside a stage (chunk units) for every 16-wide k-step
-  int w_off[NT][KS], a_off[MT][KS];
+  // Fragment positions inside a stage (chunk units) for every 16-wide k-step: one address per operand and k-step, the
+  // tiles of a wavefront are whole multiples of 32 rows apart (the swizzle repeats every 16 rows) and sit in the
+  // immediate offset of the read.
+  constexpr int WR = (EPI == EPI_SWIGLU && !MIXED) ? WN / 2 : WN;
+  static_assert(WR % 32 == 0 && WM % 32 == 0, "wavefront tiles start at multiples of 32 rows");
+  auto w_row = [](int nt) { return (EPI == EPI_SWIGLU && !MIXED && nt >= NT / 2) ? BN / 2 + (nt - NT / 2) * 32 : nt * 32; };
+  int w_off[KS], a_off[KS];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    int r;
-    if constexpr (EPI == EPI_SWIGLU && !MIXED)
-      r = (nt < NT / 2 ? wn * (WN / 2) + nt * 32 : BN / 2 + wn * (WN / 2) + (nt - NT / 2) * 32) + l32;
-    else
-      r = wn * WN + nt * 32 + l32;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) w_off[nt][ks] = BM * 8 + r * 8 + ((2 * ks + x) ^ fswz(r));
-  }
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const int r = wm * WM + mt * 32 + l32;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) a_off[mt][ks] = r * 8 + ((2 * ks + x) ^ fswz(r));
+  for (int ks = 0; ks < KS; ++ks) {
+    const int c = (2 * ks + x) ^ fswz(l32);
+    w_off[ks] = BM * 8 + (wn * WR + l32) * 8 + c;
+    a_off[ks] = (wm * WM + l32) * 8 + c;
   }
 
   f32x16 acc[NT][MT];
@@ -273,33 +268,45 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // One k-tile: KS k-steps of G groups of four MFMAs.  WITH_LOADS: the loads of k-tile nkt_ (into
-  // stage nst_) are issued in the first half of the groups.
-  constexpr int MPG = (NT * MT) % 4 == 0 ? 4 : 2;   // MFMAs per group
+  // One k-tile: KS k-steps of G groups of MFMAs, the next k-step's fragment reads spread over the groups.  The barrier
+  // stands before the LAST k-step: at that point every wavefront holds the fragments of that k-step already, so the
+  // tile's stage is free and is refilled from there on, and the next k-tile (whose loads every wavefront has waited
+  // for) can be read: its first fragments arrive under the last k-step's MFMAs.  With the barrier at the end of the
+  // k-tile the MFMAs idle for one LDS latency per k-tile, and the loads have half a k-tile less to arrive in.
+  constexpr int MPG = (NT * MT) % 4 == 0 ? 4 : (NT * MT) % 2 == 0 ? 2 : 1;   // MFMAs per group
   constexpr int G = NT * MT / MPG;             // groups per k-step
-  constexpr int TG = KS * G;                   // groups per k-tile
   constexpr int NF = NT + MT;                  // fragments per k-step
+  constexpr int LG = 2 * G;                    // groups that issue loads: the last k-step's and the next tile's first
   static_assert(NT * MT % MPG == 0, "wavefront tile must hold whole groups of MFMA tiles");
-#define VLC_COMPUTE_TILE(cst_, WITH_LOADS, nkt_, nst_)                                                        \
+  bf16x8 wf[2][NT], af[2][MT];
+#define VLC_READ_FRAGS(st_, ks_, buf_, g_)                                                                    \
+  _Pragma("unroll") for (int f = 0; f < NF; ++f) {                                                            \
+    if ((g_) < 0 || f * G / NF == (g_)) {                                                                     \
+      if (f < NT) wf[buf_][f < NT ? f : 0] = __builtin_bit_cast(bf16x8, VLC_GEMM_FRAG((st_)[w_off[ks_] + w_row(f < NT ? f : 0) * 8])); \
+      else af[buf_][f >= NT ? f - NT : 0] = __builtin_bit_cast(bf16x8, VLC_GEMM_FRAG((st_)[a_off[ks_] + (f >= NT ? f - NT : 0) * 256])); \
+    }                                                                                                         \
+  }
+  // cst_ / nst_: stages of this and the next k-tile.  FIRST_: the second half of the loads of k-tile lkt0_ into stage
+  // lst0_ (the previous tile's stage); LAST_: the first half of those of k-tile lkt1_ into this tile's stage; WAIT_: the
+  // wait that leaves only the loads of the tiles after the next one in flight; NEXT_: there is a next tile.
+#define VLC_COMPUTE_TILE(cst_, nst_, FIRST_, lkt0_, lst0_, LAST_, lkt1_, NEXT_, WAIT_)                        \
   {                                                                                                           \
     const u32x4* st_ = lds + (cst_) * STAGE_CHUNKS;                                                           \
-    bf16x8 wf[2][NT], af[2][MT];                                                                              \
-    _Pragma("unroll") for (int nt = 0; nt < NT; ++nt) wf[0][nt] = __builtin_bit_cast(bf16x8, VLC_GEMM_FRAG(st_[w_off[nt][0]])); \
-    _Pragma("unroll") for (int mt = 0; mt < MT; ++mt) af[0][mt] = __builtin_bit_cast(bf16x8, VLC_GEMM_FRAG(st_[a_off[mt][0]])); \
+    const u32x4* sn_ = lds + (nst_) * STAGE_CHUNKS;                                                           \
     _Pragma("unroll") for (int ks = 0; ks < KS; ++ks) {                                                       \
+      if (ks == KS - 1 && (NEXT_)) {                                                                          \
+        WAIT_;                                                                                                \
+        __syncthreads();                                                                                      \
+      }                                                                                                       \
       _Pragma("unroll") for (int g = 0; g < G; ++g) {                                                         \
-        if (WITH_LOADS) {                                                                                     \
-          _Pragma("unroll") for (int i = 0; i < LOADS; ++i)                                                   \
-            if (i * (TG / 2) / LOADS == ks * G + g) VLC_DMA(nkt_, i, nst_);                                    \
+        if (ks == 0 && (FIRST_)) {                                                                            \
+          _Pragma("unroll") for (int i = 0; i < LOADS; ++i) if (i * LG / LOADS == G + g) VLC_DMA(lkt0_, i, lst0_); \
         }                                                                                                     \
-        if (ks + 1 < KS) {                                                                                    \
-          _Pragma("unroll") for (int f = 0; f < NF; ++f) {                                                    \
-            if (f * G / NF == g) {                                                                            \
-              if (f < NT) wf[(ks + 1) & 1][f < NT ? f : 0] = __builtin_bit_cast(bf16x8, VLC_GEMM_FRAG(st_[w_off[f < NT ? f : 0][ks + 1]])); \
-              else af[(ks + 1) & 1][f >= NT ? f - NT : 0] = __builtin_bit_cast(bf16x8, VLC_GEMM_FRAG(st_[a_off[f >= NT ? f - NT : 0][ks + 1]])); \
-            }                                                                                                 \
-          }                                                                                                   \
+        if (ks == KS - 1 && (LAST_)) {                                                                        \
+          _Pragma("unroll") for (int i = 0; i < LOADS; ++i) if (i * LG / LOADS == g) VLC_DMA(lkt1_, i, cst_);   \
         }                                                                                                     \
+        if (ks + 1 < KS) { VLC_READ_FRAGS(st_, ks + 1 < KS ? ks + 1 : 0, (ks + 1) & 1, g) }                    \
+        else if (NEXT_) { VLC_READ_FRAGS(sn_, 0, 0, g) }                                                       \
         __builtin_amdgcn_sched_barrier(0);                                                                    \
         _Pragma("unroll") for (int j = 0; j < MPG; ++j) {                                                     \
           const int t_ = g * MPG + j;                                                                         \
@@ -339,34 +346,42 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
 #else
 #define VLC_GEMM_FRAG(x_) (x_)
 #endif
-  // prologue: fill STAGES-1 stages
+  // prologue: fill every stage, read the first fragments
 #pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
+  for (int s = 0; s < STAGES; ++s)
     if (s < KT) { VLC_ISSUE(s, s) }
+  if (KT >= STAGES) { VLC_WAITCNT_VM((STAGES - 1) * LOADS); } else { VLC_WAITCNT_VM(0); }
+  __syncthreads();
+  VLC_READ_FRAGS(lds, 0, 0, -1)
   int kt = 0;
+  // steady state: while k-tile kt is consumed, the loads of kt + STAGES - 1 are completed and those of kt + STAGES begun
+  // (the first tile's FIRST_ loads are part of the prologue: kt > 0 is the same for the whole grid)
   if constexpr (STAGES == 2) {
     // two k-tiles per trip, so that the stage every fragment address refers to is a constant of the code
     // and the addresses of both stages stay in registers (no address arithmetic inside the loop)
-    for (; kt + 2 < KT; kt += 2) {
-      VLC_WAITCNT_VM(0);
-      __syncthreads();
-      VLC_COMPUTE_TILE(0, true, kt + 1, 1)
-      VLC_WAITCNT_VM(0);
-      __syncthreads();
-      VLC_COMPUTE_TILE(1, true, kt + 2, 0)
+    if (KT > 2) {
+      VLC_COMPUTE_TILE(0, 1, false, 0, 0, true, 2, true, VLC_WAITCNT_VM(0))
+      for (kt = 1; kt + 3 < KT; kt += 2) {
+        VLC_COMPUTE_TILE(1, 0, true, kt + 1, 0, true, kt + 2, true, VLC_WAITCNT_VM(0))
+        VLC_COMPUTE_TILE(0, 1, true, kt + 2, 1, true, kt + 3, true, VLC_WAITCNT_VM(0))
+      }
+      if (kt + 2 < KT) {
+        VLC_COMPUTE_TILE(1, 0, true, kt + 1, 0, true, kt + 2, true, VLC_WAITCNT_VM(0))
+        ++kt;
+      }
     }
-  }
-  for (; kt + STAGES - 1 < KT; ++kt) {   // steady state: k-tile kt+STAGES-1 is fetched while kt is consumed
-    VLC_WAITCNT_VM((STAGES - 2) * LOADS);          // this wavefront's part of k-tile kt has landed
-    __syncthreads();                               // everyone's part has; stage (kt-1)%STAGES is free
-    VLC_COMPUTE_TILE(kt % STAGES, true, kt + STAGES - 1, (kt + STAGES - 1) % STAGES)
+  } else {
+    for (; kt + STAGES < KT; ++kt)
+      VLC_COMPUTE_TILE(kt % STAGES, (kt + 1) % STAGES, kt > 0, kt + STAGES - 1, (kt + STAGES - 1) % STAGES, true,
+                       kt + STAGES, true, VLC_WAITCNT_VM((STAGES - 2) * LOADS))
   }
   for (; kt < KT; ++kt) {                // drain
-    const int later = KT - 1 - kt;
-    if (later >= 2) { VLC_WAITCNT_VM(2 * LOADS); } else if (later == 1) { VLC_WAITCNT_VM(LOADS); } else { VLC_WAITCNT_VM(0); }
-    __syncthreads();
-    VLC_COMPUTE_TILE(kt % STAGES, false, 0, 0)
+    const bool first = kt > 0 && kt + STAGES - 1 < KT;
+    const int later = min(KT - 2 - kt, STAGES - 2);   // tiles after the next one still in flight
+    VLC_COMPUTE_TILE(kt % STAGES, (kt + 1) % STAGES, first, kt + STAGES - 1, (kt + STAGES - 1) % STAGES, false, 0, kt + 1 < KT,
+                     { if (later >= 4) { VLC_WAITCNT_VM(4 * LOADS); } else if (later == 3) { VLC_WAITCNT_VM(3 * LOADS); } else if (later == 2) { VLC_WAITCNT_VM(2 * LOADS); } else if (later == 1) { VLC_WAITCNT_VM(LOADS); } else { VLC_WAITCNT_VM(0); } })
   }
+#undef VLC_READ_FRAGS
 #undef VLC_ISSUE
 #undef VLC_DMA
 #undef VLC_LDS_DST
@@ -750,116 +765,133 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
   return VLC_OK;
 }
 
-// Tile choice.  Many rows: 256 x 256 tiles, 4 wavefronts of 128 x 128 or 8 of 64 x 128.  Few rows: two workgroups per CU, on
-// 128 x 192 tiles for gate|up (4 wavefronts of 64 x 96: 32 gate, 32 up and a mixed tile of 16 + 16 columns, so that
-// each holds the gate and the up columns of its 48 outputs), and on 128 x 128 (4 wavefronts of 64 x 64) or 128 x 192
-// tiles (4 of 64 x 96) for the others, whose k range is split as well if the tiles still leave most of the 256 CUs idle.
+// Tile choice.  Every configuration runs its k-loop at 1.1 ... 1.35 PFLOP/s when the chip is full of its workgroups, so
+// what decides is how well the product's tiles fill whole rounds of the 256 CUs and how much of them is padding; with few
+// rows, how many bytes of W are in flight.  The list therefore spans the tile areas from 64 x 128 to 256 x 256, each
+// with the deepest ring that fits the LDS (one workgroup per CU: an HBM miss takes longer than one k-tile, so a two-stage
+// ring cannot run a k-tile in under 1 us however small it is), and the cheapest by the model below is launched.
+//
+// Per configuration: time of one k-tile (us) with few workgroups on the chip and with all CUs busy (shared bandwidth,
+// power), measured over 33 ... 930 rows at three decoder shapes.
+//     BM   BN  WGM WGN STAGES OCC  light  full
+#define VLC_GEMM_TILES(X)                \
+  X(64, 128, 1, 4, 6, 1, 0.45f, 0.50f)   \
+  X(64, 192, 2, 2, 5, 1, 0.60f, 0.65f)   \
+  X(128, 128, 2, 2, 4, 1, 0.46f, 0.50f)  \
+  X(128, 160, 4, 1, 4, 1, 0.57f, 0.68f)  \
+  X(128, 192, 2, 2, 3, 1, 0.58f, 0.70f)  \
+  X(128, 256, 2, 2, 3, 1, 0.72f, 0.92f)  \
+  X(192, 128, 2, 2, 4, 1, 0.55f, 0.68f)  \
+  X(192, 192, 2, 2, 3, 1, 0.75f, 0.95f)  \
+  X(160, 256, 1, 4, 3, 1, 0.80f, 1.07f)  \
+  X(192, 256, 2, 2, 2, 1, 1.07f, 1.28f)  \
+  X(320, 192, 2, 2, 2, 1, 1.02f, 1.48f)  \
+  X(256, 256, 4, 2, 2, 1, 1.15f, 1.62f)  \
+  X(128, 160, 4, 1, 2, 2, 0.77f, 1.15f)  \
+  X(128, 192, 2, 2, 2, 2, 0.81f, 1.30f)
+
+struct TileChoice {
+  int index;        // into VLC_GEMM_TILES
+  int splits;       // k ranges (> 1: float partials)
+  bool split_tail;  // share the last round's tiles out along k
+};
+
+// Cost model (us): rounds of resident workgroups, each its k-tiles plus a start and an end; the weights can arrive no
+// faster than HBM delivers; the partials of a split k range are read back by the kernel that sums them, the blocks of a
+// split last round by tail_reduce_kernel.
+TileChoice choose_tile(int64_t M, int64_t N, int64_t K, bool swiglu, bool may_split, int64_t ws_bytes) {
+  struct Tile { int bm, bn, occ; float light, full; };
+#define X(BM, BN, WGM, WGN, S, OCC, L, F) {BM, BN, OCC, L, F},
+  static constexpr Tile kTiles[] = {VLC_GEMM_TILES(X)};
+#undef X
+  constexpr int kCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
+  const int KT = (int)(K / BK);
+  const float weight_us = (float)(swiglu ? 2 * N : N) * (float)K * 2.0f / 5.67e6f;
+  TileChoice best = {0, 1, false};
+  float best_us = 0.f;
+  for (int i = 0; i < kCount; ++i) {
+    const Tile& t = kTiles[i];
+    const int cn = swiglu ? t.bn / 2 : t.bn;
+    const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + cn - 1) / cn);
+    const int64_t slots = 256 * t.occ;
+    const float area = (float)(t.bm * t.bn), ends = 2.5f + 2.5f * (float)t.occ * area / 65536.0f;
+    auto round_us = [&](int64_t wgs, int kt) {   // one round of wgs <= slots workgroups of kt k-tiles
+      return (float)kt * (t.light + (t.full - t.light) * (float)wgs / (float)slots) + ends;
+    };
+    for (int sp = 1; sp <= (may_split ? 8 : 1); ++sp) {
+      if (sp > 1 && (KT / sp < 4 || (int64_t)sp * M * N * 4 > ws_bytes)) break;
+      const int per = (KT + sp - 1) / sp;
+      const int64_t wgs = tiles * ((KT + per - 1) / per), full = wgs / slots, tail = wgs % slots;
+      float us = (float)full * round_us(slots, per);
+      bool split_tail = false;
+      if (tail > 0) {
+        float tail_us = round_us(tail, per);
+        if (sp == 1 && full > 0) {
+          int64_t tsp = slots / tail < KT / 8 ? slots / tail : KT / 8;
+          const int64_t fit = ws_bytes / (tail * (int64_t)(area * 4.0f));
+          if (tsp > fit) tsp = fit;
+          if (tsp >= 2) {
+            const float shared = round_us(tail * tsp, (int)((KT + tsp - 1) / tsp)) + 5.0f + (float)(tail * tsp) * area * 1.6e-6f;
+            if (shared < tail_us) {
+              tail_us = shared;
+              split_tail = true;
+            }
+          }
+        }
+        us += tail_us;
+      }
+      us = (us < weight_us ? weight_us : us) + 0.05f * us;   // among those that HBM holds up: the cheaper k-loop
+      if (sp > 1) us += 2.5f + (float)sp * (float)M * (float)N * 1.0e-6f;
+      if ((i == 0 && sp == 1) || us < best_us) {
+        best_us = us;
+        best = {i, sp, split_tail};
+      }
+    }
+  }
+  return best;
+}
+
 template <int EPI>
 int dispatch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc, int64_t M, int64_t N,
                   int64_t K, const void* bias, const void* resid, int64_t ldr, const int32_t* rmap,
                   void* splitk_ws, int64_t splitk_ws_bytes, int* deferred, hipStream_t st) {
   const int KT = (int)(K / BK);
-  // 256 x 256 tiles (one workgroup per CU) against the small tiles (two per CU).
-  bool big;
-  if constexpr (EPI == EPI_SWIGLU) {
-    // Both in rounds of resident workgroups, the last round shortened by the tail split as launch_bf16 does it.
-    // A round of 256 x 256 tiles takes 1.09 rounds of 128 x 192 tiles (measured rates 1.26 and 1.03 PFLOP/s with
-    // thousands of tiles); its workgroups have nobody beside them on the CU to cover their start, their end and the
-    // float blocks of a split tile, which with few rounds costs about a quarter round per launch and a fifth per
-    // split tail (fitted on 596 ... 1600 rows at three shapes: the small tile wins up to about 1000 rows).
-    auto rounds = [KT](int64_t tiles, int slots, float split_cost) {
-      const int64_t full = tiles / slots, tail = tiles % slots;
-      float r = (float)full;
-      if (tail > 0) {
-        const int64_t tsp = full > 0 ? (slots / tail < KT / 8 ? slots / tail : KT / 8) : 1;
-        r += tsp >= 2 ? 1.0f / (float)tsp + split_cost : 1.0f;
+  const bool may_split = EPI != EPI_SWIGLU && splitk_ws;
+  const TileChoice c = choose_tile(M, N, K, EPI == EPI_SWIGLU, may_split, splitk_ws ? splitk_ws_bytes : 0);
+  if (c.splits > 1) {
+    if constexpr (EPI != EPI_SWIGLU) {
+      const int per = (KT + c.splits - 1) / c.splits, splits = (KT + per - 1) / per;
+      int rc = VLC_OK, i = 0;
+#define X(BM, BN, WGM, WGN, S, OCC, L, F)                                                                         \
+  if (c.index == i++)                                                                                             \
+    rc = launch_bf16<BM, BN, WGM, WGN, S, OCC, EPI_PARTIAL>(A, lda, W, splitk_ws, N, M, N, K, nullptr, nullptr, 0, \
+                                                            nullptr, splits, per, nullptr, 0, st);
+      VLC_GEMM_TILES(X)
+#undef X
+      if (rc) return rc;
+      if (deferred) {   // the caller's next kernel sums the partials and applies the epilogue
+        *deferred = splits;
+        return VLC_OK;
       }
-      return r;
-    };
-    const int64_t tiles_big = ((M + 255) / 256) * ((N + 127) / 128), tiles_small = ((M + 127) / 128) * ((N + 95) / 96);
-    big = 1.09f * rounds(tiles_big, 256, 0.2f) + 0.25f < rounds(tiles_small, 512, 0.1f);
-  } else {
-    // with few output columns (the o, down and qkv products) there are not enough 256 x 256 tiles for the 256 CUs
-    // until several thousand rows: the small tiles with a split k range stay ahead
-    big = M >= 1536 && ((M + 255) / 256) * ((N + 255) / 256) >= 200;
-  }
-  if (big) {
-    // gate|up: 4 wavefronts of 128 x 128; the others: 8 wavefronts of 64 x 128 (no spilled registers around the
-    // loop; the projection with float output gains 8 %, gate|up would lose 2 %)
-    if constexpr (EPI == EPI_SWIGLU)
-      return launch_bf16<256, 256, 2, 2, 2, 1, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT,
-                                                    splitk_ws, splitk_ws_bytes, st);
-    else
-      return launch_bf16<256, 256, 4, 2, 2, 1, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT,
-                                                    splitk_ws, splitk_ws_bytes, st);
-  }
-  if constexpr (EPI == EPI_SWIGLU) {
-    return launch_bf16<128, 192, 2, 2, 2, 2, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT, splitk_ws,
-                                                  splitk_ws_bytes, st);
-  } else {
-    // Tile width (128 or 192 columns) and number of k ranges, by cost in units of one 128 x 128 workgroup's
-    // k-tile (~1.2 us; 1.35 of them for a 128 x 192 k-tile): (rounds of the 512 resident workgroups) x (k-tiles
-    // per workgroup), plus, when the k range is split, a second kernel (2 units) and per split one float
-    // matrix written and read back (8 bytes per element at ~4 TB/s = 1.7e-6 units per element).  At least
-    // 8 k-tiles per split; no split from 384 tiles on.
-    if constexpr (EPI == EPI_BIAS_F32) {
-      // At most one 64-row tile of rows (the first-token head: a few requests against the whole output matrix): the
-      // product is bound by reading the matrix once, so 64 x 128 tiles on a four-stage ring, one workgroup per CU -
-      // 4 % faster there than 128 x 192 tiles (195-200 us against 203-208 at 152064 x 3584).
-      if (M <= 64)
-        return launch_bf16<64, 128, 2, 2, 4, 1, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT, nullptr, 0, st);
-    }
-    int splits = 1, width = 128;
-    float best = 0.f;
-    for (int tn = 128; tn <= 192; tn += 64) {
-      const int64_t tiles = ((M + 127) / 128) * ((N + tn - 1) / tn);
-      const float unit = tn == 128 ? 1.0f : 1.35f;
-      const float whole = (float)((tiles + 511) / 512) * (float)KT * unit;
-      if (tn == 128 || whole < best) {
-        best = whole;
-        splits = 1;
-        width = tn;
-      }
-      if (!splitk_ws || tiles >= 384) continue;
-      for (int sp = 2; sp <= 8; ++sp) {
-        if (KT / sp < 8 || (int64_t)sp * M * N * 4 > splitk_ws_bytes) break;
-        const float cost = (float)(((tiles * sp + 511) / 512) * ((KT + sp - 1) / sp)) * unit + 2.0f +
-                           (float)sp * (float)(M * N) * 1.7e-6f;
-        if (cost < best) {
-          best = cost;
-          splits = sp;
-          width = tn;
-        }
-      }
-    }
-    if (splits <= 1) {
-      if (width == 192)
-        return launch_bf16<128, 192, 2, 2, 2, 2, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT,
-                                                      splitk_ws, splitk_ws_bytes, st);
-      return launch_bf16<128, 128, 2, 2, 2, 2, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT,
-                                                    splitk_ws, splitk_ws_bytes, st);
-    }
-    const int per = (KT + splits - 1) / splits;
-    splits = (KT + per - 1) / per;
-    int rc;
-    if (width == 192)
-      rc = launch_bf16<128, 192, 2, 2, 2, 2, EPI_PARTIAL>(A, lda, W, splitk_ws, N, M, N, K, nullptr, nullptr, 0,
-                                                          nullptr, splits, per, nullptr, 0, st);
-    else
-      rc = launch_bf16<128, 128, 2, 2, 2, 2, EPI_PARTIAL>(A, lda, W, splitk_ws, N, M, N, K, nullptr, nullptr, 0,
-                                                          nullptr, splits, per, nullptr, 0, st);
-    if (rc) return rc;
-    if (deferred) {   // the caller's next kernel sums the partials and applies the epilogue
-      *deferred = splits;
+      const int64_t threads = M * (N / 4);
+      hipLaunchKernelGGL(splitk_epilogue_kernel<EPI>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
+                         (const float*)splitk_ws, splits, (uint16_t*)C, ldc, (int)M, (int)N, (const uint16_t*)bias,
+                         (const uint16_t*)resid, ldr, rmap);
+      VLC_CHECK_LAUNCH("splitk_epilogue");
       return VLC_OK;
     }
-    const int64_t threads = M * (N / 4);
-    hipLaunchKernelGGL(splitk_epilogue_kernel<EPI>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
-                       (const float*)splitk_ws, splits, (uint16_t*)C, ldc, (int)M, (int)N, (const uint16_t*)bias,
-                       (const uint16_t*)resid, ldr, rmap);
-    VLC_CHECK_LAUNCH("splitk_epilogue");
-    return VLC_OK;
   }
+  void* tail_ws = c.split_tail ? splitk_ws : nullptr;
+  int i = 0;
+  // 256 x 256: gate|up on 4 wavefronts of 128 x 128, the others on 8 of 64 x 128 (no spilled registers around the
+  // loop; the projection with float output gains 8 %, gate|up would lose 2 %)
+#define X(BM, BN, WGM, WGN, S, OCC, L, F)                                                                            \
+  if (c.index == i++)                                                                                                \
+    return launch_bf16<BM, BN, BM == 256 && EPI == EPI_SWIGLU ? 2 : WGM, WGN, S, OCC, EPI>(                          \
+        A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT, tail_ws, splitk_ws_bytes, st);
+  VLC_GEMM_TILES(X)
+#undef X
+  return fail(VLC_ERR_SHAPE, "gemm(bf16): no tile");
 }
 
 // Output tiles of 128 rows (grouped: 64) x 128 columns (SwiGLU: 64) from 96 of them on, else 16 x 16 tiles with the k
