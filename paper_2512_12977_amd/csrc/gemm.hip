@@ -118,7 +118,8 @@ enum { EPI_PARTIAL = 100 };   // internal: float partial sums of one k-range (sp
 // GROUPED (mixture-of-experts): the row tiles come from a device-resident table; entry t holds an
 // expert and the range [m0, m_end) of rows it owns (at most BM of them); the tile multiplies these
 // rows - fetched through amap when given - with that expert's matrix W + expert * w_stride.
-// Workgroups beyond the table's length (only known on the device) exit at once.
+// Workgroups beyond the table's length (only known on the device) exit at once, and the XCDs share out the tiles that
+// are there (dealt by the largest possible length, 37 rows per expert left two of the eight XCDs idle).
 template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool GROUPED = false>
 __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
     const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ W, uint16_t* __restrict__ C,
@@ -160,6 +161,10 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   u32x4* lds = reinterpret_cast<u32x4*>(smem);
 
+  if constexpr (GROUPED) {   // the table's real length: every XCD gets its share of what is there, the rest leaves
+    tiles_m = *g_ntiles;
+    if ((int)blockIdx.x >= tiles_m * tiles_n) return;
+  }
   const int tiles = tiles_m * tiles_n;
   int split = 0, pid = blockIdx.x, tail_block = -1;   // tail_block >= 0: this workgroup owns one k-range of a tail tile
   if constexpr (EPI == EPI_PARTIAL) {
@@ -179,7 +184,6 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
   int m0 = tm * BM;
   const int n0 = tn * CN;
   if constexpr (GROUPED) {
-    if (tm >= *g_ntiles) return;
     const GroupTile g = gtab[tm];
     m0 = g.m0;
     M = g.m_end;
@@ -970,13 +974,14 @@ int64_t gemm_splitk_ws_bytes(int64_t n_rows, int64_t max_n) {
 }
 
 // Rows per tile of the grouped GEMMs, from the mean number of rows per group.  Few rows per group: every
-// matrix is streamed from HBM exactly once and nothing is reused, so the tile is small (64 x 128) and the
-// ring three stages deep - with two workgroups per CU that keeps 64 KB of matrix data in flight per CU,
-// what the HBM latency needs; a two-stage ring of 128 x 128 tiles stalls at half of that.
+// matrix is streamed from HBM exactly once and nothing is reused, so the tile is small (64 x 128, below 20 rows per
+// group 32 x 128) and the ring three (four) stages deep - with two workgroups per CU that keeps 64 (96) KB of matrix data
+// in flight per CU, what the HBM latency needs; a two-stage ring of 128 x 128 tiles stalls at half of that.  Per layer of
+// 128 experts (2048 x 768): 6 rows per expert 32-row tiles save 4 us, 37 rows per expert they cost 27 us.
 int gemm_group_tile_rows(int64_t rows, int n_groups, int dtype) {
   if (dtype != VLC_BF16) return 64;
   const int64_t mean = rows / (n_groups > 0 ? n_groups : 1);
-  return mean >= 192 ? 256 : (mean >= 56 ? 128 : 64);
+  return mean >= 192 ? 256 : (mean >= 56 ? 128 : (mean >= 20 ? 64 : 32));
 }
 
 int launch_gemm_grouped(const void* A, int64_t lda, const int32_t* amap, const void* W, int64_t w_stride, void* C,
@@ -998,15 +1003,20 @@ int launch_gemm_grouped(const void* A, int64_t lda, const int32_t* amap, const v
     // 32-bit lane offsets: rows fetched through amap are offsets from A itself (amap values are below a_rows)
     if ((amap ? a_rows : 256) * lda * 2 >= ((int64_t)1 << 31) || ((epilogue == EPI_SWIGLU ? N : 0) + 256) * K * 2 >= ((int64_t)1 << 31))
       return fail(VLC_ERR_SHAPE, "grouped gemm(bf16): operand rows span more than 2 GiB");
-    if (tile_rows == 256) {
+    if (tile_rows == 256) {   // gate|up (long k) on 8 wavefronts, down on 4: 12 us per layer at 444 rows per expert
       if (epilogue == EPI_SWIGLU)
-        return launch_bf16_grouped<256, 256, 2, 2, 2, 1, EPI_SWIGLU>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
+        return launch_bf16_grouped<256, 256, 4, 2, 2, 1, EPI_SWIGLU>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
       return launch_bf16_grouped<256, 256, 2, 2, 2, 1, EPI_BIAS>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
     }
     if (tile_rows == 64) {
       if (epilogue == EPI_SWIGLU)
-        return launch_bf16_grouped<64, 128, 2, 2, 3, 2, EPI_SWIGLU>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
+        return launch_bf16_grouped<64, 128, 1, 4, 3, 2, EPI_SWIGLU>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
       return launch_bf16_grouped<64, 128, 2, 2, 3, 2, EPI_BIAS>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
+    }
+    if (tile_rows == 32) {
+      if (epilogue == EPI_SWIGLU)
+        return launch_bf16_grouped<32, 128, 1, 4, 4, 2, EPI_SWIGLU>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
+      return launch_bf16_grouped<32, 128, 1, 4, 4, 2, EPI_BIAS>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
     }
     if (epilogue == EPI_SWIGLU)
       return launch_bf16_grouped<128, 128, 2, 2, 2, 2, EPI_SWIGLU>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);

@@ -41,7 +41,7 @@ Workspace layout(const vlc_layer_shape& s, int64_t n) {
     w.moe_offset = at; at += align256((E + 1) * 4);
     w.moe_rank = at;   at += align256(pairs * 4);
     w.moe_count = at;  at += align256(E * 4);
-    w.moe_tiles = at;  at += align256((pairs / 64 + E + 1) * (int64_t)sizeof(vlc::GroupTile));   // 64: smallest tile
+    w.moe_tiles = at;  at += align256((pairs / 32 + E + 1) * (int64_t)sizeof(vlc::GroupTile));   // 32: smallest tile
     w.moe_ntiles = at; at += 256;
     w.moe_row = at;    at += align256(pairs * 4);
   }

@@ -247,3 +247,12 @@ def test_moe_random_expert_counts_widths_and_rows(seed):
     wl = syn.Workload("moe_random%d" % seed, sh, [req], 1, "static", static_k=0, seed=300 + seed)
     g = check_moe_layer(wl, 0)
     assert g["moe_idx"].shape == (rows, top_k)
+
+
+@pytest.mark.parametrize("rows", [3, 76, 80, 220, 224, 764, 768])
+def test_moe_rows_per_expert_around_the_tile_sizes(rows):
+    """Mean rows per expert just below and at the lines between the 32-, 64-, 128- and 256-row tiles (top 2 of 8)."""
+    sh = syn.Shape("moe_tiles", L=1, H=256, Hq=4, Hkv=2, D=128, I=192, rope_base=1e4, dtype="bf16", qkv_bias=False,
+                   qk_norm=True, mrope_section=(24, 20, 20), n_experts=8, top_k=2, text_scale=1.0, residual_proj_scale=0.01)
+    req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
+    check_moe_layer(syn.Workload("moe_tiles%d" % rows, sh, [req], 1, "static", static_k=0, seed=700 + rows), 0)
