@@ -52,6 +52,11 @@ constexpr int VR = 128;       // virtual rows per workgroup
 constexpr int K_TILE_CHUNKS = KB * 16;      // [64 keys][16 chunks of 8 d]
 constexpr int V_TILE_CHUNKS = KB * 16;      // same shape
 constexpr int ATT_STAGE_CHUNKS = K_TILE_CHUNKS + V_TILE_CHUNKS;   // one K tile + one V tile
+// The running maximum is only a reference for the exponents: it moves, and O is rescaled, when a row's maximum has
+// outgrown it by more than 2^REF_SLACK.  Probabilities then stay below 2^REF_SLACK, their rounding to bf16 is relative
+// and the sums are float, so nothing is lost; with the exact maximum some row of a wavefront moves in every other key
+// block of a long context, 64 multiplications each time.
+constexpr float REF_SLACK = 8.0f;
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -67,14 +72,16 @@ __device__ __forceinline__ int v_swz(int key, int c) { return c ^ ((key & 3) << 
 // which serialises the prefetch with the block it was meant to overlap.  This way the copies are
 // tracked only by the explicit waits at the end of each key block (the key loop has no other
 // vector-memory instruction).  M0 holds the LDS address and is written right before each use.
-__device__ __forceinline__ void dma16(const void* gptr, u32x4* lds_dst) {
+// The global address is a wavefront-uniform base (scalar registers) plus a 32-bit byte offset per lane, so a copy
+// needs no vector address arithmetic.
+__device__ __forceinline__ void dma16(const void* uniform_base, uint32_t lane_byte_off, u32x4* lds_dst) {
 #ifdef VLC_ABLATE_ATT_COPIES   // measurement build: no K/V tile ever reaches LDS (the rings hold pseudo-random values)
   return;
 #endif
   const uint32_t a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_dst;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
-               : "s"(a), "v"(gptr)
+               : "s"(a), "v"(lane_byte_off), "s"(uniform_base)
                : "memory");
 }
 
@@ -271,11 +278,12 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
   // start at a time; lanes outside the run see every key masked.
   int seg_begin = 0;
   while (seg_begin < rows_here) {
-    const int seg_start = s_start[seg_begin];
+    const int seg_start = __builtin_amdgcn_readfirstlane(s_start[seg_begin]);
     int seg_end = seg_begin + 1;
     while (seg_end < rows_here && s_start[seg_end] == seg_start) ++seg_end;
     int seg_max = 0;
     for (int r = seg_begin; r < seg_end; ++r) seg_max = max(seg_max, s_len[r]);
+    seg_max = __builtin_amdgcn_readfirstlane(seg_max);
 
     int len[RT];
     int w_max = 0, w_min = 0x7fffffff;
@@ -310,14 +318,12 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
   {                                                                                                            \
     const int key0_ = (kb_) * KB;                                                                              \
     u32x4* dst_ = lds + (lds_chunk0_) + wave * 256;                                                            \
+    const char* blk_ = reinterpret_cast<const char*>(base_) + (int64_t)key0_ * kv_row_bytes;                   \
     if (key0_ + KB <= seg_max) { /* whole block inside the run: uniform base + invariant lane offset */        \
-      const char* blk_ = reinterpret_cast<const char*>(base_) + (int64_t)key0_ * kv_row_bytes;                 \
-      _Pragma("unroll") for (int i = 0; i < 4; ++i) dma16(blk_ + go_[i], dst_ + i * 64);                       \
+      _Pragma("unroll") for (int i = 0; i < 4; ++i) dma16(blk_, go_[i], dst_ + i * 64);                        \
     } else { /* last block of the run: rows past the end re-read the last row */                               \
-      _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                          \
-        const int64_t gk_ = (int64_t)min(key0_ + t_key[i], last_key) * kv_row_elems;                           \
-        dma16(base_ + gk_ + c_[i] * 8, dst_ + i * 64);                                                         \
-      }                                                                                                        \
+      _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                            \
+        dma16(blk_, (uint32_t)min(t_key[i], last_key - key0_) * kv_row_bytes + c_[i] * 16, dst_ + i * 64);     \
     }                                                                                                          \
   }
 #define VLC_ATT_ISSUE_K(kb_, stage_) VLC_ATT_ISSUE_TILE(kbase, k_go, k_c, kb_, (stage_) * K_TILE_CHUNKS)
@@ -362,7 +368,7 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
       _Pragma("unroll") for (int mt = 0; mt < 2; ++mt)                                                         \
         _Pragma("unroll") for (int j = 0; j < 16; ++j) mx_ = fmaxf(mx_, ST[rt][mt][j]);                        \
       mx_ = pair_max(mx_) * scale_log2;   /* scale > 0: max commutes with it */                                \
-      const float m_new_ = fmaxf(m_run[rt], mx_);                                                              \
+      const float m_new_ = mx_ > m_run[rt] + REF_SLACK ? mx_ : m_run[rt];                                      \
       const float m_use_ = (m_new_ == -INFINITY) ? 0.f : m_new_;                                               \
       alpha_[rt] = __builtin_amdgcn_exp2f(m_run[rt] - m_use_);   /* m_run = -inf -> 0 */                       \
       grew_ = grew_ || (m_new_ > m_run[rt]);                                                                   \
