@@ -152,7 +152,29 @@ __device__ __forceinline__ f32x16 ablated_mfma(bf16x8 a, bf16x8 b, f32x16 c) {  
 #define VLC_ATT_MFMA_PV(a_, b_, c_) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, b_, c_, 0, 0, 0)
 #endif
 
-// SPLIT: blockIdx.z handles the z-th share of split_blocks key blocks of each run (the last share also what
+// Block id -> (kv head, row tile); tile < 0: none.  XCD = id % 8.  With share = 8 / Hkv XCDs per kv head (Hkv divides 8)
+// XCD x works on head x / share and takes tiles x % share, x % share + share, ...; otherwise the (head, tile) pairs in
+// head order are dealt to the XCDs in contiguous pieces.
+__host__ __device__ inline int att_grid(int tiles, int Hkv) {
+  const int share = Hkv <= 8 && 8 % Hkv == 0 ? 8 / Hkv : 0;
+  return share ? 8 * ((tiles + share - 1) / share) : tiles * Hkv;
+}
+__device__ __forceinline__ void att_tile(int id, int tiles, int Hkv, int* kvh, int* tile) {
+  int t;
+  if (Hkv <= 8 && 8 % Hkv == 0) {
+    const int share = 8 / Hkv, xcd = id % 8;
+    *kvh = xcd / share;
+    t = id / 8 * share + xcd % share;
+  } else {
+    const int total = tiles * Hkv, per = total / 8;
+    const int vid = id < per * 8 ? (id % 8) * per + id / 8 : id;
+    *kvh = vid / tiles;
+    t = vid - *kvh * tiles;
+  }
+  *tile = tiles - 1 - t;
+}
+
+// SPLIT: blockIdx.y = z handles the z-th share of split_blocks key blocks of each run (the last share also what
 // lies beyond) and leaves an un-normalised partial (O as float, running max, running sum) for
 // attention_merge_kernel; a workgroup whose share starts beyond the tile's longest row leaves at once and writes
 // nothing.  Used when there are too few (row tile, kv head) pairs to occupy the chip and the key loop is the
@@ -186,14 +208,15 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     lds[i] = v;
   }
 #endif
-  // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  The remap hands every XCD
-  // one contiguous range of (kv head, row tile) pairs, so the workgroups resident on an XCD at the
-  // same time are neighbouring row tiles of one request and kv head and stream the same K/V.
-  const int lin = blockIdx.y * gridDim.x + blockIdx.x, total = gridDim.x * gridDim.y;
-  const int per = total / 8;
-  const int vid = lin < per * 8 ? (lin % 8) * per + lin / 8 : lin;
-  const int kvh = vid / gridDim.x;
-  const int row0 = (vid - kvh * gridDim.x) * rows_per_tile;
+  // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Every XCD works on one kv head at a time, so
+  // that the workgroups resident on it stream the same K/V; XCDs that share a kv head (fewer than 8) take its row tiles
+  // in turn, because later tiles see more keys: contiguous halves leave the XCD with the early rows idle a third of
+  // the time.  Late tiles come first, so that the last workgroups to start are short ones.
+  const int tiles = (n + rows_per_tile - 1) / rows_per_tile;
+  int kvh, tile;
+  att_tile(blockIdx.x, tiles, Hkv, &kvh, &tile);
+  if (tile < 0) return;
+  const int row0 = tile * rows_per_tile;
   const int rows_here = min(rows_per_tile, n - row0);
 
   if (tid < rows_per_tile) {                       // rows_per_tile <= 128 * RT <= 256 threads
@@ -205,7 +228,7 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
   if (SPLIT) {   // nothing of this tile reaches this share's first key: attention_merge_kernel will not read it
     int tile_max = 0;
     for (int r = 0; r < rows_here; ++r) tile_max = max(tile_max, s_len[r]);
-    if ((int64_t)blockIdx.z * split_blocks * KB >= tile_max) return;
+    if ((int64_t)blockIdx.y * split_blocks * KB >= tile_max) return;
   }
 
   // this lane's virtual rows (one per row tile)
@@ -308,8 +331,8 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     const int all_blocks = (seg_max + KB - 1) / KB;
     int kb_first = 0, n_blocks = all_blocks;        // this workgroup's share of the run's key blocks
     if (SPLIT) {
-      kb_first = min(all_blocks, (int)blockIdx.z * split_blocks);
-      n_blocks = (blockIdx.z + 1 == gridDim.z ? all_blocks : min(all_blocks, kb_first + split_blocks)) - kb_first;
+      kb_first = min(all_blocks, (int)blockIdx.y * split_blocks);
+      n_blocks = (blockIdx.y + 1 == gridDim.y ? all_blocks : min(all_blocks, kb_first + split_blocks)) - kb_first;
     }
     const int last_key = seg_max - 1;               // loads never leave the run's key range
 
@@ -502,7 +525,7 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     const float l_tot = pair_sum(l_run[rt]);
     if (!vr_ok[rt]) continue;
     if (SPLIT) {
-      const int64_t rh = ((int64_t)blockIdx.z * n + (row0 + r_local[rt])) * Hq + head[rt];
+      const int64_t rh = ((int64_t)blockIdx.y * n + (row0 + r_local[rt])) * Hq + head[rt];
       float* po = part_o + rh * ATT_D;
 #pragma unroll
       for (int md = 0; md < ATT_D / 32; ++md)
@@ -743,7 +766,7 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     if (nsplit > 1) {
       float* part_o = static_cast<float*>(ws);
       float* part_ml = part_o + (int64_t)nsplit * n * Hq * ATT_D;
-      const dim3 grid((unsigned)tiles, (unsigned)Hkv, (unsigned)nsplit);
+      const dim3 grid((unsigned)att_grid((int)tiles, Hkv), (unsigned)nsplit);
       hipLaunchKernelGGL((attention_bf16_kernel<true, 1>), grid, dim3(256), 0, st, (const uint16_t*)q, q_stride,
                          (const uint16_t*)k_cache, (const uint16_t*)v_cache, row_kv_start, row_kv_len, (int)n,
                          Hq, Hkv, g, rows_per_tile, scale * 1.4426950408889634f, (uint16_t*)out, split_blocks, part_o,
@@ -755,7 +778,7 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
       VLC_CHECK_LAUNCH("attention_merge");
       return VLC_OK;
     }
-    const dim3 grid((unsigned)tiles, (unsigned)Hkv);
+    const dim3 grid((unsigned)att_grid((int)tiles, Hkv));
     hipLaunchKernelGGL((attention_bf16_kernel<false, 1>), grid, dim3(256), 0, st, (const uint16_t*)q, q_stride,
                        (const uint16_t*)k_cache, (const uint16_t*)v_cache, row_kv_start, row_kv_len, (int)n,
                        Hq, Hkv, g, rows_per_tile, scale * 1.4426950408889634f, (uint16_t*)out, 1, nullptr,
