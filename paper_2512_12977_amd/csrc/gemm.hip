@@ -280,7 +280,9 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
   constexpr int MPG = (NT * MT) % 4 == 0 ? 4 : (NT * MT) % 2 == 0 ? 2 : 1;   // MFMAs per group
   constexpr int G = NT * MT / MPG;             // groups per k-step
   constexpr int NF = NT + MT;                  // fragments per k-step
-  constexpr int LG = 2 * G;                    // groups that issue loads: the last k-step's and the next tile's first
+  // groups that issue loads: those of the last k-step and of the next tile's first (all in the last k-step: 596-row
+  // prefill 1.7 % and 72B shape 4 % slower, spread over a third k-step: no difference)
+  constexpr int LG = 2 * G;
   static_assert(NT * MT % MPG == 0, "wavefront tile must hold whole groups of MFMA tiles");
   bf16x8 wf[2][NT], af[2][MT];
 #define VLC_READ_FRAGS(st_, ks_, buf_, g_)                                                                    \
@@ -533,8 +535,11 @@ __global__ __launch_bounds__(256) void splitk_epilogue_kernel(const float* __res
   }
 }
 
-// Sum over k-ranges of the tail tiles' float blocks + epilogue.  grid (BM * QN / 256, tail tiles), QN = quads of
-// output columns per tile; a thread owns four consecutive columns of one row.
+// Sum over k-ranges of the tail tiles' float blocks + epilogue.  grid ((BM / 32) * ceil(QN / 16), tail tiles), QN = quads
+// of output columns per tile; a workgroup owns 32 rows x 16 quads.  It reads the blocks as they lie (lanes: consecutive
+// rows of a quad) and turns the sums around in LDS, so that residual and output are touched in pieces of whole rows
+// (64 columns at a time): 66 tiles of 256 x 256 in three ranges 32 -> 13 us, against lanes that each stored
+// 8 bytes of another row.
 template <int BM, int BN, int EPI>
 __global__ __launch_bounds__(256) void tail_reduce_kernel(const float* __restrict__ P, int splits, int full_tiles,
                                                           int tiles_m, int tiles_n, uint16_t* __restrict__ C,
@@ -543,44 +548,71 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const float* __restric
                                                           const uint16_t* __restrict__ resid, int64_t ldr,
                                                           const int32_t* __restrict__ rmap) {
   constexpr int CN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
+  constexpr int QN = CN / 4, QB = (QN + 15) / 16;
+  __shared__ float4 turned[32][17];
   const int t = blockIdx.y;
   int tm, tn;
   tile_coords(full_tiles + t, tiles_m * tiles_n, tiles_m, tiles_n, &tm, &tn);
-  const int id = blockIdx.x * 256 + threadIdx.x;
-  const int jq = id / BM, ml = id - jq * BM;          // consecutive threads: consecutive rows (contiguous float4 reads)
-  const int m = tm * BM + ml, n = tn * CN + 4 * jq;
-  if (m >= M || n >= N) return;
-  const float* base = P + (int64_t)t * splits * (BM * BN) + ((int64_t)jq * BM + ml) * 4;
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f), u = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int k = 0; k < splits; ++k) {
-    const float4 a = *reinterpret_cast<const float4*>(base + (int64_t)k * (BM * BN));
-    s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
-    if constexpr (EPI == EPI_SWIGLU) {
-      const float4 b = *reinterpret_cast<const float4*>(base + (int64_t)k * (BM * BN) + (int64_t)(BN / 8) * BM * 4);
-      u.x += b.x; u.y += b.y; u.z += b.z; u.w += b.w;
+  const int r0 = (int)(blockIdx.x / QB) * 32, q0 = (int)(blockIdx.x % QB) * 16;
+  const float* base = P + (int64_t)t * splits * (BM * BN);
+  {
+    const int ml = threadIdx.x & 31;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int ql = (threadIdx.x >> 5) + 8 * i, jq = q0 + ql;
+      if (jq >= QN) break;
+      const float* p = base + ((int64_t)jq * BM + r0 + ml) * 4;
+      float4 s = make_float4(0.f, 0.f, 0.f, 0.f), u = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int k0 = 0; k0 < splits; k0 += 4) {   // four ranges' loads together
+        float4 a[4], b[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          a[k] = b[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (k0 + k < splits) {
+            a[k] = *reinterpret_cast<const float4*>(p + (int64_t)(k0 + k) * (BM * BN));
+            if constexpr (EPI == EPI_SWIGLU)
+              b[k] = *reinterpret_cast<const float4*>(p + (int64_t)(k0 + k) * (BM * BN) + (int64_t)(BN / 8) * BM * 4);
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          s.x += a[k].x; s.y += a[k].y; s.z += a[k].z; s.w += a[k].w;
+          if constexpr (EPI == EPI_SWIGLU) { u.x += b[k].x; u.y += b[k].y; u.z += b[k].z; u.w += b[k].w; }
+        }
+      }
+      if constexpr (EPI == EPI_SWIGLU) {
+        s.x = silu_f(s.x) * u.x; s.y = silu_f(s.y) * u.y; s.z = silu_f(s.z) * u.z; s.w = silu_f(s.w) * u.w;
+      }
+      turned[ml][ql] = s;
     }
   }
-  if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_F32) {
-    if (bias) {
-      const uint2 b = *reinterpret_cast<const uint2*>(bias + n);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int id = i * 256 + (int)threadIdx.x, ml = id >> 4, ql = id & 15;
+    const int m = tm * BM + r0 + ml, n = tn * CN + 4 * (q0 + ql);
+    if (m >= M || n >= N || q0 + ql >= QN) continue;
+    float4 s = turned[ml][ql];
+    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_F32) {
+      if (bias) {
+        const uint2 b = *reinterpret_cast<const uint2*>(bias + n);
+        s.x += __uint_as_float(b.x << 16); s.y += __uint_as_float(b.x & 0xffff0000u);
+        s.z += __uint_as_float(b.y << 16); s.w += __uint_as_float(b.y & 0xffff0000u);
+      }
+    } else if constexpr (EPI == EPI_RESIDUAL) {
+      const int64_t rrow = rmap ? (int64_t)rmap[m] : (int64_t)m;
+      const uint2 b = *reinterpret_cast<const uint2*>(resid + rrow * ldr + n);
       s.x += __uint_as_float(b.x << 16); s.y += __uint_as_float(b.x & 0xffff0000u);
       s.z += __uint_as_float(b.y << 16); s.w += __uint_as_float(b.y & 0xffff0000u);
     }
-  } else if constexpr (EPI == EPI_RESIDUAL) {
-    const int64_t rrow = rmap ? (int64_t)rmap[m] : (int64_t)m;
-    const uint2 b = *reinterpret_cast<const uint2*>(resid + rrow * ldr + n);
-    s.x += __uint_as_float(b.x << 16); s.y += __uint_as_float(b.x & 0xffff0000u);
-    s.z += __uint_as_float(b.y << 16); s.w += __uint_as_float(b.y & 0xffff0000u);
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    s.x = silu_f(s.x) * u.x; s.y = silu_f(s.y) * u.y; s.z = silu_f(s.z) * u.z; s.w = silu_f(s.w) * u.w;
-  }
-  if constexpr (EPI == EPI_BIAS_F32) {
-    *reinterpret_cast<float4*>(reinterpret_cast<float*>(C) + (int64_t)m * ldc + n) = s;
-  } else {
-    uint2 o;
-    o.x = pack_bf16x2(s.x, s.y);
-    o.y = pack_bf16x2(s.z, s.w);
-    *reinterpret_cast<uint2*>(C + (int64_t)m * ldc + n) = o;
+    if constexpr (EPI == EPI_BIAS_F32) {
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(C) + (int64_t)m * ldc + n) = s;
+    } else {
+      uint2 o;
+      o.x = pack_bf16x2(s.x, s.y);
+      o.y = pack_bf16x2(s.z, s.w);
+      *reinterpret_cast<uint2*>(C + (int64_t)m * ldc + n) = o;
+    }
   }
 }
 
@@ -760,7 +792,7 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
   VLC_CHECK_LAUNCH("gemm_bf16");
   if constexpr (EPI != EPI_PARTIAL) {
     if (tail > 0) {
-      hipLaunchKernelGGL((tail_reduce_kernel<BM, BN, EPI>), dim3(BM * (CN / 4) / 256, tail), dim3(256), 0, st,
+      hipLaunchKernelGGL((tail_reduce_kernel<BM, BN, EPI>), dim3(BM / 32 * ((CN / 4 + 15) / 16), tail), dim3(256), 0, st,
                          (const float*)tail_ws, tsp, full, tiles_m, tiles_n, (uint16_t*)C, ldc, (int)M, (int)N,
                          (const uint16_t*)bias, (const uint16_t*)resid, ldr, rmap);
       VLC_CHECK_LAUNCH("gemm_tail_reduce");
