@@ -334,6 +334,10 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_kernel(const uint4* __restri
   if (yrow < 0) return;                    // the same for the whole workgroup
   const int64_t srow = map ? (int64_t)map[row] : row;
   const uint4* xr = x + srow * chunks;
+  uint4 wr[MAXC];                          // ahead of the reduction: its latency is hidden
+#pragma unroll
+  for (int j = 0; j < MAXC; ++j)
+    if ((int)threadIdx.x + j * kThreads < chunks) wr[j] = w[threadIdx.x + j * kThreads];
   float v[MAXC][VEC];
   float ss = 0.f;
 #pragma unroll
@@ -359,7 +363,7 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_kernel(const uint4* __restri
     const int c = threadIdx.x + j * kThreads;
     if (c < chunks) {
       float wv[VEC], o[VEC];
-      Chunk<T>::unpack(w[c], wv);
+      Chunk<T>::unpack(wr[j], wv);
 #pragma unroll
       for (int i = 0; i < VEC; ++i) o[i] = v[j][i] * r * wv[i];
       y[yrow * chunks + c] = Chunk<T>::pack(o);
@@ -379,6 +383,10 @@ __global__ __launch_bounds__(kThreads) void sum_residual_rmsnorm_kernel(
   const int64_t row = blockIdx.x;
   const int64_t rrow = rmap ? (int64_t)rmap[row] : row;
   const int64_t yrow = ymap ? (int64_t)ymap[row] : row;    // < 0: h is written, the norm is not wanted
+  uint4 wr[MAXC];                          // ahead of the reduction: its latency is hidden
+#pragma unroll
+  for (int j = 0; j < MAXC; ++j)
+    if ((int)threadIdx.x + j * kThreads < chunks) wr[j] = w[threadIdx.x + j * kThreads];
   float v[MAXC][8];
   float ss = 0.f;
 #pragma unroll
@@ -426,7 +434,7 @@ __global__ __launch_bounds__(kThreads) void sum_residual_rmsnorm_kernel(
     const int c = threadIdx.x + j * kThreads;
     if (c < chunks) {
       float wv[8], o[8];
-      CB::unpack(w[c], wv);
+      CB::unpack(wr[j], wv);
 #pragma unroll
       for (int i = 0; i < 8; ++i) o[i] = v[j][i] * r * wv[i];
       y[yrow * chunks + c] = CB::pack(o);
