@@ -52,11 +52,6 @@ constexpr int VR = 128;       // virtual rows per workgroup
 constexpr int K_TILE_CHUNKS = KB * 16;      // [64 keys][16 chunks of 8 d]
 constexpr int V_TILE_CHUNKS = KB * 16;      // same shape
 constexpr int ATT_STAGE_CHUNKS = K_TILE_CHUNKS + V_TILE_CHUNKS;   // one K tile + one V tile
-// The running maximum is only a reference for the exponents: it moves, and O is rescaled, when a row's maximum has
-// outgrown it by more than 2^REF_SLACK.  Probabilities then stay below 2^REF_SLACK, their rounding to bf16 is relative
-// and the sums are float, so nothing is lost; with the exact maximum some row of a wavefront moves in every other key
-// block of a long context, 64 multiplications each time.
-constexpr float REF_SLACK = 8.0f;
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -391,7 +386,7 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
       _Pragma("unroll") for (int mt = 0; mt < 2; ++mt)                                                         \
         _Pragma("unroll") for (int j = 0; j < 16; ++j) mx_ = fmaxf(mx_, ST[rt][mt][j]);                        \
       mx_ = pair_max(mx_) * scale_log2;   /* scale > 0: max commutes with it */                                \
-      const float m_new_ = mx_ > m_run[rt] + REF_SLACK ? mx_ : m_run[rt];                                      \
+      const float m_new_ = fmaxf(m_run[rt], mx_);                                                              \
       const float m_use_ = (m_new_ == -INFINITY) ? 0.f : m_new_;                                               \
       alpha_[rt] = __builtin_amdgcn_exp2f(m_run[rt] - m_use_);   /* m_run = -inf -> 0 */                       \
       grew_ = grew_ || (m_new_ > m_run[rt]);                                                                   \
