@@ -92,6 +92,22 @@ __device__ __forceinline__ float pair_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// largest value of the wavefront, in every lane: within rows of 16 lanes by DPP, between them by register swaps
+template <int CTRL>
+__device__ __forceinline__ int max_dpp(int v) {
+  return max(v, __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ int wave_max(int v) {
+  v = max_dpp<0xb1>(v);     // quad_perm [1,0,3,2]
+  v = max_dpp<0x4e>(v);     // quad_perm [2,3,0,1]
+  v = max_dpp<0x141>(v);    // row_half_mirror
+  v = max_dpp<0x140>(v);    // row_mirror
+  const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+  v = max((int)a[0], (int)a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+  return max((int)b[0], (int)b[1]);
+}
+
 #define VLC_ATT_WAIT_VM0() __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8) | (0 << 14))
 
 // Measurement variants (python -m paper_2512_12977_amd.build --tag T --define VLC_ABLATE_...): each takes one
@@ -220,9 +236,20 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     s_len[tid] = ok ? row_kv_len[row0 + tid] : 0;
   }
   __syncthreads();
+  // rows lane, lane + 64, ... of the tile in registers: runs and maxima are found by ballots and wavefront maxima (walking
+  // the rows through LDS costs a launch of few key blocks 2 us of its 15)
+  constexpr int RL = VR * RT / 64;
+  int row_start[RL], row_len[RL];
+  int tile_max = 0;
+#pragma unroll
+  for (int i = 0; i < RL; ++i) {
+    const bool ok = lane + 64 * i < rows_here;
+    row_start[i] = ok ? s_start[lane + 64 * i] : -1;
+    row_len[i] = ok ? s_len[lane + 64 * i] : 0;
+    tile_max = max(tile_max, row_len[i]);
+  }
   if (SPLIT) {   // nothing of this tile reaches this share's first key: attention_merge_kernel will not read it
-    int tile_max = 0;
-    for (int r = 0; r < rows_here; ++r) tile_max = max(tile_max, s_len[r]);
+    tile_max = __builtin_amdgcn_readfirstlane(wave_max(tile_max));
     if ((int64_t)blockIdx.y * split_blocks * KB >= tile_max) return;
   }
 
@@ -297,10 +324,20 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
   int seg_begin = 0;
   while (seg_begin < rows_here) {
     const int seg_start = __builtin_amdgcn_readfirstlane(s_start[seg_begin]);
-    int seg_end = seg_begin + 1;
-    while (seg_end < rows_here && s_start[seg_end] == seg_start) ++seg_end;
+    int seg_end = rows_here;                        // first later row of another request
+#pragma unroll
+    for (int i = RL - 1; i >= 0; --i) {
+      const int r = lane + 64 * i;
+      const uint64_t other = __ballot(r > seg_begin && r < rows_here && row_start[i] != seg_start);
+      if (other) seg_end = 64 * i + __builtin_ctzll(other);
+    }
     int seg_max = 0;
-    for (int r = seg_begin; r < seg_end; ++r) seg_max = max(seg_max, s_len[r]);
+#pragma unroll
+    for (int i = 0; i < RL; ++i) {
+      const int r = lane + 64 * i;
+      if (r >= seg_begin && r < seg_end) seg_max = max(seg_max, row_len[i]);
+    }
+    seg_max = wave_max(seg_max);
     seg_max = __builtin_amdgcn_readfirstlane(seg_max);
 
     int len[RT];
@@ -315,11 +352,8 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
       w_min = min(w_min, vr_ok[rt] ? len[rt] : 0x7fffffff);
     }
     // longest / shortest visible range among this wavefront's rows (uniform per wavefront)
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      w_max = max(w_max, __shfl_xor(w_max, o));
-      w_min = min(w_min, __shfl_xor(w_min, o));
-    }
+    w_max = __builtin_amdgcn_readfirstlane(wave_max(w_max));
+    w_min = -__builtin_amdgcn_readfirstlane(wave_max(-w_min));
 
     const uint16_t* kbase = kc + (int64_t)seg_start * kv_row_elems + (int64_t)kvh * ATT_D;
     const uint16_t* vbase = vc + (int64_t)seg_start * kv_row_elems + (int64_t)kvh * ATT_D;
