@@ -66,12 +66,12 @@ __device__ __forceinline__ void tile_coords(int pid, int total, int tiles_m, int
 // bytes of a bf16 C row.
 //
 // Operands reach LDS straight from global memory (global_load_lds, 16 bytes per lane, no register
-// staging) through a ring of STAGES k-tiles of 64 columns, so the next k-tile is in flight while
+// staging) through a ring of STAGES k-tiles of 64 columns, so the next k-tiles are in flight while
 // the current one is consumed.  Inside a k-tile the instruction stream is laid out in groups of four
-// MFMAs, each preceded by its share of the next k-step's fragment reads and - in the first half of
-// the k-tile only, so every load has at least half a k-tile of latency cover - of the next k-tile's
-// global loads; sched_barrier keeps the compiler from regrouping them.  A wavefront-level load writes 64 consecutive 16-byte chunks of LDS
-// in lane order; the XOR swizzle that keeps the later 16-byte fragment reads of consecutive rows
+// MFMAs, each preceded by its share of the next k-step's fragment reads and - in the last k-step of a
+// tile and the first of the next, so every load has at least half a k-tile of latency cover - of the
+// loads that refill the stage just read; sched_barrier keeps the compiler from regrouping them.  A
+// wavefront-level load writes 64 consecutive 16-byte chunks of LDS in lane order; the XOR swizzle that keeps the later 16-byte fragment reads of consecutive rows
 // in different banks is therefore applied on the global side (which chunk of its row each lane
 // fetches).  Fragments are double-buffered in registers across the four 16-wide k-steps.
 //
@@ -892,6 +892,13 @@ int dispatch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ld
                   int64_t K, const void* bias, const void* resid, int64_t ldr, const int32_t* rmap,
                   void* splitk_ws, int64_t splitk_ws_bytes, int* deferred, hipStream_t st) {
   const int KT = (int)(K / BK);
+  if constexpr (EPI == EPI_BIAS_F32) {
+    // The first-token head: a few requests against a whole output matrix, no k split.  With a short k range the start and
+    // end of a workgroup count: 64 x 128 tiles on a four-stage ring take 136 ... 167 us for 1 ... 64 requests at
+    // 151936 x 2048 (128 x 160 tiles, the choice of the model: 152 ... 173), 190 ... 235 at 152064 x 3584 (193 ... 227).
+    if (M <= 64 && !splitk_ws && K < 3072)
+      return launch_bf16<64, 128, 2, 2, 4, 1, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT, nullptr, 0, st);
+  }
   const bool may_split = EPI != EPI_SWIGLU && splitk_ws;
   const TileChoice c = choose_tile(M, N, K, EPI == EPI_SWIGLU, may_split, splitk_ws ? splitk_ws_bytes : 0);
   if (c.splits > 1) {
@@ -997,9 +1004,8 @@ int launch_f32_grouped(const void* A, int64_t lda, const int32_t* amap, const vo
 
 }  // namespace
 
-// Whole-GEMM split-K only runs when a GEMM has fewer than 384 tiles of 128 x 128, and then uses about
-// 512 / tiles splits: splits * M * N floats stay below 2 * 512 * 128 * 128 * 4 bytes.  The tail split
-// writes at most one float block per resident workgroup: 256 x (256 x 256) or 512 x (128 x 128) floats.
+// Float scratch of the split k ranges and of the split tiles of a last round: choose_tile and launch_bf16 split only
+// what fits.  64 MB is one float block per resident workgroup at the largest block: 256 x (256 x 256) floats.
 int64_t gemm_splitk_ws_bytes(int64_t n_rows, int64_t max_n) {
   (void)max_n;
   return n_rows > 0 ? (int64_t)64 << 20 : 0;
@@ -1076,7 +1082,8 @@ int launch_gemm(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
     if (K % BK) return fail(VLC_ERR_SHAPE, "gemm(bf16): K=%lld must be a multiple of %d", (long long)K, BK);
     if (N % 4 || lda % 8 || ldc % 4 || (epilogue == EPI_RESIDUAL && ldr % 4))
       return fail(VLC_ERR_SHAPE, "gemm(bf16): N, lda, ldc, ldr must keep 8-byte (A: 16-byte) alignment");
-    // lane offsets of the loads are 32-bit byte offsets from the tile's first row (SwiGLU: up rows sit N rows on)
+    // lane offsets of the loads are unsigned 32-bit byte offsets from the tile's first row (SwiGLU: up rows sit N rows
+    // on); below 2 GiB for 256 rows they are below 4 GiB for the largest tile
     if (256 * lda * 2 >= ((int64_t)1 << 31) || ((epilogue == EPI_SWIGLU ? N : 0) + 256) * K * 2 >= ((int64_t)1 << 31))
       return fail(VLC_ERR_SHAPE, "gemm(bf16): a tile's rows span more than 2 GiB (lda=%lld N=%lld K=%lld)",
                   (long long)lda, (long long)N, (long long)K);

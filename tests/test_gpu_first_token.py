@@ -139,7 +139,8 @@ def test_first_token_f32_around_the_tile_edges(n_req, vocab, H):
 @pytest.mark.parametrize("n_req,vocab,H", [
     (1, 256, 64), (97, 4096, 448), (192, 12292, 64), (321, 6148, 64), (129, 12292, 128), (641, 4096, 576), (300, 12292, 192),
     (321, 12292, 64), (193, 24580, 128), (1100, 6148, 320), (129, 24580, 320), (320, 16384, 448), (1300, 6148, 192),
-    (300, 24580, 64), (320, 24580, 256), (641, 16384, 320), (400, 24580, 192), (321, 24580, 448), (1700, 6148, 64)])
+    (300, 24580, 64), (320, 24580, 256), (641, 16384, 320), (400, 24580, 192), (321, 24580, 448), (1700, 6148, 64),
+    (64, 260, 3008), (65, 260, 3008), (64, 260, 3072)])
 def test_first_token_bf16_tiles_and_rings(n_req, vocab, H):
     """bf16 products that the tile choice spreads over its list (64 x 128 to 256 x 256), with ragged rows and columns and
     k ranges shorter than, equal to and longer than the rings (1 to 9 k-tiles)."""
