@@ -721,9 +721,10 @@ __global__ __launch_bounds__(64 * F32_WAVES) void attention_f32_kernel(const flo
       float vv[UNROLL][DL];
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) {
+        // past the end: the load stays in range, its value (which may be an infinity) does not count
         const float* vp = vbase + (int64_t)min(first + j + u, len - 1) * kv_row + DL * lane;
 #pragma unroll
-        for (int e = 0; e < DL; ++e) vv[u][e] = vp[e];
+        for (int e = 0; e < DL; ++e) vv[u][e] = j + u < keys ? vp[e] : 0.f;
       }
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) {

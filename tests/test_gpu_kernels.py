@@ -286,6 +286,34 @@ def test_attention_f32_around_the_key_chunks(D):
     attention_case("f32", 6, 2, D, [(1300, slots)], seed=31 + D)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_attention_f32_infinity_in_the_last_visible_value_row(D):
+    """An infinity in a visible value row is the result of its element and leaves the others alone, also in the row
+    that a group of 16 keys is filled up with (key counts that are no multiple of 16, of 64 and of 512)."""
+    lens = [1, 2, 15, 16, 17, 63, 65, 250, 511, 513, 700]
+    rng = np.random.default_rng(57 + D)
+    n, Hq, Hkv, S = len(lens), 4, 2, sum(lens)
+    q, K = rng.standard_normal((n, Hq, D)).astype(np.float32), rng.standard_normal((S, Hkv, D)).astype(np.float32)
+    V = rng.standard_normal((S, Hkv, D)).astype(np.float32)
+    starts = np.concatenate([[0], np.cumsum(lens)[:-1]])
+    last = starts + np.asarray(lens) - 1
+    V[last, 0, 3] = np.inf
+    V[last, 1, D - 1] = -np.inf
+    out = torch.zeros((n, Hq, D), device=DEV)
+    vlc.vlc_sparse_q_attention(to_dev(q, "f32"), to_dev(K, "f32"), to_dev(V, "f32"), i32(starts), i32(lens),
+                               1.0 / math.sqrt(D), out)
+    got = back(out)
+    assert np.all(got[:, :2, 3] == np.inf) and np.all(got[:, 2:, D - 1] == -np.inf)
+    Vf = V.copy()
+    Vf[~np.isfinite(Vf)] = 0.0
+    for i, L in enumerate(lens):
+        a = starts[i]
+        want = orc.attention_rows(q[i:i + 1].astype(np.float64), K[a:a + L].astype(np.float64),
+                                  Vf[a:a + L].astype(np.float64), np.asarray([L]), 1.0 / math.sqrt(D))[0]
+        got[i, :2, 3], got[i, 2:, D - 1] = want[:2, 3], want[2:, D - 1]
+        assert_close(got[i], want, "f32", "the finite elements at %d keys" % L)
+
+
 def test_attention_long_context_bf16():
     """7B head layout, S = 4500: rows at the start of each 'image' and a trailing text run."""
     S = 4500
