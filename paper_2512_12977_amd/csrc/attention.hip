@@ -747,7 +747,7 @@ __global__ __launch_bounds__(64 * F32_WAVES) void attention_f32_kernel(const flo
       lt += red_l[w];
       o += red_o[w][tid];
     }
-    out[((int64_t)row * Hq + head) * D + tid] = lt > 0.f ? o / lt : 0.f;
+    out[((int64_t)row * Hq + head) * D + tid] = len > 0 ? o / lt : 0.f;   // a NaN sum stays NaN
   }
 }
 

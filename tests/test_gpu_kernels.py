@@ -314,6 +314,25 @@ def test_attention_f32_infinity_in_the_last_visible_value_row(D):
         assert_close(got[i], want, "f32", "the finite elements at %d keys" % L)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_attention_f32_nan_scores_stay_visible(D):
+    """A key whose score is a NaN makes the rows that see it NaN (not zero), and no others."""
+    rng = np.random.default_rng(61 + D)
+    S, Hq, Hkv = 600, 4, 2
+    lens = [0, 1, 99, 100, 101, 512, 520, 600]
+    q, K = rng.standard_normal((len(lens), Hq, D)).astype(np.float32), rng.standard_normal((S, Hkv, D)).astype(np.float32)
+    V = rng.standard_normal((S, Hkv, D)).astype(np.float32)
+    K[99, 0, 5] = np.nan
+    K[515, 1, 0] = np.nan
+    out = torch.zeros((len(lens), Hq, D), device=DEV)
+    vlc.vlc_sparse_q_attention(to_dev(q, "f32"), to_dev(K, "f32"), to_dev(V, "f32"), i32(np.zeros(len(lens))), i32(lens),
+                               1.0 / math.sqrt(D), out)
+    got = np.isnan(back(out))
+    for i, L in enumerate(lens):
+        assert got[i, :2].all() == (L > 99) and got[i, :2].any() == (L > 99), L
+        assert got[i, 2:].all() == (L > 515) and got[i, 2:].any() == (L > 515), L
+
+
 def test_attention_long_context_bf16():
     """7B head layout, S = 4500: rows at the start of each 'image' and a trailing text run."""
     S = 4500
