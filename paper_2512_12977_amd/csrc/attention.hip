@@ -645,15 +645,19 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 }
 
 // ---------------------------------------------------------------------------------------------
-// f32 kernel: one workgroup per (row, head).  Keys in chunks of 512: a thread scores one key, the chunk's
-// probabilities meet in LDS, and the PV product runs with the lanes over d (whole value rows, coalesced), each
-// wavefront on its 64 keys of the chunk.  Bound by latency at the sizes of the fp32 configuration: 61 rows x 4 heads
-// over 304 keys take 8.5 us; one wavefront per (row, head) with the keys over its lanes, which walks five keys one
-// after the other and then adds 64 partial outputs by shuffles, took 23.5 us.
+// f32 kernel: one workgroup of F32_WAVES wavefronts per (row, head).  Keys in chunks of 64 * F32_WAVES: a thread scores
+// one key, the chunk's probabilities meet in LDS, and the PV product runs with the lanes over d (whole value rows,
+// coalesced), each wavefront on its 64 keys of the chunk.  Bound by latency at the sizes of the fp32 configuration: 61 rows
+// x 4 heads over 304 keys take 8.5 us on eight wavefronts; one wavefront per (row, head) with the keys over its lanes,
+// which walks five keys one after the other and then adds 64 partial outputs by shuffles, took 23.5 us.
 // ---------------------------------------------------------------------------------------------
-constexpr int F32_WAVES = 8;        // 512 keys per chunk
+// (row, head) pairs from which one wavefront each is enough: the pairs themselves then fill the chip (8192 wavefronts), and
+// eight wavefronts per pair idle where there are few keys.  D = 64, one / eight wavefronts: 1200 pairs 122 / 91 us at 1500
+// keys, 9.5 / 15.6 at 64; 2400 pairs 180 / 175 and 11.6 / 25.5; 32000 pairs 1744 / 2099 and 84 / 295 (two and four
+// wavefronts lie between).
+constexpr int64_t kF32OneWavePairs = 2048;
 
-template <int D>
+template <int D, int F32_WAVES>
 __global__ __launch_bounds__(64 * F32_WAVES) void attention_f32_kernel(const float* __restrict__ q, int64_t q_stride,
                                                             const float* __restrict__ kc,
                                                             const float* __restrict__ vc,
@@ -672,7 +676,7 @@ __global__ __launch_bounds__(64 * F32_WAVES) void attention_f32_kernel(const flo
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kvh = head / g;
   const float* qp = q + (int64_t)row * q_stride + (int64_t)head * D;
-  if (tid < D) sq[tid] = qp[tid] * scale;
+  for (int d = tid; d < D; d += 64 * F32_WAVES) sq[d] = qp[d] * scale;
   const int len = row_kv_len[row];
   const int64_t start = row_kv_start[row];
   const int64_t kv_row = (int64_t)Hkv * D;
@@ -740,14 +744,14 @@ __global__ __launch_bounds__(64 * F32_WAVES) void attention_f32_kernel(const flo
 #pragma unroll
   for (int e = 0; e < DL; ++e) red_o[wave][DL * lane + e] = acc[e];
   __syncthreads();
-  if (tid < D) {
+  for (int d = tid; d < D; d += 64 * F32_WAVES) {
     float lt = 0.f, o = 0.f;
 #pragma unroll
     for (int w = 0; w < F32_WAVES; ++w) {
       lt += red_l[w];
-      o += red_o[w][tid];
+      o += red_o[w][d];
     }
-    out[((int64_t)row * Hq + head) * D + tid] = len > 0 ? o / lt : 0.f;   // a NaN sum stays NaN
+    out[((int64_t)row * Hq + head) * D + d] = len > 0 ? o / lt : 0.f;   // a NaN sum stays NaN
   }
 }
 
@@ -817,18 +821,19 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     return VLC_OK;
   }
   if (dtype == VLC_F32) {
-    if (n > 0x7fffffff || Hq > 65535) return fail(VLC_ERR_SHAPE, "attention(f32): grid too large");
-    const dim3 grid((unsigned)n, (unsigned)Hq);
-    if (D == 64)
-      hipLaunchKernelGGL(attention_f32_kernel<64>, grid, dim3(64 * F32_WAVES), 0, st, (const float*)q, q_stride,
-                         (const float*)k_cache, (const float*)v_cache, row_kv_start, row_kv_len, Hq, Hkv, g,
-                         scale, (float*)out);
-    else if (D == 128)
-      hipLaunchKernelGGL(attention_f32_kernel<128>, grid, dim3(64 * F32_WAVES), 0, st, (const float*)q, q_stride,
-                         (const float*)k_cache, (const float*)v_cache, row_kv_start, row_kv_len, Hq, Hkv, g,
-                         scale, (float*)out);
-    else
-      return fail(VLC_ERR_SHAPE, "attention(f32): D=%d unsupported", D);
+    // at most 2^32 - 1 threads along a grid dimension, 64 per row here (that many rows take the one-wavefront kernel)
+    if (n >= (int64_t)1 << 26 || Hq > 65535) return fail(VLC_ERR_SHAPE, "attention(f32): grid too large");
+    if (D != 64 && D != 128) return fail(VLC_ERR_SHAPE, "attention(f32): D=%d unsupported", D);
+    const bool one = n * Hq >= kF32OneWavePairs;
+#define VLC_LAUNCH_F32_ATT(D_, W_)                                                                                  \
+  hipLaunchKernelGGL((attention_f32_kernel<D_, W_>), dim3((unsigned)n, (unsigned)Hq), dim3(64 * W_), 0, st,        \
+                     (const float*)q, q_stride, (const float*)k_cache, (const float*)v_cache, row_kv_start, row_kv_len, \
+                     Hq, Hkv, g, scale, (float*)out)
+    if (D == 64 && one) VLC_LAUNCH_F32_ATT(64, 1);
+    else if (D == 64) VLC_LAUNCH_F32_ATT(64, 8);
+    else if (one) VLC_LAUNCH_F32_ATT(128, 1);
+    else VLC_LAUNCH_F32_ATT(128, 8);
+#undef VLC_LAUNCH_F32_ATT
     VLC_CHECK_LAUNCH("attention_f32");
     return VLC_OK;
   }

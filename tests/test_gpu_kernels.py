@@ -333,6 +333,27 @@ def test_attention_f32_nan_scores_stay_visible(D):
         assert got[i, 2:].all() == (L > 515) and got[i, 2:].any() == (L > 515), L
 
 
+@pytest.mark.parametrize("Hq,n", [(1, 2047), (1, 2048), (7, 292), (7, 293), (16, 128), (16, 127)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_attention_f32_around_the_workgroup_widths(D, Hq, n):
+    """(row, head) pairs on both sides of 2048, where the workgroup narrows from eight wavefronts to one; key counts around
+    the 64 keys of a wavefront."""
+    some = [-1, 0, 1, 15, 16, 62, 63, 64, 127, 128, 190, 191, 299]
+    attention_case("f32", Hq, 1, D, [(300, [some[i % len(some)] for i in range(n)])], seed=71 + n)
+
+
+def test_attention_f32_more_rows_than_wide_workgroups_fit_a_grid():
+    """2^23 + 3 rows: 512 threads per row would pass the 2^32 threads of a grid dimension.  One key per row, so the result
+    is its value row."""
+    n, D = (1 << 23) + 3, 64
+    q = torch.ones((n, 1, D), device=DEV)
+    K, V = torch.randn((7, 1, D), device=DEV), torch.randn((7, 1, D), device=DEV)
+    start = (torch.arange(n, device=DEV) * 7 // n).to(torch.int32)     # rows of one request lie together
+    out = torch.zeros((n, 1, D), device=DEV)
+    vlc.vlc_sparse_q_attention(q, K, V, start, torch.ones(n, device=DEV, dtype=torch.int32), 1.0, out)
+    assert torch.equal(out, V[start.long()])
+
+
 def test_attention_long_context_bf16():
     """7B head layout, S = 4500: rows at the start of each 'image' and a trailing text run."""
     S = 4500
