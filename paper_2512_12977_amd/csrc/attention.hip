@@ -765,6 +765,31 @@ int64_t attention_ws_bytes(int64_t n, int Hq, int Hkv, int D, int dtype) {
   return nsplit * n * Hq * (ATT_D + 2) * 4;
 }
 
+// Few workgroups (512 are resident at once, two per CU): the key loop of the longest rows is the critical path, so their
+// key range is shared out in pieces of split_blocks key blocks: as few blocks as keep the grid within 1024 workgroups
+// and 8 shares (the workspace), but at least 4 (shorter shares cost more in partials and merging than they save).  Without
+// a bound on the lengths: 8 blocks per share, the last share takes the rest.
+// 256 to 341 (row tile, kv head) pairs take three shares and not two, though two are faster where nearly half of the rows
+// are a text at the very end: 264 pairs of the 8B layout over 20800 keys, two / three shares, 280 / 224 us with rows
+// spread evenly, 283 / 225 with texts at both ends, 266 / 204 with most rows in front, 305 / 370 with the text at the end
+// (the lengths are not known here); the mean over such layouts changes sides at about 320 pairs.
+int attention_key_shares(int64_t n, int Hq, int Hkv, int64_t max_kv_len, int64_t ws_bytes, int* split_blocks) {
+  const int rows_per_tile = VR / (Hq / Hkv);
+  const int64_t pairs = (n + rows_per_tile - 1) / rows_per_tile * Hkv;
+  *split_blocks = 8;
+  if (pairs >= 512) return 1;
+  int shares = (int)(1024 / pairs);
+  if (shares > 8) shares = 8;
+  while (shares > 1 && (int64_t)shares * n * Hq * (ATT_D + 2) * 4 > ws_bytes) --shares;
+  if (max_kv_len > 0) {
+    const int64_t blocks = (max_kv_len + KB - 1) / KB;
+    *split_blocks = (int)((blocks + shares - 1) / shares);
+    if (*split_blocks < 4) *split_blocks = 4;
+    shares = (int)((blocks + *split_blocks - 1) / *split_blocks);
+  }
+  return shares;
+}
+
 int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const void* v_cache,
                      const int32_t* row_kv_start, const int32_t* row_kv_len, int64_t n, int Hq, int Hkv,
                      int D, float scale, void* out, int dtype, void* ws, int64_t ws_bytes, int64_t max_kv_len,
@@ -780,23 +805,8 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     // more registers than a wavefront has (147 spilled) and one wavefront per SIMD overlaps nothing.
     const int rows_per_tile = VR / g;
     const int64_t tiles = (n + rows_per_tile - 1) / rows_per_tile;
-    // Few workgroups (512 are resident at once, two per CU): the key loop of the longest rows is the
-    // critical path, so their key range is shared out in pieces of split_blocks key blocks: as few blocks as
-    // keep the grid within 1024 workgroups and 8 shares (the workspace), but at least 4 (shorter shares cost
-    // more in partials and merging than they save).  Without a bound on the lengths: 8 blocks per share, the
-    // last share takes the rest.
-    int nsplit = 1, split_blocks = 8;
-    if (ws && tiles * Hkv < 512) {
-      nsplit = tiles * Hkv >= 256 ? 2 : (int)(1024 / (tiles * Hkv));   // 296 pairs: two shares -26 us per layer against three
-      if (nsplit > 8) nsplit = 8;
-      while (nsplit > 1 && (int64_t)nsplit * n * Hq * (ATT_D + 2) * 4 > ws_bytes) --nsplit;
-      if (max_kv_len > 0) {
-        const int64_t blocks = (max_kv_len + KB - 1) / KB;
-        split_blocks = (int)((blocks + nsplit - 1) / nsplit);
-        if (split_blocks < 4) split_blocks = 4;
-        nsplit = (int)((blocks + split_blocks - 1) / split_blocks);
-      }
-    }
+    int split_blocks = 8;
+    const int nsplit = ws ? attention_key_shares(n, Hq, Hkv, max_kv_len, ws_bytes, &split_blocks) : 1;
     if (nsplit > 1) {
       float* part_o = static_cast<float*>(ws);
       float* part_ml = part_o + (int64_t)nsplit * n * Hq * ATT_D;
@@ -841,6 +851,13 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
 }
 
 }  // namespace vlc
+
+extern "C" int vlc_probe_attention_shares(int64_t n, int Hq, int Hkv, int64_t max_kv_len) {
+  if (n <= 0 || Hkv <= 0 || Hq <= 0 || Hq % Hkv || Hq / Hkv > vlc::VR) return 0;
+  int split_blocks;
+  return vlc::attention_key_shares(n, Hq, Hkv, max_kv_len, vlc::attention_ws_bytes(n, Hq, Hkv, vlc::ATT_D, VLC_BF16),
+                                   &split_blocks);
+}
 
 extern "C" int vlc_sparse_q_attention(const void* q, const void* k_cache, const void* v_cache,
                                       const int32_t* row_kv_start, const int32_t* row_kv_len, int64_t n,

@@ -97,6 +97,8 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
                      int D, float scale, void* out, int dtype, void* ws, int64_t ws_bytes, int64_t max_kv_len,
                      hipStream_t st);   // max_kv_len: upper bound of row_kv_len if known, else 0
 int64_t attention_ws_bytes(int64_t n, int Hq, int Hkv, int D, int dtype);
+// workgroups that share the key range of a (row tile, kv head) pair in the bf16 kernel, and the key blocks of a share
+int attention_key_shares(int64_t n, int Hq, int Hkv, int64_t max_kv_len, int64_t ws_bytes, int* split_blocks);
 
 enum Epilogue {
   EPI_BIAS = 0,      // C = A W^T + bias[n]               (bias may be NULL)
@@ -159,4 +161,10 @@ int launch_moe_combine_norm(const void* h1, const void* y, const float* wts, con
                             float eps, int dtype, hipStream_t st);
 
 }  // namespace vlc
+
+// What the dispatch rules choose, for tests (host only, not part of the C ABI).
+extern "C" {
+// key shares of the bf16 attention of a layer with n rows whose longest row sees max_kv_len keys
+int vlc_probe_attention_shares(int64_t n, int Hq, int Hkv, int64_t max_kv_len);
+}
 #endif

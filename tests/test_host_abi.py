@@ -323,6 +323,21 @@ def test_layer_forward_chained_argument_checks():
     assert f(a, None, None, None, None, None, None, None, 0, None, 1, None, None, None) == 1      # weights / plan
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(28, 4), (32, 8), (64, 8), (32, 4), (4, 2)])
+def test_attention_key_shares(Hq, Hkv):
+    """Shares of the key range by the number of (row tile, kv head) pairs: as many as keep the grid within 1024 workgroups,
+    8 at most, none from 512 pairs on, and no share shorter than four key blocks of 64."""
+    f = vlc.lib().vlc_probe_attention_shares
+    f.argtypes, f.restype = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64], ctypes.c_int
+    rows = 128 // (Hq // Hkv)
+    for pairs in list(range(Hkv, 640, Hkv)):
+        n = pairs // Hkv * rows - rows // 2
+        want = 1 if pairs >= 512 else min(8, 1024 // pairs)
+        assert f(n, Hq, Hkv, 64 * 840) == want, (pairs, n)          # 840: a multiple of 1 ... 8
+        for keys in (1, 64, 256, 257, 512, 1000, 2048):
+            assert f(n, Hq, Hkv, keys) <= max(1, -(-(-(-keys // 64)) // 4)), (pairs, keys)
+
+
 def test_header_is_plain_c_and_the_library_links_from_c(tmp_path):
     """include/vlcache.h compiles as C99 (-pedantic, warnings as errors) and a C program linked against the library
     gets the planner's result (host entry points only: no GPU needed)."""
