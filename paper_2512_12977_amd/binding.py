@@ -49,8 +49,7 @@ class LayerPlan(C.Structure):
 
 
 def lib_path() -> str:
-    """libvlcache.so beside this file; VLC_LIB names another build of the same library (e.g. one made with
-    `python -m paper_2512_12977_amd.build --tag T --define D` for an ablation measurement)."""
+    """libvlcache.so beside this file; VLC_LIB names another build of the same library."""
     return os.environ.get("VLC_LIB") or os.path.join(_HERE, "libvlcache.so")
 
 

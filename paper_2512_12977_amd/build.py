@@ -5,7 +5,6 @@ import os
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
-from typing import Sequence
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -24,21 +23,15 @@ def _hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def build(verbose: bool = True, tag: str = "", defines: Sequence[str] = ()) -> str:
-    """Compile every source and link the shared library; returns its path.  With a tag the result is
-    libvlcache_<tag>.so (beside the product library, which is left alone) built with the given -D macros:
-    the measurement variants of the kernels (see the VLC_ABLATE_* macros in csrc/attention.hip)."""
+def build(verbose: bool = True) -> str:
+    """Compile every source and link the shared library; returns its path."""
     hipcc = _hipcc()
-    objdir = os.path.join(HERE, "_build", tag) if tag else os.path.join(HERE, "_build")
+    objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    lib = os.path.join(HERE, "libvlcache_%s.so" % tag) if tag else LIB
-    if defines and not tag:
-        raise ValueError("macros change what the kernels compute: give the variant a tag")
-    extra = ["-D" + d for d in defines]
 
     def compile_one(src: str) -> str:
         obj = os.path.join(objdir, src + ".o")
-        cmd = [hipcc, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
         if r.returncode != 0:
@@ -49,13 +42,13 @@ def build(verbose: bool = True, tag: str = "", defines: Sequence[str] = ()) -> s
 
     with ThreadPoolExecutor(max_workers=6) as ex:
         objs = list(ex.map(compile_one, SOURCES))
-    cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs]
+    cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
     if verbose:
-        print("built", lib)
-    return lib
+        print("built", LIB)
+    return LIB
 
 
 def build_host_check(verbose: bool = False) -> str:
@@ -90,9 +83,4 @@ def build_host_check(verbose: bool = False) -> str:
 
 
 if __name__ == "__main__":
-    import argparse
-    ap = argparse.ArgumentParser()
-    ap.add_argument("--tag", default="", help="build libvlcache_<tag>.so instead of the product library")
-    ap.add_argument("--define", action="append", default=[], help="-D macro for a tagged measurement variant")
-    a = ap.parse_args()
-    build(tag=a.tag, defines=a.define)
+    build()

@@ -70,9 +70,6 @@ __device__ __forceinline__ int v_swz(int key, int c) { return c ^ ((key & 3) << 
 // The global address is a wavefront-uniform base (scalar registers) plus a 32-bit byte offset per lane, so a copy
 // needs no vector address arithmetic.
 __device__ __forceinline__ void dma16(const void* uniform_base, uint32_t lane_byte_off, u32x4* lds_dst) {
-#ifdef VLC_ABLATE_ATT_COPIES   // measurement build: no K/V tile ever reaches LDS (the rings hold pseudo-random values)
-  return;
-#endif
   const uint32_t a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_dst;
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
@@ -109,59 +106,6 @@ __device__ __forceinline__ int wave_max(int v) {
 }
 
 #define VLC_ATT_WAIT_VM0() __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8) | (0 << 14))
-
-// Measurement variants (python -m paper_2512_12977_amd.build --tag T --define VLC_ABLATE_...): each takes one
-// ingredient of the key loop out - the results are wrong, only the timing is of interest - to show what that
-// ingredient costs: the K or V^T fragment reads from LDS (all or every other one), the exponentials, the scale-and-subtract
-// in front of them, the S^T or the PV MFMAs, the workgroup barrier of a key block, the K/V copies into LDS.
-#ifdef VLC_ABLATE_K_READS
-#define VLC_ATT_KFRAG(expr_) (u32x4{(uint32_t)lane, 0x3c003c00u, (uint32_t)wave, 0x3c003c00u})
-#else
-#define VLC_ATT_KFRAG(expr_) (expr_)
-#endif
-#ifdef VLC_ABLATE_V_READS
-#define VLC_ATT_VFRAG(expr_) (s16x4{(short)lane, (short)0x3c00, (short)wave, (short)0x3c00})
-#else
-#define VLC_ATT_VFRAG(expr_) (expr_)
-#endif
-#ifdef VLC_ABLATE_EXP
-#define VLC_ATT_EXP2(x_) (x_)
-#else
-#define VLC_ATT_EXP2(x_) __builtin_amdgcn_exp2f(x_)
-#endif
-#ifdef VLC_ABLATE_SOFTMAX_FMA   // the exponent's argument without the scale-and-subtract (one vector op per score less)
-#define VLC_ATT_EXP_ARG(s_, scale_, m_) (s_)
-#else
-#define VLC_ATT_EXP_ARG(s_, scale_, m_) fmaf(s_, scale_, -(m_))
-#endif
-#ifdef VLC_ABLATE_HALF_READS    // every other K / V^T fragment read left out: each fragment read feeds two MFMAs
-#define VLC_ATT_READ_NOW(i_) (((i_) & 1) == 0)
-#define VLC_ATT_FRAG_BUF(i_) (((i_) >> 1) & 1)
-#else
-#define VLC_ATT_READ_NOW(i_) true
-#define VLC_ATT_FRAG_BUF(i_) ((i_) & 1)
-#endif
-#ifdef VLC_ABLATE_BLOCK_BARRIER // no workgroup barrier per key block (LDS addresses do not depend on what is read)
-#define VLC_ATT_BLOCK_BARRIER()
-#else
-#define VLC_ATT_BLOCK_BARRIER() __syncthreads()
-#endif
-#if defined(VLC_ABLATE_QK_MFMA) || defined(VLC_ABLATE_PV_MFMA)
-__device__ __forceinline__ f32x16 ablated_mfma(bf16x8 a, bf16x8 b, f32x16 c) {   // one vector op that keeps the data flow
-  c[0] += (float)a[0] * (float)b[0];
-  return c;
-}
-#endif
-#ifdef VLC_ABLATE_QK_MFMA
-#define VLC_ATT_MFMA_QK(a_, b_, c_) ablated_mfma(a_, b_, c_)
-#else
-#define VLC_ATT_MFMA_QK(a_, b_, c_) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, b_, c_, 0, 0, 0)
-#endif
-#ifdef VLC_ABLATE_PV_MFMA
-#define VLC_ATT_MFMA_PV(a_, b_, c_) ablated_mfma(a_, b_, c_)
-#else
-#define VLC_ATT_MFMA_PV(a_, b_, c_) __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_, b_, c_, 0, 0, 0)
-#endif
 
 // Block id -> (kv head, row tile); tile < 0: none.  XCD = id % 8.  With share = 8 / Hkv XCDs per kv head (Hkv divides 8)
 // XCD x works on head x / share and takes tiles x % share, x % share + share, ...; otherwise the (head, tile) pairs in
@@ -207,18 +151,6 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, x = lane >> 5;
-#ifdef VLC_ABLATE_ATT_COPIES
-  // pseudo-random finite bf16 values, so that the MFMAs draw the power of a real product
-  for (int i = tid; i < 2 * ATT_STAGE_CHUNKS; i += 256) {
-    uint32_t h = (uint32_t)i * 2654435761u + blockIdx.x * 40503u;
-    u32x4 v;
-    for (int e = 0; e < 4; ++e) {
-      h ^= h >> 13; h *= 0x5bd1e995u; h ^= h >> 15;
-      v[e] = (h & 0x807f807fu) | 0x3f003f00u;
-    }
-    lds[i] = v;
-  }
-#endif
   // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Every XCD works on one kv head at a time, so
   // that the workgroups resident on it stream the same K/V; XCDs that share a kv head (fewer than 8) take its row tiles
   // in turn, because later tiles see more keys: contiguous halves leave the XCD with the early rows idle a third of
@@ -388,14 +320,14 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
       _Pragma("unroll") for (int mt = 0; mt < 2; ++mt)                                                         \
         _Pragma("unroll") for (int e = 0; e < 16; ++e) ST[rt][mt][e] = 0.f;                                    \
     u32x4 kf_[2];   /* fragment i+1 is read while fragment i is multiplied */                                  \
-    kf_[0] = VLC_ATT_KFRAG(*reinterpret_cast<const u32x4*>(sk_ + k_rd[0]));                                    \
+    kf_[0] = *reinterpret_cast<const u32x4*>(sk_ + k_rd[0]);                                                  \
     _Pragma("unroll") for (int i = 0; i < 2 * (ATT_D / 16); ++i) {                                             \
       const int mt = i / (ATT_D / 16), ks = i % (ATT_D / 16);                                                  \
-      if (i + 1 < 2 * (ATT_D / 16) && VLC_ATT_READ_NOW(i + 1))                                                 \
-        kf_[VLC_ATT_FRAG_BUF(i + 1)] = VLC_ATT_KFRAG(*reinterpret_cast<const u32x4*>(sk_ + k_rd[(i + 1) % (ATT_D / 16)] +  \
-                                                                         ((i + 1) / (ATT_D / 16)) * (32 * 256))); \
+      if (i + 1 < 2 * (ATT_D / 16))                                                                           \
+        kf_[(i + 1) & 1] = *reinterpret_cast<const u32x4*>(sk_ + k_rd[(i + 1) % (ATT_D / 16)] +               \
+                                                                         ((i + 1) / (ATT_D / 16)) * (32 * 256)); \
       _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                                        \
-        ST[rt][mt] = VLC_ATT_MFMA_QK(__builtin_bit_cast(bf16x8, kf_[VLC_ATT_FRAG_BUF(i)]), qf[rt][ks], ST[rt][mt]); \
+        ST[rt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf_[i & 1]), qf[rt][ks], ST[rt][mt], 0, 0, 0); \
     }                                                                                                          \
   }
     // keys of the block beyond a lane's visible range are masked (only where the block crosses it)
@@ -428,7 +360,7 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
       float psum_ = 0.f;                                                                                       \
       _Pragma("unroll") for (int mt = 0; mt < 2; ++mt)                                                         \
         _Pragma("unroll") for (int j = 0; j < 16; ++j) {                                                       \
-          const float p_ = VLC_ATT_EXP2(VLC_ATT_EXP_ARG(ST[rt][mt][j], scale_log2, m_use_));                             \
+          const float p_ = __builtin_amdgcn_exp2f(fmaf(ST[rt][mt][j], scale_log2, -m_use_));                  \
           ST[rt][mt][j] = p_;                                                                                  \
           psum_ += p_;                                                                                         \
         }                                                                                                      \
@@ -458,15 +390,15 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     bf16x8 pf_[RT];                                                                                            \
     s16x4 vh_[2][2];   /* V^T fragment i+1 is read while fragment i is multiplied */                           \
     _Pragma("unroll") for (int r = 0; r < 2; ++r)                                                              \
-      vh_[0][r] = VLC_ATT_VFRAG(__builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)( \
-          const_cast<unsigned char*>(sv_) + v_rd[0] + (8 * r) * 256)));                                        \
+      vh_[0][r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(         \
+          const_cast<unsigned char*>(sv_) + v_rd[0] + (8 * r) * 256));                                        \
     _Pragma("unroll") for (int i = 0; i < 4 * (ATT_D / 32); ++i) {                                             \
       const int t = i / (ATT_D / 32), md = i % (ATT_D / 32);                                                   \
-      if (i + 1 < 4 * (ATT_D / 32) && VLC_ATT_READ_NOW(i + 1)) {                                               \
+      if (i + 1 < 4 * (ATT_D / 32)) {                                                                         \
         const int t1 = (i + 1) / (ATT_D / 32), md1 = (i + 1) % (ATT_D / 32);                                   \
         _Pragma("unroll") for (int r = 0; r < 2; ++r)                                                          \
-          vh_[VLC_ATT_FRAG_BUF(i + 1)][r] = VLC_ATT_VFRAG(__builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)( \
-              const_cast<unsigned char*>(sv_) + v_rd[md1] + (16 * t1 + 8 * r) * 256)));                        \
+          vh_[(i + 1) & 1][r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)( \
+              const_cast<unsigned char*>(sv_) + v_rd[md1] + (16 * t1 + 8 * r) * 256));                        \
       }                                                                                                        \
       if (md == 0) {                                                                                           \
         _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                                      \
@@ -477,9 +409,9 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
             pf_[rt][2 * e + 1] = pb_[1];                                                                       \
           }                                                                                                    \
       }                                                                                                        \
-      const s16x8 vv_ = __builtin_shufflevector(vh_[VLC_ATT_FRAG_BUF(i)][0], vh_[VLC_ATT_FRAG_BUF(i)][1], 0, 1, 2, 3, 4, 5, 6, 7); \
+      const s16x8 vv_ = __builtin_shufflevector(vh_[i & 1][0], vh_[i & 1][1], 0, 1, 2, 3, 4, 5, 6, 7);        \
       _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                                        \
-        o_acc[rt][md] = VLC_ATT_MFMA_PV(__builtin_bit_cast(bf16x8, vv_), pf_[rt], o_acc[rt][md]);              \
+        o_acc[rt][md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv_), pf_[rt], o_acc[rt][md], 0, 0, 0); \
     }                                                                                                          \
   }
     // One key block j (S^T already in CUR): fetch ahead, start the next block's S^T into NXT (its MFMAs
@@ -504,7 +436,7 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
       __builtin_amdgcn_s_setprio(0);                                                                           \
     }                                                                                                          \
     VLC_ATT_WAIT_VM0();   /* this wavefront's shares of the tiles fetched above have landed */                 \
-    VLC_ATT_BLOCK_BARRIER();                                                                                   \
+    __syncthreads();                                                                                          \
   }
 
     __syncthreads();                 // the rings are free (previous run finished reading them)
