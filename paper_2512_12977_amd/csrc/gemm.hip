@@ -468,7 +468,7 @@ __global__ __launch_bounds__(256) void splitk_epilogue_kernel(const float* __res
 #pragma unroll
   for (int k = 0; k < 8; ++k)
     if (k < splits) { s.x += part[k].x; s.y += part[k].y; s.z += part[k].z; s.w += part[k].w; }
-  if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_F32) {
+  if constexpr (EPI == EPI_BIAS_F32) {
     if (bias) {
       const uint2 b = *reinterpret_cast<const uint2*>(bias + n);
       s.x += __uint_as_float(b.x << 16); s.y += __uint_as_float(b.x & 0xffff0000u);
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const float* __restric
     const int m = tm * BM + r0 + ml, n = tn * CN + 4 * (q0 + ql);
     if (m >= M || n >= N || q0 + ql >= QN) continue;
     float4 s = turned[ml][ql];
-    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_F32) {
+    if constexpr (EPI == EPI_BIAS_F32) {
       if (bias) {
         const uint2 b = *reinterpret_cast<const uint2*>(bias + n);
         s.x += __uint_as_float(b.x << 16); s.y += __uint_as_float(b.x & 0xffff0000u);
@@ -1043,7 +1043,6 @@ int launch_gemm(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
       return fail(VLC_ERR_SHAPE, "gemm(bf16): a tile's rows span more than 2 GiB (lda=%lld N=%lld K=%lld)",
                   (long long)lda, (long long)N, (long long)K);
     switch (epilogue) {
-      case EPI_BIAS: return dispatch_bf16<EPI_BIAS>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, splitk_ws, splitk_ws_bytes, deferred, st);
       case EPI_BIAS_F32: return dispatch_bf16<EPI_BIAS_F32>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, splitk_ws, splitk_ws_bytes, deferred, st);
       case EPI_RESIDUAL: return dispatch_bf16<EPI_RESIDUAL>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, splitk_ws, splitk_ws_bytes, deferred, st);
       case EPI_SWIGLU: return dispatch_bf16<EPI_SWIGLU>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, splitk_ws, splitk_ws_bytes, deferred, st);

@@ -101,10 +101,10 @@ int64_t attention_ws_bytes(int64_t n, int Hq, int Hkv, int D, int dtype);
 int attention_key_shares(int64_t n, int Hq, int Hkv, int64_t max_kv_len, int64_t ws_bytes, int* split_blocks);
 
 enum Epilogue {
-  EPI_BIAS = 0,      // C = A W^T + bias[n]               (bias may be NULL)
+  EPI_BIAS = 0,      // C = A W^T + bias[n]               (bias may be NULL); bf16: grouped products only
   EPI_RESIDUAL = 1,  // C = A W^T + resid[rmap ? rmap[m] : m, n]
   EPI_SWIGLU = 2,    // W = [gate(I rows); up(I rows)], C[m, j] = silu(A Wg^T)[m,j] * (A Wu^T)[m,j], N = I
-  EPI_BIAS_F32 = 3   // as EPI_BIAS but C is a float matrix whatever the input type (no rounding)
+  EPI_BIAS_F32 = 3   // C = A W^T + bias[n], C a float matrix whatever the input type (no rounding)
 };
 // C[M,N] = epilogue(A[M,K] (row stride lda) * W[N(or 2N),K]^T); C row stride ldc.
 // splitk_ws: optional float scratch for split-K partials (used when the output has few tiles);
