@@ -94,7 +94,7 @@ __device__ __forceinline__ int fswz(int row) { return (row & 7) ^ ((row >> 3) & 
 // keeps a live value in M0 across statements (it is reserved and written right before each use).
 // The global address is a wavefront-uniform base (scalar registers) plus a 32-bit byte offset per lane: the lane
 // offsets never change, the base moves along k with scalar adds, so the k-loop holds no vector address arithmetic
-// (a vector instruction of a wavefront does not overlap with its own MFMAs).
+// (a wavefront's own vector instructions run under its MFMAs, but only about five of them per 32-cycle MFMA).
 __device__ __forceinline__ void dma16(const void* uniform_base, uint32_t lane_byte_off, uint32_t lds_byte_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
@@ -708,6 +708,23 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   }
 }
 
+// Tail split: the chip holds `slots` workgroups at once; the tiles of the last, partly filled round are shared out over as
+// many k ranges as fit into the idle slots and the scratch, at least 8 k-tiles each.  ways = 1: not split.
+struct LastRound {
+  int tiles, ways, kt;   // tiles of the last round, k ranges per tile, k-tiles per range
+};
+LastRound split_last_round(int64_t tiles, int slots, int KT, int64_t block_bytes, int64_t ws_bytes) {
+  LastRound r = {(int)(tiles % slots), 1, KT};
+  if (r.tiles == 0 || tiles < slots) return r;
+  int64_t ways = slots / r.tiles;
+  if (ways > KT / 8) ways = KT / 8;
+  if (ways > ws_bytes / (r.tiles * block_bytes)) ways = ws_bytes / (r.tiles * block_bytes);
+  if (ways < 2) return r;
+  r.kt = (int)((KT + ways - 1) / ways);
+  r.ways = (KT + r.kt - 1) / r.kt;
+  return r;
+}
+
 template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI>
 int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc, int64_t M, int64_t N,
                 int64_t K, const void* bias, const void* resid, int64_t ldr, const int32_t* rmap, int splits,
@@ -718,26 +735,15 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
   const size_t lds = (size_t)STAGES * (BM + BN) * BK * 2;
   auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI>;
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
-  // Tail split: the chip holds `slots` workgroups at once; the tiles of the last, partly filled round are
-  // shared out over as many k-ranges as fit into the idle slots (at least 8 k-tiles each).
-  constexpr int slots = 256 * OCC;
   const int KT = (int)(K / BK);
   int full = tiles * splits, tail = 0, tsp = 1, tkt = kt_per_split;
   if constexpr (EPI != EPI_PARTIAL) {
-    tail = tiles % slots;
-    if (tail_ws && tail > 0 && tiles > tail) {
-      tsp = slots / tail;
-      if (tsp > KT / 8) tsp = KT / 8;
-      const int64_t fit = tail_ws_bytes / ((int64_t)tail * BM * BN * 4);
-      if (tsp > fit) tsp = (int)fit;
-    }
-    if (tsp >= 2) {
-      tkt = (KT + tsp - 1) / tsp;
-      tsp = (KT + tkt - 1) / tkt;
+    const LastRound r = split_last_round(tiles, 256 * OCC, KT, (int64_t)BM * BN * 4, tail_ws ? tail_ws_bytes : 0);
+    if (r.ways > 1) {
+      tail = r.tiles;
+      tsp = r.ways;
+      tkt = r.kt;
       full = tiles - tail;
-    } else {
-      tail = 0;
-      tsp = 1;
     }
   }
   hipLaunchKernelGGL(kern, dim3(full + tail * tsp), dim3(WGM * WGN * 64), lds, st, (const uint16_t*)A, lda,
@@ -758,28 +764,38 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
 
 // Tile choice.  Every configuration runs its k-loop at 1.1 ... 1.35 PFLOP/s when the chip is full of its workgroups, so
 // what decides is how well the product's tiles fill whole rounds of the 256 CUs and how much of them is padding; with few
-// rows, how many bytes of W are in flight.  The list therefore spans the tile areas from 64 x 128 to 256 x 256, each
-// with the deepest ring that fits the LDS (one workgroup per CU: an HBM miss takes longer than one k-tile, so a two-stage
-// ring cannot run a k-tile in under 1 us however small it is), and the cheapest by the model below is launched.
+// rows, how many bytes of W are in flight.  The list therefore spans the tile areas from 64 x 128 to 256 x 256, and the
+// cheapest by the model below is launched.  Rings of three or four stages where the LDS holds them (an HBM miss takes longer
+// than a small k-tile, so a two-stage ring cannot run one in under 1 us); the deepest that fit gain no more: 128 x 128 on five
+// stages is 2-3 % slower than on four, 128 x 192 on four as fast as on three, 64 x 128 on six as fast as on four.
 //
-// Per configuration: time of one k-tile (us) with few workgroups on the chip and with all CUs busy (shared bandwidth,
-// power), measured over 33 ... 930 rows at three decoder shapes.
-//     BM   BN  WGM WGN STAGES OCC  light  full
-#define VLC_GEMM_TILES(X)                \
-  X(64, 128, 1, 4, 6, 1, 0.45f, 0.50f)   \
-  X(64, 192, 2, 2, 5, 1, 0.60f, 0.65f)   \
-  X(128, 128, 2, 2, 4, 1, 0.46f, 0.50f)  \
-  X(128, 160, 4, 1, 4, 1, 0.57f, 0.68f)  \
-  X(128, 192, 2, 2, 3, 1, 0.58f, 0.70f)  \
-  X(128, 256, 2, 2, 3, 1, 0.72f, 0.92f)  \
-  X(192, 128, 2, 2, 4, 1, 0.55f, 0.68f)  \
-  X(192, 192, 2, 2, 3, 1, 0.75f, 0.95f)  \
-  X(160, 256, 1, 4, 3, 1, 0.80f, 1.07f)  \
-  X(192, 256, 2, 2, 2, 1, 1.07f, 1.28f)  \
-  X(320, 192, 2, 2, 2, 1, 1.02f, 1.48f)  \
-  X(256, 256, 4, 2, 2, 1, 1.15f, 1.62f)  \
-  X(128, 160, 4, 1, 2, 2, 0.77f, 1.15f)  \
-  X(128, 192, 2, 2, 2, 2, 0.81f, 1.30f)
+// Per configuration: time of one k-tile (us) with few workgroups on the chip, with one full round of them and with many
+// rounds (power).  All numbers of the model were fitted together, to the stage times of 1500 products of 2 ... 24000 rows in
+// four decoder shapes and of the heads, with every tile, every number of k ranges and both ends of a last round, so that its
+// choice is as little slower as possible than the best of them: 0.6 % on average there, 0.8 % at a fifth shape that the fit
+// did not see (the prices before, from 33 ... 930 rows: 2.0 and 1.5 %, up to 8 % at many rows).
+// USE: 0 all epilogues, 1 all but SwiGLU, 2 SwiGLU only, 3 float output without scratch (the heads; in the layers never the
+// fastest).  256 x 256: gate|up on 4 wavefronts of 128 x 128, the others on 8 of 64 x 128 (no spilled registers around the
+// loop; the projection with float output gains 8 %, gate|up would lose 2 %).
+//     BM   BN  WGM WGN STAGES OCC USE light  full  many
+#define VLC_GEMM_TILES(X)                             \
+  X(64, 128, 2, 2, 4, 1, 0, 0.460f, 0.390f, 0.423f)     \
+  X(128, 128, 2, 2, 4, 1, 0, 0.637f, 0.524f, 0.488f)    \
+  X(128, 160, 4, 1, 4, 1, 0, 0.498f, 0.633f, 0.685f)    \
+  X(128, 256, 2, 2, 3, 1, 0, 0.704f, 0.886f, 1.010f)    \
+  X(192, 128, 2, 2, 4, 1, 1, 0.698f, 0.691f, 0.866f)    \
+  X(192, 192, 2, 2, 3, 1, 0, 0.816f, 0.889f, 1.066f)    \
+  X(160, 256, 1, 4, 3, 1, 0, 0.812f, 1.037f, 1.080f)    \
+  X(192, 256, 2, 2, 2, 1, 0, 0.807f, 1.272f, 1.256f)    \
+  X(320, 192, 2, 2, 2, 1, 0, 1.146f, 1.475f, 1.432f)    \
+  X(256, 256, 4, 2, 2, 1, 1, 1.458f, 1.599f, 1.524f)    \
+  X(128, 192, 2, 2, 2, 2, 0, 0.980f, 1.485f, 1.314f)    \
+  X(256, 256, 2, 2, 2, 1, 2, 1.459f, 1.480f, 1.571f)    \
+  X(128, 160, 4, 1, 2, 2, 3, 0.942f, 0.949f, 1.237f)    \
+  X(128, 192, 2, 2, 3, 1, 1, 0.639f, 0.724f, 1.008f)
+constexpr bool tile_serves(int use, int epi) {
+  return use == 0 || (use == 1 && epi != EPI_SWIGLU) || (use == 2 && epi == EPI_SWIGLU) || (use == 3 && epi == EPI_BIAS_F32);
+}
 
 struct TileChoice {
   int index;        // into VLC_GEMM_TILES
@@ -787,42 +803,68 @@ struct TileChoice {
   bool split_tail;  // share the last round's tiles out along k
 };
 
-// Cost model (us): rounds of resident workgroups, each its k-tiles plus a start and an end; the weights can arrive no
-// faster than HBM delivers; the partials of a split k range are read back by the kernel that sums them, the blocks of a
-// split last round by tail_reduce_kernel.
-TileChoice choose_tile(int64_t M, int64_t N, int64_t K, bool swiglu, bool may_split, int64_t ws_bytes) {
-  struct Tile { int bm, bn, occ; float light, full; };
-#define X(BM, BN, WGM, WGN, S, OCC, L, F) {BM, BN, OCC, L, F},
+// Price (us) of a product: rounds of resident workgroups, each its k-tiles plus a start and an end.  A k-tile takes the
+// longer of its multiplication and of the arrival of the weights that the resident workgroups ask for in that time (HBM), and
+// a little of the other.  A split k range costs the kernel that sums the partials its reading (the RoPE kernel more than
+// the norms); as a kernel of its own also a launch.  A split last round costs tail_reduce_kernel.
+constexpr float kPriceHbm = 6.91e6f;          // bytes per us of weights
+constexpr float kPriceHbmAligned = 0.62f;     // share of it left when all k ranges start at multiples of 4 KiB (one channel)
+constexpr float kPriceOther = 0.070f;         // share of the shorter of the two that shows
+constexpr float kPriceRounds = 2.13f;         // rounds past the first after which a k-tile takes its "many" time
+constexpr float kPriceEnds = 2.73f, kPriceEndsArea = 3.61f;            // start and end: per workgroup, per 256 x 256 outputs
+constexpr float kPriceEndsFloat = 0.72f;                               // more of the latter for float output
+constexpr float kPriceEnds8 = 0.74f, kPriceEndsFloat8 = 0.56f;         // the last two on eight wavefronts, as shares
+constexpr float kPriceTail = 6.85f, kPriceTailElem = 1.69e-6f;         // split last round: launch, per float of its blocks
+constexpr float kPriceSumQkv = 1.58f, kPriceSumQkvElem = 1.47e-6f;     // split k range: per launch, per partial sum
+constexpr float kPriceSum = 1.40f, kPriceSumElem = 1.01e-6f;
+constexpr float kPriceSumLaunch = 2.5f;       // not deferred to the caller's next kernel
+// The two-per-CU tile of the heads against 64 x 128, 151936 output rows, 1 / 8 / 64 requests: K = 2048 140 / 142 / 163 against
+// 127 / 133 / 162 us (rows start 4 KiB apart, which the prices do not know; 128 requests 187 against 191 for the next best),
+// 2560 145 / 150 / 180 against 143 / 151 / 186, 8192 424 / 432 / 465 against 439 / 442 / 484.
+constexpr int64_t kHeadTileK = 2560;
+
+TileChoice choose_tile(int64_t M, int64_t N, int64_t K, int epi, bool deferred, int64_t ws_bytes) {
+  struct Tile { int bm, bn, waves, occ, use; float light, full, many; };
+#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA) {BM, BN, WGM * WGN, OCC, USE, L, F, MA},
   static constexpr Tile kTiles[] = {VLC_GEMM_TILES(X)};
 #undef X
   constexpr int kCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
   const int KT = (int)(K / BK);
-  const float weight_us = (float)(swiglu ? 2 * N : N) * (float)K * 2.0f / 5.67e6f;
-  TileChoice best = {0, 1, false};
+  const bool float_out = epi == EPI_BIAS_F32, may_split = epi != EPI_SWIGLU && ws_bytes > 0;
+  TileChoice best = {-1, 1, false};
   float best_us = 0.f;
   for (int i = 0; i < kCount; ++i) {
     const Tile& t = kTiles[i];
-    const int cn = swiglu ? t.bn / 2 : t.bn;
-    const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + cn - 1) / cn);
-    const int64_t slots = 256 * t.occ;
-    const float area = (float)(t.bm * t.bn), ends = 2.5f + 2.5f * (float)t.occ * area / 65536.0f;
-    auto round_us = [&](int64_t wgs, int kt) {   // one round of wgs <= slots workgroups of kt k-tiles
-      return (float)kt * (t.light + (t.full - t.light) * (float)wgs / (float)slots) + ends;
-    };
+    if (!tile_serves(t.use, epi) || (t.use == 3 && (ws_bytes > 0 || (M <= 64 && K < kHeadTileK)))) continue;
+    const int cn = epi == EPI_SWIGLU ? t.bn / 2 : t.bn;
+    const int64_t tiles_m = (M + t.bm - 1) / t.bm, tiles = tiles_m * ((N + cn - 1) / cn);
+    const int slots = 256 * t.occ;
+    const float area = (float)(t.bm * t.bn), area_share = (float)t.occ * area / 65536.0f;
+    const bool eight = t.waves == 8;
     for (int sp = 1; sp <= (may_split ? 8 : 1); ++sp) {
       if (sp > 1 && (KT / sp < 4 || (int64_t)sp * M * N * 4 > ws_bytes)) break;
       const int per = (KT + sp - 1) / sp;
       const int64_t wgs = tiles * ((KT + per - 1) / per), full = wgs / slots, tail = wgs % slots;
+      float ends = kPriceEnds + kPriceEndsArea * (eight ? kPriceEnds8 : 1.0f) * area_share;
+      if (float_out || sp > 1) ends += kPriceEndsFloat * (eight ? kPriceEndsFloat8 : 1.0f) * area_share;
+      float later = ((float)wgs / (float)slots - 1.0f) / kPriceRounds;
+      later = later < 0.f ? 0.f : (later > 1.f ? 1.f : later);
+      const float busy = t.full + (t.many - t.full) * later;
+      // weights asked for per k-tile by n workgroups: those of a column tile (and k range) share them
+      const float hbm_us = (float)t.bn * (float)(BK * 2) / (float)tiles_m / (kPriceHbm * (sp > 1 && per % 32 == 0 ? kPriceHbmAligned : 1.0f));
+      auto round_us = [&](int64_t n, int kt) {   // one round of n <= slots workgroups of kt k-tiles
+        const float m = t.light + (busy - t.light) * (float)n / (float)slots, h = (float)n * hbm_us;
+        return (float)kt * (m > h ? m + kPriceOther * h : h + kPriceOther * m) + ends;
+      };
       float us = (float)full * round_us(slots, per);
       bool split_tail = false;
       if (tail > 0) {
         float tail_us = round_us(tail, per);
-        if (sp == 1 && full > 0) {
-          int64_t tsp = slots / tail < KT / 8 ? slots / tail : KT / 8;
-          const int64_t fit = ws_bytes / (tail * (int64_t)(area * 4.0f));
-          if (tsp > fit) tsp = fit;
-          if (tsp >= 2) {
-            const float shared = round_us(tail * tsp, (int)((KT + tsp - 1) / tsp)) + 5.0f + (float)(tail * tsp) * area * 1.6e-6f;
+        if (sp == 1) {
+          const LastRound r = split_last_round(tiles, slots, KT, (int64_t)t.bm * t.bn * 4, ws_bytes);
+          if (r.ways > 1) {
+            const int64_t blocks = (int64_t)r.tiles * r.ways;
+            const float shared = round_us(blocks, r.kt) + kPriceTail + (float)blocks * area * kPriceTailElem;
             if (shared < tail_us) {
               tail_us = shared;
               split_tail = true;
@@ -831,9 +873,10 @@ TileChoice choose_tile(int64_t M, int64_t N, int64_t K, bool swiglu, bool may_sp
         }
         us += tail_us;
       }
-      us = (us < weight_us ? weight_us : us) + 0.05f * us;   // among those that HBM holds up: the cheaper k-loop
-      if (sp > 1) us += 2.5f + (float)sp * (float)M * (float)N * 1.0e-6f;
-      if ((i == 0 && sp == 1) || us < best_us) {
+      if (sp > 1)
+        us += (float_out ? kPriceSumQkv : kPriceSum) + (deferred ? 0.f : kPriceSumLaunch) +
+              (float)sp * (float)M * (float)N * (float_out ? kPriceSumQkvElem : kPriceSumElem);
+      if (best.index < 0 || us < best_us) {
         best_us = us;
         best = {i, sp, split_tail};
       }
@@ -847,23 +890,17 @@ int dispatch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ld
                   int64_t K, const void* bias, const void* resid, int64_t ldr, const int32_t* rmap,
                   void* splitk_ws, int64_t splitk_ws_bytes, int* deferred, hipStream_t st) {
   const int KT = (int)(K / BK);
-  if constexpr (EPI == EPI_BIAS_F32) {
-    // The first-token head: a few requests against a whole output matrix, no k split.  With a short k range the start and
-    // end of a workgroup count: 64 x 128 tiles on a four-stage ring take 136 ... 167 us for 1 ... 64 requests at
-    // 151936 x 2048 (128 x 160 tiles, the choice of the model: 152 ... 173), 190 ... 235 at 152064 x 3584 (193 ... 227).
-    if (M <= 64 && !splitk_ws && K < 3072)
-      return launch_bf16<64, 128, 2, 2, 4, 1, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT, nullptr, 0, st);
-  }
-  const bool may_split = EPI != EPI_SWIGLU && splitk_ws;
-  const TileChoice c = choose_tile(M, N, K, EPI == EPI_SWIGLU, may_split, splitk_ws ? splitk_ws_bytes : 0);
+  const TileChoice c = choose_tile(M, N, K, EPI, deferred != nullptr, splitk_ws ? splitk_ws_bytes : 0);
   if (c.splits > 1) {
     if constexpr (EPI != EPI_SWIGLU) {
       const int per = (KT + c.splits - 1) / c.splits, splits = (KT + per - 1) / per;
       int rc = VLC_OK, i = 0;
-#define X(BM, BN, WGM, WGN, S, OCC, L, F)                                                                         \
-  if (c.index == i++)                                                                                             \
-    rc = launch_bf16<BM, BN, WGM, WGN, S, OCC, EPI_PARTIAL>(A, lda, W, splitk_ws, N, M, N, K, nullptr, nullptr, 0, \
-                                                            nullptr, splits, per, nullptr, 0, st);
+#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA)                                                                    \
+  if (c.index == i++) {                                                                                              \
+    if constexpr (USE != 3 && tile_serves(USE, EPI))                                                                 \
+      rc = launch_bf16<BM, BN, WGM, WGN, S, OCC, EPI_PARTIAL>(A, lda, W, splitk_ws, N, M, N, K, nullptr, nullptr, 0, \
+                                                              nullptr, splits, per, nullptr, 0, st);                 \
+  }
       VLC_GEMM_TILES(X)
 #undef X
       if (rc) return rc;
@@ -881,12 +918,12 @@ int dispatch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ld
   }
   void* tail_ws = c.split_tail ? splitk_ws : nullptr;
   int i = 0;
-  // 256 x 256: gate|up on 4 wavefronts of 128 x 128, the others on 8 of 64 x 128 (no spilled registers around the
-  // loop; the projection with float output gains 8 %, gate|up would lose 2 %)
-#define X(BM, BN, WGM, WGN, S, OCC, L, F)                                                                            \
-  if (c.index == i++)                                                                                                \
-    return launch_bf16<BM, BN, BM == 256 && EPI == EPI_SWIGLU ? 2 : WGM, WGN, S, OCC, EPI>(                          \
-        A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT, tail_ws, splitk_ws_bytes, st);
+#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA)                                                                      \
+  if (c.index == i++) {                                                                                                \
+    if constexpr (tile_serves(USE, EPI))                                                                               \
+      return launch_bf16<BM, BN, WGM, WGN, S, OCC, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT,      \
+                                                        tail_ws, splitk_ws_bytes, st);                                 \
+  }
   VLC_GEMM_TILES(X)
 #undef X
   return fail(VLC_ERR_SHAPE, "gemm(bf16): no tile");
@@ -1060,3 +1097,21 @@ int launch_gemm(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
 }
 
 }  // namespace vlc
+
+extern "C" int vlc_probe_gemm_choice(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred, int32_t* out) {
+  if (M <= 0 || N <= 0 || K < vlc::BK || K % vlc::BK || !out) return VLC_ERR_SHAPE;
+  const int64_t ws = scratch ? vlc::gemm_splitk_ws_bytes(M, N) : 0;
+  const vlc::TileChoice c = vlc::choose_tile(M, N, K, epilogue, deferred != 0, ws);
+  int i = 0;
+#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA)                                                               \
+  if (c.index == i++) {                                                                                          \
+    const int64_t cn = epilogue == vlc::EPI_SWIGLU ? BN / 2 : BN;                                                \
+    const int64_t tiles = ((M + BM - 1) / BM) * ((N + cn - 1) / cn);                                             \
+    const vlc::LastRound r = vlc::split_last_round(tiles, 256 * OCC, (int)(K / vlc::BK), (int64_t)BM * BN * 4, ws); \
+    const int32_t o[5] = {BM, BN, OCC, c.splits, c.splits == 1 && c.split_tail ? r.ways : 1};                    \
+    for (int e = 0; e < 5; ++e) out[e] = o[e];                                                                   \
+  }
+  VLC_GEMM_TILES(X)
+#undef X
+  return VLC_OK;
+}

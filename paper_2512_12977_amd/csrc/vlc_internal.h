@@ -166,5 +166,9 @@ int launch_moe_combine_norm(const void* h1, const void* y, const float* wts, con
 extern "C" {
 // key shares of the bf16 attention of a layer with n rows whose longest row sees max_kv_len keys
 int vlc_probe_attention_shares(int64_t n, int Hq, int Hkv, int64_t max_kv_len);
+// bf16 product with one of the Epilogue values (EPI_BIAS_F32, EPI_RESIDUAL, EPI_SWIGLU; N as in launch_gemm), with or without
+// a layer's float scratch: out = {tile rows, tile columns (SwiGLU: gate and up), workgroups per CU, k ranges of the whole
+// product, k ranges of the tiles of its last round}
+int vlc_probe_gemm_choice(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred, int32_t* out);
 }
 #endif

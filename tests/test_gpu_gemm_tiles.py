@@ -1,0 +1,147 @@
+"""The bf16 products of a layer on every tile configuration that the dispatcher launches: whole, with a split k range, and with
+a last round whose tiles are split along k.  The layers below are small stand-ins (a few columns, many rows, or the other
+way round) whose products land on each of them; what a product lands on is asked of the library, so that a change of the
+prices cannot move the cases away from the kernels unnoticed."""
+import ctypes
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2512_12977_amd as vlc
+import vlc_synth as syn
+from paper_2512_12977_amd import runner as R
+
+DEV = "cuda"
+RESIDUAL, SWIGLU, FLOAT = 1, 2, 3
+
+# (hidden size, MLP width, query heads, kv heads, rows); rows and columns are ragged against most of the tiles
+LAYERS = [
+    (320, 128, 4, 1, 4), (704, 448, 5, 1, 2712), (2176, 448, 1, 1, 5552), (320, 1472, 4, 4, 3238), (2368, 448, 1, 1, 2448),
+    (704, 3264, 16, 8, 3275), (448, 1664, 8, 4, 4107), (3136, 1088, 1, 1, 3661), (2240, 128, 1, 1, 2835),
+    (448, 3776, 7, 1, 6194), (3008, 128, 2, 2, 1942), (7040, 192, 2, 1, 3255), (896, 256, 5, 1, 9865),
+    (896, 512, 7, 1, 8465), (256, 2752, 1, 1, 2113), (704, 3328, 1, 1, 1933), (320, 4544, 7, 1, 11073),
+    (3712, 1856, 1, 1, 13119), (448, 8064, 5, 1, 12299), (448, 9984, 1, 1, 6799), (5760, 448, 7, 1, 2134),
+    (704, 7808, 1, 1, 6835), (1088, 5824, 1, 1, 8206), (2560, 2368, 2, 1, 6845), (5760, 832, 7, 1, 2712),
+    (4992, 704, 1, 1, 13693), (832, 4992, 1, 1, 16465), (8000, 576, 10, 2, 639), (640, 9216, 1, 1, 13715),
+    (3072, 2752, 5, 1, 6697), (3520, 3200, 1, 1, 10415), (5056, 192, 5, 1, 16867), (8192, 128, 4, 4, 6724),
+    (1152, 128, 28, 4, 14412), (2816, 128, 16, 2, 14722), (128, 128, 56, 8, 578)]
+# (requests, vocabulary, hidden size) of heads, on the tile that only they use
+HEADS = [(100, 151936, 64), (65, 151936, 192), (8, 152064, 3584), (127, 152060, 320)]
+
+
+
+def choice(epilogue, M, N, K, scratch=1, deferred=1):
+    """((tile rows, tile columns, workgroups per CU), epilogue, "whole" | "k ranges" | "split last round")"""
+    f = vlc.lib().vlc_probe_gemm_choice
+    f.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    o = (ctypes.c_int32 * 5)()
+    assert f(epilogue, M, N, K, scratch, deferred, o) == 0
+    return tuple(o[:3]), epilogue, "k ranges" if o[3] > 1 else "split last round" if o[4] > 1 else "whole"
+
+
+def layer_choices(H, I, Hq, Hkv, rows):
+    """The four products of a chained layer, and the down projection of one that is not."""
+    hd, nqkv = Hq * 128, (Hq + 2 * Hkv) * 128
+    return {"qkv": choice(FLOAT, rows, nqkv, H), "o": choice(RESIDUAL, rows, H, hd), "gate_up": choice(SWIGLU, rows, I, H),
+            "down": choice(RESIDUAL, rows, H, I), "down alone": choice(RESIDUAL, rows, H, I, 1, 0)}
+
+
+def test_every_choice_is_among_the_tested_layers():
+    """1 to 30000 rows at the decoder shapes of the workloads and three more, and the heads: no tile is launched with an
+    epilogue and a split that the layers of this file do not run."""
+    tested = {choice(FLOAT, rows, vocab, H, 0, 0) for rows, vocab, H in HEADS}
+    for l in LAYERS:
+        tested |= set(layer_choices(*l).values())
+    shapes = [(s.H, s.I, s.Hq, s.Hkv) for s in syn.SHAPES.values() if s.dtype == "bf16" and s.D == 128]
+    shapes += [(5120, 13824, 40, 8), (1536, 8960, 12, 2), (2048, 11008, 16, 2)]
+    for H, I, Hq, Hkv in shapes:
+        rows = 1
+        while rows < 30000:
+            for name, c in layer_choices(H, I, Hq, Hkv, rows).items():
+                assert c in tested, (name, H, I, Hq, Hkv, rows, c)
+            rows = max(rows + 1, int(rows * 1.01))
+    for H in (64, 512, 2048, 2560, 3072, 3584, 4096, 8192):
+        for vocab in (256, 4096, 32000, 151936, 152064):
+            for rows in (1, 8, 33, 64, 65, 128, 129, 300, 700, 2000):
+                assert choice(FLOAT, rows, vocab, H, 0, 0) in tested, (H, vocab, rows)
+
+
+def test_choices_that_measure_faster():
+    """Products at which the prices once named a slower tile (stage times in us, that tile against the expected one)."""
+    whole = lambda M, N, K, e: choice(e, M, N, K)[0]
+    assert whole(18944, 4608, 3584, FLOAT) == (256, 256, 1)       # 619 / 580 with 320 x 192
+    assert whole(24000, 10240, 8192, FLOAT) == (256, 256, 1)      # 3846 / 3559
+    assert whole(24000, 8192, 29568, RESIDUAL) == (256, 256, 1)   # 10505 / 9762
+    assert choice(RESIDUAL, 40, 8192, 8192)[0][0] <= 128          # k ranges that do not all start on one channel: 48 / 41
+    o = (ctypes.c_int32 * 5)()
+    vlc.lib().vlc_probe_gemm_choice(RESIDUAL, 40, 8192, 8192, 1, 1, o)
+    assert o[3] > 1 and -(-128 // o[3]) % 32 != 0, list(o)
+    for H in (2560, 3584, 8192):                                  # heads with few columns: 28 / 26, 49 / 43
+        for rows in (1, 8, 64):
+            assert choice(FLOAT, rows, 4096, H, 0, 0)[0] == (64, 128, 1)
+
+
+def close(got, want, rtol, atol, what):
+    err = (got.float() - want).abs()
+    bad = err > atol + rtol * want.abs()
+    assert not bad.any(), "%s: %d of %d outside tolerance, first at %s, largest error %.3e" % (
+        what, int(bad.sum()), bad.numel(), tuple(bad.nonzero()[0].tolist()), err.max().item())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,I,Hq,Hkv,rows", LAYERS)
+def test_layer_products_on_every_tile(H, I, Hq, Hkv, rows):
+    """All rows and columns of the four products against float32 matmuls of the same inputs (the GPU's own previous stage).
+    Float outputs: both sides sum at most 8128 float products of about 0.016 in some order, typically 1e-4 apart; a
+    missing or doubled k-tile shows as 0.1 and more.  bf16 outputs: one rounding (2^-9) on top, twice that allowed."""
+    sh = dataclasses.replace(syn.SHAPES["tiny_bf16"], L=1, H=H, I=I, Hq=Hq, Hkv=Hkv)
+    print("layer", H, I, Hq, Hkv, rows, layer_choices(H, I, Hq, Hkv, rows), flush=True)
+    rec, dt = R.make_shape(sh), torch.bfloat16
+    plans = R.DevicePlans([syn.Request([syn.Segment(0, rows, False)], 0)], 1, k=np.zeros(1, dtype=np.int32), all_rows=True)
+    assert plans.n_rows == [rows]
+    W = R.DeviceWeights.random(sh, dt, 41)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows)
+    h_in = torch.randn((rows, H), generator=g, device=DEV).to(dt)
+    kc = torch.zeros((rows, Hkv, 128), device=DEV, dtype=dt)
+    vc, h_out, chained = torch.zeros_like(kc), torch.empty_like(h_in), torch.empty_like(h_in)
+    ws = R.Workspace(rec, rows)
+    record = plans.record(0, rows, rows)
+    vlc.vlc_layer_forward(rec, W.rec, record, h_in, h_out, kc, vc, ws.t)
+    off = vlc.vlc_layer_workspace_layout(rec, rows)
+
+    def stage(name, cols, t):
+        size = 4 if t == torch.float32 else 2
+        return ws.t[off[name]:off[name] + rows * cols * size].view(t).reshape(rows, cols)
+
+    f = lambda t: t.float()
+    w = {k: f(v) for k, v in W.t.items() if v is not None}
+    close(stage("qkv", sh.n_qkv, torch.float32), torch.addmm(w["b_qkv"], f(stage("xn", H, dt)), w["w_qkv"].T), 1e-3, 1e-3, "q|k|v")
+    close(stage("h1", H, dt), f(h_in) + f(stage("o", Hq * 128, dt)) @ w["w_o"].T, 2.0 ** -8, 1e-3, "o projection + residual")
+    gate, up = (f(stage("n2", H, dt)) @ w["w_gate_up"].T).split(I, 1)
+    close(stage("act", I, dt), torch.nn.functional.silu(gate) * up, 2.0 ** -8, 2e-3, "gate|up + SwiGLU")
+    del gate, up
+    want = f(stage("h1", H, dt)) + f(stage("act", I, dt)) @ w["w_down"].T
+    close(h_out, want, 2.0 ** -8, 1e-3, "down projection + residual")
+    # chained: the same layer, but the kernel after the down projection also takes the next norm and sums its k ranges
+    vlc.vlc_layer_forward_chained(rec, W.rec, record, h_in, chained, kc, vc, ws.t, False, W.t["w_ln1"])
+    close(chained, want, 2.0 ** -8, 1e-3, "down projection + residual, chained")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,vocab,H", HEADS)
+def test_head_products(rows, vocab, H):
+    """All logits against a float32 matmul of the GPU's normed rows (which open the workspace); tolerance as above."""
+    assert choice(FLOAT, rows, vocab, H, 0, 0)[0] == (128, 160, 2)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(vocab + rows)
+    h = torch.randn((rows, H), generator=g, device=DEV).to(torch.bfloat16)
+    w = (0.02 * torch.randn((vocab, H), generator=g, device=DEV)).to(torch.bfloat16)
+    logits, token = torch.zeros((rows, vocab), device=DEV), torch.zeros(rows, device=DEV, dtype=torch.int32)
+    ws = torch.empty(vlc.vlc_first_token_workspace_bytes(H, rows, vlc.VLC_BF16), device=DEV, dtype=torch.uint8)
+    vlc.vlc_first_token(h, torch.arange(rows, device=DEV, dtype=torch.int32), 1e-6, torch.ones(H, device=DEV, dtype=torch.bfloat16),
+                        w, logits, token, ws)
+    normed = ws[:rows * H * 2].view(torch.bfloat16).reshape(rows, H)
+    close(logits, normed.float() @ w.float().T, 1e-3, 1e-3, "logits")
