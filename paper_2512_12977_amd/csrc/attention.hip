@@ -416,8 +416,8 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
   }
     // One key block j (S^T already in CUR): fetch ahead, start the next block's S^T into NXT (its MFMAs
     // are independent of this block's softmax arithmetic, so the two interleave), finish this block.
-    // The PV product runs at a raised wave priority: two wavefronts share a SIMD, and a wavefront's own vector
-    // instructions do not overlap with its MFMAs, so the matrix pipe is only kept busy when one wavefront
+    // The PV product runs at a raised wave priority: two wavefronts share a SIMD, and a wavefront hides only about five
+    // of its own vector instructions under an MFMA, so the matrix pipe is only kept busy when one wavefront
     // multiplies while the other does its softmax arithmetic.  With equal priorities two wavefronts that reach
     // their MFMA phases together alternate instruction by instruction and stay in step; the priority lets the
     // one already in its pure-MFMA phase run ahead, which puts the pair out of step (-6 % kernel time).

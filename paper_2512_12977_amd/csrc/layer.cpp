@@ -334,9 +334,9 @@ extern "C" int vlc_first_token(const void* h, const int32_t* rows, int64_t n_req
   hipStream_t st = (hipStream_t)stream;
   int rc = vlc::launch_rmsnorm(h, rows, w_norm, workspace, n_req, H, eps, dtype, st);
   if (rc) return rc;
-  // The output matrix is streamed once (vocab * H elements) by the GEMM: 128-row MFMA tiles whose few real rows are
-  // the requests - HBM-bound whatever the count (a kernel that kept the rows in LDS and formed the products with
-  // dot instructions was slower from two requests on: every 16 bytes of the matrix cost a 16-byte LDS read per row).
+  // The output matrix is streamed once (vocab * H elements) by the GEMM: MFMA tiles of 64 rows and more whose few real
+  // rows are the requests - HBM-bound whatever the count (a kernel that kept the rows in LDS and formed the products
+  // with dot instructions was slower from two requests on: every 16 bytes of the matrix cost a 16-byte LDS read per row).
   rc = vlc::launch_gemm(workspace, H, w_out, logits, vocab, n_req, vocab, H, vlc::EPI_BIAS_F32, nullptr, nullptr, 0,
                         nullptr, dtype, nullptr, 0, st);
   if (rc) return rc;

@@ -125,10 +125,11 @@ def test_first_token_full_vocabulary_7b():
 
 
 @pytest.mark.parametrize("n_req,vocab,H", [(1, 4, 64), (15, 20, 64), (16, 16, 128), (17, 132, 320), (61, 512, 1024),
-                                           (128, 16384, 64), (128, 32768, 64), (129, 16388, 192), (255, 16384, 64)])
+                                           (128, 16384, 64), (128, 32768, 64), (129, 16388, 192), (255, 16384, 64),
+                                           (128, 12160, 64), (128, 12164, 64), (130, 6020, 64)])
 def test_first_token_f32_around_the_tile_edges(n_req, vocab, H):
     """fp32 products around the edges of both tilings: 16 x 16 outputs with the k range shared by four wavefronts (K from
-    one k-step per wavefront on) and, from 256 tiles of 128 x 128 on, wavefronts of 64 x 64."""
+    one k-step per wavefront on) and, from 96 tiles of 128 x 128 on (95 and 96 of them among the cases), wavefronts of 64 x 64."""
     import dataclasses
     shape = dataclasses.replace(syn.SHAPES["tiny"], H=H, vocab=vocab)
     Wh = syn.head_weights(shape, 900 + n_req)
@@ -142,8 +143,9 @@ def test_first_token_f32_around_the_tile_edges(n_req, vocab, H):
     (300, 24580, 64), (320, 24580, 256), (641, 16384, 320), (400, 24580, 192), (321, 24580, 448), (1700, 6148, 64),
     (64, 260, 3008), (65, 260, 3008), (64, 260, 3072)])
 def test_first_token_bf16_tiles_and_rings(n_req, vocab, H):
-    """bf16 products that the tile choice spreads over its list (64 x 128 to 256 x 256), with ragged rows and columns and
-    k ranges shorter than, equal to and longer than the rings (1 to 9 k-tiles)."""
+    """bf16 products with float output and no scratch, whole tiles from 64 x 128 up, with ragged rows and columns and k ranges
+    shorter than, equal to and longer than the rings (1 to 9 k-tiles; the last three 47 and 48).  Which tile a product
+    lands on, split k ranges and the other epilogues: test_gpu_gemm_tiles.py."""
     import dataclasses
     shape = dataclasses.replace(syn.SHAPES["tiny_bf16"], H=H, vocab=vocab)
     Wh = syn.head_weights(shape, 950 + n_req)
