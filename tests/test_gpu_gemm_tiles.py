@@ -72,7 +72,12 @@ def test_choices_that_measure_faster():
     """Products at which the prices once named a slower tile (stage times in us, that tile against the expected one)."""
     whole = lambda M, N, K, e: choice(e, M, N, K)[0]
     assert whole(18944, 4608, 3584, FLOAT) == (256, 256, 1)       # 619 / 580 with 320 x 192
+    for rows in (22912, 26000, 33500):                            # 889 / 810, 996 / 941, 1283 / 1194
+        assert whole(rows, 4608, 3584, FLOAT) == (256, 256, 1)
     assert whole(24000, 10240, 8192, FLOAT) == (256, 256, 1)      # 3846 / 3559
+    for rows in (20500, 36000):                                   # 16592 / 15959, 29035 / 28031
+        assert whole(rows, 29568, 8192, SWIGLU) == (256, 256, 1)
+    assert whole(36000, 8192, 29568, RESIDUAL) == (256, 256, 1)   # 15872 / 15006
     assert whole(24000, 8192, 29568, RESIDUAL) == (256, 256, 1)   # 10505 / 9762
     assert choice(RESIDUAL, 40, 8192, 8192)[0][0] <= 128          # k ranges that do not all start on one channel: 48 / 41
     o = (ctypes.c_int32 * 5)()
