@@ -818,11 +818,12 @@ constexpr float kPriceTail = 6.85f, kPriceTailElem = 1.69e-6f;         // split 
 constexpr float kPriceSumQkv = 1.58f, kPriceSumQkvElem = 1.47e-6f;     // split k range: per launch, per partial sum
 constexpr float kPriceSum = 1.40f, kPriceSumElem = 1.01e-6f;
 constexpr float kPriceSumLaunch = 2.5f;       // not deferred to the caller's next kernel
-// 320 x 192 over many rounds, where the operands and a float output no longer stay in the memory-side cache, against
-// 256 x 256: 7B q|k|v 22912 / 26000 / 33500 rows 889 / 996 / 1283 against 810 / 941 / 1194 us (at 20500, under six rounds, 741 against
-// 749); 72B gate|up 20500 / 36000 rows 16.6 / 29.0 against 16.0 / 28.0 ms, down 36000 rows 15.9 against 15.0 ms.
+// 320 x 192 over many rounds against 256 x 256 (why it falls behind is not measured; the operands and a float output
+// outgrow the 256 MB memory-side cache there): 7B q|k|v 22912 / 26000 / 33500 rows 889 / 996 / 1283 against 810 / 941 / 1194
+// us (at 20500, just over six rounds, 741 against 749); 72B gate|up 20500 / 36000 rows 16.6 / 29.0 against 16.0 / 28.0 ms,
+// down 36000 rows 15.9 against 15.0 ms.
 constexpr int kLongRoundsFloat = 6, kLongRounds = 12;   // rounds from which it is priced higher, the latter for
-constexpr int64_t kLongK = 8192;                        // these k ranges (at K <= 5120 it stays the faster one at any length)
+constexpr int64_t kLongK = 8192;                        // these k ranges (at K <= 5120 it is ahead, or 2 % behind at most)
 constexpr float kPriceLongFloat = 1.06f, kPriceLong = 1.035f;
 // The two-per-CU tile of the heads against 64 x 128, 151936 output rows, 1 / 8 / 64 requests: K = 2048 140 / 142 / 163 against
 // 127 / 133 / 162 us (rows start 4 KiB apart, which the prices do not know; 128 requests 187 against 191 for the next best),
