@@ -110,22 +110,59 @@ __device__ __forceinline__ void dma16(const void* uniform_base, uint32_t lane_by
 // acc += W fragment x activation fragment, in place.  Written as an instruction because the compiler, free to give the result
 // of the builtin other registers than the addend, moved half of the accumulators once per k-tile (452 moves beside 240
 // MFMAs in the loop of 320 x 192).  accumulation_regs is a constant of the unrolled code.
-// Nothing but these instructions touches the accumulators inside the loop; mfma_settle() stands before their first use behind it.
+// The compiler's own waits know nothing of these instructions.  One takes 4 passes, and what is no MFMA that adds to its result
+// may touch that only 8 wait states later; inside the loop nothing does, and the last k-step of a workgroup takes
+// mfma_add_last, whose wait is part of the same statement: a copy or a spill of an accumulator, which the compiler may
+// place right behind the statement that wrote it, comes after the wait.  (One wait behind the loop left room in front of it:
+// in 256 x 256 on four wavefronts and in 320 x 256, 2 to 14 accumulators were spilled there.)
 __device__ __forceinline__ void mfma_add(f32x4& acc, const bf16x8& w, const bf16x8& a, bool accumulation_regs) {
   if (accumulation_regs)
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(a));
   else
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(w), "v"(a));
 }
-// The waits between these and the vector instructions that write (at most 2 cycles of distance) or read (19) the
-// accumulators; the compiler adds them for its own MFMAs only.
-__device__ __forceinline__ void mfma_settle(f32x4& acc, bool accumulation_regs) {
+// N of them and one wait, about 20 cycles per statement over the MFMAs' own.  In statements of 8 that does not show (7B at 596
+// rows 1248 / 1245 us, before / after); in statements of 4 the same prefill was 0.6 % slower (1275 / 1283).
+template <int N>
+__device__ __forceinline__ void mfma_add_last(f32x4* const (&c)[N], const bf16x8* const (&w)[N], const bf16x8* const (&a)[N],
+                                              bool accumulation_regs) {
+  static_assert(N == 8 || N == 4 || N == 1, "statements of 8, 4 or 1 tiles");
+#define VLC_MFMA(C, W, A) "v_mfma_f32_16x16x32_bf16 %" #C ", %" #W ", %" #A ", %" #C "\n\t"
+#define VLC_LAST_1(R) asm volatile(VLC_MFMA(0, 1, 2) "s_nop 7" : "+" R(*c[0]) : "v"(*w[0]), "v"(*a[0]))
+#define VLC_LAST_4(R)                                                                                              \
+  asm volatile(VLC_MFMA(0, 4, 8) VLC_MFMA(1, 5, 9) VLC_MFMA(2, 6, 10) VLC_MFMA(3, 7, 11) "s_nop 7"                  \
+               : "+" R(*c[0]), "+" R(*c[1]), "+" R(*c[2]), "+" R(*c[3])                                            \
+               : "v"(*w[0]), "v"(*w[1]), "v"(*w[2]), "v"(*w[3]), "v"(*a[0]), "v"(*a[1]), "v"(*a[2]), "v"(*a[3]))
+#define VLC_LAST_8(R)                                                                                              \
+  asm volatile(VLC_MFMA(0, 8, 16) VLC_MFMA(1, 9, 17) VLC_MFMA(2, 10, 18) VLC_MFMA(3, 11, 19)                       \
+               VLC_MFMA(4, 12, 20) VLC_MFMA(5, 13, 21) VLC_MFMA(6, 14, 22) VLC_MFMA(7, 15, 23) "s_nop 7"           \
+               : "+" R(*c[0]), "+" R(*c[1]), "+" R(*c[2]), "+" R(*c[3]), "+" R(*c[4]), "+" R(*c[5]), "+" R(*c[6]),  \
+                 "+" R(*c[7])                                                                                      \
+               : "v"(*w[0]), "v"(*w[1]), "v"(*w[2]), "v"(*w[3]), "v"(*w[4]), "v"(*w[5]), "v"(*w[6]), "v"(*w[7]),    \
+                 "v"(*a[0]), "v"(*a[1]), "v"(*a[2]), "v"(*a[3]), "v"(*a[4]), "v"(*a[5]), "v"(*a[6]), "v"(*a[7]))
+  if constexpr (N == 8) {
+    if (accumulation_regs) VLC_LAST_8("a");
+    else VLC_LAST_8("v");
+  } else if constexpr (N == 4) {
+    if (accumulation_regs) VLC_LAST_4("a");
+    else VLC_LAST_4("v");
+  } else {
+    if (accumulation_regs) VLC_LAST_1("a");
+    else VLC_LAST_1("v");
+  }
+#undef VLC_LAST_8
+#undef VLC_LAST_4
+#undef VLC_LAST_1
+#undef VLC_MFMA
+}
+// A vector instruction's result may be read by an MFMA two wait states later: the zeroed accumulators pass through here
+// before the wait in front of the loop.
+__device__ __forceinline__ void mfma_operand(f32x4& acc, bool accumulation_regs) {
   if (accumulation_regs)
     asm volatile("" : "+a"(acc));
   else
     asm volatile("" : "+v"(acc));
 }
-__device__ __forceinline__ void mfma_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
 #define VLC_WAITCNT_VM(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14))
 
@@ -271,7 +308,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
   }
 
   // one wavefront per SIMD: the first 64 tiles in accumulation registers, what is over in vector registers
-  constexpr int ACC = OCC * NW <= 4 ? 64 : 0;
+  constexpr int ACC = OCC * NW <= 4 ? 64 : 0;   // a multiple of 8: mfma_add_last takes tiles of one kind
   f32x4 acc[NT][MT];
 #pragma unroll
   for (int i = 0; i < NT; ++i)
@@ -303,14 +340,17 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
   }
   constexpr int RN = TWO ? (2 * G + 4) / 5 : G;            // groups that read the fragments of a k-step
   constexpr int L0 = TWO ? RN : G, LN = TWO ? 2 * (G - RN) : G;   // groups that refill the stage: LN from L0 on
+  // The MFMAs of a k-step walk its tiles in a snake: one operand changes at a time.
+  auto nt_of = [](int t) { return t / MT; };
+  auto mt_of = [](int t) { return (t / MT & 1) ? MT - 1 - t % MT : t % MT; };
   // cst_ / nst_: stages of this and the next k-tile.  LOAD_: refill this tile's stage with k-tile lkt_; WAIT_: the wait that
-  // leaves only the loads of the tiles after the next one in flight; NEXT_: there is a next tile.  The MFMAs of a k-step
-  // walk its tiles in a snake: one operand changes at a time.
-#define VLC_COMPUTE_TILE(cst_, nst_, LOAD_, lkt_, NEXT_, WAIT_)                                               \
+  // leaves only the loads of the tiles after the next one in flight; NEXT_: there is a next tile.  GROUPS_: groups to run, 2 G or,
+  // without the second k-step, G.
+#define VLC_COMPUTE_TILE(cst_, nst_, LOAD_, lkt_, NEXT_, WAIT_, GROUPS_)                                      \
   {                                                                                                           \
     const u32x4* st_ = lds + (cst_) * STAGE_CHUNKS;                                                           \
     const u32x4* sn_ = lds + (nst_) * STAGE_CHUNKS;                                                           \
-    _Pragma("unroll") for (int g = 0; g < 2 * G; ++g) {                                                       \
+    _Pragma("unroll") for (int g = 0; g < (GROUPS_); ++g) {                                                   \
       if (TWO && g == L0 && (LOAD_)) __syncthreads();                                                         \
       if (g == 2 * G - RN && (NEXT_)) {                                                                       \
         WAIT_;                                                                                                \
@@ -323,25 +363,22 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
       else if (g >= 2 * G - RN && (NEXT_)) { VLC_READ_FRAGS(sn_, 0, 0, g - (2 * G - RN)) }                     \
       __builtin_amdgcn_sched_barrier(0);                                                                      \
       _Pragma("unroll") for (int j = 0; j < MPG; ++j) {                                                       \
-        const int t_ = g % G * MPG + j, nt_ = t_ / MT, mt_ = (nt_ & 1) ? MT - 1 - t_ % MT : t_ % MT;           \
-        mfma_add(acc[nt_][mt_], wf[g / G][nt_], af[g / G][mt_], nt_ * MT + mt_ < ACC);                         \
+        const int t_ = g % G * MPG + j, nt_ = nt_of(t_), mt_ = mt_of(t_);                                      \
+        mfma_add(acc[nt_][mt_], wf[g / G][nt_], af[g / G][mt_], t_ < ACC);                                     \
       }                                                                                                       \
       __builtin_amdgcn_sched_barrier(0);                                                                      \
     }                                                                                                         \
   }
 
-#define VLC_SETTLE()                                                                                          \
-  __builtin_amdgcn_sched_barrier(0);                                                                          \
-  _Pragma("unroll") for (int i = 0; i < NT; ++i)                                                              \
-    _Pragma("unroll") for (int j = 0; j < MT; ++j) mfma_settle(acc[i][j], i * MT + j < ACC);                  \
-  mfma_settle();                                                                                              \
-  __builtin_amdgcn_sched_barrier(0);
-
   // prologue: fill every stage, read the first fragments
 #pragma unroll
   for (int s = 0; s < STAGES; ++s)
     if (s < KT) { VLC_ISSUE(s, s) }
-  VLC_SETTLE()
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) mfma_operand(acc[nt_of(t)][mt_of(t)], t < ACC);
+  asm volatile("s_nop 15" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
   if (KT >= STAGES) { VLC_WAITCNT_VM((STAGES - 1) * LOADS); } else { VLC_WAITCNT_VM(0); }
   __syncthreads();
   VLC_READ_FRAGS(lds, 0, 0, -1)
@@ -351,24 +388,43 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
     // two k-tiles per trip, so that the stage every fragment address refers to is a constant of the code
     // and the addresses of both stages stay in registers (no address arithmetic inside the loop)
     for (; kt + 3 < KT; kt += 2) {
-      VLC_COMPUTE_TILE(0, 1, true, kt + 2, true, VLC_WAITCNT_VM(TWO ? LOADS : 0))
-      VLC_COMPUTE_TILE(1, 0, true, kt + 3, true, VLC_WAITCNT_VM(TWO ? LOADS : 0))
+      VLC_COMPUTE_TILE(0, 1, true, kt + 2, true, VLC_WAITCNT_VM(TWO ? LOADS : 0), 2 * G)
+      VLC_COMPUTE_TILE(1, 0, true, kt + 3, true, VLC_WAITCNT_VM(TWO ? LOADS : 0), 2 * G)
     }
     if (kt + 2 < KT) {
-      VLC_COMPUTE_TILE(0, 1, true, kt + 2, true, VLC_WAITCNT_VM(TWO ? LOADS : 0))
+      VLC_COMPUTE_TILE(0, 1, true, kt + 2, true, VLC_WAITCNT_VM(TWO ? LOADS : 0), 2 * G)
       ++kt;
     }
   } else {
     for (; kt + STAGES < KT; ++kt)
-      VLC_COMPUTE_TILE(kt % STAGES, (kt + 1) % STAGES, true, kt + STAGES, true, VLC_WAITCNT_VM((STAGES - 2) * LOADS))
+      VLC_COMPUTE_TILE(kt % STAGES, (kt + 1) % STAGES, true, kt + STAGES, true, VLC_WAITCNT_VM((STAGES - 2) * LOADS), 2 * G)
   }
-  for (; kt < KT; ++kt) {                // drain
+  for (; kt + 1 < KT; ++kt) {            // drain
     const int later = min(KT - 2 - kt, STAGES - 2);   // tiles after the next one still in flight
-    VLC_COMPUTE_TILE(kt % STAGES, (kt + 1) % STAGES, false, 0, kt + 1 < KT,
-                     { if (later >= 4) { VLC_WAITCNT_VM(4 * LOADS); } else if (later == 3) { VLC_WAITCNT_VM(3 * LOADS); } else if (later == 2) { VLC_WAITCNT_VM(2 * LOADS); } else if (later == 1) { VLC_WAITCNT_VM(LOADS); } else { VLC_WAITCNT_VM(0); } })
+    VLC_COMPUTE_TILE(kt % STAGES, (kt + 1) % STAGES, false, 0, true,
+                     { if (later >= 4) { VLC_WAITCNT_VM(4 * LOADS); } else if (later == 3) { VLC_WAITCNT_VM(3 * LOADS); } else if (later == 2) { VLC_WAITCNT_VM(2 * LOADS); } else if (later == 1) { VLC_WAITCNT_VM(LOADS); } else { VLC_WAITCNT_VM(0); } }, 2 * G)
   }
-  VLC_SETTLE()
-#undef VLC_SETTLE
+  // the last k-tile: nothing is left to load or to read ahead, and its second k-step waits for its own results
+  VLC_COMPUTE_TILE(kt % STAGES, 0, false, 0, false, , G)
+#define VLC_ACC(t_) &acc[nt_of(t_)][mt_of(t_)]
+#define VLC_W(t_) &wf[1][nt_of(t_)]
+#define VLC_A(t_) &af[1][mt_of(t_)]
+#pragma unroll
+  for (int t = 0; t + 8 <= TILES; t += 8)
+    mfma_add_last<8>({VLC_ACC(t), VLC_ACC(t + 1), VLC_ACC(t + 2), VLC_ACC(t + 3), VLC_ACC(t + 4), VLC_ACC(t + 5), VLC_ACC(t + 6), VLC_ACC(t + 7)},
+                     {VLC_W(t), VLC_W(t + 1), VLC_W(t + 2), VLC_W(t + 3), VLC_W(t + 4), VLC_W(t + 5), VLC_W(t + 6), VLC_W(t + 7)},
+                     {VLC_A(t), VLC_A(t + 1), VLC_A(t + 2), VLC_A(t + 3), VLC_A(t + 4), VLC_A(t + 5), VLC_A(t + 6), VLC_A(t + 7)}, t < ACC);
+  if constexpr (TILES % 8 >= 4) {
+    constexpr int t = TILES / 8 * 8;
+    mfma_add_last<4>({VLC_ACC(t), VLC_ACC(t + 1), VLC_ACC(t + 2), VLC_ACC(t + 3)}, {VLC_W(t), VLC_W(t + 1), VLC_W(t + 2), VLC_W(t + 3)},
+                     {VLC_A(t), VLC_A(t + 1), VLC_A(t + 2), VLC_A(t + 3)}, t < ACC);
+  }
+#pragma unroll
+  for (int t = TILES / 4 * 4; t < TILES; ++t) mfma_add_last<1>({VLC_ACC(t)}, {VLC_W(t)}, {VLC_A(t)}, t < ACC);
+#undef VLC_ACC
+#undef VLC_W
+#undef VLC_A
+  __builtin_amdgcn_sched_barrier(0);
 #undef VLC_READ_FRAGS
 #undef VLC_ISSUE
 #undef VLC_DMA
