@@ -1179,3 +1179,13 @@ extern "C" int vlc_probe_gemm_choice(int epilogue, int64_t M, int64_t N, int64_t
 #undef X
   return VLC_OK;
 }
+
+extern "C" int vlc_probe_gemm_waves(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred) {
+  if (M <= 0 || N <= 0 || K < vlc::BK || K % vlc::BK) return 0;
+  const vlc::TileChoice c =
+      vlc::choose_tile(M, N, K, epilogue, deferred != 0, scratch ? vlc::gemm_splitk_ws_bytes(M, N) : 0);
+#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA) WGM * WGN,
+  static constexpr int kWaves[] = {VLC_GEMM_TILES(X)};
+#undef X
+  return kWaves[c.index];
+}

@@ -184,5 +184,7 @@ int vlc_probe_attention_shares(int64_t n, int Hq, int Hkv, int64_t max_kv_len);
 // a layer's float scratch: out = {tile rows, tile columns (SwiGLU: gate and up), workgroups per CU, k ranges of the whole
 // product, k ranges of the tiles of its last round}
 int vlc_probe_gemm_choice(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred, int32_t* out);
+// wavefronts per workgroup of the same choice (0: no such product): 256 x 256 is listed with four and with eight
+int vlc_probe_gemm_waves(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred);
 }
 #endif
