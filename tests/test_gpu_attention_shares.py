@@ -1,5 +1,6 @@
 """Attention whose key ranges are shared out over several workgroups (few rows) against the whole form of the kernel on the
 same queries, keys and values."""
+import ctypes
 import dataclasses
 
 import numpy as np
@@ -13,9 +14,17 @@ from paper_2512_12977_amd import runner as R
 DEV = "cuda"
 
 
+def most_shares(n, Hq, Hkv, slots):
+    """The most shares that a row tile of such a layer may take; 1: nothing is shared out."""
+    f = vlc.lib().vlc_probe_attention_shares
+    f.argtypes, f.restype = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64], ctypes.c_int
+    return f(n, Hq, Hkv, slots)
+
+
 def layer_attention(Hq, Hkv, requests, seed=3, spoil=None):
     """One layer over requests given as runs of (computed rows, keys that are only read): the queries, the attention output
-    of the layer, and that of the stand-alone entry point (which shares nothing out).  spoil(h_in) may edit the input."""
+    of the layer, that of the stand-alone entry point (which shares nothing out), the rows and the most shares.
+    spoil(h_in) may edit the input."""
     sh = dataclasses.replace(syn.SHAPES["tiny_bf16"], L=1, H=256, I=64, Hq=Hq, Hkv=Hkv)
     reqs, at = [], 0
     for runs in requests:
@@ -44,12 +53,12 @@ def layer_attention(Hq, Hkv, requests, seed=3, spoil=None):
     q, shared = stage("q").clone(), stage("o").float()
     whole = torch.empty_like(q)
     vlc.vlc_sparse_q_attention(q, kc, vc, plans.dev[0]["kv_start"], plans.dev[0]["kv_len"], 128 ** -0.5, whole)
-    return shared, whole.float(), n
+    return shared, whole.float(), n, most_shares(n, Hq, Hkv, at)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv,requests", [
-    (28, 4, [[(1, 0)]]),                                                   # one row, one key
+    (28, 4, [[(1, 0)]]),                                                   # one row, one key: whole on both sides
     (28, 4, [[(27, 1369), (43, 0)]]),                                      # a question about an image
     (32, 8, [[(61, 1247), (33, 1350), (33, 1400), (87, 0)]]),              # images between texts, ragged ends
     (64, 8, [[(10, 1290)] * 8 + [(256, 0)]]),                              # most rows at the very end
@@ -58,17 +67,24 @@ def layer_attention(Hq, Hkv, requests, seed=3, spoil=None):
     (12, 3, [[(200, 2000), (100, 0)]]),                                    # kv heads that do not divide the XCDs
     (5, 5, [[(130, 500), (300, 0)], [(17, 0)]]),
     (128, 1, [[(300, 700), (55, 0)]]),                                     # a tile is one row
-    (16, 1, [[(4080, 0)]]),                                                # 510 pairs: the last count that shares, tiles of up to 64 blocks
+    (16, 1, [[(4080, 0)]]),                                                # 510 pairs, tiles of up to 64 blocks
+    (16, 1, [[(4088, 0)]]),                                                # 511 pairs in 512 slots: the last count that shares
     (8, 8, [[(100, 64 * 130), (40, 0)]]),                                  # the most shares, long ranges
 ])
 def test_shared_keys_equal_whole(Hq, Hkv, requests):
     """Both forms round probabilities and outputs to bf16 once; their running maxima differ, so a probability may round
     the other way (2^-9 of it): the outputs differ by rounding, 2^-8 of a value and 2^-9 of the values' scale."""
-    shared, whole, n = layer_attention(Hq, Hkv, requests)
+    shared, whole, n, shares = layer_attention(Hq, Hkv, requests)
+    assert (shares > 1) == (n > 1)
     err = (shared - whole).abs()
     bad = err > 2.0 ** -8 * whole.abs() + 2.0 ** -8
     assert not bad.any(), (n, int(bad.sum()), err.max().item(), bad.nonzero()[0].tolist())
     assert ((shared - whole).norm() / whole.norm()).item() < 2e-3
+
+
+def test_sharing_ends_at_512_pairs():
+    """4088 rows are 511 tiles of 8 rows, the last count that shares; 4089 are 512."""
+    assert most_shares(4088, 16, 1, 4088) == 2 and most_shares(4089, 16, 1, 4089) == 1
 
 
 @pytest.mark.gpu
@@ -77,6 +93,7 @@ def test_a_nan_query_row_stays_nan_in_every_share():
     def spoil(h):
         h[1396] = float("nan")                   # a row of the text behind the image
 
-    shared, whole, n = layer_attention(28, 4, [[(27, 1369), (43, 0)]], spoil=spoil)
+    shared, whole, n, shares = layer_attention(28, 4, [[(27, 1369), (43, 0)]], spoil=spoil)
+    assert shares > 1
     row = 27                                     # the rows in front, then the first of that text
     assert torch.isnan(whole[row]).all() and torch.isnan(shared[row]).all()

@@ -325,8 +325,8 @@ def test_layer_forward_chained_argument_checks():
 
 @pytest.mark.parametrize("Hq,Hkv", [(28, 4), (32, 8), (64, 8), (32, 4), (4, 2)])
 def test_attention_key_shares(Hq, Hkv):
-    """Shares of the key range by the number of (row tile, kv head) pairs: as many as keep the grid within 1024 workgroups,
-    8 at most, none from 512 pairs on, and no share shorter than four key blocks of 64."""
+    """The most shares that a row tile may take, by the number of (row tile, kv head) pairs: 1024 / pairs (twice its part of
+    the 512 workgroups of the launch), 8 at most, none from 512 pairs on, and no share shorter than four key blocks of 64."""
     f = vlc.lib().vlc_probe_attention_shares
     f.argtypes, f.restype = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64], ctypes.c_int
     rows = 128 // (Hq // Hkv)
