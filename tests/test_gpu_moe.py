@@ -146,7 +146,7 @@ def test_moe_30b_a3b_shape_layer_stage_by_stage():
     print("pairs per expert: min %d median %d max %d" % (counts.min(), np.median(counts), counts.max()))
 
 
-def test_moe_many_pairs_grouped_with_atomic_ranks():
+def test_moe_many_pairs_grouped_by_many_workgroups():
     """81840 (row, expert) pairs: 64 workgroups count and place their slices of them, and with 10000 rows per expert
     the grouped GEMMs run on 256-row tiles.  330 short text-only requests."""
     sh = syn.SHAPES["tiny_moe_bf16"]
