@@ -207,8 +207,8 @@ def hbm_kernels(hev, stream, iters=20):
 
 
 def machine_probes(hev, stream):
-    """What this machine delivers with nothing in the way: the register-only MFMA loop of vlc_probe_mfma_bf16 (operands of
-    random bits draw the power of a real GEMM, constant ones do not: the clock differs) and a 1 GiB row copy through
+    """What this machine delivers with nothing in the way: the register-only loop of vlc_probe_mfma_bf16 over the instruction of
+    the GEMMs (operands of random bits draw the power of a real GEMM, constant ones do not: the clock differs) and a 1 GiB row copy through
     vlc_gather_rows (1 GiB read + 1 GiB written)."""
     import torch
     import paper_2512_12977_amd as vlc
@@ -718,8 +718,9 @@ def main() -> int:
         "kernels": kernels,
         "kernels_source": "HIP-event stage durations of a separate pass with all stage events (3 steps, same inputs); "
                           "fractions are achieved algorithmic rate / published peak (2.5 PFLOP/s dense bf16 MFMA, 8 TB/s HBM); "
-                          "frac_of_measured_ceiling: the same rate / what machine_probes measured on this box (MFMA loop on random "
-                          "operands, 1 GiB row copy)",
+                          "frac_of_measured_ceiling: the same rate / what machine_probes measured on this box (loop of "
+                          "v_mfma_f32_16x16x32_bf16 on random operands, 1 GiB row copy; the attention multiplies with the "
+                          "slower 32x32x16)",
         "hbm_kernels": hbm,
         "machine_probes": probes,
         "stages": stages,

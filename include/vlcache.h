@@ -429,8 +429,8 @@ int vlc_mean_squared_error(const float* a, const float* b, int64_t n, double* ou
                            int64_t workspace_bytes, void* stream);
 
 /*
- * Measurement aid, no part of the method: one launch of a register-only loop of v_mfma_f32_32x32x16_bf16 on every
- * CU (one workgroup per CU, waves_per_simd wavefronts per SIMD, iters x 8 MFMAs per wavefront on operands read once
+ * Measurement aid, no part of the method: one launch of a register-only loop of v_mfma_f32_16x16x32_bf16 on every
+ * CU (one workgroup per CU, waves_per_simd wavefronts per SIMD, iters x 16 MFMAs per wavefront on operands read once
  * from `operands`), against which bench.py sets the rates of the GEMM and attention kernels: with operands of random
  * bits it shows what the matrix pipe delivers at the clock the chip sustains under a real kernel's power draw.
  *   operands: device, >= 131072 bytes of bf16 data, 16-byte aligned; out: device float [>= CUs * 256 * waves_per_simd]

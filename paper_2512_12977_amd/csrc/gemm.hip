@@ -65,7 +65,8 @@ __device__ __forceinline__ void tile_coords(int pid, int total, int tiles_m, int
 // n = 4*(l/16) + j (j = register index): four consecutive n per lane, i.e. 8 contiguous bytes of a bf16 C row.
 //
 // 16x16x32 and not 32x32x16: the large products run at the power limit of the card, and a loop of nothing but MFMAs on
-// normal operands reaches 2.09 PFLOP/s with 16x16x32 there, 1.82 with 32x32x16 (2.45 both on zeros).  7B at 18944 rows, before /
+// random operands reaches 2.04 (one wavefront per SIMD) to 2.18 PFLOP/s with 16x16x32 there (vlc_probe_mfma_bf16), 1.70 to 1.82
+// with 32x32x16 (2.4 both on constants).  7B at 18944 rows, before /
 // after: gate|up 3944 / 3782 us, down 2086 / 1957; at 5824 rows gate|up 1258 / 1211.
 //
 // Operands reach LDS straight from global memory (global_load_lds, 16 bytes per lane, no register

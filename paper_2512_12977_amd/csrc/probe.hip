@@ -1,6 +1,7 @@
 // Measurement aid for the roofline discussion (no part of the method): a register-only MFMA loop.
-// Every wavefront keeps four independent 32x32 accumulators and issues v_mfma_f32_32x32x16_bf16 back to back on
-// operands it loaded once, so nothing but the matrix pipe (and the clock the chip sustains under that load) limits it.
+// Every wavefront keeps eight independent 16x16 accumulators and issues v_mfma_f32_16x16x32_bf16, the instruction of the
+// GEMMs, back to back on operands it loaded once, so nothing but the matrix pipe (and the clock the chip sustains under that
+// load) limits it.
 // With operands of random bits the power draw - and with it the clock - is that of a real GEMM; with constant
 // operands it is lower.  The rate a kernel reaches is set against this figure beside the published peak.
 #include <hip/hip_runtime.h>
@@ -10,10 +11,10 @@
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-constexpr int kProbeMfmaPerIter = 8;
+constexpr int kProbeMfmaPerIter = 16, kProbeAccumulators = 8;
 
 __global__ __launch_bounds__(512) void mfma_probe_kernel(const u32x4* __restrict__ operands, float* __restrict__ out,
                                                          int iters) {
@@ -21,19 +22,17 @@ __global__ __launch_bounds__(512) void mfma_probe_kernel(const u32x4* __restrict
   const int slot = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) & 63, lane = threadIdx.x & 63;
   const bf16x8 a = __builtin_bit_cast(bf16x8, operands[slot * 128 + lane]);
   const bf16x8 b = __builtin_bit_cast(bf16x8, operands[slot * 128 + 64 + lane]);
-  f32x16 acc[4];
+  f32x4 acc[kProbeAccumulators];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+  for (int j = 0; j < kProbeAccumulators; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
     for (int j = 0; j < kProbeMfmaPerIter; ++j)
-      acc[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j & 3], 0, 0, 0);
+      acc[j % kProbeAccumulators] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[j % kProbeAccumulators], 0, 0, 0);
   }
   float s = 0.f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) s += acc[j][lane & 15];
+  for (int j = 0; j < kProbeAccumulators; ++j) s += acc[j][lane & 3];
   out[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
@@ -56,6 +55,6 @@ extern "C" int vlc_probe_mfma_bf16(const void* operands, int64_t operand_bytes, 
   hipLaunchKernelGGL(mfma_probe_kernel, dim3(cus), dim3(threads), 0, (hipStream_t)stream,
                      static_cast<const u32x4*>(operands), out, iters);
   VLC_CHECK_LAUNCH("mfma_probe");
-  *flops = (double)cus * (threads / 64) * (double)iters * kProbeMfmaPerIter * (2.0 * 32 * 32 * 16);
+  *flops = (double)cus * (threads / 64) * (double)iters * kProbeMfmaPerIter * (2.0 * 16 * 16 * 32);
   return VLC_OK;
 }
