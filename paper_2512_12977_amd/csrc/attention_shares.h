@@ -52,8 +52,10 @@ __device__ __forceinline__ int ceil_div(int a, int b, float inv_b) {   // a belo
 // Used when there are too few (row tile, kv head) pairs to occupy the chip and the key loop is the critical path.  Every kv
 // head has `slots` workgroups.  A row tile that sees b key blocks is shared out over ceil(b / len) of them, in pieces of
 // about equal length; len is the smallest share length with which the pieces of all tiles fit the slots - one round of
-// workgroups that all work about equally long, whatever the rows' layout.  (Pieces of a common length cut from the
-// whole batch's key range, as before, are many or few by the layout and take up to a second round.)  Attention per layer, before /
+// workgroups, whatever the rows' layout.  They work about equally long where a tile's rows belong to one request; a tile that
+// straddles r requests is planned by its longest row but walks its pieces once for each of them, so that with packed short
+// questions the longest workgroups take up to r times what the plan gives them.  (Pieces of a common length cut from the whole
+// batch's key range, as before, are many or few by the layout and take up to a second round.)  Attention per layer, before /
 // after: 8 images and a text at the end (72B shape, 296 pairs) 206 / 167 us, four images between texts (7B, 212 pairs)
 // 63 / 55, three images (8B, 112 pairs) 39 / 32, a question (7B, 24 pairs) 14.2 / 13.
 // Found by one workgroup of 256 threads of the kernel in front of the attention (RoPE + scatter, at most 1 us longer for

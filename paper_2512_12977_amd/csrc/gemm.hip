@@ -10,7 +10,6 @@ namespace vlc {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // a 16-byte chunk (native vector: stays in registers)
 
@@ -100,7 +99,7 @@ __device__ __forceinline__ int fswz(int row) { return row & 7; }
 // keeps a live value in M0 across statements (it is reserved and written right before each use).
 // The global address is a wavefront-uniform base (scalar registers) plus a 32-bit byte offset per lane: the lane
 // offsets never change, the base moves along k with scalar adds, so the k-loop holds no vector address arithmetic
-// (a wavefront's own vector instructions run under its MFMAs, but only about five of them per 32-cycle MFMA).
+// (a wavefront's own vector instructions run under its MFMAs, but an MFMA lasts only 16 cycles, four instructions).
 __device__ __forceinline__ void dma16(const void* uniform_base, uint32_t lane_byte_off, uint32_t lds_byte_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
@@ -827,8 +826,11 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
 // five decoder shapes and of heads, with every tile, every number of k ranges and both ends of a last round (27000 times, cold
 // weights), so that its choice is as little slower as possible than the best of them: 0.5 % on average, 36 products more
 // than 3 % (left out of the fit, the fifth shape is at 1.2 %).  A list without one of the tiles costs 0.1 ... 1.3 % more.
-// USE: 0 all epilogues, 1 all but SwiGLU (an odd number of column tiles per wavefront, or never the fastest there), 2 SwiGLU
-// only, 3 float output without scratch (the heads; in the layers never the fastest).  256 x 256 on 8 wavefronts of
+// These are numbers of a fit and no measured times (192 x 128 is priced lower over many rounds than in one): they hold over the
+// sizes fitted.  K = 29568 was not: 320 x 256 would take 8469 us where 8833 are chosen (24000 rows, 8192 columns), 12655 where
+// 13745 (36000 rows).
+// USE: 0 all epilogues, 1 all but SwiGLU (an odd number of column tiles per wavefront, or never the fastest there), 3 float
+// output without scratch (the heads; in the layers never the fastest).  256 x 256 on 8 wavefronts of
 // 64 x 128 over many rounds, on 4 of 128 x 128 over few.
 //     BM   BN  WGM WGN STAGES OCC USE light  full  many
 #define VLC_GEMM_TILES(X)                             \
@@ -852,7 +854,7 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
   X(320, 256, 2, 2, 2, 1, 1, 1.313f, 1.674f, 1.734f)    \
   X(128, 160, 4, 1, 2, 2, 3, 0.701f, 0.838f, 0.991f)
 constexpr bool tile_serves(int use, int epi) {
-  return use == 0 || (use == 1 && epi != EPI_SWIGLU) || (use == 2 && epi == EPI_SWIGLU) || (use == 3 && epi == EPI_BIAS_F32);
+  return use == 0 || (use == 1 && epi != EPI_SWIGLU) || (use == 3 && epi == EPI_BIAS_F32);
 }
 
 struct TileChoice {
@@ -1051,7 +1053,8 @@ int launch_f32_grouped(const void* A, int64_t lda, const int32_t* amap, const vo
 }  // namespace
 
 // Float scratch of the split k ranges and of the split tiles of a last round: choose_tile and launch_bf16 split only
-// what fits.  64 MB is one float block per resident workgroup at the largest block: 256 x (256 x 256) floats.
+// what fits.  64 MB is one float block per resident workgroup at 256 x 256; of 320 x 256 it holds 204 blocks, which caps the k
+// ranges of such a last round.
 int64_t gemm_splitk_ws_bytes(int64_t n_rows, int64_t max_n) {
   (void)max_n;
   return n_rows > 0 ? (int64_t)64 << 20 : 0;
@@ -1061,7 +1064,8 @@ int64_t gemm_splitk_ws_bytes(int64_t n_rows, int64_t max_n) {
 // matrix is streamed from HBM exactly once and nothing is reused, so the tile is small (64 x 128, below 9 rows per
 // group 32 x 128) and the ring three (four) stages deep - with two workgroups per CU that keeps 64 (96) KB of matrix data
 // in flight per CU, what the HBM latency needs; a two-stage ring of 128 x 128 tiles stalls at half of that.  More rows: the tile that
-// pads an expert's rows least at a k-loop that is still fast.  gate|up + down of one layer of 128 experts (2048 x 768), us:
+// pads an expert's rows least at a k-loop that is still fast.  Lines by the mean alone, from this one shape with an even load:
+// gate|up + down of one layer of 128 experts (2048 x 768), us:
 //   rows per expert    6    10    56    94   163   281   444
 //   32               211   221
 //   64               212   218   274   330   421   611   877
