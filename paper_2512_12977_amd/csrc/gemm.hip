@@ -121,8 +121,8 @@ __device__ __forceinline__ void mfma_add(f32x4& acc, const bf16x8& w, const bf16
   else
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(w), "v"(a));
 }
-// N of them and one wait, about 20 cycles per statement over the MFMAs' own.  In statements of 8 that does not show (7B at 596
-// rows 1248 / 1245 us, before / after); in statements of 4 the same prefill was 0.6 % slower (1275 / 1283).
+// N of them and one wait, about 20 cycles per statement over the MFMAs' own.  In statements of 8 that hardly shows (7B prefill of
+// 596 rows 1248 / 1245 and 1271 / 1275 us, before / after, on two cards); in statements of 4 it was 1275 / 1283.
 template <int N>
 __device__ __forceinline__ void mfma_add_last(f32x4* const (&c)[N], const bf16x8* const (&w)[N], const bf16x8* const (&a)[N],
                                               bool accumulation_regs) {
@@ -826,9 +826,8 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
 // five decoder shapes and of heads, with every tile, every number of k ranges and both ends of a last round (27000 times, cold
 // weights), so that its choice is as little slower as possible than the best of them: 0.5 % on average, 36 products more
 // than 3 % (left out of the fit, the fifth shape is at 1.2 %).  A list without one of the tiles costs 0.1 ... 1.3 % more.
-// These are numbers of a fit and no measured times (192 x 128 is priced lower over many rounds than in one): they hold over the
-// sizes fitted.  K = 29568 was not: 320 x 256 would take 8469 us where 8833 are chosen (24000 rows, 8192 columns), 12655 where
-// 13745 (36000 rows).
+// These are numbers of a fit and no measured times (192 x 128 is priced lower over many rounds than in one), and they miss: at
+// 8192 columns and K = 29568, 320 x 256 takes 8469 us where 256 x 256 is chosen with 8833 (24000 rows), 12655 against 13745 (36000).
 // USE: 0 all epilogues, 1 all but SwiGLU (an odd number of column tiles per wavefront, or never the fastest there), 3 float
 // output without scratch (the heads; in the layers never the fastest).  256 x 256 on 8 wavefronts of
 // 64 x 128 over many rounds, on 4 of 128 x 128 over few.
