@@ -4,6 +4,8 @@
 // Epilogues: + bias, + residual (optionally gathered through a row map), SwiGLU of a gate|up pair.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "vlc_internal.h"
 
 namespace vlc {
@@ -84,6 +86,16 @@ __device__ __forceinline__ void tile_coords(int pid, int total, int tiles_m, int
 // last, partly filled round would cost as much as a full one.  The tiles of that round (ids from
 // full_tiles on) are then shared out over tail_splits workgroups each, along k; these write their
 // accumulators as float blocks to tail_ws and tail_reduce_kernel sums them and applies the epilogue.
+//
+// RESIDENT: one round of workgroups stays for all tiles and asks for the next tile's first k-tiles under the last k-step of
+// this one (gemm_may_stay, kStayRounds): no workgroup starts, reads its arguments and waits for its first k-tiles in
+// between.  Products of few k-tiles gain most: gate|up / down of 128 experts (2048 x 768) at 444 rows each 354 -> 333 and 262 -> 248
+// us; 7B gate|up at 5824 rows 1134 -> 1110, at 18944 rows (43 rounds, at the card's power limit) 3765 -> 3745.  Up to two rounds
+// nothing is gained, and products that stream their weights through small tiles are no faster (37 rows per expert) or slower.
+//
+// The epilogue reads its residual rows (and bias) ahead of the stores, and whole tiles store without a condition: each
+// 16 x 16 output tile under a condition of its own is a memory round trip, the compiler waits for its load in front of its store.
+// q|k|v at 5824 rows (7B, 320 x 192) 189 -> 168 us, O 165 -> 153; O at 900 rows (128 x 128) 37.4 -> 35.7, q|k|v 43 -> 40.5.
 constexpr int BK = 64;
 
 // A fragment read takes 16 bytes of 16 consecutive rows in four neighbouring chunks of 8 elements.  The LDS serves it in
@@ -128,13 +140,13 @@ __device__ __forceinline__ void mfma_add_last(f32x4* const (&c)[N], const bf16x8
                                               bool accumulation_regs) {
   static_assert(N == 8 || N == 4 || N == 1, "statements of 8, 4 or 1 tiles");
 #define VLC_MFMA(C, W, A) "v_mfma_f32_16x16x32_bf16 %" #C ", %" #W ", %" #A ", %" #C "\n\t"
-#define VLC_LAST_1(R) asm volatile(VLC_MFMA(0, 1, 2) "s_nop 7" : "+" R(*c[0]) : "v"(*w[0]), "v"(*a[0]))
+#define VLC_LAST_1(R) asm volatile("s_nop 1\n\t" VLC_MFMA(0, 1, 2) "s_nop 7" : "+" R(*c[0]) : "v"(*w[0]), "v"(*a[0]))
 #define VLC_LAST_4(R)                                                                                              \
-  asm volatile(VLC_MFMA(0, 4, 8) VLC_MFMA(1, 5, 9) VLC_MFMA(2, 6, 10) VLC_MFMA(3, 7, 11) "s_nop 7"                  \
+  asm volatile("s_nop 1\n\t" VLC_MFMA(0, 4, 8) VLC_MFMA(1, 5, 9) VLC_MFMA(2, 6, 10) VLC_MFMA(3, 7, 11) "s_nop 7"                  \
                : "+" R(*c[0]), "+" R(*c[1]), "+" R(*c[2]), "+" R(*c[3])                                            \
                : "v"(*w[0]), "v"(*w[1]), "v"(*w[2]), "v"(*w[3]), "v"(*a[0]), "v"(*a[1]), "v"(*a[2]), "v"(*a[3]))
 #define VLC_LAST_8(R)                                                                                              \
-  asm volatile(VLC_MFMA(0, 8, 16) VLC_MFMA(1, 9, 17) VLC_MFMA(2, 10, 18) VLC_MFMA(3, 11, 19)                       \
+  asm volatile("s_nop 1\n\t" VLC_MFMA(0, 8, 16) VLC_MFMA(1, 9, 17) VLC_MFMA(2, 10, 18) VLC_MFMA(3, 11, 19)                       \
                VLC_MFMA(4, 12, 20) VLC_MFMA(5, 13, 21) VLC_MFMA(6, 14, 22) VLC_MFMA(7, 15, 23) "s_nop 7"           \
                : "+" R(*c[0]), "+" R(*c[1]), "+" R(*c[2]), "+" R(*c[3]), "+" R(*c[4]), "+" R(*c[5]), "+" R(*c[6]),  \
                  "+" R(*c[7])                                                                                      \
@@ -166,6 +178,12 @@ __device__ __forceinline__ void mfma_operand(f32x4& acc, bool accumulation_regs)
 
 #define VLC_WAITCNT_VM(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14))
 
+// Whether a kernel is built so that its workgroups can stay for several tiles (RESIDENT): tiles of 192 x 192 outputs and more on
+// four wavefronts.  Not 320 x 256, whose sums and fragments leave no registers for the next tile's addresses, nor eight
+// wavefronts, two per SIMD, which fill each other's waits (and spill).
+constexpr bool gemm_may_stay(int bm, int bn, int waves) { return waves == 4 && bm * bn >= 192 * 192 && bm * bn <= 256 * 256; }
+constexpr int kStayRounds = 3;   // rounds of tiles from which they do
+
 enum { EPI_PARTIAL = 100 };   // internal: float partial sums of one k-range (split-K)
 
 //
@@ -174,12 +192,12 @@ enum { EPI_PARTIAL = 100 };   // internal: float partial sums of one k-range (sp
 // rows - fetched through amap when given - with that expert's matrix W + expert * w_stride.
 // Workgroups beyond the table's length (only known on the device) exit at once, and the XCDs share out the tiles that
 // are there (dealt by the largest possible length, 37 rows per expert left two of the eight XCDs idle).
-template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool GROUPED = false>
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool RESIDENT, bool GROUPED = false>
 __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
     const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ W, uint16_t* __restrict__ C,
     int64_t ldc, int M, int N, int K, const uint16_t* __restrict__ bias, const uint16_t* __restrict__ resid,
     int64_t ldr, const int32_t* __restrict__ rmap, int tiles_m, int tiles_n, int kt_per_split, int full_tiles,
-    int tail_splits, float* __restrict__ tail_ws, const GroupTile* __restrict__ gtab,
+    int tail_splits, int items, float* __restrict__ tail_ws, const GroupTile* __restrict__ gtab,
     const int32_t* __restrict__ g_ntiles, const int32_t* __restrict__ amap, int64_t w_stride) {
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;      // wavefront tile
@@ -188,6 +206,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
   constexpr int A_INSTR = BM * 8 / 64 / NW, W_INSTR = BN * 8 / 64 / NW;   // wavefront loads per k-tile
   constexpr int LOADS = A_INSTR + W_INSTR;
   constexpr int KS = BK / 32;
+  constexpr bool TAIL = !GROUPED && EPI != EPI_PARTIAL;
   static_assert(KS == 2, "two k-steps per k-tile");
   // columns of C covered by this tile: SwiGLU consumes a gate and an up row per output column
   constexpr int CN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
@@ -201,43 +220,47 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
 
   if constexpr (GROUPED) {   // the table's real length: every XCD gets its share of what is there, the rest leaves
     tiles_m = *g_ntiles;
-    if ((int)blockIdx.x >= tiles_m * tiles_n) return;
+    items = full_tiles = tiles_m * tiles_n;
+    if ((int)blockIdx.x >= items) return;
   }
   const int tiles = tiles_m * tiles_n;
-  int split = 0, pid = blockIdx.x, tail_block = -1;   // tail_block >= 0: this workgroup owns one k-range of a tail tile
-  if constexpr (EPI == EPI_PARTIAL) {
-    // the whole grid (k range major) is dealt to the XCDs in contiguous pieces: an XCD then works on one or two
-    // k ranges and its L2 holds only their slices of A, instead of every XCD streaming all of A
-    const int b = xcd_contiguous(blockIdx.x, gridDim.x);
-    split = b / tiles;
-    pid = b - split * tiles;
-  } else if ((int)blockIdx.x >= full_tiles) {
-    tail_block = blockIdx.x - full_tiles;
-    const int t = tail_block / tail_splits;
-    split = tail_block - t * tail_splits;
-    pid = full_tiles + t;
-  }
-  int tm, tn;
-  tile_coords<EPI != EPI_PARTIAL>(pid, tiles, tiles_m, tiles_n, &tm, &tn);
-  int m0 = tm * BM;
-  const int n0 = tn * CN;
-  int expert = 0;
-  if constexpr (GROUPED) {
-    const GroupTile g = gtab[tm];
-    m0 = g.m0;
-    M = g.m_end;
-    expert = g.expert;
-    W += (int64_t)expert * w_stride;
-  }
+  // what a workgroup multiplies next: a tile of C, one k range of it, or one k range of a tail tile (tail_block >= 0)
+  struct Item {
+    int split, tail_block, tn, m0, m_end, n0, expert;
+  };
+  auto locate = [&](int item) {
+    Item t = {0, -1, 0, 0, M, 0, 0};
+    int pid = item;
+    if constexpr (EPI == EPI_PARTIAL) {
+      // all items (k range major) are dealt to the XCDs in contiguous pieces: an XCD then works on one or two
+      // k ranges and its L2 holds only their slices of A, instead of every XCD streaming all of A
+      const int b = xcd_contiguous(item, items);
+      t.split = b / tiles;
+      pid = b - t.split * tiles;
+    } else if (item >= full_tiles) {
+      t.tail_block = item - full_tiles;
+      const int tail = t.tail_block / tail_splits;
+      t.split = t.tail_block - tail * tail_splits;
+      pid = full_tiles + tail;
+    }
+    int tm;
+    tile_coords<EPI != EPI_PARTIAL>(pid, tiles, tiles_m, tiles_n, &tm, &t.tn);
+    t.m0 = tm * BM;
+    t.n0 = t.tn * CN;
+    if constexpr (GROUPED) {
+      const GroupTile g = gtab[tm];
+      t.m0 = g.m0;
+      t.m_end = g.m_end;
+      t.expert = g.expert;
+    }
+    return t;
+  };
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int lane = tid & 63;
   const int wm = wave / WGN, wn = wave % WGN;
-  const int l16 = lane & 15, lg = lane >> 4;
 
-  const int kt_begin = split * kt_per_split;
-  const int kt_end = (EPI == EPI_PARTIAL || tail_block >= 0) ? min(K / BK, kt_begin + kt_per_split) : K / BK;
-  const int KT = kt_end - kt_begin;
   // Experts with few rows read their weights once: the column tiles start at different k-tiles and walk around the end of the
   // range.  In step, all of them ask for the same 128 bytes out of 4 KiB at a time (rows of 2048 are 4 KiB apart), which few
   // channels hold.  The start depends on the column tile and the expert alone, so that a row's sums do not depend on its place in
@@ -246,41 +269,48 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
   // dense products: the wrap costs them 0.4 ... 1 % where several row tiles share the weights (7B at 596 rows), and
   // with one row tile the gain is 0.5 % (rows of 3584; the heads: none).
   constexpr bool WRAP = GROUPED && STAGES > 2;
-  const int k_first = WRAP ? (tn + 5 * expert) % KT : 0;
+  int KT = 0, k_first = 0;
   auto k_tile = [&](int kt) { return WRAP ? kt + (kt + k_first < KT ? k_first : k_first - KT) : kt; };
 
-  // ---- global source of each of this wavefront's loads: a uniform base (first row of the tile, k-tile
-  // kt_begin) and a per-lane byte offset.  Rows fetched through amap are offsets from A itself.
+  // ---- global source of each of this wavefront's loads: a uniform base (first row of the tile, first k-tile) and a
+  // per-lane byte offset.  Rows fetched through amap are offsets from A itself.
   uint32_t a_lane[A_INSTR], w_lane[W_INSTR];
+  const uint16_t *a_base = nullptr, *w_base = nullptr;
   const bool mapped = GROUPED && amap != nullptr;
-  const uint16_t* a_base = A + (mapped ? (int64_t)0 : (int64_t)m0 * lda) + (int64_t)kt_begin * BK;
-  const uint16_t* w_base = W + (int64_t)n0 * K + (int64_t)kt_begin * BK;
-#pragma unroll
-  for (int i = 0; i < A_INSTR; ++i) {
-    const int p = (wave * A_INSTR + i) * 64 + lane;        // LDS chunk this lane fills
-    const int r = p >> 3, c = (p & 7) ^ fswz(r);
-    int gr = m0 + r;
-    gr = gr < M ? gr : M - 1;                              // ragged tail: re-read the last row
-    int64_t rel = gr - m0;
+  int a_row[A_INSTR];                                      // mapped: rows of A behind this lane's rows of the tile
+  auto fetch_rows = [&](const Item& t) {
     if constexpr (GROUPED) {
-      if (mapped) rel = amap[gr];
-    }
-    a_lane[i] = (uint32_t)((rel * lda + c * 8) * 2);
-  }
+      if (mapped) {
 #pragma unroll
-  for (int i = 0; i < W_INSTR; ++i) {
-    const int p = (wave * W_INSTR + i) * 64 + lane;
-    const int r = p >> 3, c = (p & 7) ^ fswz(r);
-    int gr;
-    if constexpr (EPI == EPI_SWIGLU) {
-      gr = n0 + (r < BN / 2 ? r : N + r - BN / 2);
-    } else {
-      gr = n0 + r;
+        for (int i = 0; i < A_INSTR; ++i) a_row[i] = amap[min(t.m0 + (((wave * A_INSTR + i) * 64 + lane) >> 3), t.m_end - 1)];
+      }
     }
-    const int limit = (EPI == EPI_SWIGLU) ? 2 * N : N;
-    gr = gr < limit ? gr : limit - 1;
-    w_lane[i] = (uint32_t)(((int64_t)(gr - n0) * K + c * 8) * 2);
-  }
+  };
+  auto aim = [&](const Item& t) {
+    const int kt_begin = t.split * kt_per_split;
+    KT = ((EPI == EPI_PARTIAL || t.tail_block >= 0) ? min(K / BK, kt_begin + kt_per_split) : K / BK) - kt_begin;
+    k_first = WRAP ? (t.tn + 5 * t.expert) % KT : 0;
+    a_base = A + (mapped ? (int64_t)0 : (int64_t)t.m0 * lda) + (int64_t)kt_begin * BK;
+    w_base = W + (int64_t)t.expert * w_stride + (int64_t)t.n0 * K + (int64_t)kt_begin * BK;
+#pragma unroll
+    for (int i = 0; i < A_INSTR; ++i) {
+      const int p = (wave * A_INSTR + i) * 64 + lane;        // LDS chunk this lane fills
+      const int r = p >> 3, c = (p & 7) ^ fswz(r);
+      int64_t rel = min(r, t.m_end - 1 - t.m0);              // ragged tail: re-read the last row
+      if constexpr (GROUPED) {
+        if (mapped) rel = a_row[i];
+      }
+      a_lane[i] = (uint32_t)((rel * lda + c * 8) * 2);
+    }
+#pragma unroll
+    for (int i = 0; i < W_INSTR; ++i) {
+      const int p = (wave * W_INSTR + i) * 64 + lane;
+      const int r = p >> 3, c = (p & 7) ^ fswz(r);
+      const int row = EPI == EPI_SWIGLU && r >= BN / 2 ? N + r - BN / 2 : r;
+      const int last = (EPI == EPI_SWIGLU ? 2 * N : N) - 1 - t.n0;
+      w_lane[i] = (uint32_t)(((int64_t)min(row, last) * K + c * 8) * 2);
+    }
+  };
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
   // LDS byte address of this wavefront's i-th load of a stage (A part first, then W)
 #define VLC_LDS_DST(stage_, i_)                                                                              \
@@ -302,18 +332,16 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
   int w_off[KS], a_off[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    const int c = (4 * ks + lg) ^ fswz(l16);
+    const int l16 = lane & 15, c = (4 * ks + (lane >> 4)) ^ fswz(l16);
     w_off[ks] = BM * 8 + (wn * WR + l16) * 8 + c;
     a_off[ks] = (wm * WM + l16) * 8 + c;
   }
 
-  // one wavefront per SIMD: the first 64 tiles in accumulation registers, what is over in vector registers
-  constexpr int ACC = OCC * NW <= 4 ? 64 : 0;   // a multiple of 8: mfma_add_last takes tiles of one kind
+  // one wavefront per SIMD: the first 64 tiles in accumulation registers, what is over in vector registers.  A multiple of
+  // 8: mfma_add_last takes tiles of one kind.  Of 64 tiles 56, or the compiler, left with no free accumulation register, moves one
+  // in the middle of the last k-tile.
+  constexpr int ACC = OCC * NW > 4 ? 0 : RESIDENT && NT * MT == 64 ? 56 : 64;
   f32x4 acc[NT][MT];
-#pragma unroll
-  for (int i = 0; i < NT; ++i)
-#pragma unroll
-    for (int j = 0; j < MT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // One k-tile: two k-steps of G groups of MFMAs, the fragment reads of the next k-step spread over groups of this one.
   // ONE BARRIER, before the second k-step: every wavefront holds the fragments of that k-step by then, so the tile's stage
@@ -370,10 +398,27 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
     }                                                                                                         \
   }
 
-  // prologue: fill every stage, read the first fragments
+  // One item after the other.  The next one's first k-tiles are asked for under the last k-step of this one, when its ring
+  // is free, and arrive under that and the epilogue.
+  int item = blockIdx.x;
+  Item cur = locate(item);
+  fetch_rows(cur);
+  aim(cur);
 #pragma unroll
   for (int s = 0; s < STAGES; ++s)
     if (s < KT) { VLC_ISSUE(s, s) }
+  for (;;) {
+  asm volatile("" : "+v"(lane));         // what follows from the lane is worked out anew for every item, not kept
+  const bool more = RESIDENT && item + (int)gridDim.x < items;
+  Item nxt = cur;
+  if (more) {
+    nxt = locate(item + (int)gridDim.x);
+    fetch_rows(nxt);
+  }
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int j = 0; j < MT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int t = 0; t < TILES; ++t) mfma_operand(acc[nt_of(t)][mt_of(t)], t < ACC);
@@ -404,97 +449,172 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
     VLC_COMPUTE_TILE(kt % STAGES, (kt + 1) % STAGES, false, 0, true,
                      { if (later >= 4) { VLC_WAITCNT_VM(4 * LOADS); } else if (later == 3) { VLC_WAITCNT_VM(3 * LOADS); } else if (later == 2) { VLC_WAITCNT_VM(2 * LOADS); } else if (later == 1) { VLC_WAITCNT_VM(LOADS); } else { VLC_WAITCNT_VM(0); } }, 2 * G)
   }
-  // the last k-tile: nothing is left to load or to read ahead, and its second k-step waits for its own results
-  VLC_COMPUTE_TILE(kt % STAGES, 0, false, 0, false, , G)
+  // The last k-tile: nothing is left to read ahead.  Its MFMAs in front of a branch wait for their own results: the last group
+  // of the first k-step, and all of the second.
 #define VLC_ACC(t_) &acc[nt_of(t_)][mt_of(t_)]
-#define VLC_W(t_) &wf[1][nt_of(t_)]
-#define VLC_A(t_) &af[1][mt_of(t_)]
-#pragma unroll
-  for (int t = 0; t + 8 <= TILES; t += 8)
-    mfma_add_last<8>({VLC_ACC(t), VLC_ACC(t + 1), VLC_ACC(t + 2), VLC_ACC(t + 3), VLC_ACC(t + 4), VLC_ACC(t + 5), VLC_ACC(t + 6), VLC_ACC(t + 7)},
-                     {VLC_W(t), VLC_W(t + 1), VLC_W(t + 2), VLC_W(t + 3), VLC_W(t + 4), VLC_W(t + 5), VLC_W(t + 6), VLC_W(t + 7)},
-                     {VLC_A(t), VLC_A(t + 1), VLC_A(t + 2), VLC_A(t + 3), VLC_A(t + 4), VLC_A(t + 5), VLC_A(t + 6), VLC_A(t + 7)}, t < ACC);
-  if constexpr (TILES % 8 >= 4) {
-    constexpr int t = TILES / 8 * 8;
-    mfma_add_last<4>({VLC_ACC(t), VLC_ACC(t + 1), VLC_ACC(t + 2), VLC_ACC(t + 3)}, {VLC_W(t), VLC_W(t + 1), VLC_W(t + 2), VLC_W(t + 3)},
-                     {VLC_A(t), VLC_A(t + 1), VLC_A(t + 2), VLC_A(t + 3)}, t < ACC);
+#define VLC_W(b_, t_) &wf[b_][nt_of(t_)]
+#define VLC_A(b_, t_) &af[b_][mt_of(t_)]
+  // tiles [first_, first_ + count_) with the fragments of buffer b_; BEFORE_(j): in front of statement j
+#define VLC_LAST(b_, first_, count_, BEFORE_)                                                                 \
+  {                                                                                                           \
+    _Pragma("unroll") for (int j = 0; j + 8 <= (count_); j += 8) {                                            \
+      const int t = (first_) + j;                                                                             \
+      BEFORE_(j / 8)                                                                                          \
+      mfma_add_last<8>({VLC_ACC(t), VLC_ACC(t + 1), VLC_ACC(t + 2), VLC_ACC(t + 3), VLC_ACC(t + 4), VLC_ACC(t + 5), VLC_ACC(t + 6), VLC_ACC(t + 7)},  \
+                       {VLC_W(b_, t), VLC_W(b_, t + 1), VLC_W(b_, t + 2), VLC_W(b_, t + 3), VLC_W(b_, t + 4), VLC_W(b_, t + 5), VLC_W(b_, t + 6), VLC_W(b_, t + 7)}, \
+                       {VLC_A(b_, t), VLC_A(b_, t + 1), VLC_A(b_, t + 2), VLC_A(b_, t + 3), VLC_A(b_, t + 4), VLC_A(b_, t + 5), VLC_A(b_, t + 6), VLC_A(b_, t + 7)}, t < ACC); \
+    }                                                                                                         \
+    if constexpr ((count_) % 8 >= 4) {                                                                        \
+      constexpr int t = (first_) + (count_) / 8 * 8;                                                          \
+      BEFORE_((count_) / 8)                                                                                   \
+      mfma_add_last<4>({VLC_ACC(t), VLC_ACC(t + 1), VLC_ACC(t + 2), VLC_ACC(t + 3)},                          \
+                       {VLC_W(b_, t), VLC_W(b_, t + 1), VLC_W(b_, t + 2), VLC_W(b_, t + 3)},                  \
+                       {VLC_A(b_, t), VLC_A(b_, t + 1), VLC_A(b_, t + 2), VLC_A(b_, t + 3)}, t < ACC);        \
+    }                                                                                                         \
+    _Pragma("unroll") for (int j = 0; j < (count_) % 4; ++j) {                                                \
+      const int t = (first_) + (count_) / 4 * 4 + j;                                                          \
+      BEFORE_((count_) / 8 + ((count_) % 8 >= 4 ? 1 : 0) + j)                                                 \
+      mfma_add_last<1>({VLC_ACC(t)}, {VLC_W(b_, t)}, {VLC_A(b_, t)}, t < ACC);                                \
+    }                                                                                                         \
   }
-#pragma unroll
-  for (int t = TILES / 4 * 4; t < TILES; ++t) mfma_add_last<1>({VLC_ACC(t)}, {VLC_W(t)}, {VLC_A(t)}, t < ACC);
+  VLC_COMPUTE_TILE(kt % STAGES, 0, false, 0, false, , G - 1)
+  {
+    const u32x4* st_ = lds + kt % STAGES * STAGE_CHUNKS;
+    if (G - 1 < RN) { VLC_READ_FRAGS(st_, 1, 1, G - 1) }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#define VLC_NOTHING(j_)
+  VLC_LAST(0, TILES - MPG, MPG, VLC_NOTHING)
+  __builtin_amdgcn_sched_barrier(0);
+  int fill = 0;                          // stages of the next item to ask for
+  if (more) {
+    __syncthreads();                     // every wavefront holds its last fragments
+    aim(nxt);
+    fill = min(STAGES, KT);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  constexpr int STATEMENTS = TILES / 8 + (TILES % 8 >= 4 ? 1 : 0) + TILES % 4;
+  // its share of the next item's loads before statement j_
+#define VLC_FILL(j_)                                                                                          \
+  _Pragma("unroll") for (int s = 0; s < STAGES; ++s) {                                                        \
+    if (s < fill) {                                                                                           \
+      _Pragma("unroll") for (int i = 0; i < LOADS; ++i) if ((s * LOADS + i) * STATEMENTS / (STAGES * LOADS) == (j_)) VLC_DMA(s, i, s); \
+    }                                                                                                         \
+  }                                                                                                           \
+  __builtin_amdgcn_sched_barrier(0);
+  VLC_LAST(1, 0, TILES, VLC_FILL)
+#undef VLC_FILL
+#undef VLC_NOTHING
+#undef VLC_LAST
 #undef VLC_ACC
 #undef VLC_W
 #undef VLC_A
   __builtin_amdgcn_sched_barrier(0);
+
+  // ---- epilogue ---------------------------------------------------------------------------------
+  constexpr int ONT = (EPI == EPI_SWIGLU) ? NT / 2 : NT;   // output tiles along n per wavefront
+  constexpr int OWN = (EPI == EPI_SWIGLU) ? WN / 2 : WN;   // output columns per wavefront
+  const int l16 = lane & 15, lg = lane >> 4;
+  // EDGE: rows or columns of the tile are past the end.  Bias and residual are read ahead of the stores (the bias once, the
+  // residual of the next 16 rows before these are stored), past the end from the last valid place.
+  // Every path takes the sums through mfma_operand first, so that the compiler does not copy all of them out of their registers
+  // ahead of the paths.
+  auto own = [&](int nt, int mt) { mfma_operand(acc[nt][mt], nt * MT + ((nt & 1) ? MT - 1 - mt : mt) < ACC); };
+  auto finish = [&](auto edge) {
+    constexpr bool EDGE = decltype(edge)::value;
+    const int m_last = cur.m_end - 1;
+    const int n_first = cur.n0 + wn * OWN + 4 * lg;        // + 16 * nt; N is a multiple of 4
+    auto column = [&](int nt) { return EDGE ? min(n_first + nt * 16, N - 4) : n_first + nt * 16; };
+    constexpr bool WITH_BIAS = EPI == EPI_BIAS_F32 /* EPI_BIAS: the experts' products, without one */, RESID = EPI == EPI_RESIDUAL;
+    uint2 bias_q[WITH_BIAS ? NT : 1], resid_q[2][RESID ? NT : 1];
+    int r_row[RESID ? MT : 1];
+    if constexpr (WITH_BIAS) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) bias_q[nt] = make_uint2(0x80008000u, 0x80008000u);   // -0: adds nothing
+      if (bias) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) bias_q[nt] = *reinterpret_cast<const uint2*>(bias + column(nt));
+      }
+    }
+    auto read_resid = [&](int mt) {
+      const uint16_t* r = resid + (int64_t)r_row[RESID ? mt : 0] * ldr;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) resid_q[mt & 1][RESID ? nt : 0] = *reinterpret_cast<const uint2*>(r + column(nt));
+    };
+    if constexpr (RESID) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) r_row[mt] = EDGE ? min(cur.m0 + wm * WM + mt * 16 + l16, m_last) : cur.m0 + wm * WM + mt * 16 + l16;
+      if (rmap) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) r_row[mt] = rmap[r_row[mt]];
+      }
+      read_resid(0);
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const int m = cur.m0 + wm * WM + mt * 16 + l16;
+      if constexpr (RESID) {
+        if (mt + 1 < MT) read_resid(mt + 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);                   // one row of tiles after the other: few registers beside the sums
+#pragma unroll
+      for (int nt = 0; nt < ONT; ++nt) {
+        const int n = n_first + nt * 16;
+        if (EDGE && (m > m_last || n >= N)) continue;
+        float v[4];
+        own(nt, mt);
+        if constexpr (EPI == EPI_SWIGLU) own(nt + NT / 2, mt);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[nt][mt][e];
+        if constexpr (WITH_BIAS || RESID) {
+          const uint2 b = WITH_BIAS ? bias_q[WITH_BIAS ? nt : 0] : resid_q[mt & 1][RESID ? nt : 0];
+          v[0] += __uint_as_float(b.x << 16); v[1] += __uint_as_float(b.x & 0xffff0000u);
+          v[2] += __uint_as_float(b.y << 16); v[3] += __uint_as_float(b.y & 0xffff0000u);
+        } else if constexpr (EPI == EPI_SWIGLU) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = silu_f(v[e]) * acc[nt + NT / 2][mt][e];
+        }
+        if constexpr (EPI == EPI_PARTIAL) {
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(C) + ((int64_t)cur.split * M + m) * ldc + n) =
+              make_float4(v[0], v[1], v[2], v[3]);
+        } else if constexpr (EPI == EPI_BIAS_F32) {        // unrounded float output (C is a float matrix)
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(C) + (int64_t)m * ldc + n) = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+          uint2 o;
+          o.x = pack_bf16x2(v[0], v[1]);
+          o.y = pack_bf16x2(v[2], v[3]);
+          *reinterpret_cast<uint2*>(C + (int64_t)m * ldc + n) = o;
+        }
+      }
+    }
+  };
+  if (TAIL && cur.tail_block >= 0) {
+    // raw accumulators as a float block [BN/4][BM][4] (lanes of consecutive m write 512 contiguous bytes)
+    float* P = tail_ws + (int64_t)cur.tail_block * (BM * BN);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        own(nt, mt);
+        const int j = wn * WR + w_row(nt) + 4 * lg;        // SwiGLU: gate columns of the tile first, then its up columns
+        *reinterpret_cast<float4*>(P + ((int64_t)(j >> 2) * BM + wm * WM + mt * 16 + l16) * 4) =
+            make_float4(acc[nt][mt][0], acc[nt][mt][1], acc[nt][mt][2], acc[nt][mt][3]);
+      }
+    }
+  } else if (cur.m0 + BM <= cur.m_end && cur.n0 + CN <= N) {
+    finish(std::false_type{});
+  } else {
+    finish(std::true_type{});
+  }
+  if (!more) return;
+  cur = nxt;
+  item += (int)gridDim.x;
+  }
 #undef VLC_READ_FRAGS
 #undef VLC_ISSUE
 #undef VLC_DMA
 #undef VLC_LDS_DST
 #undef VLC_COMPUTE_TILE
-
-  // ---- tail tile: raw accumulators as a float block [BN/4][BM][4] (lanes of consecutive m write 512 contiguous bytes)
-  if constexpr (EPI != EPI_PARTIAL) {
-    if (tail_block >= 0) {
-      float* P = tail_ws + (int64_t)tail_block * (BM * BN);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const int ml = wm * WM + mt * 16 + l16;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const int j = wn * WR + w_row(nt) + 4 * lg;   // SwiGLU: gate columns of the tile first, then its up columns
-          *reinterpret_cast<float4*>(P + ((int64_t)(j >> 2) * BM + ml) * 4) =
-              make_float4(acc[nt][mt][0], acc[nt][mt][1], acc[nt][mt][2], acc[nt][mt][3]);
-        }
-      }
-      return;
-    }
-  }
-
-  // ---- epilogue ---------------------------------------------------------------------------------
-  constexpr int ONT = (EPI == EPI_SWIGLU) ? NT / 2 : NT;   // output tiles along n per wavefront
-  constexpr int OWN = (EPI == EPI_SWIGLU) ? WN / 2 : WN;   // output columns per wavefront
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const int m = m0 + wm * WM + mt * 16 + l16;
-    if (m >= M) continue;
-    int64_t rrow = 0;
-    if constexpr (EPI == EPI_RESIDUAL) rrow = rmap ? (int64_t)rmap[m] : (int64_t)m;
-#pragma unroll
-    for (int nt = 0; nt < ONT; ++nt) {
-      const int n = n0 + wn * OWN + nt * 16 + 4 * lg;
-      if (n >= N) continue;                                  // N is a multiple of 4
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = acc[nt][mt][e];
-      if constexpr (EPI == EPI_PARTIAL) {
-        float* P = reinterpret_cast<float*>(C) + ((int64_t)split * M + m) * ldc + n;
-        *reinterpret_cast<float4*>(P) = make_float4(v[0], v[1], v[2], v[3]);
-        continue;
-      }
-      if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_F32) {
-        if (bias) {
-          const uint2 b = *reinterpret_cast<const uint2*>(bias + n);
-          v[0] += __uint_as_float(b.x << 16); v[1] += __uint_as_float(b.x & 0xffff0000u);
-          v[2] += __uint_as_float(b.y << 16); v[3] += __uint_as_float(b.y & 0xffff0000u);
-        }
-      } else if constexpr (EPI == EPI_RESIDUAL) {
-        const uint2 b = *reinterpret_cast<const uint2*>(resid + rrow * ldr + n);
-        v[0] += __uint_as_float(b.x << 16); v[1] += __uint_as_float(b.x & 0xffff0000u);
-        v[2] += __uint_as_float(b.y << 16); v[3] += __uint_as_float(b.y & 0xffff0000u);
-      } else if constexpr (EPI == EPI_SWIGLU) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = silu_f(v[e]) * acc[nt + NT / 2][mt][e];
-      }
-      if constexpr (EPI == EPI_BIAS_F32) {   // unrounded float output (C is a float matrix)
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(C) + (int64_t)m * ldc + n) =
-            make_float4(v[0], v[1], v[2], v[3]);
-      } else {
-        uint2 o;
-        o.x = pack_bf16x2(v[0], v[1]);
-        o.y = pack_bf16x2(v[2], v[3]);
-        *reinterpret_cast<uint2*>(C + (int64_t)m * ldc + n) = o;
-      }
-    }
-  }
 }
 
 // Sum of the split-K partials [splits][M][N] (float) + epilogue; one thread per 4 columns.
@@ -783,8 +903,6 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
   const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + CN - 1) / CN);
   const int tiles = tiles_m * tiles_n;
   const size_t lds = (size_t)STAGES * (BM + BN) * BK * 2;
-  auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI>;
-  if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
   const int KT = (int)(K / BK);
   int full = tiles * splits, tail = 0, tsp = 1, tkt = kt_per_split;
   if constexpr (EPI != EPI_PARTIAL) {
@@ -796,9 +914,14 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
       full = tiles - tail;
     }
   }
-  hipLaunchKernelGGL(kern, dim3(full + tail * tsp), dim3(WGM * WGN * 64), lds, st, (const uint16_t*)A, lda,
+  const int items = full + tail * tsp;
+  constexpr bool MAY_STAY = EPI != EPI_PARTIAL && gemm_may_stay(BM, BN, WGM * WGN);
+  const bool stay = MAY_STAY && items > kStayRounds * 256 * OCC;
+  auto kern = stay ? gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, MAY_STAY> : gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, false>;
+  if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
+  hipLaunchKernelGGL(kern, dim3(stay ? 256 * OCC : items), dim3(WGM * WGN * 64), lds, st, (const uint16_t*)A, lda,
                      (const uint16_t*)W, (uint16_t*)C, ldc, (int)M, (int)N, (int)K, (const uint16_t*)bias,
-                     (const uint16_t*)resid, ldr, rmap, tiles_m, tiles_n, tkt, full, tsp, (float*)tail_ws,
+                     (const uint16_t*)resid, ldr, rmap, tiles_m, tiles_n, tkt, full, tsp, items, (float*)tail_ws,
                      (const GroupTile*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr, (int64_t)0);
   VLC_CHECK_LAUNCH("gemm_bf16");
   if constexpr (EPI != EPI_PARTIAL) {
@@ -1018,12 +1141,13 @@ int launch_bf16_grouped(const void* A, int64_t lda, const int32_t* amap, const v
   constexpr int CN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
   const int tiles_n = (int)((N + CN - 1) / CN);
   const size_t lds = (size_t)STAGES * (BM + BN) * BK * 2;
-  auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, true>;
+  constexpr bool STAY = gemm_may_stay(BM, BN, WGM * WGN);
+  auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, STAY, true>;
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
-  const int grid = max_tiles_m * tiles_n;
+  const int most = max_tiles_m * tiles_n, grid = STAY && most > 256 * OCC ? 256 * OCC : most;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), lds, st, (const uint16_t*)A, lda, (const uint16_t*)W,
                      (uint16_t*)C, ldc, 0, (int)N, (int)K, (const uint16_t*)nullptr, (const uint16_t*)nullptr,
-                     (int64_t)0, (const int32_t*)nullptr, max_tiles_m, tiles_n, (int)(K / BK), grid, 1,
+                     (int64_t)0, (const int32_t*)nullptr, max_tiles_m, tiles_n, (int)(K / BK), most, 1, most,
                      (float*)nullptr, gtab, g_ntiles, amap, w_stride);
   VLC_CHECK_LAUNCH("gemm_bf16_grouped");
   return VLC_OK;

@@ -1,0 +1,36 @@
+"""bf16 products whose workgroups stay for several tiles and ask for the next one's first k-tiles before they store the last
+one's outputs: k ranges shorter than the ring of stages and longer, ragged rows and columns, last rounds split along k, and
+experts whose row tiles are only known on the device."""
+import pytest
+
+import vlc_synth as syn
+from test_gpu_gemm_tiles import FLOAT, RESIDUAL, SWIGLU, choice, test_layer_products_on_every_tile as check_layer
+from test_gpu_moe import check_moe_layer
+
+# (product, its epilogue, last round split) of the layer (H, I, Hq, Hkv, rows) that stays
+CASES = [("gate_up", False, (64, 4096, 1, 1, 5000)), ("gate_up", False, (128, 4160, 1, 1, 8191)), ("gate_up", False, (192, 4096, 1, 1, 16390)),
+         ("qkv", False, (64, 192, 40, 8, 12001)), ("gate_up", True, (2048, 2048, 1, 1, 16390)), ("gate_up", True, (2048, 6464, 1, 1, 4097))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("product,split,layer", CASES)
+def test_products_of_many_rounds(product, split, layer):
+    """More than three rounds of tiles on four wavefronts (asked of the library), at the tolerances of the tests of the tiles."""
+    H, I, Hq, Hkv, rows = layer
+    epilogue, N = {"qkv": (FLOAT, (Hq + 2 * Hkv) * 128), "gate_up": (SWIGLU, I), "o": (RESIDUAL, H)}[product]
+    (bm, bn, occ, waves), _, how = choice(epilogue, rows, N, H)
+    tiles = -(-rows // bm) * -(-N // (bn // 2 if epilogue == SWIGLU else bn))
+    assert waves == 4 and 192 * 192 <= bm * bn <= 256 * 256 and tiles > 3 * 256 * occ, (bm, bn, waves, tiles)
+    assert (how == "split last round") == split, how
+    check_layer(H, I, Hq, Hkv, rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,H,I", [(2600, 3328, 64), (2600, 3264, 192), (1800, 128, 2176), (900, 192, 2240)])
+def test_experts_of_many_tiles(rows, H, I):
+    """2 of 8 experts; more tiles than workgroups in the down projection (one and three k-tiles), then in gate|up, whose rows are
+    fetched through the pair list (two and three k-tiles); tiles of 256 rows, in the last case of 192."""
+    sh = syn.Shape("moe_stay", L=1, H=H, Hq=4, Hkv=2, D=128, I=I, rope_base=1e4, dtype="bf16", qkv_bias=False, qk_norm=True,
+                   mrope_section=(24, 20, 20), n_experts=8, top_k=2, text_scale=1.0, residual_proj_scale=0.01)
+    req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
+    check_moe_layer(syn.Workload("moe_stay%d_%d" % (rows, I), sh, [req], 1, "static", static_k=0, seed=1200 + I), 0)
