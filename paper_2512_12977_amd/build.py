@@ -13,6 +13,9 @@ LIB = os.path.join(HERE, "libvlcache.so")
 SOURCES = ["api.cpp", "planner.cpp", "layer.cpp", "stream_kernels.hip", "gemm.hip", "attention.hip", "moe.hip", "noalloc.hip", "probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the first 14 words of a kernel's arguments wait in scalar registers when a workgroup starts, instead of being
+         # fetched by its first instructions (0.6 ... 0.8 us of every launch)
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 

@@ -134,11 +134,10 @@ __device__ __forceinline__ void att_piece(int id, int Hkv, int* kvh, int* piece)
 // fragment reads alone would need the whole LDS bandwidth at full MFMA rate).
 template <bool SPLIT, int RT>
 __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
-    const uint16_t* __restrict__ q, int64_t q_stride, const uint16_t* __restrict__ kc,
-    const uint16_t* __restrict__ vc, const int32_t* __restrict__ row_kv_start,
-    const int32_t* __restrict__ row_kv_len, int n, int Hq, int Hkv, int g, int rows_per_tile,
-    float scale_log2, uint16_t* __restrict__ out, const int4* __restrict__ pieces, float* __restrict__ part_o,
-    float* __restrict__ part_ml) {
+    const int4* __restrict__ pieces, const int32_t* __restrict__ row_kv_start, const int32_t* __restrict__ row_kv_len,
+    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc, int n, int Hkv, int g, int rows_per_tile,
+    const uint16_t* __restrict__ q, int64_t q_stride, int Hq, float scale_log2, uint16_t* __restrict__ out,
+    float* __restrict__ part_o, float* __restrict__ part_ml) {
   __shared__ u32x4 lds[2 * ATT_STAGE_CHUNKS];     // 64 KB: K ring (2 tiles), then V ring (2 tiles)
   __shared__ int s_start[VR * RT];
   __shared__ int s_len[VR * RT];
@@ -518,9 +517,9 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
 // shares of the row's tile.  One thread per 8 output elements.
 __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ part_o,
                                                               const float* __restrict__ part_ml,
-                                                              const int32_t* __restrict__ tile_shares, int rows_per_tile,
-                                                              const int32_t* __restrict__ row_kv_len,
-                                                              int Hq, int64_t rows_heads, uint16_t* __restrict__ out) {
+                                                              const int32_t* __restrict__ tile_shares,
+                                                              const int32_t* __restrict__ row_kv_len, int64_t rows_heads,
+                                                              int rows_per_tile, int Hq, uint16_t* __restrict__ out) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t rh = id / (ATT_D / 8);
   const int c = (int)(id - rh * (ATT_D / 8));
@@ -588,12 +587,10 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 constexpr int64_t kF32OneWavePairs = 2048;
 
 template <int D, int F32_WAVES>
-__global__ __launch_bounds__(64 * F32_WAVES) void attention_f32_kernel(const float* __restrict__ q, int64_t q_stride,
-                                                            const float* __restrict__ kc,
-                                                            const float* __restrict__ vc,
+__global__ __launch_bounds__(64 * F32_WAVES) void attention_f32_kernel(const float* __restrict__ q, const int32_t* __restrict__ row_kv_len,
                                                             const int32_t* __restrict__ row_kv_start,
-                                                            const int32_t* __restrict__ row_kv_len, int Hq,
-                                                            int Hkv, int g, float scale,
+                                                            const float* __restrict__ kc, const float* __restrict__ vc,
+                                                            int q_stride, int Hkv, int g, float scale, int Hq,
                                                             float* __restrict__ out) {
   constexpr int DL = D / 64;                       // output elements per lane
   constexpr int UNROLL = 16;                       // value rows in flight
@@ -749,21 +746,20 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     const int64_t tiles = (n + rows_per_tile - 1) / rows_per_tile;
     if (shares && shares->max_shares > 1) {
       hipLaunchKernelGGL((attention_bf16_kernel<true, 1>), dim3((unsigned)(shares->slots * Hkv)), dim3(256), 0, st,
-                         (const uint16_t*)q, q_stride, (const uint16_t*)k_cache, (const uint16_t*)v_cache, row_kv_start,
-                         row_kv_len, (int)n, Hq, Hkv, g, rows_per_tile, scale * 1.4426950408889634f, (uint16_t*)out,
-                         (const int4*)shares->pieces, shares->part_o, shares->part_ml);
+                         (const int4*)shares->pieces, row_kv_start, row_kv_len, (const uint16_t*)k_cache, (const uint16_t*)v_cache,
+                         (int)n, Hkv, g, rows_per_tile, (const uint16_t*)q, q_stride, Hq, scale * 1.4426950408889634f,
+                         (uint16_t*)out, shares->part_o, shares->part_ml);
       VLC_CHECK_LAUNCH("attention_bf16(split)");
       const int64_t threads = n * Hq * (ATT_D / 8);
       hipLaunchKernelGGL(attention_merge_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, shares->part_o,
-                         shares->part_ml, (const int32_t*)shares->tile_shares, rows_per_tile, row_kv_len, Hq, n * Hq, (uint16_t*)out);
+                         shares->part_ml, (const int32_t*)shares->tile_shares, row_kv_len, n * Hq, rows_per_tile, Hq, (uint16_t*)out);
       VLC_CHECK_LAUNCH("attention_merge");
       return VLC_OK;
     }
     const dim3 grid((unsigned)att_grid((int)tiles, Hkv));
-    hipLaunchKernelGGL((attention_bf16_kernel<false, 1>), grid, dim3(256), 0, st, (const uint16_t*)q, q_stride,
-                       (const uint16_t*)k_cache, (const uint16_t*)v_cache, row_kv_start, row_kv_len, (int)n,
-                       Hq, Hkv, g, rows_per_tile, scale * 1.4426950408889634f, (uint16_t*)out, nullptr, nullptr,
-                       nullptr);
+    hipLaunchKernelGGL((attention_bf16_kernel<false, 1>), grid, dim3(256), 0, st, nullptr, row_kv_start, row_kv_len,
+                       (const uint16_t*)k_cache, (const uint16_t*)v_cache, (int)n, Hkv, g, rows_per_tile, (const uint16_t*)q,
+                       q_stride, Hq, scale * 1.4426950408889634f, (uint16_t*)out, nullptr, nullptr);
     VLC_CHECK_LAUNCH("attention_bf16");
     return VLC_OK;
   }
@@ -774,8 +770,8 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     const bool one = n * Hq >= kF32OneWavePairs;
 #define VLC_LAUNCH_F32_ATT(D_, W_)                                                                                  \
   hipLaunchKernelGGL((attention_f32_kernel<D_, W_>), dim3((unsigned)n, (unsigned)Hq), dim3(64 * W_), 0, st,        \
-                     (const float*)q, q_stride, (const float*)k_cache, (const float*)v_cache, row_kv_start, row_kv_len, \
-                     Hq, Hkv, g, scale, (float*)out)
+                     (const float*)q, row_kv_len, row_kv_start, (const float*)k_cache, (const float*)v_cache, (int)q_stride, \
+                     Hkv, g, scale, Hq, (float*)out)
     if (D == 64 && one) VLC_LAUNCH_F32_ATT(64, 1);
     else if (D == 64) VLC_LAUNCH_F32_ATT(64, 8);
     else if (one) VLC_LAUNCH_F32_ATT(128, 1);

@@ -192,8 +192,8 @@ enum { EPI_PARTIAL = 100 };   // internal: float partial sums of one k-range (sp
 // rows - fetched through amap when given - with that expert's matrix W + expert * w_stride.
 // Workgroups beyond the table's length (only known on the device) exit at once, and the XCDs share out the tiles that
 // are there (dealt by the largest possible length, 37 rows per expert left two of the eight XCDs idle).
-template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool RESIDENT, bool GROUPED = false>
-__global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool RESIDENT, bool GROUPED>
+__device__ __forceinline__ void gemm_bf16_items(
     const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ W, uint16_t* __restrict__ C,
     int64_t ldc, int M, int N, int K, const uint16_t* __restrict__ bias, const uint16_t* __restrict__ resid,
     int64_t ldr, const int32_t* __restrict__ rmap, int tiles_m, int tiles_n, int kt_per_split, int full_tiles,
@@ -617,13 +617,35 @@ __global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
 #undef VLC_COMPUTE_TILE
 }
 
+// The entries.  What a workgroup needs for its first loads comes first: 14 words of arguments are in scalar registers when a
+// workgroup starts (see build.py), the others it has to fetch.
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool RESIDENT>
+__global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ W, int K, int N, int lda, int tiles_n, int M, int tiles_m,
+    int kt_per_split, int full_tiles, int tail_splits, int items, uint16_t* __restrict__ C, int64_t ldc,
+    const uint16_t* __restrict__ bias, const uint16_t* __restrict__ resid, int64_t ldr, const int32_t* __restrict__ rmap,
+    float* __restrict__ tail_ws) {
+  gemm_bf16_items<BM, BN, WGM, WGN, STAGES, OCC, EPI, RESIDENT, false>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, tiles_m,
+                                                                       tiles_n, kt_per_split, full_tiles, tail_splits, items, tail_ws,
+                                                                       nullptr, nullptr, nullptr, 0);
+}
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool RESIDENT, bool GROUPED>
+__global__ __launch_bounds__(WGM * WGN * 64, OCC) void gemm_bf16_kernel(
+    const int32_t* __restrict__ g_ntiles, const GroupTile* __restrict__ gtab, const int32_t* __restrict__ amap,
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ W, int K, int N, int lda, int tiles_n, int64_t w_stride,
+    uint16_t* __restrict__ C, int64_t ldc) {
+  static_assert(GROUPED, "the other entry");
+  gemm_bf16_items<BM, BN, WGM, WGN, STAGES, OCC, EPI, RESIDENT, true>(A, lda, W, C, ldc, 0, N, K, nullptr, nullptr, 0, nullptr, 0,
+                                                                      tiles_n, K / BK, 0, 1, 0, nullptr, gtab, g_ntiles, amap, w_stride);
+}
+
 // Sum of the split-K partials [splits][M][N] (float) + epilogue; one thread per 4 columns.
 template <int EPI>
-__global__ __launch_bounds__(256) void splitk_epilogue_kernel(const float* __restrict__ P, int splits,
-                                                              uint16_t* __restrict__ C, int64_t ldc, int M, int N,
-                                                              const uint16_t* __restrict__ bias,
+__global__ __launch_bounds__(256) void splitk_epilogue_kernel(const float* __restrict__ P, int splits, int M, int N,
                                                               const uint16_t* __restrict__ resid, int64_t ldr,
-                                                              const int32_t* __restrict__ rmap) {
+                                                              const int32_t* __restrict__ rmap,
+                                                              const uint16_t* __restrict__ bias,
+                                                              uint16_t* __restrict__ C, int64_t ldc) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int nq = N / 4;
   const int64_t m = id / nq;
@@ -755,12 +777,10 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const float* __restric
 // instructions, 4 ... 8 workgroups walking k in 16-wide steps behind barriers, took 43 ... 98 us.
 // KW = 1 (enough tiles for the chip): 2 x 2 wavefronts, each with its own output tiles; up to 106 TFLOP/s (47 before).
 template <int MT, int NT, int WGM, int WGN, int KW, int EPI, bool GROUPED = false>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda,
-                                                       const float* __restrict__ W, float* __restrict__ C,
-                                                       int64_t ldc, int M, int N, int K,
-                                                       const float* __restrict__ bias,
-                                                       const float* __restrict__ resid, int64_t ldr,
-                                                       const int32_t* __restrict__ rmap,
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int K, int M,
+                                                       int N, int lda, const float* __restrict__ bias,
+                                                       const float* __restrict__ resid, const int32_t* __restrict__ rmap,
+                                                       float* __restrict__ C, int64_t ldc, int64_t ldr,
                                                        const GroupTile* __restrict__ gtab,
                                                        const int32_t* __restrict__ g_ntiles,
                                                        const int32_t* __restrict__ amap, int64_t w_stride) {
@@ -919,10 +939,9 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
   const bool stay = MAY_STAY && items > kStayRounds * 256 * OCC;
   auto kern = stay ? gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, MAY_STAY> : gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, false>;
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
-  hipLaunchKernelGGL(kern, dim3(stay ? 256 * OCC : items), dim3(WGM * WGN * 64), lds, st, (const uint16_t*)A, lda,
-                     (const uint16_t*)W, (uint16_t*)C, ldc, (int)M, (int)N, (int)K, (const uint16_t*)bias,
-                     (const uint16_t*)resid, ldr, rmap, tiles_m, tiles_n, tkt, full, tsp, items, (float*)tail_ws,
-                     (const GroupTile*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr, (int64_t)0);
+  hipLaunchKernelGGL(kern, dim3(stay ? 256 * OCC : items), dim3(WGM * WGN * 64), lds, st, (const uint16_t*)A, (const uint16_t*)W,
+                     (int)K, (int)N, (int)lda, tiles_n, (int)M, tiles_m, tkt, full, tsp, items, (uint16_t*)C, ldc,
+                     (const uint16_t*)bias, (const uint16_t*)resid, ldr, rmap, (float*)tail_ws);
   VLC_CHECK_LAUNCH("gemm_bf16");
   if constexpr (EPI != EPI_PARTIAL) {
     if (tail > 0) {
@@ -1088,8 +1107,8 @@ int dispatch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ld
       }
       const int64_t threads = M * (N / 4);
       hipLaunchKernelGGL(splitk_epilogue_kernel<EPI>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
-                         (const float*)splitk_ws, splits, (uint16_t*)C, ldc, (int)M, (int)N, (const uint16_t*)bias,
-                         (const uint16_t*)resid, ldr, rmap);
+                         (const float*)splitk_ws, splits, (int)M, (int)N, (const uint16_t*)resid, ldr, rmap,
+                         (const uint16_t*)bias, (uint16_t*)C, ldc);
       VLC_CHECK_LAUNCH("splitk_epilogue");
       return VLC_OK;
     }
@@ -1123,8 +1142,8 @@ int launch_f32(const void* A, int64_t lda, const void* W, void* C, int64_t ldc, 
   const int64_t gy = large ? lm : (M + 15) / 16;
   const dim3 grid((unsigned)(large ? ln : (N + 15) / 16), (unsigned)gy);
 #define VLC_LAUNCH_F32(...)                                                                                        \
-  hipLaunchKernelGGL((gemm_f32_kernel<__VA_ARGS__, EPI>), grid, dim3(256), 0, st, (const float*)A, lda, (const float*)W, \
-                     (float*)C, ldc, (int)M, (int)N, (int)K, (const float*)bias, (const float*)resid, ldr, rmap,   \
+  hipLaunchKernelGGL((gemm_f32_kernel<__VA_ARGS__, EPI>), grid, dim3(256), 0, st, (const float*)A, (const float*)W, \
+                     (int)K, (int)M, (int)N, (int)lda, (const float*)bias, (const float*)resid, rmap, (float*)C, ldc, ldr, \
                      (const GroupTile*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr, (int64_t)0)
   if (large) VLC_LAUNCH_F32(4, NT, 2, 2, 1);
   else VLC_LAUNCH_F32(1, 1, 1, 1, 4);
@@ -1145,10 +1164,8 @@ int launch_bf16_grouped(const void* A, int64_t lda, const int32_t* amap, const v
   auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, STAY, true>;
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
   const int most = max_tiles_m * tiles_n, grid = STAY && most > 256 * OCC ? 256 * OCC : most;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), lds, st, (const uint16_t*)A, lda, (const uint16_t*)W,
-                     (uint16_t*)C, ldc, 0, (int)N, (int)K, (const uint16_t*)nullptr, (const uint16_t*)nullptr,
-                     (int64_t)0, (const int32_t*)nullptr, max_tiles_m, tiles_n, (int)(K / BK), most, 1, most,
-                     (float*)nullptr, gtab, g_ntiles, amap, w_stride);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), lds, st, g_ntiles, gtab, amap, (const uint16_t*)A, (const uint16_t*)W,
+                     (int)K, (int)N, (int)lda, tiles_n, w_stride, (uint16_t*)C, ldc);
   VLC_CHECK_LAUNCH("gemm_bf16_grouped");
   return VLC_OK;
 }
@@ -1163,9 +1180,9 @@ int launch_f32_grouped(const void* A, int64_t lda, const int32_t* amap, const vo
   const int64_t gy = large ? max_tiles_m : (int64_t)max_tiles_m * 4;
   const dim3 grid((unsigned)(large ? ln : (N + 15) / 16), (unsigned)gy);
 #define VLC_LAUNCH_F32(...)                                                                                       \
-  hipLaunchKernelGGL((gemm_f32_kernel<__VA_ARGS__, EPI, true>), grid, dim3(256), 0, st, (const float*)A, lda,     \
-                     (const float*)W, (float*)C, ldc, 0, (int)N, (int)K, (const float*)nullptr,                  \
-                     (const float*)nullptr, (int64_t)0, (const int32_t*)nullptr, gtab, g_ntiles, amap, w_stride)
+  hipLaunchKernelGGL((gemm_f32_kernel<__VA_ARGS__, EPI, true>), grid, dim3(256), 0, st, (const float*)A,          \
+                     (const float*)W, (int)K, 0, (int)N, (int)lda, (const float*)nullptr, (const float*)nullptr, \
+                     (const int32_t*)nullptr, (float*)C, ldc, (int64_t)0, gtab, g_ntiles, amap, w_stride)
   if (large) VLC_LAUNCH_F32(2, NT, 2, 2, 1);
   else VLC_LAUNCH_F32(1, 1, 1, 1, 4);
 #undef VLC_LAUNCH_F32

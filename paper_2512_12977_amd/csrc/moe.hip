@@ -72,10 +72,9 @@ __device__ __forceinline__ uint64_t wave_max(uint64_t k) {
 // one wavefront per row
 // logits: `splits` float partial matrices [n, E] (split_stride floats apart) whose sum are the scores
 // (1: the scores themselves).
-__global__ __launch_bounds__(256) void moe_route_kernel(const float* __restrict__ logits, int splits,
-                                                        int64_t split_stride, float* __restrict__ sum_out,
-                                                        int64_t n, int E, int K,
-                                                        int32_t* __restrict__ idx, float* __restrict__ wts) {
+__global__ __launch_bounds__(256) void moe_route_kernel(const float* __restrict__ logits, int64_t split_stride,
+                                                        int64_t n, int splits, int E, int K, int32_t* __restrict__ idx,
+                                                        float* __restrict__ wts, float* __restrict__ sum_out) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= n) return;
@@ -316,9 +315,9 @@ __global__ __launch_bounds__(256) void moe_combine_kernel(const T* __restrict__ 
 template <typename T, int MAXC>
 __global__ __launch_bounds__(256) void moe_combine_norm_kernel(const T* __restrict__ h1, const T* __restrict__ y,
                                                                const float* __restrict__ wts,
-                                                               const int32_t* __restrict__ pair_pos, int K, int H,
-                                                               T* __restrict__ out, const T* __restrict__ nw,
-                                                               T* __restrict__ yn, const int32_t* __restrict__ ymap,
+                                                               const int32_t* __restrict__ pair_pos,
+                                                               const int32_t* __restrict__ ymap, const T* __restrict__ nw,
+                                                               int K, int H, T* __restrict__ out, T* __restrict__ yn,
                                                                float inv_h, float eps) {
   constexpr int VEC = 16 / sizeof(T);
   const int64_t row = blockIdx.x;
@@ -395,8 +394,8 @@ int launch_moe_route(const float* logits, int splits, int64_t split_stride, floa
                 top_k, kMaxTopK);
   if (n * top_k > INT32_MAX) return fail(VLC_ERR_SHAPE, "moe: too many (row, expert) pairs");
   const int64_t pairs = n * top_k;
-  hipLaunchKernelGGL(moe_route_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, logits, splits, split_stride,
-                     sum_out, n, n_experts, top_k, s.idx, s.wts);
+  hipLaunchKernelGGL(moe_route_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, logits, split_stride, n, splits,
+                     n_experts, top_k, s.idx, s.wts, sum_out);
   VLC_CHECK_LAUNCH("moe_route");
   if (pairs <= kSmallPlanPairs) {
     hipLaunchKernelGGL(moe_plan_small_kernel, dim3(1), dim3(1024), 0, st, (const int32_t*)s.idx, pairs, top_k,
@@ -448,7 +447,7 @@ int launch_moe_combine_norm(const void* h1, const void* y, const float* wts, con
   const float inv_h = 1.0f / (float)H;
 #define VLC_LAUNCH_MCN(T, MAXC)                                                                              \
   hipLaunchKernelGGL((moe_combine_norm_kernel<T, MAXC>), dim3((unsigned)n), dim3(256), 0, st, (const T*)h1,  \
-                     (const T*)y, wts, pair_pos, top_k, H, (T*)out, (const T*)norm_w, (T*)normed, ymap, inv_h, eps)
+                     (const T*)y, wts, pair_pos, ymap, (const T*)norm_w, top_k, H, (T*)out, (T*)normed, inv_h, eps)
   if (chunks <= 256 * 2) {
     if (dtype == VLC_BF16) VLC_LAUNCH_MCN(uint16_t, 2); else VLC_LAUNCH_MCN(float, 2);
   } else if (chunks <= 256 * 8) {

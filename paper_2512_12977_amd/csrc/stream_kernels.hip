@@ -212,10 +212,10 @@ constexpr int kMaxSplits = 8;   // the GEMM never splits the k range into more p
 // are spread over CH consecutive lanes, which exchange their partial sums of squares).
 template <typename T, int D, bool SUM>
 __global__ __launch_bounds__(kThreads) void rope_qk_scatter_kernel(
-    const float* __restrict__ qkv, int splits, int64_t split_stride, const uint16_t* __restrict__ bias,
-    float* __restrict__ qkv_sum, const int32_t* __restrict__ pos, const int32_t* __restrict__ pos3,
-    const T* __restrict__ w_qn, const T* __restrict__ w_kn, float eps, const int32_t* __restrict__ slot,
-    int64_t n, int Hq, int Hkv, RopeFreq freq, uint4* __restrict__ q_out,
+    const float* __restrict__ qkv, int64_t split_stride, const int32_t* __restrict__ pos, const uint16_t* __restrict__ bias,
+    int64_t n, int splits, int Hq, int Hkv, float eps, const int32_t* __restrict__ slot,
+    const int32_t* __restrict__ pos3, const T* __restrict__ w_qn, const T* __restrict__ w_kn, float* __restrict__ qkv_sum,
+    RopeFreq freq, uint4* __restrict__ q_out,
     uint4* __restrict__ k_cache, uint4* __restrict__ v_cache, AttentionShares shares) {
   constexpr int VEC = Chunk<T>::VEC;
   constexpr int CH = (D / 2) / VEC;
@@ -383,9 +383,9 @@ __global__ __launch_bounds__(kThreads) void rmsnorm_kernel(const uint4* __restri
 // stand-alone split-K epilogue (partials in split order, then the residual).
 template <int MAXC>
 __global__ __launch_bounds__(kThreads) void sum_residual_rmsnorm_kernel(
-    const float* __restrict__ part, int splits, int64_t split_stride, const uint4* __restrict__ resid,
-    const int32_t* __restrict__ rmap, const uint4* __restrict__ w, uint4* __restrict__ h,
-    uint4* __restrict__ y, int chunks, float inv_h, float eps, const int32_t* __restrict__ ymap) {
+    const int32_t* __restrict__ rmap, const int32_t* __restrict__ ymap, const uint4* __restrict__ w,
+    const float* __restrict__ part, int64_t split_stride, const uint4* __restrict__ resid, int splits, int chunks,
+    uint4* __restrict__ h, uint4* __restrict__ y, float inv_h, float eps) {
   using CB = Chunk<uint16_t>;
   const int64_t row = blockIdx.x;
   const int64_t rrow = rmap ? (int64_t)rmap[row] : row;
@@ -591,9 +591,9 @@ int launch_rope_qk_scatter(const float* qkv32, const int32_t* pos, const int32_t
   const dim3 grid((unsigned)((threads + kThreads - 1) / kThreads + (plan.max_shares > 1)));
 #define VLC_LAUNCH_RQS(T, DD, SUM)                                                                    \
   hipLaunchKernelGGL((rope_qk_scatter_kernel<T, DD, SUM>), grid, dim3(kThreads), 0, st,               \
-                     SUM ? partials : qkv32, splits, split_stride, (const uint16_t*)bias,             \
-                     const_cast<float*>(qkv32), pos, pos3, (const T*)w_qnorm, (const T*)w_knorm, eps, \
-                     slot, n, Hq, Hkv, f, (uint4*)q_out, (uint4*)k_cache, (uint4*)v_cache, plan)
+                     SUM ? partials : qkv32, split_stride, pos, (const uint16_t*)bias, n, splits,     \
+                     Hq, Hkv, eps, slot, pos3, (const T*)w_qnorm, (const T*)w_knorm,                  \
+                     const_cast<float*>(qkv32), f, (uint4*)q_out, (uint4*)k_cache, (uint4*)v_cache, plan)
   if (splits > 1 && D == 128) VLC_LAUNCH_RQS(uint16_t, 128, true);
   else if (splits > 1 && D == 64) VLC_LAUNCH_RQS(uint16_t, 64, true);
   else if (dtype == VLC_BF16 && D == 128) VLC_LAUNCH_RQS(uint16_t, 128, false);
@@ -642,9 +642,9 @@ int launch_sum_residual_rmsnorm(const float* partials, int splits, const void* r
   const float inv_h = 1.0f / (float)H;
   const int64_t split_stride = n * (int64_t)H;
 #define VLC_LAUNCH_SRN(MAXC)                                                                          \
-  hipLaunchKernelGGL((sum_residual_rmsnorm_kernel<MAXC>), grid, dim3(kThreads), 0, st, partials,      \
-                     splits, split_stride, (const uint4*)resid, rmap, (const uint4*)w, (uint4*)h,     \
-                     (uint4*)y, chunks, inv_h, eps, ymap)
+  hipLaunchKernelGGL((sum_residual_rmsnorm_kernel<MAXC>), grid, dim3(kThreads), 0, st, rmap, ymap,    \
+                     (const uint4*)w, partials, split_stride, (const uint4*)resid, splits, chunks,    \
+                     (uint4*)h, (uint4*)y, inv_h, eps)
   if (chunks <= kThreads * 2) VLC_LAUNCH_SRN(2);
   else if (chunks <= kThreads * 4) VLC_LAUNCH_SRN(4);
   else if (chunks <= kThreads * 8) VLC_LAUNCH_SRN(8);
