@@ -12,7 +12,7 @@ namespace vlc {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -29,16 +29,20 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) { return f32_t
 // bf16 MFMA kernel, D = 128
 // ---------------------------------------------------------------------------------------------
 // Tile: VR = 128 "virtual rows" = (query row, head of the kv group) pairs, head fastest; 4 wavefronts
-// of 32 virtual rows each, two workgroups per CU.  Keys are consumed in blocks of 64.
+// of 32 virtual rows (two tiles of 16) each, two workgroups per CU.  Keys are consumed in blocks of 64.
 //
-// Both products are computed transposed so that every lane owns exactly one virtual row:
+// Both products are computed transposed so that a lane's accumulators belong to two virtual rows only:
 //   S^T[key, vr] = K[key, :] . Q[vr, :]      MFMA A = K fragment (LDS), B = Q fragment (registers)
 //   O^T[d,  vr] += V^T[d, key] P^T[key, vr]  MFMA A = V^T fragment (LDS), B = P^T (from S^T registers)
-// In the 32x32 accumulator layout lane l holds column vr = l % 32 and rows 8*(j/4) + 4*(l/32) + j%4,
-// so a row's running max / sum / rescale factor are per-lane scalars and the only cross-lane step is
-// one exchange between lanes l and l^32.  The S^T accumulators feed the second MFMA directly: its
-// contraction index is just a relabeling of keys, as long as the V^T fragment uses the same
-// relabeling, which is how V^T is laid out in LDS.
+// In the 16x16 accumulator layout lane l holds column vr = l % 16 and rows 4*(l/16) + j, so running max, sum and rescale
+// factor of a row are per-lane scalars and the only cross-lane step is one exchange between the four lanes of a row.  The S^T
+// accumulators of two key tiles feed the second MFMA directly: its contraction index is just a relabeling of keys, as long as the
+// V^T fragment uses the same relabeling, which is how it is read from LDS.
+//
+// 16x16x32 and not 32x32x16: from some thousand rows on the kernel runs at the power limit of the card (1.6 of 2.4 GHz), and a loop of
+// MFMAs on random operands reaches 1.70 ... 1.82 PFLOP/s with 32x32x16 there, 2.04 ... 2.18 with 16x16x32.  The K and V fragments are
+// as large and feed as many products.  By itself at 18944 rows (28 / 4 heads, 3.9 TFLOP) 3631 -> 3474 us and, on a card that
+// throttles more, 4230 -> 4029; inside the layer 3754 -> 3683; 7104 rows (32 / 4 heads) 741 -> 710, inside the layer 795 -> 778; 5824 rows 248 -> 238.
 //
 // K/V blocks go through a two-stage LDS ring: while block kb is consumed, the K and V tiles of block
 // kb+1 are copied global -> LDS directly, both row-major [key][d] (the XOR swizzles are applied by
@@ -56,10 +60,10 @@ constexpr int ATT_STAGE_CHUNKS = K_TILE_CHUNKS + V_TILE_CHUNKS;   // one K tile 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 
-// K tile: chunk XOR key%16 (16-byte fragment reads of consecutive keys hit different banks).
-// V tile: chunk XOR (key%4)*4 (a transposing read touches 4 consecutive keys x 64 bytes).
+// K tile: chunk XOR key%16 (a 16-byte fragment read takes 16 keys x 4 chunks; each of its four turns touches every bank once).
+// V tile: chunk XOR (key%8)*2 (a transposing read takes 16 keys x 32 bytes).
 __device__ __forceinline__ int k_swz(int key, int c) { return c ^ (key & 15); }
-__device__ __forceinline__ int v_swz(int key, int c) { return c ^ ((key & 3) << 2); }
+__device__ __forceinline__ int v_swz(int key, int c) { return c ^ ((key & 7) << 1); }
 
 // One wavefront-level global -> LDS copy of 64 x 16 bytes (lane l's 16 bytes land at dst + l).  Issued
 // as inline assembly: through the builtin the compiler, unable to tell the LDS write apart from the
@@ -77,16 +81,24 @@ __device__ __forceinline__ void dma16(const void* uniform_base, uint32_t lane_by
                : "memory");
 }
 
-// max / sum over the two lanes (l, l ^ 32) that share a virtual row, in both of them: the swap puts
-// the upper half's values beside the lower half's without an LDS round trip (a ds_bpermute here
-// would also make the wavefront wait for every fragment read in flight)
-__device__ __forceinline__ float pair_max(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+// Max / sum over the four lanes (l, l ^ 16, l ^ 32, l ^ 48) that share a virtual row, of both rows of a lane, in all of them: the
+// swaps put one half's values beside the other's without an LDS round trip (a ds_bpermute here would also make the
+// wavefront wait for every fragment read in flight)
+__device__ __forceinline__ float2 row_max(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  const float m = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));          // a's in the lower half, b's in the upper
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  const float t = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+  return make_float2(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
-__device__ __forceinline__ float pair_sum(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+__device__ __forceinline__ float2 row_sum(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  const float m = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  const float t = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+  return make_float2(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 
 #define VLC_ATT_WAIT_VM0() __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8) | (0 << 14))
@@ -128,22 +140,18 @@ __device__ __forceinline__ void att_piece(int id, int Hkv, int* kvh, int* piece)
 
 // SPLIT: the workgroup handles one share of the keys of a row tile (plan_attention_shares) and leaves an un-normalised partial (O as
 // float, running max, running sum) for attention_merge_kernel.
-// RT: 32-row tiles of virtual rows per wavefront.  RT = 1: 128 virtual rows per workgroup, two
-// workgroups per CU.  RT = 2: 256 virtual rows, one workgroup per CU; every K and V fragment read
-// from LDS then feeds two MFMAs, which halves the LDS traffic per flop (with one row tile the
-// fragment reads alone would need the whole LDS bandwidth at full MFMA rate).
-template <bool SPLIT, int RT>
-__global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
+template <bool SPLIT>
+__global__ __launch_bounds__(256, 2) void attention_bf16_kernel(
     const int4* __restrict__ pieces, const int32_t* __restrict__ row_kv_start, const int32_t* __restrict__ row_kv_len,
     const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc, int n, int Hkv, int g, int rows_per_tile,
     const uint16_t* __restrict__ q, int64_t q_stride, int Hq, float scale_log2, uint16_t* __restrict__ out,
     float* __restrict__ part_o, float* __restrict__ part_ml) {
   __shared__ u32x4 lds[2 * ATT_STAGE_CHUNKS];     // 64 KB: K ring (2 tiles), then V ring (2 tiles)
-  __shared__ int s_start[VR * RT];
-  __shared__ int s_len[VR * RT];
+  __shared__ int s_start[VR];
+  __shared__ int s_len[VR];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, x = lane >> 5;
+  const int l16 = lane & 15, x = lane >> 4;
   // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Every XCD works on one kv head at a time, so
   // that the workgroups resident on it stream the same K/V; XCDs that share a kv head (fewer than 8) take its row tiles
   // in turn, because later tiles see more keys: contiguous halves leave the XCD with the early rows idle a third of
@@ -164,7 +172,7 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
   const int row0 = tile * rows_per_tile;
   const int rows_here = min(rows_per_tile, n - row0);
 
-  if (tid < rows_per_tile) {                       // rows_per_tile <= 128 * RT <= 256 threads
+  if (tid < rows_per_tile) {                       // rows_per_tile <= 128 threads
     const bool ok = tid < rows_here;
     s_start[tid] = ok ? row_kv_start[row0 + tid] : -1;
     s_len[tid] = ok ? row_kv_len[row0 + tid] : 0;
@@ -172,7 +180,7 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
   __syncthreads();
   // rows lane, lane + 64, ... of the tile in registers: runs and maxima are found by ballots and wavefront maxima (walking
   // the rows through LDS costs a launch of few key blocks 2 us of its 15)
-  constexpr int RL = VR * RT / 64;
+  constexpr int RL = VR / 64;
   int row_start[RL], row_len[RL];
 #pragma unroll
   for (int i = 0; i < RL; ++i) {
@@ -181,38 +189,33 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     row_len[i] = ok ? s_len[lane + 64 * i] : 0;
   }
 
-  // this lane's virtual rows (one per row tile)
-  int r_local[RT], head[RT], my_len[RT];
-  bool vr_ok[RT];
+  // this lane's virtual rows
+  int r_local[2], head[2], my_len[2];
+  bool vr_ok[2];
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int vr = (wave * RT + rt) * 32 + l32;
-    r_local[rt] = vr / g;
-    head[rt] = kvh * g + (vr - r_local[rt] * g);
-    vr_ok[rt] = r_local[rt] < rows_here;
-    my_len[rt] = vr_ok[rt] ? s_len[r_local[rt]] : 0;
+  for (int v = 0; v < 2; ++v) {
+    const int vr = wave * 32 + v * 16 + l16;
+    r_local[v] = vr / g;
+    head[v] = kvh * g + (vr - r_local[v] * g);
+    vr_ok[v] = r_local[v] < rows_here;
+    my_len[v] = vr_ok[v] ? s_len[r_local[v]] : 0;
   }
 
-  // Q fragments: Q[vr][16*ks + 8*x .. +8).  They are fetched together with the first K and V tiles of the first
+  // Q fragments: Q[vr][32*ks + 8*x .. +8).  They are fetched together with the first K and V tiles of the first
   // run of rows (one memory latency instead of two, which counts when a workgroup has only a few key blocks).
-  bf16x8 qf[RT][ATT_D / 16];
+  bf16x8 qf[2][ATT_D / 32];
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
+  for (int v = 0; v < 2; ++v)
 #pragma unroll
-    for (int ks = 0; ks < ATT_D / 16; ++ks) qf[rt][ks] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+    for (int ks = 0; ks < ATT_D / 32; ++ks) qf[v][ks] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
   bool q_loaded = false;
 
-  f32x16 o_acc[RT][ATT_D / 32];
-  float m_run[RT], l_run[RT];
+  f32x4 o_acc[ATT_D / 16][2];
+  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    m_run[rt] = -INFINITY;
-    l_run[rt] = 0.f;
+  for (int i = 0; i < ATT_D / 16; ++i)
 #pragma unroll
-    for (int i = 0; i < ATT_D / 32; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) o_acc[rt][i][e] = 0.f;
-  }
+    for (int v = 0; v < 2; ++v) o_acc[i][v] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int64_t kv_row_elems = (int64_t)Hkv * ATT_D;
 
@@ -231,21 +234,16 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     k_go[i] = (uint32_t)t_key[i] * kv_row_bytes + k_c[i] * 16;
     v_go[i] = (uint32_t)t_key[i] * kv_row_bytes + v_c[i] * 16;
   }
-  // K fragment reads: key 32*mt + l32, chunk (2*ks + x) ^ (key % 16); byte offset for mt = 0, stage 0
-  int k_rd[ATT_D / 16];
+  // K fragment reads: key 16*kt + l16, chunk (4*ks + x) ^ (key % 16); byte offset for kt = 0, stage 0
+  int k_rd[ATT_D / 32];
 #pragma unroll
-  for (int ks = 0; ks < ATT_D / 16; ++ks) k_rd[ks] = (l32 * 16 + k_swz(l32, 2 * ks + x)) * 16;
-  // transposing V reads: lane s of a 16-lane group points at key s/4, columns 4*(s%4) of the group's
-  // 16-wide d range; groups 0/1 take the two d halves of a 32-wide tile, groups 0-1 / 2-3 are x = 0 / 1.
-  // Byte offset for t = r = 0, stage 0, per 32-wide d tile (the swizzle term (key%4)*4 is lane-constant).
-  const int tr_key = 4 * x + ((lane & 15) >> 2);                 // + 16*t + 8*r
-  const int tr_d = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);      // + 32*md
-  int v_rd[ATT_D / 32];
+  for (int ks = 0; ks < ATT_D / 32; ++ks) k_rd[ks] = (l16 * 16 + k_swz(l16, 4 * ks + x)) * 16;
+  // transposing V reads: lane s of 16-lane group x points at key 4*x + s/4, columns 4*(s%4) of a 16-wide d tile
+  const int tr_key = 4 * x + (l16 >> 2);                 // + 32*t + 16*h
+  int v_rd[ATT_D / 16];
 #pragma unroll
-  for (int md = 0; md < ATT_D / 32; ++md) {
-    const int d0 = 32 * md + tr_d;
-    v_rd[md] = (tr_key * 16 + v_swz(tr_key, d0 >> 3)) * 16 + (d0 & 4) * 2;
-  }
+  for (int dt = 0; dt < ATT_D / 16; ++dt)
+    v_rd[dt] = (tr_key * 16 + v_swz(tr_key, 2 * dt + ((l16 & 3) >> 1))) * 16 + (l16 & 1) * 8;
 
   // Rows of different requests (different row_kv_start) may share a tile: handle one run of equal
   // start at a time; lanes outside the run see every key masked.
@@ -268,20 +266,19 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     seg_max = wave_max(seg_max);
     seg_max = __builtin_amdgcn_readfirstlane(seg_max);
 
-    int len[RT];
-    int w_max = 0, w_min = 0x7fffffff;
+    int len[2], longest = 0, shortest = -0x7fffffff;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const bool in_seg = vr_ok[rt] && r_local[rt] >= seg_begin && r_local[rt] < seg_end;
-      len[rt] = in_seg ? my_len[rt] : 0;
-      w_max = max(w_max, len[rt]);
-      // padding lanes (no row behind them) are left out: nothing of theirs is stored, so they need no
-      // masking - otherwise the wavefront that holds the tile's padding would mask every block
-      w_min = min(w_min, vr_ok[rt] ? len[rt] : 0x7fffffff);
+    for (int v = 0; v < 2; ++v) {
+      const bool in_seg = vr_ok[v] && r_local[v] >= seg_begin && r_local[v] < seg_end;
+      len[v] = in_seg ? my_len[v] : 0;
+      longest = max(longest, len[v]);
+      if (vr_ok[v]) shortest = max(shortest, -len[v]);
     }
-    // longest / shortest visible range among this wavefront's rows (uniform per wavefront)
-    w_max = __builtin_amdgcn_readfirstlane(wave_max(w_max));
-    w_min = -__builtin_amdgcn_readfirstlane(wave_max(-w_min));
+    // longest / shortest visible range among this wavefront's rows (uniform per wavefront); padding lanes (no row behind
+    // them) are left out of the shortest: nothing of theirs is stored, so they need no
+    // masking - otherwise the wavefront that holds the tile's padding would mask every block
+    const int w_max = __builtin_amdgcn_readfirstlane(wave_max(longest));
+    const int w_min = -__builtin_amdgcn_readfirstlane(wave_max(shortest));
 
     const uint16_t* kbase = kc + (int64_t)seg_start * kv_row_elems + (int64_t)kvh * ATT_D;
     const uint16_t* vbase = vc + (int64_t)seg_start * kv_row_elems + (int64_t)kvh * ATT_D;
@@ -308,115 +305,108 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
   }
 #define VLC_ATT_ISSUE_K(kb_, stage_) VLC_ATT_ISSUE_TILE(kbase, k_go, k_c, kb_, (stage_) * K_TILE_CHUNKS)
 #define VLC_ATT_ISSUE_V(kb_, stage_) VLC_ATT_ISSUE_TILE(vbase, v_go, v_c, kb_, 2 * K_TILE_CHUNKS + (stage_) * V_TILE_CHUNKS)
-    // S^T of one key block: ST[rt][mt] = K Q^T from K ring stage kst_; a K fragment serves every row tile
+    // S^T of one key block: ST[kt][v] = K Q^T from K ring stage kst_; a K fragment serves both row tiles
 #define VLC_ATT_QK(ST, kst_)                                                                                   \
   {                                                                                                            \
     const unsigned char* sk_ = reinterpret_cast<const unsigned char*>(lds) + (kst_) * (K_TILE_CHUNKS * 16);    \
-    _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                                          \
-      _Pragma("unroll") for (int mt = 0; mt < 2; ++mt)                                                         \
-        _Pragma("unroll") for (int e = 0; e < 16; ++e) ST[rt][mt][e] = 0.f;                                    \
-    u32x4 kf_[2];   /* fragment i+1 is read while fragment i is multiplied */                                  \
-    kf_[0] = *reinterpret_cast<const u32x4*>(sk_ + k_rd[0]);                                                  \
-    _Pragma("unroll") for (int i = 0; i < 2 * (ATT_D / 16); ++i) {                                             \
-      const int mt = i / (ATT_D / 16), ks = i % (ATT_D / 16);                                                  \
-      if (i + 1 < 2 * (ATT_D / 16))                                                                           \
-        kf_[(i + 1) & 1] = *reinterpret_cast<const u32x4*>(sk_ + k_rd[(i + 1) % (ATT_D / 16)] +               \
-                                                                         ((i + 1) / (ATT_D / 16)) * (32 * 256)); \
-      _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                                        \
-        ST[rt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf_[i & 1]), qf[rt][ks], ST[rt][mt], 0, 0, 0); \
+    _Pragma("unroll") for (int i = 0; i < 8; ++i) ST[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};               \
+    u32x4 kf_[4];   /* four fragments are read ahead */                                                        \
+    _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                              \
+      kf_[i] = *reinterpret_cast<const u32x4*>(sk_ + k_rd[0] + i * (16 * 256));                                \
+    _Pragma("unroll") for (int i = 0; i < 16; ++i) {                                                           \
+      _Pragma("unroll") for (int v = 0; v < 2; ++v)                                                            \
+        ST[i & 3][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf_[i & 3]), qf[v][i >> 2], ST[i & 3][v], 0, 0, 0); \
+      if (i + 4 < 16) kf_[i & 3] = *reinterpret_cast<const u32x4*>(sk_ + k_rd[(i + 4) >> 2] + (i & 3) * (16 * 256));  \
     }                                                                                                          \
   }
     // keys of the block beyond a lane's visible range are masked (only where the block crosses it)
 #define VLC_ATT_MASK(ST, key0_)                                                                                \
   {                                                                                                            \
     if ((key0_) + KB > w_min) {                                                                                \
-      _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                                        \
-        _Pragma("unroll") for (int mt = 0; mt < 2; ++mt)                                                       \
-          _Pragma("unroll") for (int j = 0; j < 16; ++j) {                                                     \
-            const int key_ = (key0_) + 32 * mt + 8 * (j >> 2) + 4 * x + (j & 3);                               \
-            ST[rt][mt][j] = key_ < len[rt] ? ST[rt][mt][j] : -INFINITY;                                        \
-          }                                                                                                    \
+      _Pragma("unroll") for (int v = 0; v < 2; ++v)                                                            \
+        _Pragma("unroll") for (int i = 0; i < 16; ++i) {                                                       \
+          const int key_ = (key0_) + 16 * (i >> 2) + 4 * x + (i & 3);                                          \
+          ST[i >> 2][v][i & 3] = key_ < len[v] ? ST[i >> 2][v][i & 3] : -INFINITY;                             \
+        }                                                                                                      \
     }                                                                                                          \
   }
-    // online softmax (base 2) of ST: branch-free, so that it shares a basic block with the next
-    // block's S^T MFMAs; leaves probabilities in ST and the rescale factors in alpha_ / grew_
-#define VLC_ATT_SOFTMAX(ST)                                                                                    \
-    float alpha_[RT];                                                                                          \
-    bool grew_ = false;                                                                                        \
-    _Pragma("unroll") for (int rt = 0; rt < RT; ++rt) {                                                        \
-      float mx_ = -INFINITY;                                                                                   \
-      _Pragma("unroll") for (int mt = 0; mt < 2; ++mt)                                                         \
-        _Pragma("unroll") for (int j = 0; j < 16; ++j) mx_ = fmaxf(mx_, ST[rt][mt][j]);                        \
-      mx_ = pair_max(mx_) * scale_log2;   /* scale > 0: max commutes with it */                                \
-      const float m_new_ = fmaxf(m_run[rt], mx_);                                                              \
-      const float m_use_ = (m_new_ == -INFINITY) ? 0.f : m_new_;                                               \
-      alpha_[rt] = __builtin_amdgcn_exp2f(m_run[rt] - m_use_);   /* m_run = -inf -> 0 */                       \
-      grew_ = grew_ || (m_new_ > m_run[rt]);                                                                   \
-      m_run[rt] = m_new_;                                                                                      \
-      float psum_ = 0.f;                                                                                       \
-      _Pragma("unroll") for (int mt = 0; mt < 2; ++mt)                                                         \
-        _Pragma("unroll") for (int j = 0; j < 16; ++j) {                                                       \
-          const float p_ = __builtin_amdgcn_exp2f(fmaf(ST[rt][mt][j], scale_log2, -m_use_));                  \
-          ST[rt][mt][j] = p_;                                                                                  \
-          psum_ += p_;                                                                                         \
-        }                                                                                                      \
-      l_run[rt] = l_run[rt] * alpha_[rt] + psum_;                                                              \
-    }
-    // order template for the shared block: two K fragment reads up front, then per fragment RT MFMAs,
-    // eight vector ops each, and the read of the fragment after next
+    // online softmax (base 2), first part: the new references of the rows and the rescale factors
+#define VLC_ATT_REFERENCE(ST)                                                                                  \
+    float mx_[2] = {-INFINITY, -INFINITY};                                                                     \
+    _Pragma("unroll") for (int v = 0; v < 2; ++v)                                                              \
+      _Pragma("unroll") for (int i = 0; i < 16; ++i) mx_[v] = fmaxf(mx_[v], ST[i >> 2][v][i & 3]);             \
+    const float2 both_ = row_max(mx_[0], mx_[1]);   /* scale > 0: max commutes with it */                      \
+    const float m_new_[2] = {fmaxf(m_run[0], both_.x * scale_log2), fmaxf(m_run[1], both_.y * scale_log2)};    \
+    const float m_use_[2] = {m_new_[0] == -INFINITY ? 0.f : m_new_[0], m_new_[1] == -INFINITY ? 0.f : m_new_[1]}; \
+    const float alpha_[2] = {__builtin_amdgcn_exp2f(m_run[0] - m_use_[0]),   /* m_run = -inf -> 0 */           \
+                             __builtin_amdgcn_exp2f(m_run[1] - m_use_[1])};                                    \
+    const bool grew_ = m_new_[0] > m_run[0] || m_new_[1] > m_run[1];                                           \
+    m_run[0] = m_new_[0];                                                                                      \
+    m_run[1] = m_new_[1];
+    // second part: the probabilities of key tiles [first_, last_), in place
+#define VLC_ATT_EXP(ST, first_, last_)                                                                         \
+    _Pragma("unroll") for (int i = 4 * (first_); i < 4 * (last_); ++i)                                         \
+      _Pragma("unroll") for (int v = 0; v < 2; ++v)                                                            \
+        ST[i >> 2][v][i & 3] = __builtin_amdgcn_exp2f(fmaf(ST[i >> 2][v][i & 3], scale_log2, -m_use_[v]));
+    // order template for the block of the next block's S^T: four K fragment reads up front, then per fragment two MFMAs, vector
+    // work of this block's softmax behind each, and a read
 #define VLC_ATT_INTERLEAVE()                                                                                   \
-    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                                                         \
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);                                                         \
     _Pragma("unroll") for (int g_ = 0; g_ < 16; ++g_) {                                                        \
-      _Pragma("unroll") for (int rt = 0; rt < RT; ++rt) {                                                      \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                     \
-        __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);                                                     \
-      }                                                                                                        \
-      if (g_ < 14) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                          \
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                       \
+      __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);                                                       \
+      __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);                                                       \
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                       \
+      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);                                                       \
+      __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);                                                       \
+      if (g_ < 12) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                          \
     }
-    // O rescale (only when some row's maximum moved) and O^T += V^T P^T from V ring stage vst_;
-    // a V^T fragment serves every row tile
-#define VLC_ATT_RESCALE_PV(ST, vst_)                                                                           \
-  {                                                                                                            \
+    // O rescale (only when some row's maximum moved)
+#define VLC_ATT_RESCALE()                                                                                      \
     if (__any(grew_)) {                                                                                        \
-      _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                                        \
-        _Pragma("unroll") for (int i = 0; i < ATT_D / 32; ++i)                                                 \
-          _Pragma("unroll") for (int e = 0; e < 16; ++e) o_acc[rt][i][e] *= alpha_[rt];                        \
-    }                                                                                                          \
+      _Pragma("unroll") for (int v = 0; v < 2; ++v) {                                                          \
+        _Pragma("unroll") for (int i = 0; i < ATT_D / 16; ++i)                                                 \
+          _Pragma("unroll") for (int e = 0; e < 4; ++e) o_acc[i][v][e] *= alpha_[v];                           \
+        l_run[v] *= alpha_[v];                                                                                 \
+      }                                                                                                        \
+    }
+    // row sums and O^T += V^T P^T from V ring stage vst_; a V^T fragment (32 keys x 16 d) serves both row tiles
+#define VLC_ATT_PV(ST, vst_)                                                                                   \
+  {                                                                                                            \
     const unsigned char* sv_ = reinterpret_cast<const unsigned char*>(lds + 2 * K_TILE_CHUNKS + (vst_) * V_TILE_CHUNKS); \
-    bf16x8 pf_[RT];                                                                                            \
-    s16x4 vh_[2][2];   /* V^T fragment i+1 is read while fragment i is multiplied */                           \
-    _Pragma("unroll") for (int r = 0; r < 2; ++r)                                                              \
-      vh_[0][r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(         \
-          const_cast<unsigned char*>(sv_) + v_rd[0] + (8 * r) * 256));                                        \
-    _Pragma("unroll") for (int i = 0; i < 4 * (ATT_D / 32); ++i) {                                             \
-      const int t = i / (ATT_D / 32), md = i % (ATT_D / 32);                                                   \
-      if (i + 1 < 4 * (ATT_D / 32)) {                                                                         \
-        const int t1 = (i + 1) / (ATT_D / 32), md1 = (i + 1) % (ATT_D / 32);                                   \
-        _Pragma("unroll") for (int r = 0; r < 2; ++r)                                                          \
-          vh_[(i + 1) & 1][r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)( \
-              const_cast<unsigned char*>(sv_) + v_rd[md1] + (16 * t1 + 8 * r) * 256));                        \
+    float psum_[2] = {0.f, 0.f};                                                                               \
+    _Pragma("unroll") for (int t = 0; t < 2; ++t) {                                                            \
+      bf16x8 pf_[2];                                                                                           \
+      _Pragma("unroll") for (int v = 0; v < 2; ++v)                                                            \
+        _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                                        \
+          f32x2 pr_ = {ST[2 * t + (e >> 1)][v][2 * (e & 1)], ST[2 * t + (e >> 1)][v][2 * (e & 1) + 1]};        \
+          const bf16x2 pb_ = __builtin_convertvector(pr_, bf16x2);                                             \
+          pf_[v][2 * e] = pb_[0];                                                                              \
+          pf_[v][2 * e + 1] = pb_[1];                                                                          \
+        }                                                                                                      \
+      _Pragma("unroll") for (int dt = 0; dt < ATT_D / 16; ++dt) {                                              \
+        s16x4 vh_[2];                                                                                          \
+        _Pragma("unroll") for (int h = 0; h < 2; ++h)                                                          \
+          vh_[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(         \
+              const_cast<unsigned char*>(sv_) + v_rd[dt] + (32 * t + 16 * h) * 256));                          \
+        const s16x8 vv_ = __builtin_shufflevector(vh_[0], vh_[1], 0, 1, 2, 3, 4, 5, 6, 7);                     \
+        _Pragma("unroll") for (int v = 0; v < 2; ++v) {                                                        \
+          o_acc[dt][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vv_), pf_[v], o_acc[dt][v], 0, 0, 0); \
+          psum_[v] += ST[2 * t + (dt >> 2)][v][dt & 3];                                                        \
+        }                                                                                                      \
       }                                                                                                        \
-      if (md == 0) {                                                                                           \
-        _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                                      \
-          _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                                      \
-            f32x2 pr_ = {ST[rt][t >> 1][8 * (t & 1) + 2 * e], ST[rt][t >> 1][8 * (t & 1) + 2 * e + 1]};        \
-            const bf16x2 pb_ = __builtin_convertvector(pr_, bf16x2);                                           \
-            pf_[rt][2 * e] = pb_[0];                                                                           \
-            pf_[rt][2 * e + 1] = pb_[1];                                                                       \
-          }                                                                                                    \
-      }                                                                                                        \
-      const s16x8 vv_ = __builtin_shufflevector(vh_[i & 1][0], vh_[i & 1][1], 0, 1, 2, 3, 4, 5, 6, 7);        \
-      _Pragma("unroll") for (int rt = 0; rt < RT; ++rt)                                                        \
-        o_acc[rt][md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv_), pf_[rt], o_acc[rt][md], 0, 0, 0); \
     }                                                                                                          \
+    l_run[0] += psum_[0];                                                                                      \
+    l_run[1] += psum_[1];                                                                                      \
   }
     // One key block j (S^T already in CUR): fetch ahead, start the next block's S^T into NXT (its MFMAs
     // are independent of this block's softmax arithmetic, so the two interleave), finish this block.
-    // The PV product runs at a raised wave priority: two wavefronts share a SIMD, and a wavefront hides only about five
-    // of its own vector instructions under an MFMA, so the matrix pipe is only kept busy when one wavefront
+    // Half of the probabilities are taken under the S^T MFMAs and held there (the compiler moves what only the PV block uses behind the
+    // rescale branch, where all 32 stood before: 3651 -> 3617 us at 18944 rows), half under the PV MFMAs.
+    // The PV product runs at a raised wave priority: two wavefronts share a SIMD, and the matrix pipe is only kept busy when one
     // multiplies while the other does its softmax arithmetic.  With equal priorities two wavefronts that reach
     // their MFMA phases together alternate instruction by instruction and stay in step; the priority lets the
-    // one already in its pure-MFMA phase run ahead, which puts the pair out of step (-6 % kernel time).
+    // one already in its PV phase run ahead, which puts the pair out of step (4176 -> 4029 us).
 #define VLC_ATT_BLOCK(j_, PAR, CUR, NXT)                                                                       \
   {                                                                                                            \
     if ((j_) + 2 < n_blocks) VLC_ATT_ISSUE_K(kb_first + (j_) + 2, PAR)                                         \
@@ -425,18 +415,22 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     if (key0b_ < w_max) { /* something visible for this wavefront in this block */                             \
       VLC_ATT_MASK(CUR, key0b_)                                                                                \
       VLC_ATT_QK(NXT, (PAR) ^ 1)   /* past the last block this reads a stale tile; the result is unused */     \
-      VLC_ATT_SOFTMAX(CUR)                                                                                     \
+      VLC_ATT_REFERENCE(CUR)                                                                                   \
+      VLC_ATT_EXP(CUR, 0, 2)                                                                                   \
       VLC_ATT_INTERLEAVE()                                                                                     \
-      __builtin_amdgcn_s_setprio(1);   /* see below */                                                         \
-      VLC_ATT_RESCALE_PV(CUR, PAR)                                                                             \
+      asm volatile("" : "+v"(CUR[0][0]), "+v"(CUR[0][1]), "+v"(CUR[1][0]), "+v"(CUR[1][1]));   /* see above */ \
+      __builtin_amdgcn_s_setprio(1);   /* see above */                                                         \
+      VLC_ATT_RESCALE()                                                                                        \
+      VLC_ATT_EXP(CUR, 2, 4)                                                                                   \
+      VLC_ATT_PV(CUR, PAR)                                                                                     \
       __builtin_amdgcn_s_setprio(0);                                                                           \
     }                                                                                                          \
     VLC_ATT_WAIT_VM0();   /* this wavefront's shares of the tiles fetched above have landed */                 \
-    __syncthreads();                                                                                          \
+    __syncthreads();                                                                                           \
   }
 
     __syncthreads();                 // the rings are free (previous run finished reading them)
-    f32x16 st_a[RT][2], st_b[RT][2];
+    f32x4 st_a[4][2], st_b[4][2];
     if (n_blocks > 0) {
       VLC_ATT_ISSUE_K(kb_first, 0)
       VLC_ATT_ISSUE_V(kb_first, 0)
@@ -445,12 +439,12 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
     if (!q_loaded) {
       q_loaded = true;
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const u32x4* qp = reinterpret_cast<const u32x4*>(q + (int64_t)(row0 + (vr_ok[rt] ? r_local[rt] : 0)) * q_stride +
-                                                         (int64_t)head[rt] * ATT_D);
+      for (int v = 0; v < 2; ++v) {
+        const u32x4* qp = reinterpret_cast<const u32x4*>(q + (int64_t)(row0 + (vr_ok[v] ? r_local[v] : 0)) * q_stride +
+                                                         (int64_t)head[v] * ATT_D);
 #pragma unroll
-        for (int ks = 0; ks < ATT_D / 16; ++ks)
-          if (vr_ok[rt]) qf[rt][ks] = __builtin_bit_cast(bf16x8, qp[2 * ks + x]);
+        for (int ks = 0; ks < ATT_D / 32; ++ks)
+          if (vr_ok[v]) qf[v][ks] = __builtin_bit_cast(bf16x8, qp[4 * ks + x]);
       }
     }
     // The Q loads are the only vector-memory reads the compiler knows of; completing them here, together with
@@ -469,46 +463,43 @@ __global__ __launch_bounds__(256, RT == 1 ? 2 : 1) void attention_bf16_kernel(
 #undef VLC_ATT_ISSUE_V
 #undef VLC_ATT_QK
 #undef VLC_ATT_MASK
-#undef VLC_ATT_SOFTMAX
+#undef VLC_ATT_REFERENCE
+#undef VLC_ATT_EXP
 #undef VLC_ATT_INTERLEAVE
-#undef VLC_ATT_RESCALE_PV
+#undef VLC_ATT_RESCALE
+#undef VLC_ATT_PV
 #undef VLC_ATT_BLOCK
     seg_begin = seg_end;
   }
 
-  // ---- normalise and store: lane holds d = 32*md + 8*(j/4) + 4*x + j%4 of its virtual rows ------
+  // ---- normalise and store: lane holds d = 16*dt + 4*x + j of its virtual rows ------------------
+  const float2 l_both = row_sum(l_run[0], l_run[1]);
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const float l_tot = pair_sum(l_run[rt]);
-    if (!vr_ok[rt]) continue;
+  for (int v = 0; v < 2; ++v) {
+    const float l_tot = v ? l_both.y : l_both.x;
+    if (!vr_ok[v]) continue;
     if (SPLIT) {
-      const int64_t rh = ((int64_t)share.y * n + (row0 + r_local[rt])) * Hq + head[rt];
-      float* po = part_o + rh * ATT_D;
+      const int64_t rh = ((int64_t)share.y * n + (row0 + r_local[v])) * Hq + head[v];
+      float* po = part_o + rh * ATT_D + 4 * x;
 #pragma unroll
-      for (int md = 0; md < ATT_D / 32; ++md)
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd)
-          *reinterpret_cast<float4*>(po + 32 * md + 8 * qd + 4 * x) =
-              make_float4(o_acc[rt][md][4 * qd], o_acc[rt][md][4 * qd + 1], o_acc[rt][md][4 * qd + 2],
-                          o_acc[rt][md][4 * qd + 3]);
+      for (int dt = 0; dt < ATT_D / 16; ++dt)
+        *reinterpret_cast<float4*>(po + 16 * dt) = make_float4(o_acc[dt][v][0], o_acc[dt][v][1], o_acc[dt][v][2], o_acc[dt][v][3]);
       if (x == 0) {
-        part_ml[2 * rh] = m_run[rt];
+        part_ml[2 * rh] = m_run[v];
         part_ml[2 * rh + 1] = l_tot;
       }
     } else {
       const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-      uint16_t* op = out + ((int64_t)(row0 + r_local[rt]) * Hq + head[rt]) * ATT_D;
+      uint16_t* op = out + ((int64_t)(row0 + r_local[v]) * Hq + head[v]) * ATT_D + 4 * x;
 #pragma unroll
-      for (int md = 0; md < ATT_D / 32; ++md)
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          f32x2 a0 = {o_acc[rt][md][4 * qd] * inv, o_acc[rt][md][4 * qd + 1] * inv};
-          f32x2 a1 = {o_acc[rt][md][4 * qd + 2] * inv, o_acc[rt][md][4 * qd + 3] * inv};
-          u32x2 w;
-          w[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a0, bf16x2));
-          w[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a1, bf16x2));
-          *reinterpret_cast<u32x2*>(op + 32 * md + 8 * qd + 4 * x) = w;
-        }
+      for (int dt = 0; dt < ATT_D / 16; ++dt) {
+        f32x2 a0 = {o_acc[dt][v][0] * inv, o_acc[dt][v][1] * inv};
+        f32x2 a1 = {o_acc[dt][v][2] * inv, o_acc[dt][v][3] * inv};
+        u32x2 w;
+        w[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a0, bf16x2));
+        w[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a1, bf16x2));
+        *reinterpret_cast<u32x2*>(op + 16 * dt) = w;
+      }
     }
   }
 }
@@ -745,7 +736,7 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     const int rows_per_tile = VR / g;
     const int64_t tiles = (n + rows_per_tile - 1) / rows_per_tile;
     if (shares && shares->max_shares > 1) {
-      hipLaunchKernelGGL((attention_bf16_kernel<true, 1>), dim3((unsigned)(shares->slots * Hkv)), dim3(256), 0, st,
+      hipLaunchKernelGGL((attention_bf16_kernel<true>), dim3((unsigned)(shares->slots * Hkv)), dim3(256), 0, st,
                          (const int4*)shares->pieces, row_kv_start, row_kv_len, (const uint16_t*)k_cache, (const uint16_t*)v_cache,
                          (int)n, Hkv, g, rows_per_tile, (const uint16_t*)q, q_stride, Hq, scale * 1.4426950408889634f,
                          (uint16_t*)out, shares->part_o, shares->part_ml);
@@ -757,7 +748,7 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
       return VLC_OK;
     }
     const dim3 grid((unsigned)att_grid((int)tiles, Hkv));
-    hipLaunchKernelGGL((attention_bf16_kernel<false, 1>), grid, dim3(256), 0, st, nullptr, row_kv_start, row_kv_len,
+    hipLaunchKernelGGL((attention_bf16_kernel<false>), grid, dim3(256), 0, st, nullptr, row_kv_start, row_kv_len,
                        (const uint16_t*)k_cache, (const uint16_t*)v_cache, (int)n, Hkv, g, rows_per_tile, (const uint16_t*)q,
                        q_stride, Hq, scale * 1.4426950408889634f, (uint16_t*)out, nullptr, nullptr);
     VLC_CHECK_LAUNCH("attention_bf16");
