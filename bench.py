@@ -719,8 +719,7 @@ def main() -> int:
         "kernels_source": "HIP-event stage durations of a separate pass with all stage events (3 steps, same inputs); "
                           "fractions are achieved algorithmic rate / published peak (2.5 PFLOP/s dense bf16 MFMA, 8 TB/s HBM); "
                           "frac_of_measured_ceiling: the same rate / what machine_probes measured on this box (loop of "
-                          "v_mfma_f32_16x16x32_bf16 on random operands, 1 GiB row copy; the attention multiplies with the "
-                          "slower 32x32x16)",
+                          "v_mfma_f32_16x16x32_bf16 on random operands, 1 GiB row copy)",
         "hbm_kernels": hbm,
         "machine_probes": probes,
         "stages": stages,
