@@ -176,15 +176,23 @@ __device__ __forceinline__ void mfma_operand(f32x4& acc, bool accumulation_regs)
     asm volatile("" : "+v"(acc));
 }
 
+enum { EPI_PARTIAL = 100 };   // internal: float partial sums of one k-range (split-K)
+
 #define VLC_WAITCNT_VM(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14))
 
 // Whether a kernel is built so that its workgroups can stay for several tiles (RESIDENT): tiles of 192 x 192 outputs and more on
 // four wavefronts.  Not 320 x 256, whose sums and fragments leave no registers for the next tile's addresses, nor eight
-// wavefronts, two per SIMD, which fill each other's waits (and spill).
-constexpr bool gemm_may_stay(int bm, int bn, int waves) { return waves == 4 && bm * bn >= 192 * 192 && bm * bn <= 256 * 256; }
-constexpr int kStayRounds = 3;   // rounds of tiles from which they do
-
-enum { EPI_PARTIAL = 100 };   // internal: float partial sums of one k-range (split-K)
+// wavefronts, two per SIMD, which fill each other's waits (and spill).  Not float outputs either: the waits for the next tile's
+// k-tiles also wait for the stores in front of them, twice the bytes here.  q|k|v at K = 1536 ... 5120 in 3.5 to 7 rounds 1 ... 5 %
+// slower in 80 of 84 products, going / staying: 320 x 192 at K = 2048 in 7 rounds 356 / 377 us, 320 x 160 at K = 4096 in 4 rounds
+// 323 / 327, 192 x 256 at K = 3584 in 5.5 rounds 405 / 413.
+constexpr bool gemm_may_stay(int bm, int bn, int waves, int epi) {
+  return waves == 4 && bm * bn >= 192 * 192 && bm * bn <= 256 * 256 && epi != EPI_BIAS_F32 && epi != EPI_PARTIAL;
+}
+constexpr int kStayRounds = 3;
+// Whether the workgroups of a product stay: from more than kStayRounds rounds on (items: tiles, and the k ranges of a split last
+// round's).
+bool gemm_stays(bool may, int64_t items, int slots) { return may && items > kStayRounds * slots; }
 
 //
 // GROUPED (mixture-of-experts): the row tiles come from a device-resident table; entry t holds an
@@ -935,8 +943,8 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
     }
   }
   const int items = full + tail * tsp;
-  constexpr bool MAY_STAY = EPI != EPI_PARTIAL && gemm_may_stay(BM, BN, WGM * WGN);
-  const bool stay = MAY_STAY && items > kStayRounds * 256 * OCC;
+  constexpr bool MAY_STAY = gemm_may_stay(BM, BN, WGM * WGN, EPI);
+  const bool stay = gemm_stays(MAY_STAY, items, 256 * OCC);
   auto kern = stay ? gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, MAY_STAY> : gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, false>;
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
   hipLaunchKernelGGL(kern, dim3(stay ? 256 * OCC : items), dim3(WGM * WGN * 64), lds, st, (const uint16_t*)A, (const uint16_t*)W,
@@ -1160,7 +1168,7 @@ int launch_bf16_grouped(const void* A, int64_t lda, const int32_t* amap, const v
   constexpr int CN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
   const int tiles_n = (int)((N + CN - 1) / CN);
   const size_t lds = (size_t)STAGES * (BM + BN) * BK * 2;
-  constexpr bool STAY = gemm_may_stay(BM, BN, WGM * WGN);
+  constexpr bool STAY = gemm_may_stay(BM, BN, WGM * WGN, EPI);
   auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, STAY, true>;
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
   const int most = max_tiles_m * tiles_n, grid = STAY && most > 256 * OCC ? 256 * OCC : most;
@@ -1333,4 +1341,13 @@ extern "C" int vlc_probe_gemm_waves(int epilogue, int64_t M, int64_t N, int64_t 
   static constexpr int kWaves[] = {VLC_GEMM_TILES(X)};
 #undef X
   return kWaves[c.index];
+}
+
+extern "C" int vlc_probe_gemm_stays(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred) {
+  int32_t o[5];   // rows, columns, workgroups per CU, k ranges, k ranges of the last round's tiles
+  if (vlc_probe_gemm_choice(epilogue, M, N, K, scratch, deferred, o) || o[3] > 1) return 0;
+  const int64_t cn = epilogue == vlc::EPI_SWIGLU ? o[1] / 2 : o[1], slots = 256 * o[2];
+  const int64_t tiles = ((M + o[0] - 1) / o[0]) * ((N + cn - 1) / cn);
+  const bool may = vlc::gemm_may_stay(o[0], o[1], vlc_probe_gemm_waves(epilogue, M, N, K, scratch, deferred), epilogue);
+  return vlc::gemm_stays(may, tiles + (o[4] - 1) * (tiles % slots), (int)slots);
 }

@@ -186,5 +186,7 @@ int vlc_probe_attention_shares(int64_t n, int Hq, int Hkv, int64_t max_kv_len);
 int vlc_probe_gemm_choice(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred, int32_t* out);
 // wavefronts per workgroup of the same choice (0: no such product): 256 x 256 is listed with four and with eight
 int vlc_probe_gemm_waves(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred);
+// 1 if the workgroups of the same choice stay for several tiles
+int vlc_probe_gemm_stays(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred);
 }
 #endif

@@ -4,24 +4,22 @@ experts whose row tiles are only known on the device."""
 import pytest
 
 import vlc_synth as syn
-from test_gpu_gemm_tiles import FLOAT, RESIDUAL, SWIGLU, choice, test_layer_products_on_every_tile as check_layer
+from test_gpu_gemm_tiles import RESIDUAL, SWIGLU, choice, stays, test_layer_products_on_every_tile as check_layer
 from test_gpu_moe import check_moe_layer
 
 # (product, its epilogue, last round split) of the layer (H, I, Hq, Hkv, rows) that stays
 CASES = [("gate_up", False, (64, 4096, 1, 1, 5000)), ("gate_up", False, (128, 4160, 1, 1, 8191)), ("gate_up", False, (192, 4096, 1, 1, 16390)),
-         ("qkv", False, (64, 192, 40, 8, 12001)), ("gate_up", True, (2048, 2048, 1, 1, 16390)), ("gate_up", True, (2048, 6464, 1, 1, 4097))]
+         ("gate_up", True, (2048, 2048, 1, 1, 16390)), ("gate_up", True, (2048, 6464, 1, 1, 4097)), ("o", False, (7936, 128, 8, 4, 6266))]
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("product,split,layer", CASES)
 def test_products_of_many_rounds(product, split, layer):
-    """More than three rounds of tiles on four wavefronts (asked of the library), at the tolerances of the tests of the tiles."""
+    """The workgroups stay (asked of the library), at the tolerances of the tests of the tiles."""
     H, I, Hq, Hkv, rows = layer
-    epilogue, N = {"qkv": (FLOAT, (Hq + 2 * Hkv) * 128), "gate_up": (SWIGLU, I), "o": (RESIDUAL, H)}[product]
-    (bm, bn, occ, waves), _, how = choice(epilogue, rows, N, H)
-    tiles = -(-rows // bm) * -(-N // (bn // 2 if epilogue == SWIGLU else bn))
-    assert waves == 4 and 192 * 192 <= bm * bn <= 256 * 256 and tiles > 3 * 256 * occ, (bm, bn, waves, tiles)
-    assert (how == "split last round") == split, how
+    of = {"gate_up": (SWIGLU, rows, I, H), "o": (RESIDUAL, rows, H, Hq * 128)}[product]
+    assert stays(*of), choice(*of)
+    assert (choice(*of)[2] == "split last round") == split, choice(*of)
     check_layer(H, I, Hq, Hkv, rows)
 
 

@@ -40,6 +40,8 @@ LAYERS += [
     (6080, 128, 32, 4, 3870), (9664, 128, 4, 4, 10788), (8192, 128, 64, 8, 774)]
 # q|k|v on 256 x 256 with eight wavefronts and a whole last round
 LAYERS += [(256, 128, 4, 2, 13551)]
+# q|k|v of one k-tile in many rounds
+LAYERS += [(64, 192, 40, 8, 12001)]
 # (requests, vocabulary, hidden size) of heads, on the tile that only they use
 HEADS = [(100, 151936, 64), (65, 151936, 192), (8, 152064, 3584), (127, 152060, 320)]
 
@@ -53,6 +55,13 @@ def choice(epilogue, M, N, K, scratch=1, deferred=1):
     o = (ctypes.c_int32 * 5)()
     assert f(epilogue, M, N, K, scratch, deferred, o) == 0
     return (*o[:3], waves(epilogue, M, N, K, scratch, deferred)), epilogue, "k ranges" if o[3] > 1 else "split last round" if o[4] > 1 else "whole"
+
+
+def stays(epilogue, M, N, K, scratch=1, deferred=1):
+    """Whether the workgroups of that product stay for several tiles."""
+    f = vlc.lib().vlc_probe_gemm_stays
+    f.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.c_int]
+    return bool(f(epilogue, M, N, K, scratch, deferred))
 
 
 def layer_choices(H, I, Hq, Hkv, rows):
@@ -93,6 +102,9 @@ def test_choices_that_measure_faster():
     for H in (2560, 3584, 8192):
         for rows in (1, 8, 64):
             assert choice(FLOAT, rows, 4096, H, 0, 0)[0] == (64, 128, 1, 4)
+    # float products whose workgroups stay for several tiles: q|k|v, staying against going, 546 / 538, 327 / 323, 476 / 465, 651 / 639
+    for rows, N, K in ((4183, 10240, 8192), (8262, 6144, 4096), (12395, 6144, 4096), (23616, 4608, 3584)):
+        assert not stays(FLOAT, rows, N, K)
 
 
 def close(got, want, rtol, atol, what):
