@@ -189,10 +189,18 @@ enum { EPI_PARTIAL = 100 };   // internal: float partial sums of one k-range (sp
 constexpr bool gemm_may_stay(int bm, int bn, int waves, int epi) {
   return waves == 4 && bm * bn >= 192 * 192 && bm * bn <= 256 * 256 && epi != EPI_BIAS_F32 && epi != EPI_PARTIAL;
 }
-constexpr int kStayRounds = 3;
+constexpr int kStayRounds = 3, kStayManyRounds = 20;
+constexpr int64_t kStayOperands = 400000000;   // bytes of A and W
 // Whether the workgroups of a product stay: from more than kStayRounds rounds on (items: tiles, and the k ranges of a split last
-// round's).
-bool gemm_stays(bool may, int64_t items, int slots) { return may && items > kStayRounds * slots; }
+// round's), and over more than kStayManyRounds only if the operands are not much more than the memory-side cache holds (256 MB).
+// The tiles are dealt once and for all then, so nothing keeps the XCDs in step over many of them, and an XCD that is behind
+// fetches from HBM again what the others have used.  Gate|up, going / staying, us: up to 20 rounds staying is 0.4 ... 4 % faster whatever
+// the operands (72B at 5200 rows, 19 rounds, 1054 MB: 3543 / 3503); beyond, 1.5B at 31000 rows (33 rounds, 150 MB) 1349 / 1314, 7B at 16500
+// (38 rounds, 390 MB) 3150 / 3127, but 7B at 18944 (43 rounds, 408 MB) 3706 / 3759 and at 31000 6146 / 6583, 13824 x 5120 at 13500
+// (22 rounds, 421 MB) 2767 / 2896 and at 38000 7918 / 8637, 72B at 7500 (27 rounds, 1092 MB) 5269 / 5560.
+bool gemm_stays(bool may, int64_t items, int slots, int64_t operand_bytes) {
+  return may && items > kStayRounds * slots && (items <= kStayManyRounds * slots || operand_bytes <= kStayOperands);
+}
 
 //
 // GROUPED (mixture-of-experts): the row tiles come from a device-resident table; entry t holds an
@@ -944,7 +952,7 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
   }
   const int items = full + tail * tsp;
   constexpr bool MAY_STAY = gemm_may_stay(BM, BN, WGM * WGN, EPI);
-  const bool stay = gemm_stays(MAY_STAY, items, 256 * OCC);
+  const bool stay = gemm_stays(MAY_STAY, items, 256 * OCC, (M + (EPI == EPI_SWIGLU ? 2 : 1) * N) * K * 2);
   auto kern = stay ? gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, MAY_STAY> : gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, false>;
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
   hipLaunchKernelGGL(kern, dim3(stay ? 256 * OCC : items), dim3(WGM * WGN * 64), lds, st, (const uint16_t*)A, (const uint16_t*)W,
@@ -1349,5 +1357,5 @@ extern "C" int vlc_probe_gemm_stays(int epilogue, int64_t M, int64_t N, int64_t 
   const int64_t cn = epilogue == vlc::EPI_SWIGLU ? o[1] / 2 : o[1], slots = 256 * o[2];
   const int64_t tiles = ((M + o[0] - 1) / o[0]) * ((N + cn - 1) / cn);
   const bool may = vlc::gemm_may_stay(o[0], o[1], vlc_probe_gemm_waves(epilogue, M, N, K, scratch, deferred), epilogue);
-  return vlc::gemm_stays(may, tiles + (o[4] - 1) * (tiles % slots), (int)slots);
+  return vlc::gemm_stays(may, tiles + (o[4] - 1) * (tiles % slots), (int)slots, (M + (epilogue == vlc::EPI_SWIGLU ? 2 : 1) * N) * K * 2);
 }

@@ -105,6 +105,12 @@ def test_choices_that_measure_faster():
     # float products whose workgroups stay for several tiles: q|k|v, staying against going, 546 / 538, 327 / 323, 476 / 465, 651 / 639
     for rows, N, K in ((4183, 10240, 8192), (8262, 6144, 4096), (12395, 6144, 4096), (23616, 4608, 3584)):
         assert not stays(FLOAT, rows, N, K)
+    # gate|up in many rounds over more than the caches hold, staying against going: 3759 / 3706, 6583 / 6146, 2896 / 2767, 5560 / 5269
+    for rows, N, K in ((18944, 18944, 3584), (31000, 18944, 3584), (13500, 13824, 5120), (7500, 29568, 8192)):
+        assert not stays(SWIGLU, rows, N, K)
+    # and where staying is faster: 3127 / 3150 (390 MB of operands), 3503 / 3543 (19 rounds), 1314 / 1349, 1131 / 1157
+    for rows, N, K in ((16500, 18944, 3584), (5200, 29568, 8192), (31000, 8960, 1536), (5824, 18944, 3584)):
+        assert stays(SWIGLU, rows, N, K)
 
 
 def close(got, want, rtol, atol, what):
