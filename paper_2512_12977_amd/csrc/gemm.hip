@@ -88,7 +88,7 @@ __device__ __forceinline__ void tile_coords(int pid, int total, int tiles_m, int
 // accumulators as float blocks to tail_ws and tail_reduce_kernel sums them and applies the epilogue.
 //
 // RESIDENT: one round of workgroups stays for all tiles and asks for the next tile's first k-tiles under the last k-step of
-// this one (gemm_may_stay, kStayRounds): no workgroup starts, reads its arguments and waits for its first k-tiles in
+// this one (tile_may_stay, gemm_stays): no workgroup starts, reads its arguments and waits for its first k-tiles in
 // between.  Products of few k-tiles gain most: gate|up / down of 128 experts (2048 x 768) at 444 rows each 354 -> 333 and 262 -> 248
 // us; 7B gate|up at 5824 rows 1134 -> 1110, at 18944 rows (43 rounds, at the card's power limit) 3765 -> 3745.  Up to two rounds
 // nothing is gained, and products that stream their weights through small tiles are no faster (37 rows per expert) or slower.
@@ -180,15 +180,13 @@ enum { EPI_PARTIAL = 100 };   // internal: float partial sums of one k-range (sp
 
 #define VLC_WAITCNT_VM(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14))
 
-// Whether a kernel is built so that its workgroups can stay for several tiles (RESIDENT): tiles of 192 x 192 outputs and more on
-// four wavefronts.  Not 320 x 256, whose sums and fragments leave no registers for the next tile's addresses, nor eight
-// wavefronts, two per SIMD, which fill each other's waits (and spill).  Not float outputs either: the waits for the next tile's
+// Whether the workgroups of a kernel can stay for several tiles (RESIDENT; tile_may_stay): tiles of 160 x 256 outputs and more on four
+// wavefronts, where products of more than kStayRounds rounds land on them (over 240000 products of decoder proportions, up to 60000
+// rows, residuals on two tiles only).  Not 320 x 256, whose sums and fragments leave no registers for the next tile's addresses, nor
+// eight wavefronts, two per SIMD, which fill each other's waits (and spill).  Not float outputs either: the waits for the next tile's
 // k-tiles also wait for the stores in front of them, twice the bytes here.  q|k|v at K = 1536 ... 5120 in 3.5 to 7 rounds 1 ... 5 %
 // slower in 80 of 84 products, going / staying: 320 x 192 at K = 2048 in 7 rounds 356 / 377 us, 320 x 160 at K = 4096 in 4 rounds
 // 323 / 327, 192 x 256 at K = 3584 in 5.5 rounds 405 / 413.
-constexpr bool gemm_may_stay(int bm, int bn, int waves, int epi) {
-  return waves == 4 && bm * bn >= 192 * 192 && bm * bn <= 256 * 256 && epi != EPI_BIAS_F32 && epi != EPI_PARTIAL;
-}
 constexpr int kStayRounds = 3, kStayManyRounds = 20;
 constexpr int64_t kStayOperands = 400000000;   // bytes of A and W
 // Whether the workgroups of a product stay: from more than kStayRounds rounds on (items: tiles, and the k ranges of a split last
@@ -931,7 +929,7 @@ LastRound split_last_round(int64_t tiles, int slots, int KT, int64_t block_bytes
   return r;
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI>
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool MAY_STAY>
 int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc, int64_t M, int64_t N,
                 int64_t K, const void* bias, const void* resid, int64_t ldr, const int32_t* rmap, int splits,
                 int kt_per_split, void* tail_ws, int64_t tail_ws_bytes, hipStream_t st) {
@@ -951,7 +949,6 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
     }
   }
   const int items = full + tail * tsp;
-  constexpr bool MAY_STAY = gemm_may_stay(BM, BN, WGM * WGN, EPI);
   const bool stay = gemm_stays(MAY_STAY, items, 256 * OCC, (M + (EPI == EPI_SWIGLU ? 2 : 1) * N) * K * 2);
   auto kern = stay ? gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, MAY_STAY> : gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, false>;
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
@@ -989,30 +986,32 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
 // USE: 0 all epilogues, 1 all but SwiGLU (an odd number of column tiles per wavefront, or never the fastest there), 3 float
 // output without scratch (the heads; in the layers never the fastest).  256 x 256 on 8 wavefronts of
 // 64 x 128 over many rounds, on 4 of 128 x 128 over few.
-//     BM   BN  WGM WGN STAGES OCC USE light  full  many
+// STAY: the products whose workgroups can stay, 0 none, 1 SwiGLU, 2 residuals too.
+//     BM   BN  WGM WGN STAGES OCC USE STAY light  full  many
 #define VLC_GEMM_TILES(X)                             \
-  X(64, 128, 2, 2, 4, 1, 0, 0.247f, 0.375f, 0.378f)     \
-  X(128, 96, 4, 1, 5, 1, 0, 0.338f, 0.422f, 0.422f)     \
-  X(128, 128, 2, 2, 4, 1, 0, 0.477f, 0.522f, 0.652f)    \
-  X(128, 160, 4, 1, 4, 1, 0, 0.422f, 0.616f, 0.763f)    \
-  X(160, 160, 2, 2, 4, 1, 1, 0.350f, 0.725f, 0.799f)    \
-  X(128, 256, 2, 2, 3, 1, 0, 0.580f, 0.860f, 1.049f)    \
-  X(192, 128, 2, 2, 4, 1, 1, 0.541f, 0.645f, 0.581f)    \
-  X(160, 192, 2, 2, 3, 1, 0, 0.687f, 0.740f, 0.894f)    \
-  X(192, 192, 2, 2, 3, 1, 0, 0.431f, 0.859f, 1.073f)    \
-  X(224, 192, 2, 2, 3, 1, 0, 0.570f, 1.018f, 1.036f)    \
-  X(160, 256, 2, 2, 3, 1, 0, 0.783f, 0.990f, 1.036f)    \
-  X(192, 256, 2, 2, 2, 1, 0, 0.777f, 1.097f, 1.093f)    \
-  X(256, 192, 2, 2, 2, 1, 0, 0.644f, 1.062f, 1.289f)    \
-  X(320, 160, 4, 1, 2, 1, 0, 0.536f, 1.108f, 1.146f)    \
-  X(320, 192, 2, 2, 2, 1, 0, 0.970f, 1.339f, 1.333f)    \
-  X(256, 256, 4, 2, 2, 1, 1, 0.797f, 1.458f, 1.366f)    \
-  X(256, 256, 2, 2, 2, 1, 0, 0.733f, 1.493f, 1.418f)    \
-  X(320, 256, 2, 2, 2, 1, 1, 1.313f, 1.674f, 1.734f)    \
-  X(128, 160, 4, 1, 2, 2, 3, 0.701f, 0.838f, 0.991f)
+  X(64, 128, 2, 2, 4, 1, 0, 0, 0.247f, 0.375f, 0.378f)     \
+  X(128, 96, 4, 1, 5, 1, 0, 0, 0.338f, 0.422f, 0.422f)     \
+  X(128, 128, 2, 2, 4, 1, 0, 0, 0.477f, 0.522f, 0.652f)    \
+  X(128, 160, 4, 1, 4, 1, 0, 0, 0.422f, 0.616f, 0.763f)    \
+  X(160, 160, 2, 2, 4, 1, 1, 0, 0.350f, 0.725f, 0.799f)    \
+  X(128, 256, 2, 2, 3, 1, 0, 0, 0.580f, 0.860f, 1.049f)    \
+  X(192, 128, 2, 2, 4, 1, 1, 0, 0.541f, 0.645f, 0.581f)    \
+  X(160, 192, 2, 2, 3, 1, 0, 0, 0.687f, 0.740f, 0.894f)    \
+  X(192, 192, 2, 2, 3, 1, 0, 0, 0.431f, 0.859f, 1.073f)    \
+  X(224, 192, 2, 2, 3, 1, 0, 1, 0.570f, 1.018f, 1.036f)    \
+  X(160, 256, 2, 2, 3, 1, 0, 1, 0.783f, 0.990f, 1.036f)    \
+  X(192, 256, 2, 2, 2, 1, 0, 1, 0.777f, 1.097f, 1.093f)    \
+  X(256, 192, 2, 2, 2, 1, 0, 0, 0.644f, 1.062f, 1.289f)    \
+  X(320, 160, 4, 1, 2, 1, 0, 2, 0.536f, 1.108f, 1.146f)    \
+  X(320, 192, 2, 2, 2, 1, 0, 2, 0.970f, 1.339f, 1.333f)    \
+  X(256, 256, 4, 2, 2, 1, 1, 0, 0.797f, 1.458f, 1.366f)    \
+  X(256, 256, 2, 2, 2, 1, 0, 1, 0.733f, 1.493f, 1.418f)    \
+  X(320, 256, 2, 2, 2, 1, 1, 0, 1.313f, 1.674f, 1.734f)    \
+  X(128, 160, 4, 1, 2, 2, 3, 0, 0.701f, 0.838f, 0.991f)
 constexpr bool tile_serves(int use, int epi) {
   return use == 0 || (use == 1 && epi != EPI_SWIGLU) || (use == 3 && epi == EPI_BIAS_F32);
 }
+constexpr bool tile_may_stay(int stay, int epi) { return (stay >= 1 && epi == EPI_SWIGLU) || (stay == 2 && epi == EPI_RESIDUAL); }
 
 struct TileChoice {
   int index;        // into VLC_GEMM_TILES
@@ -1038,7 +1037,7 @@ constexpr float kPriceSumLaunch = 2.5f;       // not deferred to the caller's ne
 
 TileChoice choose_tile(int64_t M, int64_t N, int64_t K, int epi, bool deferred, int64_t ws_bytes) {
   struct Tile { int bm, bn, waves, occ, use; float light, full, many; };
-#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA) {BM, BN, WGM * WGN, OCC, USE, L, F, MA},
+#define X(BM, BN, WGM, WGN, S, OCC, USE, STAY, L, F, MA) {BM, BN, WGM * WGN, OCC, USE, L, F, MA},
   static constexpr Tile kTiles[] = {VLC_GEMM_TILES(X)};
 #undef X
   constexpr int kCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
@@ -1108,11 +1107,11 @@ int dispatch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ld
     if constexpr (EPI != EPI_SWIGLU) {
       const int per = (KT + c.splits - 1) / c.splits, splits = (KT + per - 1) / per;
       int rc = VLC_OK, i = 0;
-#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA)                                                                    \
+#define X(BM, BN, WGM, WGN, S, OCC, USE, STAY, L, F, MA)                                                              \
   if (c.index == i++) {                                                                                              \
     if constexpr (USE != 3 && tile_serves(USE, EPI))                                                                 \
-      rc = launch_bf16<BM, BN, WGM, WGN, S, OCC, EPI_PARTIAL>(A, lda, W, splitk_ws, N, M, N, K, nullptr, nullptr, 0, \
-                                                              nullptr, splits, per, nullptr, 0, st);                 \
+      rc = launch_bf16<BM, BN, WGM, WGN, S, OCC, EPI_PARTIAL, false>(A, lda, W, splitk_ws, N, M, N, K, nullptr, nullptr,  \
+                                                                     0, nullptr, splits, per, nullptr, 0, st);       \
   }
       VLC_GEMM_TILES(X)
 #undef X
@@ -1131,11 +1130,11 @@ int dispatch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ld
   }
   void* tail_ws = c.split_tail ? splitk_ws : nullptr;
   int i = 0;
-#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA)                                                                      \
+#define X(BM, BN, WGM, WGN, S, OCC, USE, STAY, L, F, MA)                                                                \
   if (c.index == i++) {                                                                                                \
     if constexpr (tile_serves(USE, EPI))                                                                               \
-      return launch_bf16<BM, BN, WGM, WGN, S, OCC, EPI>(A, lda, W, C, ldc, M, N, K, bias, resid, ldr, rmap, 1, KT,      \
-                                                        tail_ws, splitk_ws_bytes, st);                                 \
+      return launch_bf16<BM, BN, WGM, WGN, S, OCC, EPI, tile_may_stay(STAY, EPI)>(A, lda, W, C, ldc, M, N, K, bias, resid,  \
+                                                                                  ldr, rmap, 1, KT, tail_ws, splitk_ws_bytes, st);  \
   }
   VLC_GEMM_TILES(X)
 #undef X
@@ -1169,14 +1168,13 @@ int launch_f32(const void* A, int64_t lda, const void* W, void* C, int64_t ldc, 
 }
 
 // Grouped launches: the grid covers the largest number of row tiles the table can hold.
-template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI>
+template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int EPI, bool STAY = false>
 int launch_bf16_grouped(const void* A, int64_t lda, const int32_t* amap, const void* W, int64_t w_stride, void* C,
                         int64_t ldc, int64_t N, int64_t K, const GroupTile* gtab, const int32_t* g_ntiles,
                         int max_tiles_m, hipStream_t st) {
   constexpr int CN = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
   const int tiles_n = (int)((N + CN - 1) / CN);
   const size_t lds = (size_t)STAGES * (BM + BN) * BK * 2;
-  constexpr bool STAY = gemm_may_stay(BM, BN, WGM * WGN, EPI);
   auto kern = gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, OCC, EPI, STAY, true>;
   if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds)) return rc;
   const int most = max_tiles_m * tiles_n, grid = STAY && most > 256 * OCC ? 256 * OCC : most;
@@ -1255,13 +1253,13 @@ int launch_gemm_grouped(const void* A, int64_t lda, const int32_t* amap, const v
       return fail(VLC_ERR_SHAPE, "grouped gemm(bf16): operand rows span more than 2 GiB");
     if (tile_rows == 256) {
       if (epilogue == EPI_SWIGLU)
-        return launch_bf16_grouped<256, 256, 2, 2, 2, 1, EPI_SWIGLU>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
-      return launch_bf16_grouped<256, 256, 2, 2, 2, 1, EPI_BIAS>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
+        return launch_bf16_grouped<256, 256, 2, 2, 2, 1, EPI_SWIGLU, true>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
+      return launch_bf16_grouped<256, 256, 2, 2, 2, 1, EPI_BIAS, true>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
     }
     if (tile_rows == 192) {
       if (epilogue == EPI_SWIGLU)
-        return launch_bf16_grouped<192, 256, 2, 2, 2, 1, EPI_SWIGLU>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
-      return launch_bf16_grouped<192, 256, 2, 2, 2, 1, EPI_BIAS>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
+        return launch_bf16_grouped<192, 256, 2, 2, 2, 1, EPI_SWIGLU, true>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
+      return launch_bf16_grouped<192, 256, 2, 2, 2, 1, EPI_BIAS, true>(A, lda, amap, W, w_stride, C, ldc, N, K, tiles, n_tiles, max_tiles, st);
     }
     if (tile_rows == 64) {
       if (epilogue == EPI_SWIGLU)
@@ -1328,7 +1326,7 @@ extern "C" int vlc_probe_gemm_choice(int epilogue, int64_t M, int64_t N, int64_t
   const int64_t ws = scratch ? vlc::gemm_splitk_ws_bytes(M, N) : 0;
   const vlc::TileChoice c = vlc::choose_tile(M, N, K, epilogue, deferred != 0, ws);
   int i = 0;
-#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA)                                                               \
+#define X(BM, BN, WGM, WGN, S, OCC, USE, STAY, L, F, MA)                                                         \
   if (c.index == i++) {                                                                                          \
     const int64_t cn = epilogue == vlc::EPI_SWIGLU ? BN / 2 : BN;                                                \
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + cn - 1) / cn);                                             \
@@ -1345,7 +1343,7 @@ extern "C" int vlc_probe_gemm_waves(int epilogue, int64_t M, int64_t N, int64_t 
   if (M <= 0 || N <= 0 || K < vlc::BK || K % vlc::BK) return 0;
   const vlc::TileChoice c =
       vlc::choose_tile(M, N, K, epilogue, deferred != 0, scratch ? vlc::gemm_splitk_ws_bytes(M, N) : 0);
-#define X(BM, BN, WGM, WGN, S, OCC, USE, L, F, MA) WGM * WGN,
+#define X(BM, BN, WGM, WGN, S, OCC, USE, STAY, L, F, MA) WGM * WGN,
   static constexpr int kWaves[] = {VLC_GEMM_TILES(X)};
 #undef X
   return kWaves[c.index];
@@ -1356,6 +1354,10 @@ extern "C" int vlc_probe_gemm_stays(int epilogue, int64_t M, int64_t N, int64_t 
   if (vlc_probe_gemm_choice(epilogue, M, N, K, scratch, deferred, o) || o[3] > 1) return 0;
   const int64_t cn = epilogue == vlc::EPI_SWIGLU ? o[1] / 2 : o[1], slots = 256 * o[2];
   const int64_t tiles = ((M + o[0] - 1) / o[0]) * ((N + cn - 1) / cn);
-  const bool may = vlc::gemm_may_stay(o[0], o[1], vlc_probe_gemm_waves(epilogue, M, N, K, scratch, deferred), epilogue);
+  const vlc::TileChoice c = vlc::choose_tile(M, N, K, epilogue, deferred != 0, scratch ? vlc::gemm_splitk_ws_bytes(M, N) : 0);
+#define X(BM, BN, WGM, WGN, S, OCC, USE, STAY, L, F, MA) STAY,
+  static constexpr int kStays[] = {VLC_GEMM_TILES(X)};
+#undef X
+  const bool may = vlc::tile_may_stay(kStays[c.index], epilogue);
   return vlc::gemm_stays(may, tiles + (o[4] - 1) * (tiles % slots), (int)slots, (M + (epilogue == vlc::EPI_SWIGLU ? 2 : 1) * N) * K * 2);
 }

@@ -9,7 +9,8 @@ from test_gpu_moe import check_moe_layer
 
 # (product, its epilogue, last round split) of the layer (H, I, Hq, Hkv, rows) that stays
 CASES = [("gate_up", False, (64, 4096, 1, 1, 5000)), ("gate_up", False, (128, 4160, 1, 1, 8191)), ("gate_up", False, (192, 4096, 1, 1, 16390)),
-         ("gate_up", True, (2048, 2048, 1, 1, 16390)), ("gate_up", True, (2048, 6464, 1, 1, 4097)), ("o", False, (7936, 128, 8, 4, 6266))]
+         ("gate_up", True, (2048, 2048, 1, 1, 16390)), ("gate_up", True, (2048, 6464, 1, 1, 4097)), ("o", False, (2880, 64, 6, 1, 16539)), ("o", True, (2368, 192, 30, 5, 16621)),
+         ("down", True, (2880, 7040, 4, 4, 16932)), ("down", False, (5696, 11328, 4, 2, 10866))]
 
 
 @pytest.mark.gpu
@@ -17,7 +18,7 @@ CASES = [("gate_up", False, (64, 4096, 1, 1, 5000)), ("gate_up", False, (128, 41
 def test_products_of_many_rounds(product, split, layer):
     """The workgroups stay (asked of the library), at the tolerances of the tests of the tiles."""
     H, I, Hq, Hkv, rows = layer
-    of = {"gate_up": (SWIGLU, rows, I, H), "o": (RESIDUAL, rows, H, Hq * 128)}[product]
+    of = {"gate_up": (SWIGLU, rows, I, H), "o": (RESIDUAL, rows, H, Hq * 128), "down": (RESIDUAL, rows, H, I)}[product]
     assert stays(*of), choice(*of)
     assert (choice(*of)[2] == "split last round") == split, choice(*of)
     check_layer(H, I, Hq, Hkv, rows)
