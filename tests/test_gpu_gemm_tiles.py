@@ -1,7 +1,7 @@
 """The bf16 products of a layer on every tile configuration that the dispatcher launches: whole, with a split k range, and with
 a last round whose tiles are split along k.  The layers below are small stand-ins (a few columns, many rows, or the other
-way round) whose products land on each of them; what a product lands on is asked of the library, so that a change of the
-prices cannot move the cases away from the kernels unnoticed."""
+way round) whose products land on each of them, with workgroups that stay for several tiles where a decoder's do; what a product lands
+on is asked of the library, so that a change of the prices cannot move the cases away from the kernels unnoticed."""
 import ctypes
 import dataclasses
 
@@ -40,6 +40,10 @@ LAYERS += [
     (6080, 128, 32, 4, 3870), (9664, 128, 4, 4, 10788), (8192, 128, 64, 8, 774)]
 # q|k|v on 256 x 256 with eight wavefronts and a whole last round
 LAYERS += [(256, 128, 4, 2, 13551)]
+# gate|up whose workgroups stay, on 224 x 192, 320 x 160 (split last round) and 192 x 256 (split last round, whole), and of two to three
+# rounds with a split last round whose workgroups go, on 320 x 192 and 256 x 256 (the other forms of both: test_gpu_gemm_resident.py)
+LAYERS += [(64, 18752, 3, 3, 983), (1344, 6848, 9, 3, 4705), (1088, 22016, 6, 3, 1137), (64, 19648, 3, 1, 1071), (3072, 24896, 12, 4, 590),
+           (3264, 8320, 2, 1, 961)]
 # q|k|v of one k-tile in many rounds
 LAYERS += [(64, 192, 40, 8, 12001)]
 # (requests, vocabulary, hidden size) of heads, on the tile that only they use
@@ -64,18 +68,24 @@ def stays(epilogue, M, N, K, scratch=1, deferred=1):
     return bool(f(epilogue, M, N, K, scratch, deferred))
 
 
+def kernel(*product):
+    """The choice, and whether its workgroups stay: a kernel of its own for the same tile and epilogue."""
+    return (*choice(*product), "stays" if stays(*product) else "goes")
+
+
 def layer_choices(H, I, Hq, Hkv, rows):
     """The four products of a chained layer, and the down projection of one that is not."""
     hd, nqkv = Hq * 128, (Hq + 2 * Hkv) * 128
-    return {"qkv": choice(FLOAT, rows, nqkv, H), "o": choice(RESIDUAL, rows, H, hd), "gate_up": choice(SWIGLU, rows, I, H),
-            "down": choice(RESIDUAL, rows, H, I), "down alone": choice(RESIDUAL, rows, H, I, 1, 0)}
+    return {"qkv": kernel(FLOAT, rows, nqkv, H), "o": kernel(RESIDUAL, rows, H, hd), "gate_up": kernel(SWIGLU, rows, I, H),
+            "down": kernel(RESIDUAL, rows, H, I), "down alone": kernel(RESIDUAL, rows, H, I, 1, 0)}
 
 
 def test_every_choice_is_among_the_tested_layers():
     """1 to 30000 rows at the decoder shapes of the workloads and three more, and the heads: no tile is launched with an
-    epilogue and a split that the layers of this file do not run."""
-    tested = {choice(FLOAT, rows, vocab, H, 0, 0) for rows, vocab, H in HEADS}
-    for l in LAYERS:
+    epilogue, a split and workgroups that stay or go which the layers of this file and of test_gpu_gemm_resident.py do not run."""
+    from test_gpu_gemm_resident import CASES
+    tested = {kernel(FLOAT, rows, vocab, H, 0, 0) for rows, vocab, H in HEADS}
+    for l in LAYERS + [layer for _, _, layer in CASES]:
         tested |= set(layer_choices(*l).values())
     shapes = [(s.H, s.I, s.Hq, s.Hkv) for s in syn.SHAPES.values() if s.dtype == "bf16" and s.D == 128]
     shapes += [(5120, 13824, 40, 8), (1536, 8960, 12, 2), (2048, 11008, 16, 2)]
@@ -88,7 +98,7 @@ def test_every_choice_is_among_the_tested_layers():
     for H in (64, 512, 2048, 2560, 3072, 3584, 4096, 8192):
         for vocab in (256, 4096, 32000, 151936, 152064):
             for rows in (1, 8, 33, 64, 65, 128, 129, 300, 700, 2000):
-                assert choice(FLOAT, rows, vocab, H, 0, 0) in tested, (H, vocab, rows)
+                assert kernel(FLOAT, rows, vocab, H, 0, 0) in tested, (H, vocab, rows)
 
 
 def test_choices_that_measure_faster():
