@@ -1,16 +1,17 @@
 """bf16 products whose workgroups stay for several tiles and ask for the next one's first k-tiles before they store the last
 one's outputs: k ranges shorter than the ring of stages and longer, ragged rows and columns, last rounds split along k, and
 experts whose row tiles are only known on the device."""
+import numpy as np
 import pytest
 
 import vlc_synth as syn
 from test_gpu_gemm_tiles import RESIDUAL, SWIGLU, choice, stays, test_layer_products_on_every_tile as check_layer
 from test_gpu_moe import check_moe_layer
 
-# (product, its epilogue, last round split) of the layer (H, I, Hq, Hkv, rows) that stays
+# (product that stays, whether its last round is split, layer: H, I, Hq, Hkv, rows)
 CASES = [("gate_up", False, (64, 4096, 1, 1, 5000)), ("gate_up", False, (128, 4160, 1, 1, 8191)), ("gate_up", False, (192, 4096, 1, 1, 16390)),
-         ("gate_up", True, (2048, 2048, 1, 1, 16390)), ("gate_up", True, (2048, 6464, 1, 1, 4097)), ("o", False, (2880, 64, 6, 1, 16539)), ("o", True, (2368, 192, 30, 5, 16621)),
-         ("down", True, (2880, 7040, 4, 4, 16932)), ("down", False, (5696, 11328, 4, 2, 10866))]
+         ("gate_up", True, (2048, 2048, 1, 1, 16390)), ("gate_up", True, (2048, 6464, 1, 1, 4097)), ("o", False, (2880, 64, 6, 1, 16539)),
+         ("o", True, (2368, 192, 30, 5, 16621)), ("down", True, (2880, 7040, 4, 4, 16932)), ("down", False, (5696, 11328, 4, 2, 10866))]
 
 
 @pytest.mark.gpu
@@ -25,11 +26,15 @@ def test_products_of_many_rounds(product, split, layer):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("rows,H,I", [(2600, 3328, 64), (2600, 3264, 192), (1800, 128, 2176), (900, 192, 2240)])
-def test_experts_of_many_tiles(rows, H, I):
-    """2 of 8 experts; more tiles than workgroups in the down projection (one and three k-tiles), then in gate|up, whose rows are
-    fetched through the pair list (two and three k-tiles); tiles of 256 rows, in the last case of 192."""
+@pytest.mark.parametrize("rows,H,I,product", [(2600, 3328, 64, "down"), (2600, 3264, 192, "down"), (1800, 128, 2432, "gate_up"), (900, 192, 3392, "gate_up")])
+def test_experts_of_many_tiles(rows, H, I, product):
+    """2 of 8 experts; more tiles than the 256 workgroups that stay, however the router loads the experts, in the down projection (one and three
+    k-tiles), then in gate|up, whose rows are fetched through the pair list (two and three k-tiles); tiles of 256 rows, in the last case of 192."""
     sh = syn.Shape("moe_stay", L=1, H=H, Hq=4, Hkv=2, D=128, I=I, rope_base=1e4, dtype="bf16", qkv_bias=False, qk_norm=True,
                    mrope_section=(24, 20, 20), n_experts=8, top_k=2, text_scale=1.0, residual_proj_scale=0.01)
     req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
-    check_moe_layer(syn.Workload("moe_stay%d_%d" % (rows, I), sh, [req], 1, "static", static_k=0, seed=1200 + I), 0)
+    g = check_moe_layer(syn.Workload("moe_stay%d_%d" % (rows, I), sh, [req], 1, "static", static_k=0, seed=1200 + I), 0)
+    tile_rows = 256 if 2 * rows // 8 >= 320 else 192        # the launcher's lines: from 320 and from 140 rows per expert on average
+    assert 2 * rows // 8 >= 140
+    row_tiles = sum(-(-int(pairs) // tile_rows) for pairs in np.diff(g["moe_offset"]))
+    assert row_tiles * -(-(2 * I if product == "gate_up" else H) // 256) > 256, (row_tiles, tile_rows)
