@@ -39,7 +39,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) { return f32_t
 // accumulators of two key tiles feed the second MFMA directly: its contraction index is just a relabeling of keys, as long as the
 // V^T fragment uses the same relabeling, which is how it is read from LDS.
 //
-// 16x16x32 and not 32x32x16: from some thousand rows on the kernel runs at the power limit of the card (1.6 of 2.4 GHz), and a loop of
+// 16x16x32 and not 32x32x16: from some thousand rows on the kernel runs at the power limit of the card (18944 rows: 1.64 of 2.4 GHz with up to
+// 18432 keys a row on one card, matrix pipe busy 57 % of the cycles; with 32x32x16 1.53 GHz and 59 % there), and a loop of
 // MFMAs on random operands reaches 1.70 ... 1.82 PFLOP/s with 32x32x16 there, 2.04 ... 2.18 with 16x16x32.  The K and V fragments are
 // as large and feed as many products.  By itself at 18944 rows (28 / 4 heads, 3.9 TFLOP) 3631 -> 3474 us and, on a card that
 // throttles more, 4230 -> 4029; inside the layer 3754 -> 3683; 7104 rows (32 / 4 heads) 741 -> 710, inside the layer 795 -> 778; 5824 rows 248 -> 238.
@@ -730,9 +731,7 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     if (D != ATT_D) return fail(VLC_ERR_SHAPE, "attention(bf16): D=%d unsupported (128 only)", D);
     if (g > VR) return fail(VLC_ERR_SHAPE, "attention(bf16): Hq/Hkv=%d exceeds %d", g, VR);
     if (q_stride % 8) return fail(VLC_ERR_SHAPE, "attention(bf16): q row stride must be a multiple of 8");
-    // 128 virtual rows per workgroup, two workgroups per CU (RT = 1).  The kernel is also written for two row
-    // tiles per wavefront (RT = 2: 256 virtual rows, one workgroup per CU), which is not launched: it needs
-    // more registers than a wavefront has (147 spilled) and one wavefront per SIMD overlaps nothing.
+    // 128 virtual rows per workgroup, two workgroups per CU
     const int rows_per_tile = VR / g;
     const int64_t tiles = (n + rows_per_tile - 1) / rows_per_tile;
     if (shares && shares->max_shares > 1) {

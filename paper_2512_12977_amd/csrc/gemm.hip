@@ -89,9 +89,11 @@ __device__ __forceinline__ void tile_coords(int pid, int total, int tiles_m, int
 //
 // RESIDENT: one round of workgroups stays for all tiles and asks for the next tile's first k-tiles under the last k-step of
 // this one (tile_may_stay, gemm_stays): no workgroup starts, reads its arguments and waits for its first k-tiles in
-// between.  Products of few k-tiles gain most: gate|up / down of 128 experts (2048 x 768) at 444 rows each 354 -> 333 and 262 -> 248
-// us; 7B gate|up at 5824 rows 1134 -> 1110, at 18944 rows (43 rounds, at the card's power limit) 3765 -> 3745.  Up to two rounds
-// nothing is gained, and products that stream their weights through small tiles are no faster (37 rows per expert) or slower.
+// between.  Products of few k-tiles gain most: gate|up / down of 128 experts (2048 x 768) at 444 rows each 378 -> 361 and 260 -> 248
+// us, at 4000 2654 -> 2644 and 1853 -> 1780; 7B gate|up at 5824 rows 1157 -> 1131.  The next tile's place costs scalar registers: all
+// are taken, and 16 ... 62 spilled to lanes of a vector register outside the k-loop.  Products that stream their weights
+// through small tiles are no faster (37 rows per expert) or slower.  The tiles are dealt once and for all, so a workgroup that
+// another stream's kernel keeps waiting holds up its whole share of them.
 //
 // The epilogue reads its residual rows (and bias) ahead of the stores, and whole tiles store without a condition: each
 // 16 x 16 output tile under a condition of its own is a memory round trip, the compiler waits for its load in front of its store.
@@ -184,18 +186,19 @@ enum { EPI_PARTIAL = 100 };   // internal: float partial sums of one k-range (sp
 // wavefronts, where products of more than kStayRounds rounds land on them (over 240000 products of decoder proportions, up to 60000
 // rows, residuals on two tiles only).  Not 320 x 256, whose sums and fragments leave no registers for the next tile's addresses, nor
 // eight wavefronts, two per SIMD, which fill each other's waits (and spill).  Not float outputs either: the waits for the next tile's
-// k-tiles also wait for the stores in front of them, twice the bytes here.  q|k|v at K = 1536 ... 5120 in 3.5 to 7 rounds 1 ... 5 %
-// slower in 80 of 84 products, going / staying: 320 x 192 at K = 2048 in 7 rounds 356 / 377 us, 320 x 160 at K = 4096 in 4 rounds
+// k-tiles also wait for the stores in front of them, twice the bytes here.  q|k|v at K = 1536 ... 5120 in 3.5 to 7 rounds is slower by
+// staying in 77 of 84 products, 1.8 % on average and up to 5.4, going / staying: 320 x 192 at K = 2048 in 7 rounds 356 / 377 us, 320 x 160 at K = 4096 in 4 rounds
 // 323 / 327, 192 x 256 at K = 3584 in 5.5 rounds 405 / 413.
 constexpr int kStayRounds = 3, kStayManyRounds = 20;
 constexpr int64_t kStayOperands = 400000000;   // bytes of A and W
 // Whether the workgroups of a product stay: from more than kStayRounds rounds on (items: tiles, and the k ranges of a split last
-// round's), and over more than kStayManyRounds only if the operands are not much more than the memory-side cache holds (256 MB).
-// The tiles are dealt once and for all then, so nothing keeps the XCDs in step over many of them, and an XCD that is behind
-// fetches from HBM again what the others have used.  Gate|up, going / staying, us: up to 20 rounds staying is 0.4 ... 4 % faster whatever
-// the operands (72B at 5200 rows, 19 rounds, 1054 MB: 3543 / 3503); beyond, 1.5B at 31000 rows (33 rounds, 150 MB) 1349 / 1314, 7B at 16500
-// (38 rounds, 390 MB) 3150 / 3127, but 7B at 18944 (43 rounds, 408 MB) 3706 / 3759 and at 31000 6146 / 6583, 13824 x 5120 at 13500
-// (22 rounds, 421 MB) 2767 / 2896 and at 38000 7918 / 8637, 72B at 7500 (27 rounds, 1092 MB) 5269 / 5560.
+// round's; between 3 and 4 rounds SwiGLU and residuals gain 3 ... 6 % at K = 1024, 1 ... 2 % at 3584, 0 ... 1 % at 8192, and not much less from
+// 1.5 rounds on), and over more than kStayManyRounds only if the operands are not much more than the memory-side cache holds (256 MB).
+// The tiles are dealt once and for all, so nothing keeps the XCDs in step over many of them; one that is behind would fetch from HBM
+// again what the others have used.  Gate|up of eight shapes, 5200 ... 38000 rows, going / staying, us: up to 20 rounds staying gains 1.7 % on
+// average whatever the operands (-0.4 ... 4.1; 72B at 5200 rows, 19 rounds, 1054 MB: 3543 / 3503), beyond them 1.6 % up to 400 MB (0.2 ... 4.4;
+// 1.5B at 31000, 33 rounds, 150 MB: 1349 / 1314; 7B at 16500, 38 rounds, 390 MB: 3150 / 3127) and loses 2.6 % over more (0.8 ... -8.3; 7B at
+// 18944, 43 rounds, 408 MB: 3706 / 3759; 13824 x 5120 at 38000, 63 rounds: 7918 / 8637; 72B at 7500, 27 rounds: 5269 / 5560).
 bool gemm_stays(bool may, int64_t items, int slots, int64_t operand_bytes) {
   return may && items > kStayRounds * slots && (items <= kStayManyRounds * slots || operand_bytes <= kStayOperands);
 }
@@ -980,7 +983,10 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
 // rounds (power).  All numbers of the model were fitted together, to the times of 700 products of 2 ... 24000 rows in
 // five decoder shapes and of heads, with every tile, every number of k ranges and both ends of a last round (27000 times, cold
 // weights), so that its choice is as little slower as possible than the best of them: 0.5 % on average, 36 products more
-// than 3 % (left out of the fit, the fifth shape is at 1.2 %).  A list without one of the tiles costs 0.1 ... 1.3 % more.
+// than 3 % (left out of the fit, the fifth shape is at 1.2 %).  That was with the kernels of that time: 534 products of 8 ... 24000 rows timed
+// with the present ones, which end sooner (residuals and float outputs above all) and may stay, are 2.0 % slower than the best of the 14
+// cheapest on average, 111 of them more than 3 %: q|k|v of K = 2048 at 60 ... 110 rows takes one k range where three to five are 20 ... 45 %
+// faster, residuals and q|k|v from 6000 rows on 256 x 256 on eight wavefronts where 320 x 256 or 320 x 192 is 6 ... 8 % faster.  A list without one of the tiles costs 0.1 ... 1.3 % more.
 // These are numbers of a fit and no measured times (192 x 128 is priced lower over many rounds than in one), and they miss: at
 // 8192 columns and K = 29568, 320 x 256 takes 8469 us where 256 x 256 is chosen with 8833 (24000 rows), 12655 against 13745 (36000).
 // USE: 0 all epilogues, 1 all but SwiGLU (an odd number of column tiles per wavefront, or never the fastest there), 3 float
@@ -1218,14 +1224,15 @@ int64_t gemm_splitk_ws_bytes(int64_t n_rows, int64_t max_n) {
 // matrix is streamed from HBM exactly once and nothing is reused, so the tile is small (64 x 128, below 9 rows per
 // group 32 x 128) and the ring three (four) stages deep - with two workgroups per CU that keeps 64 (96) KB of matrix data
 // in flight per CU, what the HBM latency needs; a two-stage ring of 128 x 128 tiles stalls at half of that.  More rows: the tile that
-// pads an expert's rows least at a k-loop that is still fast.  Lines by the mean alone, from this one shape with an even load:
-// gate|up + down of one layer of 128 experts (2048 x 768), us:
-//   rows per expert    6    10    56    94   163   281   444
-//   32               211   221
-//   64               212   218   274   330   421   611   877
-//   128              219   225   274   284   379   498   670   (gate|up on 128 x 256: 7 % faster than on 128 x 128 two per CU)
-//   192                    239   298   303   349   470   662
-//   256              252   270   302   332   376   486   636   (4 wavefronts of 128 x 128; gate|up on 8 of 64 x 128 3 % slower)
+// pads an expert's rows least at a k-loop that is still fast.  Lines by the mean alone, set with an even load before the workgroups of 192
+// and 256 rows stayed; gate|up + down of one layer of 128 experts (2048 x 768) with the present kernels, loads that differ by 15 %, us:
+//   rows per expert    6    10    37    56    80    94   120   160   200   281   360   444  1184
+//   32               208   213   262   299   350
+//   64               207   213   233   265   306   324   356   412   494   616
+//   128                          234   247   255   281   298   378   415   505   587   684  1628   (gate|up on 128 x 256)
+//   192                          247   257   267   272   280   321   391   488   537   637  1450
+//   256                          273   278   290   293   301   312   363   503   566   609  1437   (4 wavefronts of 128 x 128)
+// By these 192 rows would pay from some 90 on and 256 between 160 and 240 (at 281 the padding takes it back).
 int gemm_group_tile_rows(int64_t rows, int n_groups, int dtype) {
   if (dtype != VLC_BF16) return 64;
   const int64_t mean = rows / (n_groups > 0 ? n_groups : 1);
