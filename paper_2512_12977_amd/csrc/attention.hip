@@ -3,7 +3,7 @@
 //   bf16: MFMA flash-style kernel, one workgroup per (block of query rows, kv head); the g = Hq/Hkv
 //         query heads that share a kv head are stacked into the same tile so K/V are streamed once
 //         for all of them.
-//   f32 : one workgroup per (row, head), online softmax (the small fp32 configuration).
+//   f32 : few (row, head) pairs: one workgroup each, on vector instructions; many: MFMA tiles of 16 pairs of one kv head.
 #include <hip/hip_runtime.h>
 
 #include "attention_shares.h"
@@ -566,111 +566,319 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 }
 
 // ---------------------------------------------------------------------------------------------
-// f32 kernel: one workgroup of F32_WAVES wavefronts per (row, head).  Keys in chunks of 64 * F32_WAVES: a thread scores
-// one key, the chunk's probabilities meet in LDS, and the PV product runs with the lanes over d (whole value rows,
-// coalesced), each wavefront on its 64 keys of the chunk.  Bound by latency at the sizes of the fp32 configuration: 61 rows
-// x 4 heads over 304 keys take 8.5 us on eight wavefronts; one wavefront per (row, head) with the keys over its lanes,
-// which walks five keys one after the other and then adds 64 partial outputs by shuffles, took 23.5 us.
+// f32 kernels (the small fp32 configuration)
 // ---------------------------------------------------------------------------------------------
-// (row, head) pairs from which one wavefront each is enough: the pairs themselves then fill the chip (8192 wavefronts), and
-// eight wavefronts per pair idle where there are few keys.  D = 64, one / eight wavefronts: 1200 pairs 122 / 91 us at 1500
-// keys, 9.5 / 15.6 at 64; 2400 pairs 180 / 175 and 11.6 / 25.5; 32000 pairs 1744 / 2099 and 84 / 295 (two and four
-// wavefronts lie between).
-constexpr int64_t kF32OneWavePairs = 2048;
+// From kF32PairsPerTile (row, head) pairs on 16 of them share a workgroup of four wavefronts, from kF32OneWavePairs on one wavefront.
+// 4 / 2 heads, us, at 304 keys (in brackets at 1000), one workgroup per pair | 16 pairs on four wavefronts | on one:
+//   pairs        244           512           768           1200          4800           12000          32000
+//   D = 64    5.2 | 8.8      7.9 | 8.8     9.9 | 8.8    13.5 | 8.9     44 | 11.4    16.5 | 21.6    36.8 | 37.5 (83.8 | 102.9)
+//   D = 128   6.6 | 14.7    11.5 | 15.0   15.5 | 15.0   22.9 | 15.1    79 | 25.1    39.3 | 34.1    93.4 | 66.4 (196 | 202)
+// The kernel before, one or eight wavefronts per pair that read K and V for themselves: 55, 105 and 250 us at D = 64 and 4800, 12000 and
+// 32000 pairs over 304 keys.  Four wavefronts of which each asks for the next step's pieces ahead take 186 registers instead of
+// 136: 3 % faster up to 2400 pairs, 30 % slower at 12000.
+constexpr int64_t kF32PairsPerTile = 640, kF32OneWavePairs = 32768;
 
-template <int D, int F32_WAVES>
-__global__ __launch_bounds__(64 * F32_WAVES) void attention_f32_kernel(const float* __restrict__ q, const int32_t* __restrict__ row_kv_len,
-                                                            const int32_t* __restrict__ row_kv_start,
-                                                            const float* __restrict__ kc, const float* __restrict__ vc,
-                                                            int q_stride, int Hkv, int g, float scale, int Hq,
-                                                            float* __restrict__ out) {
-  constexpr int DL = D / 64;                       // output elements per lane
-  constexpr int UNROLL = 16;                       // value rows in flight
-  __shared__ __attribute__((aligned(16))) float sq[D];
-  __shared__ float sp[64 * F32_WAVES];                      // probabilities of the chunk
-  __shared__ float red_m[2][F32_WAVES];                  // chunk maxima of the wavefronts (two sets: one barrier per use)
-  __shared__ float red_l[F32_WAVES];
-  __shared__ float red_o[F32_WAVES][D];
+__device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
+
+// sum over the 16 lanes of a DPP row, in all of them
+__device__ __forceinline__ float sum16(float v) {
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0xb1, 0xf, 0xf, true));    // quad_perm [1,0,3,2]
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x4e, 0xf, 0xf, true));    // quad_perm [2,3,0,1]
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x141, 0xf, 0xf, true));   // row_half_mirror
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x140, 0xf, 0xf, true));   // row_mirror
+  return v;
+}
+// max / sum over lanes l, l ^ 16, l ^ 32, l ^ 48, in all of them
+__device__ __forceinline__ float max_rows(float a) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+  const float t = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+  return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+__device__ __forceinline__ float sum_rows(float a) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+  const float t = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+
+// Few (row, head) pairs: one workgroup of 16 wavefronts per pair, bound by latency.  Sixteen lanes share a key, 16 bytes of it
+// each, so that a load touches whole lines of four keys; a wavefront takes 32 keys at a time, all of whose K and V are asked for
+// together, and the workgroup 512.  D = 64, 61 rows x 4 heads over 304 / 1000 keys 5.2 / 8.9 us (one lane per key, whose load touched
+// 64 lines, and V only behind the softmax: 7.7 / 17.2).
+template <int D>
+__global__ __launch_bounds__(1024) void attention_f32_pair_kernel(
+    const float* __restrict__ q, const int32_t* __restrict__ row_kv_len, const int32_t* __restrict__ row_kv_start,
+    const float* __restrict__ kc, const float* __restrict__ vc, int q_stride, int Hkv, int g, float scale, int Hq,
+    float* __restrict__ out) {
+  constexpr int W = 16, U = 8, P = D / 64;          // wavefronts, keys per lane, 16-byte pieces per lane and key
+  __shared__ float red_m[W], red_l[W];
+  __shared__ f32x4 red_o[W][D / 4];
   const int row = blockIdx.x, head = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kvh = head / g;
-  const float* qp = q + (int64_t)row * q_stride + (int64_t)head * D;
-  for (int d = tid; d < D; d += 64 * F32_WAVES) sq[d] = qp[d] * scale;
+  const int l16 = lane & 15, x = lane >> 4, kvh = head / g;
   const int len = row_kv_len[row];
-  const int64_t start = row_kv_start[row];
-  const int64_t kv_row = (int64_t)Hkv * D;
-  const float* kbase = kc + start * kv_row + (int64_t)kvh * D;
-  const float* vbase = vc + start * kv_row + (int64_t)kvh * D;
+  const int64_t start = row_kv_start[row], kv_row = (int64_t)Hkv * D;
+  const float* qp = q + (int64_t)row * q_stride + (int64_t)head * D + 4 * l16;
+  f32x4 qv[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) qv[p] = *reinterpret_cast<const f32x4*>(qp + 64 * p) * scale;
+  const float* kbase = kc + start * kv_row + (int64_t)kvh * D + 4 * l16;
+  const float* vbase = vc + start * kv_row + (int64_t)kvh * D + 4 * l16;
   float m = -INFINITY, l = 0.f;
-  float acc[DL];
+  f32x4 acc[P];
 #pragma unroll
-  for (int e = 0; e < DL; ++e) acc[e] = 0.f;
-  __syncthreads();
-  for (int c0 = 0, it = 0; c0 < len; c0 += 64 * F32_WAVES, ++it) {
-    float s = -INFINITY;
-    if (c0 + tid < len) {
-      const float4* kp = reinterpret_cast<const float4*>(kbase + (int64_t)(c0 + tid) * kv_row);
-      s = 0.f;
+  for (int p = 0; p < P; ++p) acc[p] = zero4();
+  for (int c0 = 32 * wave; c0 < len; c0 += 32 * W) {
+    f32x4 kv[U][P], vv[U][P];
 #pragma unroll
-      for (int c = 0; c < D / 4; ++c) {
-        const float4 kv = kp[c];
-        const float4 qv = *reinterpret_cast<const float4*>(&sq[4 * c]);
-        s = fmaf(kv.x, qv.x, s);
-        s = fmaf(kv.y, qv.y, s);
-        s = fmaf(kv.z, qv.z, s);
-        s = fmaf(kv.w, qv.w, s);
-      }
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int p = 0; p < P; ++p)                   // past the end: the last visible row again, left out below
+        kv[u][p] = *reinterpret_cast<const f32x4*>(kbase + (int64_t)min(c0 + 4 * u + x, len - 1) * kv_row + 64 * p);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+        vv[u][p] = *reinterpret_cast<const f32x4*>(vbase + (int64_t)min(c0 + 4 * u + x, len - 1) * kv_row + 64 * p);
+    float s[U], mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      f32x4 t = kv[u][0] * qv[0];
+#pragma unroll
+      for (int p = 1; p < P; ++p) t += kv[u][p] * qv[p];
+      s[u] = sum16((t[0] + t[1]) + (t[2] + t[3]));
+      if (c0 + 4 * u + x >= len) s[u] = -INFINITY;
+      mx = fmaxf(mx, s[u]);
     }
-    float mx = s;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    if (lane == 0) red_m[it & 1][wave] = mx;
-    __syncthreads();                               // also: the previous chunk's probabilities have been read
-    float m_new = m;
-#pragma unroll
-    for (int w = 0; w < F32_WAVES; ++w) m_new = fmaxf(m_new, red_m[it & 1][w]);
-    const float alpha = expf(m - m_new);           // m = -inf on the first chunk -> 0
-    const float p = expf(s - m_new);               // keys past the end: 0
+    const float m_new = fmaxf(m, max_rows(mx));     // -inf only if every score so far is -inf or NaN
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = expf(m - m_use);
     m = m_new;
-    l = l * alpha + p;
-    sp[tid] = p;
+    l *= alpha;
 #pragma unroll
-    for (int e = 0; e < DL; ++e) acc[e] *= alpha;
-    // a wavefront reads the probabilities it has written itself: no barrier, only the order of its LDS accesses
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    const int first = c0 + 64 * wave;
-    const int keys = min(64, len - first);
-    for (int j = 0; j < keys; j += UNROLL) {
-      float vv[UNROLL][DL];
+    for (int p = 0; p < P; ++p) acc[p] *= alpha;
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        // past the end: the load stays in range, its value (which may be an infinity) does not count
-        const float* vp = vbase + (int64_t)min(first + j + u, len - 1) * kv_row + DL * lane;
+    for (int u = 0; u < U; ++u) {
+      const float e = expf(s[u] - m_use);
+      l += e;
+      const bool seen = c0 + 4 * u + x < len;       // a value past the end (it may be an infinity) does not count
 #pragma unroll
-        for (int e = 0; e < DL; ++e) vv[u][e] = j + u < keys ? vp[e] : 0.f;
+      for (int p = 0; p < P; ++p) acc[p] += e * (seen ? vv[u][p] : zero4());
+    }
+  }
+  l = sum_rows(l);
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[p][e] = sum_rows(acc[p][e]);
+  if (lane < 16) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) red_o[wave][16 * p + l16] = acc[p];
+    if (lane == 0) {
+      red_m[wave] = m;
+      red_l[wave] = l;
+    }
+  }
+  __syncthreads();
+  if (tid >= D) return;
+  float top = -INFINITY, lt = 0.f, o = 0.f;
+#pragma unroll
+  for (int w = 0; w < W; ++w) top = fmaxf(top, red_m[w]);
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    const float f = red_m[w] == -INFINITY ? 0.f : expf(red_m[w] - top);
+    lt += red_l[w] * f;
+    o += reinterpret_cast<const float*>(red_o[w])[tid] * f;
+  }
+  out[((int64_t)row * Hq + head) * D + tid] = len > 0 ? o / lt : 0.f;   // a NaN sum stays NaN
+}
+
+// Many pairs: 16 "virtual rows" (row, head of the kv group), head fastest, per workgroup, both products on
+// v_mfma_f32_16x16x4_f32 (exact products, float sums), transposed as in the bf16 kernel: a lane's accumulators belong to one virtual
+// row, and S^T feeds the second product from its registers.  Fragments come straight from global memory in 16-byte pieces: element e
+// of a K piece is the k-slice of MFMA e; element e of a V piece belongs to the MFMA of output columns 4i + e.  The W wavefronts
+// take every W-th step of 32 keys and meet in LDS.  K and V are read once per 16 pairs instead of once per pair.
+template <int D, int W>
+__global__ __launch_bounds__(64 * W) void attention_f32_tile_kernel(
+    const float* __restrict__ q, const int32_t* __restrict__ row_kv_len, const int32_t* __restrict__ row_kv_start,
+    const float* __restrict__ kc, const float* __restrict__ vc, int64_t pairs, int q_stride, int Hkv, int g, float scale, int Hq,
+    float* __restrict__ out) {
+  constexpr int DS = D / 16, DH = D / 64;
+  __shared__ float red_m[W][16], red_l[W][16];
+  __shared__ f32x4 red_o[W > 1 ? W : 1][W > 1 ? D / 4 : 1][17];
+  const int tid = threadIdx.x, lane = tid & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
+  const int l16 = lane & 15, x = lane >> 4, kvh = blockIdx.y;
+  const int64_t vr0 = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * 16;   // pairs: n * g of one kv head
+  if (vr0 >= pairs) return;
+  const int64_t vr = vr0 + l16;
+  const bool ok = vr < pairs;
+  const int64_t row = (ok ? vr : pairs - 1) / g;
+  const int head = kvh * g + (int)((ok ? vr : pairs - 1) - row * g);
+  const int my_start = row_kv_start[row], my_len = ok ? row_kv_len[row] : 0;
+  const int64_t kv_row = (int64_t)Hkv * D;
+  f32x4 qf[DS];
+#pragma unroll
+  for (int s = 0; s < DS; ++s)
+    qf[s] = *reinterpret_cast<const f32x4*>(q + row * q_stride + (int64_t)head * D + 16 * s + 4 * x) * scale;
+  float m = -INFINITY, l = 0.f;
+  f32x4 o[DH][4];
+#pragma unroll
+  for (int h = 0; h < DH; ++h)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) o[h][t] = zero4();
+
+  // rows of different requests may share a tile: one run of equal first slots after the other
+  int run = 0;
+  while (run < 16) {
+    const int start = __builtin_amdgcn_readlane(my_start, run);
+    const uint64_t others = __ballot(lane < 16 && lane > run && my_start != start);
+    const int run_end = others ? __builtin_ctzll(others) : 16;
+    const int len = l16 >= run && l16 < run_end ? my_len : 0;
+    const int longest = __builtin_amdgcn_readfirstlane(wave_max(len));
+    const int shortest = -__builtin_amdgcn_readfirstlane(wave_max(ok ? -len : -0x7fffffff));
+    run = run_end;
+    const float* kbase = kc + (int64_t)start * kv_row + (int64_t)kvh * D + 4 * x;
+    const float* vbase = vc + (int64_t)start * kv_row + (int64_t)kvh * D + 4 * l16;
+    for (int c0 = 32 * wave; c0 < longest; c0 += 32 * W) {
+      f32x4 kf[2][DS], vf[2][4][DH];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)                   // past the end: the last row of the run again
+#pragma unroll
+        for (int s = 0; s < DS; ++s)
+          kf[t][s] = *reinterpret_cast<const f32x4*>(kbase + (int64_t)min(c0 + 16 * t + l16, longest - 1) * kv_row + 16 * s);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int h = 0; h < DH; ++h)
+            vf[t][e][h] = *reinterpret_cast<const f32x4*>(vbase + (int64_t)min(c0 + 16 * t + 4 * x + e, longest - 1) * kv_row + 64 * h);
+      f32x4 st[2] = {zero4(), zero4()};
+#pragma unroll
+      for (int s = 0; s < DS; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+            st[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][s][e], qf[s][e], st[t], 0, 0, 0);
+      const bool partly = c0 + 32 > shortest;       // some row does not see all of these keys
+      if (partly) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (c0 + 16 * t + 4 * x + j >= len) st[t][j] = -INFINITY;
       }
+      float mx = -INFINITY;
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        const float pj = sp[64 * wave + j + u];    // 0 past the end
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int e = 0; e < DL; ++e) acc[e] = fmaf(pj, vv[u][e], acc[e]);
+        for (int j = 0; j < 4; ++j) mx = fmaxf(mx, st[t][j]);
+      const float m_new = fmaxf(m, max_rows(mx));
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = expf(m - m_use);          // m = -inf: 0
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int h = 0; h < DH; ++h)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) o[h][t] *= alpha;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          st[t][j] = expf(st[t][j] - m_use);
+          l += st[t][j];
+        }
+      // A probability of zero times an infinity is a NaN: where a key that some row does not see has such a value, the
+      // products are formed one by one, for the rows that see it.
+      bool odd = false;
+      if (partly) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int h = 0; h < DH; ++h)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) odd |= !(fabsf(vf[t][e][h][i]) < INFINITY);
+      }
+      if (__ballot(odd) == 0) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int h = 0; h < DH; ++h)
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                o[h][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][e][h][i], st[t][e], o[h][i], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            for (int y = 0; y < 4; ++y) {
+              const int key = c0 + 16 * t + 4 * y + e;
+              const float p = __shfl(st[t][e], l16 + 16 * y);
+              if (key < len) {
+                const float* vp = vc + ((int64_t)start + key) * kv_row + (int64_t)kvh * D + 16 * x;
+#pragma unroll
+                for (int h = 0; h < DH; ++h)
+#pragma unroll
+                  for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[h][i][j] = fmaf(p, vp[64 * h + 4 * j + i], o[h][i][j]);
+              }
+            }
       }
     }
   }
+  l = sum_rows(l);
+  // lane: columns 64 h + 16 x + 4 j + i of its row
+  if constexpr (W > 1) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
-  if (lane == 0) red_l[wave] = l;
+    for (int h = 0; h < DH; ++h)
 #pragma unroll
-  for (int e = 0; e < DL; ++e) red_o[wave][DL * lane + e] = acc[e];
-  __syncthreads();
-  for (int d = tid; d < D; d += 64 * F32_WAVES) {
-    float lt = 0.f, o = 0.f;
-#pragma unroll
-    for (int w = 0; w < F32_WAVES; ++w) {
-      lt += red_l[w];
-      o += red_o[w][d];
+      for (int j = 0; j < 4; ++j) red_o[wave][16 * h + 4 * x + j][l16] = f32x4{o[h][0][j], o[h][1][j], o[h][2][j], o[h][3][j]};
+    if (x == 0) {
+      red_m[wave][l16] = m;
+      red_l[wave][l16] = l;
     }
-    out[((int64_t)row * Hq + head) * D + d] = len > 0 ? o / lt : 0.f;   // a NaN sum stays NaN
+    __syncthreads();
+    // thread: virtual row id / (D / 4), four columns
+    for (int id = tid; id < 16 * (D / 4); id += 64 * W) {
+      const int r = id / (D / 4), c = id % (D / 4);
+      const int64_t v = vr0 + r;
+      if (v >= pairs) break;
+      float top = -INFINITY, lt = 0.f;
+#pragma unroll
+      for (int w = 0; w < W; ++w) top = fmaxf(top, red_m[w][r]);
+      f32x4 sum = zero4();
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        const float f = red_m[w][r] == -INFINITY ? 0.f : expf(red_m[w][r] - top);
+        lt += red_l[w][r] * f;
+        sum += red_o[w][c][r] * f;
+      }
+      const int64_t orow = v / g;
+      const int ohead = kvh * g + (int)(v - orow * g);
+      f32x4 res;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) res[i] = row_kv_len[orow] > 0 ? sum[i] / lt : 0.f;   // a NaN sum stays NaN
+      *reinterpret_cast<f32x4*>(out + (orow * Hq + ohead) * D + 4 * c) = res;
+    }
+  } else if (ok) {
+#pragma unroll
+    for (int h = 0; h < DH; ++h)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        f32x4 res;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) res[i] = my_len > 0 ? o[h][i][j] / l : 0.f;
+        *reinterpret_cast<f32x4*>(out + (row * Hq + head) * D + 64 * h + 16 * x + 4 * j) = res;
+      }
   }
 }
 
@@ -754,19 +962,31 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     return VLC_OK;
   }
   if (dtype == VLC_F32) {
-    // at most 2^32 - 1 threads along a grid dimension, 64 per row here (that many rows take the one-wavefront kernel)
     if (n >= (int64_t)1 << 26 || Hq > 65535) return fail(VLC_ERR_SHAPE, "attention(f32): grid too large");
     if (D != 64 && D != 128) return fail(VLC_ERR_SHAPE, "attention(f32): D=%d unsupported", D);
-    const bool one = n * Hq >= kF32OneWavePairs;
-#define VLC_LAUNCH_F32_ATT(D_, W_)                                                                                  \
-  hipLaunchKernelGGL((attention_f32_kernel<D_, W_>), dim3((unsigned)n, (unsigned)Hq), dim3(64 * W_), 0, st,        \
+    const int64_t pairs = n * g, tiles = (pairs + 15) / 16;   // of one kv head
+    // at most 2^32 - 1 threads along a grid dimension
+    const int64_t slices = (tiles + (1 << 22) - 1) >> 22;
+    const dim3 grid((unsigned)((tiles + slices - 1) / slices), (unsigned)Hkv, (unsigned)slices);
+#define VLC_LAUNCH_F32_TILE(D_, W_)                                                                                 \
+  hipLaunchKernelGGL((attention_f32_tile_kernel<D_, W_>), grid, dim3(64 * W_), 0, st, (const float*)q, row_kv_len,  \
+                     row_kv_start, (const float*)k_cache, (const float*)v_cache, pairs, (int)q_stride, Hkv, g, scale, Hq, (float*)out)
+#define VLC_LAUNCH_F32_PAIR(D_)                                                                                     \
+  hipLaunchKernelGGL((attention_f32_pair_kernel<D_>), dim3((unsigned)n, (unsigned)Hq), dim3(1024), 0, st,           \
                      (const float*)q, row_kv_len, row_kv_start, (const float*)k_cache, (const float*)v_cache, (int)q_stride, \
                      Hkv, g, scale, Hq, (float*)out)
-    if (D == 64 && one) VLC_LAUNCH_F32_ATT(64, 1);
-    else if (D == 64) VLC_LAUNCH_F32_ATT(64, 8);
-    else if (one) VLC_LAUNCH_F32_ATT(128, 1);
-    else VLC_LAUNCH_F32_ATT(128, 8);
-#undef VLC_LAUNCH_F32_ATT
+    if (n * Hq < kF32PairsPerTile) {
+      if (D == 64) VLC_LAUNCH_F32_PAIR(64);
+      else VLC_LAUNCH_F32_PAIR(128);
+    } else if (n * Hq < kF32OneWavePairs) {
+      if (D == 64) VLC_LAUNCH_F32_TILE(64, 4);
+      else VLC_LAUNCH_F32_TILE(128, 4);
+    } else {
+      if (D == 64) VLC_LAUNCH_F32_TILE(64, 1);
+      else VLC_LAUNCH_F32_TILE(128, 1);
+    }
+#undef VLC_LAUNCH_F32_TILE
+#undef VLC_LAUNCH_F32_PAIR
     VLC_CHECK_LAUNCH("attention_f32");
     return VLC_OK;
   }
