@@ -345,6 +345,8 @@ int vlc_layer_forward(const vlc_layer_shape* shape, const vlc_layer_weights* wei
  *   2 q|k|v projection                    3 RoPE of q,k + scatter of fresh k,v
  *   4 attention of the recomputed rows    5 output projection + residual
  *   6 post-attention RMSNorm              7 gate|up projection + SwiGLU     8 down projection + residual
+ * fp32 layers of few rows and at most 512 columns take stages 1 and 3 inside the kernel of stage 2, and stage 6 inside that of
+ * stage 7: these three are empty.
  * Everything else is identical to vlc_layer_forward.
  */
 #define VLC_LAYER_STAGES 9

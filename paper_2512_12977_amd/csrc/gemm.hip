@@ -6,6 +6,7 @@
 
 #include <type_traits>
 
+#include "rope_device.h"
 #include "vlc_internal.h"
 
 namespace vlc {
@@ -780,6 +781,30 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const float* __restric
   }
 }
 
+// Four consecutive columns n ... n + 3 of row m (v; up: SwiGLU's second factor) through the epilogue.  resid_row: its first element.
+template <int EPI>
+__device__ __forceinline__ void store_f32(f32x4 v, const f32x4& up, int m, int n, int N, const float* __restrict__ bias,
+                                          const float* __restrict__ resid, int64_t resid_row, float* __restrict__ C, int64_t ldc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (EPI == EPI_BIAS) {
+      if (bias && n + e < N) v[e] += bias[n + e];
+    } else if (EPI == EPI_RESIDUAL) {
+      if (n + e < N) v[e] += resid[resid_row + n + e];
+    } else {
+      v[e] = v[e] / (1.0f + expf(-v[e])) * up[e];
+    }
+  }
+  float* c = C + (int64_t)m * ldc + n;
+  if (N % 4 == 0 && ldc % 4 == 0) {        // four columns of a row in one store
+    if (n < N) *reinterpret_cast<f32x4*>(c) = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (n + e < N) c[e] = v[e];
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // f32 kernel: v_mfma_f32_16x16x4_f32 (exact fp32 products and sums) on operands loaded straight into registers
 // ---------------------------------------------------------------------------------------------
@@ -882,36 +907,239 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
       for (int w = 0; w < KW - 1; ++w) acc[t / MT][t % MT] += part[w][t][lane];
   }
 
-  const bool whole = N % 4 == 0 && ldc % 4 == 0;   // four columns of a row in one store
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const int m = m0 + (wm * MT + i) * 16 + l16;
     if (m >= M) continue;
     const int64_t rr = (EPI == EPI_RESIDUAL && rmap) ? (int64_t)rmap[m] : (int64_t)m;
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const int n = n0 + (wn * NT + j) * 16 + 4 * lk;
-      float v[4];
+    for (int j = 0; j < NT; ++j)
+      store_f32<EPI>(acc[j][i], acc[(EPI == EPI_SWIGLU ? NT : 0) + j][i], m, n0 + (wn * NT + j) * 16 + 4 * lk, N, bias, resid, rr * ldr, C, ldc);
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// f32 products that take the RMSNorm of their input rows with them (K <= kF32NormK): one launch instead of two, and with the
+// heads of q|k|v also the rotation and the scatter of the fresh rows
+// ---------------------------------------------------------------------------------------------
+// Bound by latency and launches: a layer of the tiny decoder (61 rows) was eight kernels of 2.5 ... 10 us, it is five.
+// Layout as in gemm_f32_kernel with KW = 4: 16 rows, WT tiles of 16 columns, wavefront kw takes k-steps kw, kw + 4, ...  Its
+// pieces of the rows stay in registers (at most 8 steps of 16), the squares meet in LDS, and every workgroup norms its rows for
+// itself; the first of a row tile also leaves them in y.  The sums are taken in the order of rmsnorm_kernel (a tree over
+// the row's 16-byte pieces, whose number is 16 i + 4 kw + lk here) and the products in the order of gemm_f32_kernel: the same bits as the two kernels.
+// w_norm = nullptr: the rows are normed already.
+constexpr int kF32NormK = 512;
+
+template <int WT>
+__device__ __forceinline__ void normed_sums_f32(const float* __restrict__ x, const int32_t* __restrict__ map,
+                                                const float* __restrict__ w_norm, int K, int M, float inv_h, float eps,
+                                                float* __restrict__ y, int m0, const float* const (&wp)[WT], f32x4 (&acc)[WT]) {
+  constexpr int KW = 4, NS = kF32NormK / 16 / KW, U = WT > 4 ? 2 : 4;   // U: k-steps of W in flight
+  __shared__ float squares[NS / 4][KW][64];
+  const int lane = threadIdx.x & 63, kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, lk = lane >> 4;
+  const int m = min(m0 + l16, M - 1), steps = K / 16;
+  const float* xp = x + (map ? (int64_t)map[m] : (int64_t)m) * K + 4 * lk;
+  f32x4 a[NS], nw[NS], wb[2][U][WT];
+  // a step past the end loads the last one again and is left out of the sums
+#define VLC_STEP(i_) (min(kw + (i_) * KW, steps - 1) * 16)
+#define VLC_NORM_LOAD_W(b_, i0_)                                                                                \
+  _Pragma("unroll") for (int u = 0; u < U; ++u) {                                                               \
+    _Pragma("unroll") for (int j = 0; j < WT; ++j) wb[b_][u][j] = *reinterpret_cast<const f32x4*>(wp[j] + VLC_STEP((i0_) + u)); \
+  }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] = acc[j][i][e];
-        if (EPI == EPI_BIAS) {
-          if (bias && n + e < N) v[e] += bias[n + e];
-        } else if (EPI == EPI_RESIDUAL) {
-          if (n + e < N) v[e] += resid[rr * ldr + n + e];
-        } else {
-          v[e] = v[e] / (1.0f + expf(-v[e])) * acc[(EPI == EPI_SWIGLU ? NT : 0) + j][i][e];
-        }
+  for (int i = 0; i < NS; ++i)
+    if (kw + (i & ~3) * KW < steps) a[i] = *reinterpret_cast<const f32x4*>(xp + VLC_STEP(i));
+  if (w_norm) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+      if (kw + (i & ~3) * KW < steps) nw[i] = *reinterpret_cast<const f32x4*>(w_norm + VLC_STEP(i) + 4 * lk);
+  }
+  VLC_NORM_LOAD_W(0, 0)
+  if (w_norm) {
+#pragma unroll
+    for (int q = 0; q < NS / 4; ++q) {
+      float p[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float ss = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ss += a[4 * q + i][e] * a[4 * q + i][e];
+        p[i] = kw + (4 * q + i) * KW < steps ? ss : 0.f;
       }
-      float* c = C + (int64_t)m * ldc + n;
-      if (whole && n < N) {
-        *reinterpret_cast<float4*>(c) = make_float4(v[0], v[1], v[2], v[3]);
-      } else {
+      squares[q][kw][lane] = (p[0] + p[2]) + (p[1] + p[3]);
+    }
+    __syncthreads();
+    float tot = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (n + e < N) c[e] = v[e];
+    for (int q = 0; q < NS / 4; ++q) {
+      float ss = (squares[q][0][lane] + squares[q][2][lane]) + (squares[q][1][lane] + squares[q][3][lane]);
+      ss += __shfl_xor(ss, 32);
+      ss += __shfl_xor(ss, 16);
+      tot += ss;
+    }
+    const float r = 1.0f / sqrtf(tot * inv_h + eps);
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[i][e] = a[i][e] * r * nw[i][e];
+    if (y && m0 + l16 < M) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+        if (kw + i * KW < steps) *reinterpret_cast<f32x4*>(y + (int64_t)m * K + VLC_STEP(i) + 4 * lk) = a[i];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < WT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i0 = 0; i0 < NS; i0 += U) {
+    if (kw + i0 * KW < steps) {
+      if (i0 + U < NS && kw + (i0 + U) * KW < steps) { VLC_NORM_LOAD_W((i0 / U + 1) & 1, i0 + U) }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (kw + (i0 + u) * KW < steps) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < WT; ++j)
+              acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wb[i0 / U & 1][u][j][e], a[i0 + u][e], acc[j], 0, 0, 0);
+        }
+    }
+  }
+#undef VLC_NORM_LOAD_W
+#undef VLC_STEP
+}
+
+template <int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_normed_kernel(const float* __restrict__ x, const float* __restrict__ w_norm,
+                                                              const float* __restrict__ W, int K, int M, int N, float inv_h,
+                                                              float eps, float* __restrict__ y, float* __restrict__ C,
+                                                              int64_t ldc) {
+  constexpr int WT = EPI == EPI_SWIGLU ? 2 : 1;
+  __shared__ f32x4 part[3][WT][64];
+  const int lane = threadIdx.x & 63, kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, lk = lane >> 4, m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+  const int n = min(n0 + l16, N - 1);
+  const float* wp[WT];
+#pragma unroll
+  for (int j = 0; j < WT; ++j) wp[j] = W + (int64_t)(j ? N + n : n) * K + 4 * lk;
+  f32x4 acc[WT];
+  normed_sums_f32<WT>(x, nullptr, w_norm, K, M, inv_h, eps, blockIdx.x == 0 ? y : nullptr, m0, wp, acc);
+  if (kw > 0) {
+#pragma unroll
+    for (int t = 0; t < WT; ++t) part[kw - 1][t][lane] = acc[t];
+  }
+  __syncthreads();
+  if (kw > 0) return;
+#pragma unroll
+  for (int t = 0; t < WT; ++t)
+#pragma unroll
+    for (int w = 0; w < 3; ++w) acc[t] += part[w][t][lane];
+  const int m = m0 + l16;
+  if (m < M) store_f32<EPI>(acc[0], acc[WT - 1], m, n0 + 4 * lk, N, nullptr, nullptr, 0, C, ldc);
+}
+
+// One head of q|k|v per workgroup: its D columns are D / 16 tiles, of which wavefront j rotates j and j + D / 32 (pairs i, i + D / 2).
+// Sines and cosines are worked out while the first loads are on their way.  As rope_qk_scatter_kernel otherwise; the unrounded
+// projection is left in qkv for the caller.
+template <int D>
+__global__ __launch_bounds__(256) void qkv_rope_f32_kernel(
+    const float* __restrict__ x, const int32_t* __restrict__ map, const float* __restrict__ w_norm, const float* __restrict__ W,
+    int K, int M, float inv_h, float eps, const int32_t* __restrict__ pos, const int32_t* __restrict__ pos3,
+    const int32_t* __restrict__ slot, int Hq, int Hkv, const float* __restrict__ bias, const float* __restrict__ w_qn,
+    const float* __restrict__ w_kn, float* __restrict__ y, float* __restrict__ qkv, float* __restrict__ q_out,
+    float* __restrict__ k_cache, float* __restrict__ v_cache, RopeFreq freq) {
+  constexpr int WT = D / 16, PT = WT / 2;
+  __shared__ f32x4 part[4][WT][64];
+  __shared__ float head_squares[PT][16];
+  const int lane = threadIdx.x & 63, kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, lk = lane >> 4, m0 = blockIdx.y * 16, h = blockIdx.x;
+  const int m = min(m0 + l16, M - 1), c = 16 * kw + 4 * lk;   // first of this lane's four pairs
+  const bool rotates = kw < PT, is_v = h >= Hq + Hkv;
+  const float* wp[WT];
+#pragma unroll
+  for (int j = 0; j < WT; ++j) wp[j] = W + (int64_t)(h * D + 16 * j + l16) * K + 4 * lk;
+  int row_slot = 0;
+  float sn[4], cs[4];
+  if (rotates) {
+    row_slot = slot[m];
+    if (!is_v) {
+      int p[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = pos3 ? pos3[3 * (int64_t)m + freq.axis[c + i]] : pos[m];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rope_sincos<false>(freq.inv_freq[c + i], p[i], &sn[i], &cs[i]);
+    }
+  }
+  f32x4 acc[WT];
+  normed_sums_f32<WT>(x, map, w_norm, K, M, inv_h, eps, h == 0 ? y : nullptr, m0, wp, acc);
+#pragma unroll
+  for (int t = 0; t < WT; ++t) part[kw][t][lane] = acc[t];
+  __syncthreads();
+  f32x4 lo, hi;
+  if (rotates) {
+    lo = part[0][kw][lane];
+    hi = part[0][kw + PT][lane];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {          // in wavefront order
+      lo += part[w][kw][lane];
+      hi += part[w][kw + PT][lane];
+    }
+    if (bias) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        lo[i] += bias[h * D + c + i];
+        hi[i] += bias[h * D + D / 2 + c + i];
       }
     }
+  }
+  const bool ok = rotates && m0 + l16 < M;
+  if (ok) {
+    float* r = qkv + (int64_t)m * ((Hq + 2 * Hkv) * D) + h * D + c;
+    *reinterpret_cast<f32x4*>(r) = lo;
+    *reinterpret_cast<f32x4*>(r + D / 2) = hi;
+  }
+  if (is_v) {                              // the same for the whole workgroup
+    if (ok && row_slot >= 0) {
+      float* d = v_cache + ((int64_t)row_slot * Hkv + h - Hq - Hkv) * D + c;
+      *reinterpret_cast<f32x4*>(d) = lo;
+      *reinterpret_cast<f32x4*>(d + D / 2) = hi;
+    }
+    return;
+  }
+  if (w_qn) {
+    if (rotates) {
+      float ss = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ss += lo[i] * lo[i] + hi[i] * hi[i];
+      ss += __shfl_xor(ss, 16);
+      ss += __shfl_xor(ss, 32);
+      if (lk == 0) head_squares[kw][l16] = ss;
+    }
+    __syncthreads();
+    if (rotates) {
+      float ss = head_squares[0][l16] + head_squares[1][l16];
+      if constexpr (PT == 4) ss += head_squares[2][l16] + head_squares[3][l16];
+      const float rn = 1.0f / sqrtf(ss * (1.0f / (float)D) + eps);
+      const float* wn = (h < Hq ? w_qn : w_kn) + c;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        lo[i] = lo[i] * rn * wn[i];
+        hi[i] = hi[i] * rn * wn[D / 2 + i];
+      }
+    }
+  }
+  if (!ok) return;
+  f32x4 olo, ohi;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    olo[i] = lo[i] * cs[i] - hi[i] * sn[i];
+    ohi[i] = hi[i] * cs[i] + lo[i] * sn[i];
+  }
+  float* d = h < Hq ? q_out + ((int64_t)m * Hq + h) * D + c : k_cache + ((int64_t)row_slot * Hkv + h - Hq) * D + c;
+  if (h < Hq || row_slot >= 0) {           // a negative slot: the row is computed, its k and v are not stored
+    *reinterpret_cast<f32x4*>(d) = olo;
+    *reinterpret_cast<f32x4*>(d + D / 2) = ohi;
   }
 }
 
@@ -1152,6 +1380,10 @@ int dispatch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ld
 // and 161 / 131 us (K = 2048), 128 tiles 41 / 49 and 163 / 244 us (vector instructions: 67 and 407 us); with 2048 tiles
 // 106 against 37 TFLOP/s.
 constexpr int64_t kF32LargeTiles = 96;
+bool f32_large_tiles(int64_t M, int64_t N, int epi) {
+  const int64_t columns = epi == EPI_SWIGLU ? 64 : 128;
+  return (M + 127) / 128 * ((N + columns - 1) / columns) >= kF32LargeTiles;
+}
 
 template <int EPI>
 int launch_f32(const void* A, int64_t lda, const void* W, void* C, int64_t ldc, int64_t M, int64_t N,
@@ -1159,7 +1391,7 @@ int launch_f32(const void* A, int64_t lda, const void* W, void* C, int64_t ldc, 
                hipStream_t st) {
   constexpr int NT = EPI == EPI_SWIGLU ? 2 : 4;
   const int64_t lm = (M + 127) / 128, ln = (N + 32 * NT - 1) / (32 * NT);
-  const bool large = lm * ln >= kF32LargeTiles;
+  const bool large = f32_large_tiles(M, N, EPI);
   const int64_t gy = large ? lm : (M + 15) / 16;
   const dim3 grid((unsigned)(large ? ln : (N + 15) / 16), (unsigned)gy);
 #define VLC_LAUNCH_F32(...)                                                                                        \
@@ -1211,6 +1443,49 @@ int launch_f32_grouped(const void* A, int64_t lda, const int32_t* amap, const vo
 }
 
 }  // namespace
+
+// The products that norm their rows themselves are those on small tiles whose rows fit the registers: on large tiles the
+// norm is read by few workgroups and its launch is a small part.
+bool gemm_f32_norms(int64_t M, int64_t N, int64_t K, int epilogue) {
+  return K % 16 == 0 && K <= kF32NormK && !f32_large_tiles(M, N, epilogue);
+}
+
+int launch_gemm_f32_normed(const void* x, const void* w_norm, const void* W, void* y, void* C, int64_t ldc, int64_t M, int64_t N,
+                           int64_t K, float eps, int epilogue, hipStream_t st) {
+  if (M <= 0 || N <= 0) return VLC_OK;
+  if (!gemm_f32_norms(M, N, K, epilogue) || M > INT32_MAX || N > INT32_MAX / 2)
+    return fail(VLC_ERR_SHAPE, "normed gemm(f32): M=%lld N=%lld K=%lld", (long long)M, (long long)N, (long long)K);
+  const dim3 grid((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16));
+  if (epilogue == EPI_SWIGLU)
+    hipLaunchKernelGGL(gemm_f32_normed_kernel<EPI_SWIGLU>, grid, dim3(256), 0, st, (const float*)x, (const float*)w_norm, (const float*)W,
+                       (int)K, (int)M, (int)N, 1.0f / (float)K, eps, (float*)y, (float*)C, ldc);
+  else if (epilogue == EPI_BIAS)
+    hipLaunchKernelGGL(gemm_f32_normed_kernel<EPI_BIAS>, grid, dim3(256), 0, st, (const float*)x, (const float*)w_norm, (const float*)W,
+                       (int)K, (int)M, (int)N, 1.0f / (float)K, eps, (float*)y, (float*)C, ldc);
+  else
+    return fail(VLC_ERR_SHAPE, "normed gemm(f32): epilogue=%d", epilogue);
+  VLC_CHECK_LAUNCH("gemm_f32_normed");
+  return VLC_OK;
+}
+
+int launch_qkv_rope_f32(const void* x, const int32_t* map, const void* w_norm, const void* W, const void* bias, int64_t M, int64_t K,
+                        float eps, const int32_t* pos, const int32_t* pos3, const int32_t* slot, int Hq, int Hkv, int D,
+                        const RopeFreq& f, const void* w_qnorm, const void* w_knorm, void* y, float* qkv32, void* q_out, void* k_cache,
+                        void* v_cache, hipStream_t st) {
+  if (M <= 0) return VLC_OK;
+  if (!gemm_f32_norms(M, (int64_t)(Hq + 2 * Hkv) * D, K, EPI_BIAS) || M > INT32_MAX || (D != 64 && D != 128))
+    return fail(VLC_ERR_SHAPE, "q|k|v + rope(f32): M=%lld K=%lld D=%d", (long long)M, (long long)K, D);
+  const dim3 grid((unsigned)(Hq + 2 * Hkv), (unsigned)((M + 15) / 16));
+#define VLC_LAUNCH_QKV(D_)                                                                                            \
+  hipLaunchKernelGGL(qkv_rope_f32_kernel<D_>, grid, dim3(256), 0, st, (const float*)x, map, (const float*)w_norm, (const float*)W, \
+                     (int)K, (int)M, 1.0f / (float)K, eps, pos, pos3, slot, Hq, Hkv, (const float*)bias, (const float*)w_qnorm, \
+                     (const float*)w_knorm, (float*)y, qkv32, (float*)q_out, (float*)k_cache, (float*)v_cache, f)
+  if (D == 64) VLC_LAUNCH_QKV(64);
+  else VLC_LAUNCH_QKV(128);
+#undef VLC_LAUNCH_QKV
+  VLC_CHECK_LAUNCH("qkv_rope_f32");
+  return VLC_OK;
+}
 
 // Float scratch of the split k ranges and of the split tiles of a last round: choose_tile and launch_bf16 split only
 // what fits.  64 MB is one float block per resident workgroup at 256 x 256; of 320 x 256 it holds 204 blocks, which caps the k

@@ -177,23 +177,32 @@ static int layer_forward_impl(const vlc_layer_shape* shape, const vlc_layer_weig
   // x = h_in[map] is never materialised: the norm reads through the map, and so does the residual.
   // (a chained call finds the normed rows in the workspace: the layer above wrote them with its last kernel)
   VLC_MARK(1);
-  if (!xn_ready) {
+  const bool f32_qkv = s.dtype == VLC_F32 && vlc::gemm_f32_norms(n, nqkv, H, vlc::EPI_BIAS);
+  if (!xn_ready && !f32_qkv) {
     rc = vlc::launch_rmsnorm(h_in, p->map, w->w_ln1, xn, n, s.H, s.eps, s.dtype, st);
     if (rc) return rc;
   }
   VLC_MARK(2);
-  int qkv_splits = 0;   // > 0: the projection is still split-K partials, summed by the next kernel
-  rc = vlc::launch_gemm(xn, H, w->w_qkv, qkv32, nqkv, n, nqkv, H, vlc::EPI_BIAS_F32, w->b_qkv, nullptr, 0,
-                        nullptr, s.dtype, skw, ws.splitk_bytes, st, &qkv_splits);
-  if (rc) return rc;
-  // RoPE at the new positions; fresh k, v overwrite their slots (after the reused tokens were placed).
-  VLC_MARK(3);
-  const vlc::AttentionShares shares =
-      vlc::attention_shares(n, s.Hq, s.Hkv, p->kv_rows, p->row_kv_len, ws.att_bytes ? base + ws.att : nullptr, ws.att_bytes);
-  rc = vlc::launch_rope_qk_scatter(qkv32, p->pos, p->slot, n, s.Hq, s.Hkv, s.D, freq, qrot, k_cache, v_cache,
-                                   s.dtype, st, static_cast<const float*>(skw), qkv_splits > 0 ? qkv_splits : 1,
-                                   w->b_qkv, mrope ? p->pos3 : nullptr, w->w_qnorm, w->w_knorm, s.eps, &shares);
-  if (rc) return rc;
+  vlc::AttentionShares shares = {};
+  if (f32_qkv) {   // small fp32 layers: norm, projection, rotation and scatter in one kernel
+    rc = vlc::launch_qkv_rope_f32(xn_ready ? xn : h_in, xn_ready ? nullptr : p->map, xn_ready ? nullptr : w->w_ln1, w->w_qkv, w->b_qkv,
+                                  n, H, s.eps, p->pos, mrope ? p->pos3 : nullptr, p->slot, s.Hq, s.Hkv, s.D, freq, w->w_qnorm,
+                                  w->w_knorm, xn_ready ? nullptr : xn, qkv32, qrot, k_cache, v_cache, st);
+    if (rc) return rc;
+    VLC_MARK(3);
+  } else {
+    int qkv_splits = 0;   // > 0: the projection is still split-K partials, summed by the next kernel
+    rc = vlc::launch_gemm(xn, H, w->w_qkv, qkv32, nqkv, n, nqkv, H, vlc::EPI_BIAS_F32, w->b_qkv, nullptr, 0,
+                          nullptr, s.dtype, skw, ws.splitk_bytes, st, &qkv_splits);
+    if (rc) return rc;
+    // RoPE at the new positions; fresh k, v overwrite their slots (after the reused tokens were placed).
+    VLC_MARK(3);
+    shares = vlc::attention_shares(n, s.Hq, s.Hkv, p->kv_rows, p->row_kv_len, ws.att_bytes ? base + ws.att : nullptr, ws.att_bytes);
+    rc = vlc::launch_rope_qk_scatter(qkv32, p->pos, p->slot, n, s.Hq, s.Hkv, s.D, freq, qrot, k_cache, v_cache,
+                                     s.dtype, st, static_cast<const float*>(skw), qkv_splits > 0 ? qkv_splits : 1,
+                                     w->b_qkv, mrope ? p->pos3 : nullptr, w->w_qnorm, w->w_knorm, s.eps, &shares);
+    if (rc) return rc;
+  }
   VLC_MARK(4);
   rc = vlc::launch_attention(qrot, hqd, k_cache, v_cache, p->row_kv_start, p->row_kv_len, n, s.Hq, s.Hkv, s.D,
                              1.0f / sqrtf((float)s.D), attn, s.dtype, &shares, st);
@@ -204,7 +213,12 @@ static int layer_forward_impl(const vlc_layer_shape* shape, const vlc_layer_weig
                         s.dtype, skw, ws.splitk_bytes, st, &o_splits);
   if (rc) return rc;
   VLC_MARK(6);
-  if (o_splits > 0)   // split-K partials: sum + residual -> h1 and the norm of h1 in one kernel
+  // small fp32 layers: the norm goes with the product that reads it (router or gate|up)
+  const bool f32_n2 = s.dtype == VLC_F32 && vlc::gemm_f32_norms(n, s.n_experts > 0 ? s.n_experts : I, H,
+                                                                s.n_experts > 0 ? vlc::EPI_BIAS : vlc::EPI_SWIGLU);
+  if (f32_n2)
+    rc = VLC_OK;
+  else if (o_splits > 0)   // split-K partials: sum + residual -> h1 and the norm of h1 in one kernel
     rc = vlc::launch_sum_residual_rmsnorm(static_cast<const float*>(skw), o_splits, h_in, p->map, w->w_ln2, h1,
                                           n2, n, s.H, s.eps, st);
   else
@@ -229,7 +243,10 @@ static int layer_forward_impl(const vlc_layer_shape* shape, const vlc_layer_weig
     void* y = base + ws.moe_y;
     const int tile_rows = vlc::gemm_group_tile_rows(pairs, E, s.dtype);
     int r_splits = 0;    // > 0: the scores are still split-K partials, summed by the choice kernel
-    rc = vlc::launch_gemm(n2, H, w->w_router, logits, E, n, E, H,
+    if (f32_n2)
+      rc = vlc::launch_gemm_f32_normed(h1, w->w_ln2, w->w_router, n2, logits, E, n, E, H, s.eps, vlc::EPI_BIAS, st);
+    else
+      rc = vlc::launch_gemm(n2, H, w->w_router, logits, E, n, E, H,
                           s.dtype == VLC_BF16 ? vlc::EPI_BIAS_F32 : vlc::EPI_BIAS, nullptr, nullptr, 0, nullptr,
                           s.dtype, skw, ws.splitk_bytes, st, &r_splits);
     if (rc) return rc;
@@ -252,8 +269,11 @@ static int layer_forward_impl(const vlc_layer_shape* shape, const vlc_layer_weig
     VLC_MARK(9);
     return VLC_OK;
   }
-  rc = vlc::launch_gemm(n2, H, w->w_gate_up, act, I, n, I, H, vlc::EPI_SWIGLU, nullptr, nullptr, 0, nullptr,
-                        s.dtype, skw, ws.splitk_bytes, st);
+  if (f32_n2)
+    rc = vlc::launch_gemm_f32_normed(h1, w->w_ln2, w->w_gate_up, n2, act, I, n, I, H, s.eps, vlc::EPI_SWIGLU, st);
+  else
+    rc = vlc::launch_gemm(n2, H, w->w_gate_up, act, I, n, I, H, vlc::EPI_SWIGLU, nullptr, nullptr, 0, nullptr,
+                          s.dtype, skw, ws.splitk_bytes, st);
   if (rc) return rc;
   VLC_MARK(8);
   // Chained: the input norm of the layer below is taken here, where the rows of h_out are at hand - with a

@@ -133,6 +133,18 @@ int launch_gemm(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
                 int* deferred = nullptr);
 int64_t gemm_splitk_ws_bytes(int64_t n_rows, int64_t max_n);
 
+// f32: C = epilogue(RMSNorm(x) * w_norm * W^T) in one kernel for the sizes that gemm_f32_norms names; the normed rows are left in y
+// [M, K] as launch_rmsnorm leaves them.  Epilogues: EPI_BIAS without a bias, EPI_SWIGLU.
+bool gemm_f32_norms(int64_t M, int64_t N, int64_t K, int epilogue);
+int launch_gemm_f32_normed(const void* x, const void* w_norm, const void* W, void* y, void* C, int64_t ldc, int64_t M, int64_t N,
+                           int64_t K, float eps, int epilogue, hipStream_t st);
+// f32: launch_rmsnorm (through map, into y; skipped with w_norm = nullptr, x then holds the normed rows), the q|k|v product
+// (into qkv32) and launch_rope_qk_scatter in one kernel, for the sizes that gemm_f32_norms(M, (Hq + 2 Hkv) D, K, EPI_BIAS) names.
+int launch_qkv_rope_f32(const void* x, const int32_t* map, const void* w_norm, const void* W, const void* bias, int64_t M, int64_t K,
+                        float eps, const int32_t* pos, const int32_t* pos3, const int32_t* slot, int Hq, int Hkv, int D,
+                        const RopeFreq& f, const void* w_qnorm, const void* w_knorm, void* y, float* qkv32, void* q_out, void* k_cache,
+                        void* v_cache, hipStream_t st);
+
 // Grouped GEMM (mixture-of-experts): C[m, :] = epilogue(A[amap ? amap[m] : m, :] * W[g]^T) for the rows m
 // of group g; the rows of a group are contiguous in C.  `tiles` (device) lists (group, first row, end row)
 // with at most tile_rows rows each, *n_tiles (device) says how many entries count; both are written by

@@ -173,6 +173,8 @@ def run_layers(shape_rec, weights: Sequence[DeviceWeights], plans: DevicePlans, 
     (chain=False: every layer norms its own input).  h0 [n_in, H] is the first layer's input, hbuf two
     [n_max, H] buffers the layers alternate between; events: per-layer stage-event arrays or None.
     Returns the buffer that holds the last layer's output rows."""
+    # fp32 layers of up to 512 columns norm their rows inside the product that reads them: a norm handed on would be a launch more
+    chain = chain and not (shape_rec.dtype == B.VLC_F32 and shape_rec.H <= 512)
     h_in, ready = h0, False
     for l in range(plans.L):
         h_out = hbuf[l & 1]

@@ -1,0 +1,41 @@
+"""The fp32 kernels of small layers: products that norm their rows themselves, and q|k|v with rotation and scatter in the same
+kernel, at the edges of their tiles and of their range."""
+import numpy as np
+import pytest
+import torch
+
+import vlc_synth as syn
+import paper_2512_12977_amd as vlc
+from paper_2512_12977_amd import runner as R
+from test_gpu_layer import check_against_oracle
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+# columns of one and of several 64-wide groups of k-steps, the last width whose rows stay in registers and one beyond
+@pytest.mark.parametrize("H,Hq,Hkv,D,bias,norm", [(64, 2, 1, 64, True, False), (192, 3, 3, 64, False, True), (320, 4, 2, 128, True, False),
+                                                   (512, 4, 1, 128, False, True), (512, 6, 2, 64, True, False), (576, 4, 2, 64, True, True)])
+@pytest.mark.parametrize("n_text", [1, 16, 33])
+def test_small_layers_around_the_tiles(H, Hq, Hkv, D, bias, norm, n_text):
+    """Two layers against the oracle at the element-wise fp32 tolerance; the chained calls, which find the normed rows in the
+    workspace and run the products without their norm, give the same bits."""
+    sh = syn.Shape("small", L=2, H=H, Hq=Hq, Hkv=Hkv, D=D, I=128, rope_base=1e4, dtype="f32", qkv_bias=bias, qk_norm=norm)
+    req = syn.Request([syn.Segment(0, n_text, False), syn.Segment(n_text, 40, True, 5, 0), syn.Segment(n_text + 40, 3, False)], 0)
+    wl = syn.Workload("small", sh, [req], 40, "static", static_k=50, seed=H + n_text)
+    check_against_oracle(wl, layers=2, teacher_forced=False, shift_ahead=True)
+    check_against_oracle(wl, layers=2, teacher_forced=False, shift_ahead=True, chain=True)
+
+    rec, plans = R.make_shape(sh), R.DevicePlans([req], 2, k=np.full(2, 50, dtype=np.int32))
+    W = [R.DeviceWeights(syn.layer_weights(sh, 1, l), torch.float32) for l in range(2)]
+    n, S = plans.n_rows[0], plans.total_slots
+    h_in, ws = torch.randn((S, H), device=DEV), R.Workspace(rec, n)
+    records, outs = [plans.record(0, S, S), plans.record(1, n, S)], []
+    for chain in (False, True):
+        kc, vc = [torch.zeros((S, Hkv, D), device=DEV) for _ in range(2)], [torch.zeros((S, Hkv, D), device=DEV) for _ in range(2)]
+        h1, h2 = torch.empty((n, H), device=DEV), torch.empty((n, H), device=DEV)
+        vlc.vlc_layer_forward_chained(rec, W[0].rec, records[0], h_in, h1, kc[0], vc[0], ws.t, False, W[1].t["w_ln1"] if chain else None)
+        vlc.vlc_layer_forward_chained(rec, W[1].rec, records[1], h1, h2, kc[1], vc[1], ws.t, chain)
+        outs.append([h1, h2] + kc + vc)
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
