@@ -1498,20 +1498,25 @@ int64_t gemm_splitk_ws_bytes(int64_t n_rows, int64_t max_n) {
 // Rows per tile of the grouped GEMMs, from the mean number of rows per group.  Few rows per group: every
 // matrix is streamed from HBM exactly once and nothing is reused, so the tile is small (64 x 128, below 9 rows per
 // group 32 x 128) and the ring three (four) stages deep - with two workgroups per CU that keeps 64 (96) KB of matrix data
-// in flight per CU, what the HBM latency needs; a two-stage ring of 128 x 128 tiles stalls at half of that.  More rows: the tile that
-// pads an expert's rows least at a k-loop that is still fast.  Lines by the mean alone, set with an even load before the workgroups of 192
-// and 256 rows stayed; gate|up + down of one layer of 128 experts (2048 x 768) with the present kernels, loads that differ by 15 %, us:
-//   rows per expert    6    10    37    56    80    94   120   160   200   281   360   444  1184
-//   32               208   213   262   299   350
-//   64               207   213   233   265   306   324   356   412   494   616
-//   128                          234   247   255   281   298   378   415   505   587   684  1628   (gate|up on 128 x 256)
-//   192                          247   257   267   272   280   321   391   488   537   637  1450
-//   256                          273   278   290   293   301   312   363   503   566   609  1437   (4 wavefronts of 128 x 128)
-// By these 192 rows would pay from some 90 on and 256 between 160 and 240 (at 281 the padding takes it back).
+// in flight per CU, what the HBM latency needs; a two-stage ring of 128 x 128 tiles stalls at half of that.  More rows: an expert's
+// rows cost their tiles, so the lines lie where most experts begin to need one tile more (192 rows per tile hold an expert of up to 190
+// or so on average, 256 one of up to 250, and then two of 192 do better than two of 256).  Two layers of 128 experts (2048 x 768), a
+// random router's loads, us of both layers with every tile, the chosen one in brackets:
+//   rows per expert    9     37     56     81    106    138    175    219    269    325    394    469    562
+//   32              (579)
+//   64               581   (703)   793    944   1060
+//   128                     706  (767)  (847)   983   1157   1217   1387   1682   1886   2185   2508   2909
+//   192                     763    830    910  (970) (1019) (1178)  1481 (1586) (1750)  2110   2372   2734
+//   256                     816    857    963   1045   1061   1195 (1340)  1697   1885 (2030) (2288) (2819)
+// (Lines at 56, 140 and 320, for 128, 192 and 256 rows: 3 % slower than the best on average, 13 % at 138; these 0.3 %, 3 % at 562.)
 int gemm_group_tile_rows(int64_t rows, int n_groups, int dtype) {
   if (dtype != VLC_BF16) return 64;
   const int64_t mean = rows / (n_groups > 0 ? n_groups : 1);
-  return mean >= 320 ? 256 : (mean >= 140 ? 192 : (mean >= 56 ? 128 : (mean >= 9 ? 64 : 32)));
+  if (mean < 56) return mean < 9 ? 32 : 64;
+  if (mean < 100) return 128;
+  if (mean < 185) return 192;
+  if (mean < 250) return 256;
+  return mean < 360 ? 192 : 256;
 }
 
 int launch_gemm_grouped(const void* A, int64_t lda, const int32_t* amap, const void* W, int64_t w_stride, void* C,

@@ -29,12 +29,24 @@ def test_products_of_many_rounds(product, split, layer):
 @pytest.mark.parametrize("rows,H,I,product", [(2600, 3328, 64, "down"), (2600, 3264, 192, "down"), (1800, 128, 2432, "gate_up"), (900, 192, 3392, "gate_up")])
 def test_experts_of_many_tiles(rows, H, I, product):
     """2 of 8 experts; more tiles than the 256 workgroups that stay, however the router loads the experts, in the down projection (one and three
-    k-tiles), then in gate|up, whose rows are fetched through the pair list (two and three k-tiles); tiles of 256 rows, in the last case of 192."""
+    k-tiles), then in gate|up, whose rows are fetched through the pair list (two and three k-tiles); tiles of 256 rows."""
     sh = syn.Shape("moe_stay", L=1, H=H, Hq=4, Hkv=2, D=128, I=I, rope_base=1e4, dtype="bf16", qkv_bias=False, qk_norm=True,
                    mrope_section=(24, 20, 20), n_experts=8, top_k=2, text_scale=1.0, residual_proj_scale=0.01)
     req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
     g = check_moe_layer(syn.Workload("moe_stay%d_%d" % (rows, I), sh, [req], 1, "static", static_k=0, seed=1200 + I), 0)
-    tile_rows = 256 if 2 * rows // 8 >= 320 else 192        # the launcher's lines: from 320 and from 140 rows per expert on average
+    tile_rows = 256 if 2 * rows // 8 >= 320 else 192        # at most as many rows as the launcher's tiles have
     assert 2 * rows // 8 >= 140
     row_tiles = sum(-(-int(pairs) // tile_rows) for pairs in np.diff(g["moe_offset"]))
     assert row_tiles * -(-(2 * I if product == "gate_up" else H) // 256) > 256, (row_tiles, tile_rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,H,I", [(600, 192, 4352), (400, 128, 5632)])
+def test_experts_of_many_tiles_of_192_rows(rows, H, I):
+    """The same on tiles of 192 rows (100 to 184 rows per expert on average): gate|up of at least eight row tiles, three and two k-tiles."""
+    assert 100 <= 2 * rows // 8 < 185 and 8 * -(-2 * I // 256) > 256
+    sh = syn.Shape("moe_192", L=1, H=H, Hq=4, Hkv=2, D=128, I=I, rope_base=1e4, dtype="bf16", qkv_bias=False, qk_norm=True,
+                   mrope_section=(24, 20, 20), n_experts=8, top_k=2, text_scale=1.0, residual_proj_scale=0.01)
+    req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
+    g = check_moe_layer(syn.Workload("moe_192_%d" % rows, sh, [req], 1, "static", static_k=0, seed=1300 + I), 0)
+    assert np.all(np.diff(g["moe_offset"]) > 0)             # every expert has a row tile

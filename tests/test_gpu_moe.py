@@ -159,7 +159,7 @@ def test_moe_many_pairs_grouped_by_many_workgroups():
 @pytest.mark.parametrize("rows", [250, 420, 700])
 def test_moe_mid_sized_groups_on_128_row_tiles(rows):
     """62, 105 and 175 rows per expert on average (8 experts, 2 per token): the grouped GEMMs run on tiles of 128 rows
-    (56 to 139 rows per expert) and of 192, with groups of one and of two row tiles, the last ragged."""
+    and, from 100 rows per expert on, of 192, with groups of one and of two row tiles, the last ragged."""
     sh = syn.SHAPES["tiny_moe_bf16"]
     req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
     wl = syn.Workload("moe_mid_%d" % rows, sh, [req], 1, "static", static_k=0, seed=18)
@@ -169,8 +169,7 @@ def test_moe_mid_sized_groups_on_128_row_tiles(rows):
 
 @pytest.mark.parametrize("rows", [35, 36, 1279, 1280, 3072, 3073, 7171])
 def test_moe_lines_of_the_row_tiles_and_of_the_grouping(rows):
-    """Both sides of the lines at 9 and 320 rows per expert (8 experts, 2 per token; the lines at 56 and 140 lie between
-    the rows above), and of the line from which slices of the pairs are grouped by workgroups of their own: 6144
+    """Both sides of the line at 9 rows per expert (8 experts, 2 per token), more than any line (320), and both sides of the line from which slices of the pairs are grouped by workgroups of their own: 6144
     pairs (one workgroup), 6146 (6 slices of 1025, the last of 1021) and 14342 (14 slices).  Requests of at most 128 rows."""
     sh = syn.SHAPES["tiny_moe_bf16"]
     sizes = [min(128, rows - s) for s in range(0, rows, 128)]
@@ -269,6 +268,12 @@ def test_moe_rows_per_expert_around_the_tile_sizes(rows):
                    qk_norm=True, mrope_section=(24, 20, 20), n_experts=8, top_k=2, text_scale=1.0, residual_proj_scale=0.01)
     req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
     check_moe_layer(syn.Workload("moe_tiles%d" % rows, sh, [req], 1, "static", static_k=0, seed=700 + rows), 0)
+
+
+@pytest.mark.parametrize("rows", [396, 400, 736, 740, 996, 1000, 1436, 1440])
+def test_moe_rows_per_expert_around_the_upper_lines(rows):
+    """Mean rows per expert just below and at the lines at 100, 185, 250 and 360 (tiles of 128, 192, 256, 192 and 256 rows)."""
+    test_moe_rows_per_expert_around_the_tile_sizes(rows)
 
 
 @pytest.mark.parametrize("H,I", [(64, 64), (128, 320), (576, 128)])
