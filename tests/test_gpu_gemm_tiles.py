@@ -46,6 +46,13 @@ LAYERS += [(64, 18752, 3, 3, 983), (1344, 6848, 9, 3, 4705), (1088, 22016, 6, 3,
            (3264, 8320, 2, 1, 961)]
 # q|k|v of one k-tile in many rounds
 LAYERS += [(64, 192, 40, 8, 12001)]
+# 96 x 96, 96 x 128, 160 x 128 and 224 x 256, and the choices that came with them; sums of up to 24704 products
+LAYERS += [
+    (512, 384, 2, 1, 5470), (128, 832, 21, 3, 8714), (64, 1344, 16, 8, 15745), (9216, 64, 2, 1, 5273),
+    (8192, 192, 64, 8, 454), (4992, 8512, 24, 3, 772), (64, 24704, 1, 1, 802), (6144, 1216, 4, 2, 6859),
+    (8192, 320, 16, 8, 513), (7040, 576, 40, 8, 3050), (3648, 22144, 24, 3, 1129), (8640, 128, 56, 8, 512),
+    (2880, 192, 32, 8, 10945), (1216, 20800, 5, 1, 1594), (1856, 22016, 16, 2, 1040), (7104, 256, 21, 3, 9397),
+    (1984, 64, 32, 4, 10637), (8192, 12544, 3, 3, 1123)]
 # (requests, vocabulary, hidden size) of heads, on the tile that only they use
 HEADS = [(100, 151936, 64), (65, 151936, 192), (8, 152064, 3584), (127, 152060, 320)]
 
