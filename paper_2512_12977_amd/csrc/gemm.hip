@@ -930,10 +930,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 // w_norm = nullptr: the rows are normed already.
 constexpr int kF32NormK = 512;
 
-template <int WT>
+// meanwhile(): what the caller has to do while the first loads are on their way.
+template <int WT, typename F>
 __device__ __forceinline__ void normed_sums_f32(const float* __restrict__ x, const int32_t* __restrict__ map,
                                                 const float* __restrict__ w_norm, int K, int M, float inv_h, float eps,
-                                                float* __restrict__ y, int m0, const float* const (&wp)[WT], f32x4 (&acc)[WT]) {
+                                                float* __restrict__ y, int m0, const float* const (&wp)[WT], f32x4 (&acc)[WT], F meanwhile) {
   constexpr int KW = 4, NS = kF32NormK / 16 / KW, U = WT > 4 ? 2 : 4;   // U: k-steps of W in flight
   __shared__ float squares[NS / 4][KW][64];
   const int lane = threadIdx.x & 63, kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -956,6 +957,8 @@ __device__ __forceinline__ void normed_sums_f32(const float* __restrict__ x, con
       if (kw + (i & ~3) * KW < steps) nw[i] = *reinterpret_cast<const f32x4*>(w_norm + VLC_STEP(i) + 4 * lk);
   }
   VLC_NORM_LOAD_W(0, 0)
+  __builtin_amdgcn_sched_barrier(0);
+  meanwhile();
   if (w_norm) {
 #pragma unroll
     for (int q = 0; q < NS / 4; ++q) {
@@ -1024,7 +1027,7 @@ __global__ __launch_bounds__(256) void gemm_f32_normed_kernel(const float* __res
 #pragma unroll
   for (int j = 0; j < WT; ++j) wp[j] = W + (int64_t)(j ? N + n : n) * K + 4 * lk;
   f32x4 acc[WT];
-  normed_sums_f32<WT>(x, nullptr, w_norm, K, M, inv_h, eps, blockIdx.x == 0 ? y : nullptr, m0, wp, acc);
+  normed_sums_f32<WT>(x, nullptr, w_norm, K, M, inv_h, eps, blockIdx.x == 0 ? y : nullptr, m0, wp, acc, [] {});
   if (kw > 0) {
 #pragma unroll
     for (int t = 0; t < WT; ++t) part[kw - 1][t][lane] = acc[t];
@@ -1059,20 +1062,24 @@ __global__ __launch_bounds__(256) void qkv_rope_f32_kernel(
   const float* wp[WT];
 #pragma unroll
   for (int j = 0; j < WT; ++j) wp[j] = W + (int64_t)(h * D + 16 * j + l16) * K + 4 * lk;
-  int row_slot = 0;
-  float sn[4], cs[4];
-  if (rotates) {
-    row_slot = slot[m];
-    if (!is_v) {
-      int p[4];
+  const int row_slot = slot[m];
+  int p[4] = {0, 0, 0, 0};
+  double f[4] = {0.0, 0.0, 0.0, 0.0};
+  if (rotates && !is_v) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) p[i] = pos3 ? pos3[3 * (int64_t)m + freq.axis[c + i]] : pos[m];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) rope_sincos<false>(freq.inv_freq[c + i], p[i], &sn[i], &cs[i]);
+    for (int i = 0; i < 4; ++i) {
+      f[i] = freq.inv_freq[c + i];
+      p[i] = pos3 ? pos3[3 * (int64_t)m + freq.axis[c + i]] : pos[m];
     }
   }
+  float sn[4], cs[4];
   f32x4 acc[WT];
-  normed_sums_f32<WT>(x, map, w_norm, K, M, inv_h, eps, h == 0 ? y : nullptr, m0, wp, acc);
+  normed_sums_f32<WT>(x, map, w_norm, K, M, inv_h, eps, h == 0 ? y : nullptr, m0, wp, acc, [&] {
+    if (rotates && !is_v) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) rope_sincos<false>(f[i], p[i], &sn[i], &cs[i]);
+    }
+  });
 #pragma unroll
   for (int t = 0; t < WT; ++t) part[kw][t][lane] = acc[t];
   __syncthreads();
