@@ -1212,52 +1212,45 @@ int launch_bf16(const void* A, int64_t lda, const void* W, void* C, int64_t ldc,
 // than a small k-tile); above 426 rows + columns two stages, with the later wait (TWO above).  With 16-wide MFMA tiles a
 // wavefront's rows and columns are any multiples of 16: 320 x 160 (7B gate|up at 596 rows, 474 tiles = 1.85 rounds: 134 us; 128 x 192
 // two per CU 150, 320 x 192 152), 224 x 192 (8B gate|up at 446 rows 75, best of the others 79), 128 x 96 (8B gate|up at
-// 97 rows, 256 tiles: 47 against 53), 256 x 192 (8B gate|up at 450 ... 510 rows, one round: 76 against 89), 160 x 160, 160 x 192, 320 x 256
-// (7B down at 5824 rows 599 against 630), 96 x 128 (7B O at 596 rows 26.7 against 28.8), 224 x 256.
+// 97 rows, 256 tiles: 47 against 53), 256 x 192, 160 x 160, 160 x 192, 320 x 256 (7B down at 5824 rows 599 against 630).
 //
 // Per configuration: time of one k-tile (us) with few workgroups on the chip, with one full round of them and with many
-// rounds (power).  All numbers of the model were fitted together, so that its choice is as little slower as possible than the best
-// configuration: to the times of 6000 products of 8 ... 24000 rows in five decoder shapes, each with up to 40 configurations
-// and together with the kernel behind it (RoPE, sum or norm), cold weights, from 3000 rows on 30 ms per configuration; the heads
-// keep the choices they had.  700 products left out of the fit are 0.9 % slower than the best on average, 90 of them more than 3 %; with the
-// prices before, fitted to kernels that ended later and did not stay, and without 96 x 96, 96 x 128, 160 x 128 and 224 x 256, 2.4 % and 213.
-// Most was gained between 60 and 1500 rows: 7B q|k|v at 313 rows 31.7 -> 26.0 us (128 x 128 in two k ranges for 64 x 128), O at 444 31.1 -> 25.6
-// (160 x 128 in three), 8B gate|up at 131 61 -> 51.3 (160 x 128 for 192 x 192); within a pass at the card's power limit (18944 rows) nothing.
-// These are numbers of a fit and no measured times (192 x 128 is priced lower over many rounds than in one), and they miss here and there:
-// q|k|v of the 8B at 320 rows takes 35.1 us where 30.0 are possible, of the 7B at 416 30.5 and 27.4.
-// 256 x 256 stands with eight wavefronts, two per SIMD, too: from four rounds on they are level with four by themselves, and among the
-// power-bound launches of a layer eight are the better (7B at 18944 rows, O and down on four: a pass of two layers 0.7 % longer, on eight 0.3 %, both
-// within what cards and runs differ by).
+// rounds (power).  All numbers of the model were fitted together, to the times of 700 products of 2 ... 24000 rows in
+// five decoder shapes and of heads, with every tile, every number of k ranges and both ends of a last round (27000 times, cold
+// weights), so that its choice is as little slower as possible than the best of them: 0.5 % on average, 36 products more
+// than 3 % (left out of the fit, the fifth shape is at 1.2 %).  That was with the kernels of that time: 534 products of 8 ... 24000 rows timed
+// with the present ones, which end sooner (residuals and float outputs above all) and may stay, are 2.0 % slower than the best of the 14
+// cheapest on average, 111 of them more than 3 %: q|k|v of K = 2048 at 60 ... 110 rows takes one k range where three to five are 20 ... 45 %
+// faster, residuals and q|k|v from 6000 rows on 256 x 256 on eight wavefronts where 320 x 256 or 320 x 192 is 6 ... 8 % faster.  A list without one of the tiles costs 0.1 ... 1.3 % more.
+// These are numbers of a fit and no measured times (192 x 128 is priced lower over many rounds than in one), and they miss: at
+// 8192 columns and K = 29568, 320 x 256 takes 8469 us where 256 x 256 is chosen with 8833 (24000 rows), 12655 against 13745 (36000).
 // USE: 0 all epilogues, 1 all but SwiGLU (an odd number of column tiles per wavefront, or never the fastest there), 3 float
-// output without scratch (the heads; in the layers never the fastest), 4 and 5 as 0 and 1 but with scratch only (not tried for the heads).
+// output without scratch (the heads; in the layers never the fastest).  256 x 256 on 8 wavefronts of
+// 64 x 128 over many rounds, on 4 of 128 x 128 over few.
 // STAY: the products whose workgroups can stay, 0 none, 1 SwiGLU, 2 residuals too.
 //     BM   BN  WGM WGN STAGES OCC USE STAY light  full  many
 #define VLC_GEMM_TILES(X)                             \
-  X(64, 128, 2, 2, 4, 1, 0, 0, 0.358f, 0.359f, 0.439f)   \
-  X(96, 96, 2, 2, 5, 1, 5, 0, 0.348f, 0.438f, 0.330f)    \
-  X(128, 96, 4, 1, 5, 1, 0, 0, 0.458f, 0.431f, 0.425f)   \
-  X(96, 128, 2, 2, 4, 1, 4, 0, 0.400f, 0.499f, 0.447f)   \
-  X(128, 128, 2, 2, 4, 1, 0, 0, 0.398f, 0.515f, 0.640f)  \
-  X(128, 160, 4, 1, 4, 1, 0, 0, 0.411f, 0.642f, 0.750f)  \
-  X(160, 128, 2, 2, 4, 1, 4, 0, 0.670f, 0.613f, 0.694f)  \
-  X(192, 128, 2, 2, 4, 1, 1, 0, 0.632f, 0.630f, 0.536f)  \
-  X(160, 160, 2, 2, 4, 1, 1, 0, 0.508f, 0.686f, 0.728f)  \
-  X(160, 192, 2, 2, 3, 1, 0, 0, 0.735f, 0.750f, 0.884f)  \
-  X(128, 256, 2, 2, 3, 1, 0, 0, 0.580f, 0.837f, 1.112f)  \
-  X(192, 192, 2, 2, 3, 1, 0, 0, 0.761f, 0.824f, 0.885f)  \
-  X(160, 256, 2, 2, 3, 1, 0, 1, 0.752f, 0.919f, 0.919f)  \
-  X(224, 192, 2, 2, 3, 1, 0, 1, 0.617f, 0.941f, 0.944f)  \
-  X(192, 256, 2, 2, 2, 1, 0, 1, 0.723f, 0.994f, 1.019f)  \
-  X(256, 192, 2, 2, 2, 1, 0, 0, 0.714f, 0.977f, 1.148f)  \
-  X(320, 160, 4, 1, 2, 1, 0, 2, 0.564f, 1.053f, 1.013f)  \
-  X(224, 256, 2, 2, 2, 1, 4, 1, 0.743f, 1.113f, 1.173f)  \
-  X(320, 192, 2, 2, 2, 1, 0, 2, 1.164f, 1.172f, 1.163f)  \
-  X(256, 256, 2, 2, 2, 1, 0, 1, 0.772f, 1.252f, 1.246f)  \
-  X(256, 256, 4, 2, 2, 1, 1, 0, 0.872f, 1.402f, 1.236f)  \
-  X(320, 256, 2, 2, 2, 1, 1, 0, 1.028f, 1.430f, 1.486f)  \
-  X(128, 160, 4, 1, 2, 2, 3, 0, 0.785f, 0.754f, 1.084f)
+  X(64, 128, 2, 2, 4, 1, 0, 0, 0.247f, 0.375f, 0.378f)     \
+  X(128, 96, 4, 1, 5, 1, 0, 0, 0.338f, 0.422f, 0.422f)     \
+  X(128, 128, 2, 2, 4, 1, 0, 0, 0.477f, 0.522f, 0.652f)    \
+  X(128, 160, 4, 1, 4, 1, 0, 0, 0.422f, 0.616f, 0.763f)    \
+  X(160, 160, 2, 2, 4, 1, 1, 0, 0.350f, 0.725f, 0.799f)    \
+  X(128, 256, 2, 2, 3, 1, 0, 0, 0.580f, 0.860f, 1.049f)    \
+  X(192, 128, 2, 2, 4, 1, 1, 0, 0.541f, 0.645f, 0.581f)    \
+  X(160, 192, 2, 2, 3, 1, 0, 0, 0.687f, 0.740f, 0.894f)    \
+  X(192, 192, 2, 2, 3, 1, 0, 0, 0.431f, 0.859f, 1.073f)    \
+  X(224, 192, 2, 2, 3, 1, 0, 1, 0.570f, 1.018f, 1.036f)    \
+  X(160, 256, 2, 2, 3, 1, 0, 1, 0.783f, 0.990f, 1.036f)    \
+  X(192, 256, 2, 2, 2, 1, 0, 1, 0.777f, 1.097f, 1.093f)    \
+  X(256, 192, 2, 2, 2, 1, 0, 0, 0.644f, 1.062f, 1.289f)    \
+  X(320, 160, 4, 1, 2, 1, 0, 2, 0.536f, 1.108f, 1.146f)    \
+  X(320, 192, 2, 2, 2, 1, 0, 2, 0.970f, 1.339f, 1.333f)    \
+  X(256, 256, 4, 2, 2, 1, 1, 0, 0.797f, 1.458f, 1.366f)    \
+  X(256, 256, 2, 2, 2, 1, 0, 1, 0.733f, 1.493f, 1.418f)    \
+  X(320, 256, 2, 2, 2, 1, 1, 0, 1.313f, 1.674f, 1.734f)    \
+  X(128, 160, 4, 1, 2, 2, 3, 0, 0.701f, 0.838f, 0.991f)
 constexpr bool tile_serves(int use, int epi) {
-  return use == 0 || use == 4 || ((use == 1 || use == 5) && epi != EPI_SWIGLU) || (use == 3 && epi == EPI_BIAS_F32);
+  return use == 0 || (use == 1 && epi != EPI_SWIGLU) || (use == 3 && epi == EPI_BIAS_F32);
 }
 constexpr bool tile_may_stay(int stay, int epi) { return (stay >= 1 && epi == EPI_SWIGLU) || (stay == 2 && epi == EPI_RESIDUAL); }
 
@@ -1271,20 +1264,21 @@ struct TileChoice {
 // longer of its multiplication and of the arrival of the weights that the resident workgroups ask for in that time (HBM), and
 // a little of the other.  A split k range costs the kernel that sums the partials its reading (the RoPE kernel more than
 // the norms); as a kernel of its own also a launch.  A split last round costs tail_reduce_kernel.
-constexpr float kPriceHbm = 7.87e6f;          // bytes per us of weights
-constexpr float kPriceHbmAligned = 0.692f;     // share of it left when all k ranges start at multiples of 4 KiB (one channel)
-constexpr float kPriceOther = 0.224f;         // share of the shorter of the two that shows
-constexpr float kPriceRounds = 2.05f;         // rounds past the first after which a k-tile takes its "many" time
-constexpr float kPriceEnds = 0.773f, kPriceEndsArea = 12.8f;            // start and end: per workgroup, per 256 x 256 outputs
-constexpr float kPriceEndsFloat = 2.36f;                               // more of the latter for float output
-constexpr float kPriceTail = 2.93f, kPriceTailElem = 0.63e-6f;         // split last round: launch, per float of its blocks
-constexpr float kPriceSumQkv = 0.646f, kPriceSumQkvElem = 1.08e-6f;     // split k range: per launch, per partial sum
-constexpr float kPriceSum = 1.09f, kPriceSumElem = 0.65e-6f;
+constexpr float kPriceHbm = 6.98e6f;          // bytes per us of weights
+constexpr float kPriceHbmAligned = 0.85f;     // share of it left when all k ranges start at multiples of 4 KiB (one channel)
+constexpr float kPriceOther = 0.275f;         // share of the shorter of the two that shows
+constexpr float kPriceRounds = 1.83f;         // rounds past the first after which a k-tile takes its "many" time
+constexpr float kPriceEnds = 1.91f, kPriceEndsArea = 8.13f;            // start and end: per workgroup, per 256 x 256 outputs
+constexpr float kPriceEndsFloat = 2.08f;                               // more of the latter for float output
+constexpr float kPriceEnds8 = 0.64f, kPriceEndsFloat8 = 2.44f;         // the last two on eight wavefronts, as shares
+constexpr float kPriceTail = 3.80f, kPriceTailElem = 0.77e-6f;         // split last round: launch, per float of its blocks
+constexpr float kPriceSumQkv = 1.58f, kPriceSumQkvElem = 1.47e-6f;     // split k range: per launch, per partial sum
+constexpr float kPriceSum = 1.40f, kPriceSumElem = 1.01e-6f;
 constexpr float kPriceSumLaunch = 2.5f;       // not deferred to the caller's next kernel
 
 TileChoice choose_tile(int64_t M, int64_t N, int64_t K, int epi, bool deferred, int64_t ws_bytes) {
-  struct Tile { int bm, bn, occ, use; float light, full, many; };
-#define X(BM, BN, WGM, WGN, S, OCC, USE, STAY, L, F, MA) {BM, BN, OCC, USE, L, F, MA},
+  struct Tile { int bm, bn, waves, occ, use; float light, full, many; };
+#define X(BM, BN, WGM, WGN, S, OCC, USE, STAY, L, F, MA) {BM, BN, WGM * WGN, OCC, USE, L, F, MA},
   static constexpr Tile kTiles[] = {VLC_GEMM_TILES(X)};
 #undef X
   constexpr int kCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
@@ -1294,17 +1288,18 @@ TileChoice choose_tile(int64_t M, int64_t N, int64_t K, int epi, bool deferred, 
   float best_us = 0.f;
   for (int i = 0; i < kCount; ++i) {
     const Tile& t = kTiles[i];
-    if (!tile_serves(t.use, epi) || (t.use == 3 && ws_bytes > 0) || (t.use >= 4 && ws_bytes == 0)) continue;
+    if (!tile_serves(t.use, epi) || (t.use == 3 && ws_bytes > 0)) continue;
     const int cn = epi == EPI_SWIGLU ? t.bn / 2 : t.bn;
     const int64_t tiles_m = (M + t.bm - 1) / t.bm, tiles = tiles_m * ((N + cn - 1) / cn);
     const int slots = 256 * t.occ;
     const float area = (float)(t.bm * t.bn), area_share = (float)t.occ * area / 65536.0f;
+    const bool eight = t.waves == 8;
     for (int sp = 1; sp <= (may_split ? 8 : 1); ++sp) {
       if (sp > 1 && (KT / sp < 4 || (int64_t)sp * M * N * 4 > ws_bytes)) break;
       const int per = (KT + sp - 1) / sp;
       const int64_t wgs = tiles * ((KT + per - 1) / per), full = wgs / slots, tail = wgs % slots;
-      float ends = kPriceEnds + kPriceEndsArea * area_share;
-      if (float_out || sp > 1) ends += kPriceEndsFloat * area_share;
+      float ends = kPriceEnds + kPriceEndsArea * (eight ? kPriceEnds8 : 1.0f) * area_share;
+      if (float_out || sp > 1) ends += kPriceEndsFloat * (eight ? kPriceEndsFloat8 : 1.0f) * area_share;
       float later = ((float)wgs / (float)slots - 1.0f) / kPriceRounds;
       later = later < 0.f ? 0.f : (later > 1.f ? 1.f : later);
       const float busy = t.full + (t.many - t.full) * later;

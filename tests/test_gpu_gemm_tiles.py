@@ -46,7 +46,7 @@ LAYERS += [(64, 18752, 3, 3, 983), (1344, 6848, 9, 3, 4705), (1088, 22016, 6, 3,
            (3264, 8320, 2, 1, 961)]
 # q|k|v of one k-tile in many rounds
 LAYERS += [(64, 192, 40, 8, 12001)]
-# 96 x 96, 96 x 128, 160 x 128 and 224 x 256, and the choices that came with them; sums of up to 24704 products
+# ragged rows and columns between the others' sizes; sums of up to 24704 products
 LAYERS += [
     (512, 384, 2, 1, 5470), (128, 832, 21, 3, 8714), (64, 1344, 16, 8, 15745), (9216, 64, 2, 1, 5273),
     (8192, 192, 64, 8, 454), (4992, 8512, 24, 3, 772), (64, 24704, 1, 1, 802), (6144, 1216, 4, 2, 6859),
