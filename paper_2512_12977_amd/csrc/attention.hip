@@ -576,7 +576,17 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const float* __res
 // The kernel before, one or eight wavefronts per pair that read K and V for themselves: 55, 105 and 250 us at D = 64 and 4800, 12000 and
 // 32000 pairs over 304 keys.  Four wavefronts of which each asks for the next step's pieces ahead take 186 registers instead of
 // 136: 3 % faster up to 2400 pairs, 30 % slower at 12000.
+// The line at 640 holds from 16 to 1000 keys; the one at 32768 is a mean: one wavefront per tile is faster there by 40 % at 16 keys (D = 128:
+// by 60 %) and level at 304 (15 % faster), and slower by 25 % (15 %) at 1000.
 constexpr int64_t kF32PairsPerTile = 640, kF32OneWavePairs = 32768;
+// Tiles with rows of several requests: what a step of such a run costs, in steps of a pair on its own (estimated from the MFMAs of
+// a step).  Rows that are all of other requests, one head per kv head, us at 16 / 304 / 1000 keys, runs | pairs | the kernel before
+// (which took every pair by itself):
+//   640 pairs, D = 64    40 | 7 | 8      126 | 20 | 20     399 | 71 | 62       D = 128    65 | 7 | 8      224 | 31 | 36     727 | 128 | 156
+//   4800                 45 | 12 | 10    208 | 145 | 136   553 | 466 | 433                146 | 23 | 17   561 | 332 | 323   1517 | 1072 | 999
+//   33000                92 | 58 | 48    934 | 896 | 843                                  271 | 153 | 123
+// Of four requests per tile: 640 pairs 12 | 7 | 8, 31 | 13 | 20, 87 | 46 | 53; 4800 pairs 13 | 11 | 12, and from 64 keys on the runs.
+template <int D> constexpr int kF32RunSteps = D == 64 ? 2 : 3;
 
 __device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 
@@ -603,9 +613,10 @@ __device__ __forceinline__ float sum_rows(float a) {
 }
 
 // Few (row, head) pairs: one workgroup of 16 wavefronts per pair, bound by latency.  Sixteen lanes share a key, 16 bytes of it
-// each, so that a load touches whole lines of four keys; a wavefront takes 32 keys at a time, all of whose K and V are asked for
-// together, and the workgroup 512.  D = 64, 61 rows x 4 heads over 304 / 1000 keys 5.2 / 8.9 us (one lane per key, whose load touched
-// 64 lines, and V only behind the softmax: 7.7 / 17.2).
+// each, so that a load touches whole lines of four keys; a wavefront takes 32 keys at a time, the workgroup 512.  At D = 64 all K and V
+// of a step are asked for together; at D = 128 they do not fit the 128 registers of 1024 threads, and part of V is loaded behind the
+// scores.  D = 64, 61 rows x 4 heads over 304 / 1000 keys 5.2 / 8.9 us (one lane per key, whose load touched 64 lines, and V only behind
+// the softmax: 7.7 / 17.2).
 template <int D>
 __global__ __launch_bounds__(1024) void attention_f32_pair_kernel(
     const float* __restrict__ q, const int32_t* __restrict__ row_kv_len, const int32_t* __restrict__ row_kv_start,
@@ -694,6 +705,67 @@ __global__ __launch_bounds__(1024) void attention_f32_pair_kernel(
   out[((int64_t)row * Hq + head) * D + tid] = len > 0 ? o / lt : 0.f;   // a NaN sum stays NaN
 }
 
+// One (row, head) pair by one wavefront, in the manner of the kernel above: 512 / D groups of four keys per step.  qp, kp, vp, op: at this
+// lane's first piece of the row.  (As the body of the kernel above too, it waited for K more often: 5 % slower at 600 pairs.)
+template <int D>
+__device__ __forceinline__ void attend_pair_f32(const float* __restrict__ qp, const float* __restrict__ kp, const float* __restrict__ vp,
+                                                int64_t kv_row, int len, float scale, float* __restrict__ op) {
+  constexpr int U = 512 / D, P = D / 64;
+  const int lane = threadIdx.x & 63, x = lane >> 4;
+  f32x4 qv[P], acc[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    qv[p] = *reinterpret_cast<const f32x4*>(qp + 64 * p) * scale;
+    acc[p] = zero4();
+  }
+  float m = -INFINITY, l = 0.f;
+  for (int c0 = 0; c0 < len; c0 += 4 * U) {
+    f32x4 kv[U][P], vv[U][P];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int p = 0; p < P; ++p)                   // past the end: the last visible row again, left out below
+        kv[u][p] = *reinterpret_cast<const f32x4*>(kp + (int64_t)min(c0 + 4 * u + x, len - 1) * kv_row + 64 * p);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+        vv[u][p] = *reinterpret_cast<const f32x4*>(vp + (int64_t)min(c0 + 4 * u + x, len - 1) * kv_row + 64 * p);
+    float s[U], mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      f32x4 t = kv[u][0] * qv[0];
+#pragma unroll
+      for (int p = 1; p < P; ++p) t += kv[u][p] * qv[p];
+      s[u] = sum16((t[0] + t[1]) + (t[2] + t[3]));
+      if (c0 + 4 * u + x >= len) s[u] = -INFINITY;
+      mx = fmaxf(mx, s[u]);
+    }
+    const float m_new = fmaxf(m, max_rows(mx));     // -inf only if every score so far is -inf or NaN
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = expf(m - m_use);
+    m = m_new;
+    l *= alpha;
+#pragma unroll
+    for (int p = 0; p < P; ++p) acc[p] *= alpha;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float e = expf(s[u] - m_use);
+      l += e;
+      const bool seen = c0 + 4 * u + x < len;       // a value past the end (it may be an infinity) does not count
+#pragma unroll
+      for (int p = 0; p < P; ++p) acc[p] += e * (seen ? vv[u][p] : zero4());
+    }
+  }
+  l = sum_rows(l);
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[p][e] = len > 0 ? sum_rows(acc[p][e]) / l : 0.f;   // a NaN sum stays NaN
+    if (lane < 16) *reinterpret_cast<f32x4*>(op + 64 * p) = acc[p];
+  }
+}
+
 // Many pairs: 16 "virtual rows" (row, head of the kv group), head fastest, per workgroup, both products on
 // v_mfma_f32_16x16x4_f32 (exact products, float sums), transposed as in the bf16 kernel: a lane's accumulators belong to one virtual
 // row, and S^T feeds the second product from its registers.  Fragments come straight from global memory in 16-byte pieces: element e
@@ -703,13 +775,15 @@ template <int D, int W>
 __global__ __launch_bounds__(64 * W) void attention_f32_tile_kernel(
     const float* __restrict__ q, const int32_t* __restrict__ row_kv_len, const int32_t* __restrict__ row_kv_start,
     const float* __restrict__ kc, const float* __restrict__ vc, int64_t pairs, int q_stride, int Hkv, int g, float scale, int Hq,
-    float* __restrict__ out) {
+    float* __restrict__ out, int shares) {
   constexpr int DS = D / 16, DH = D / 64;
   __shared__ float red_m[W][16], red_l[W][16];
   __shared__ f32x4 red_o[W > 1 ? W : 1][W > 1 ? D / 4 : 1][17];
   const int tid = threadIdx.x, lane = tid & 63, wave = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
   const int l16 = lane & 15, x = lane >> 4, kvh = blockIdx.y;
-  const int64_t vr0 = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * 16;   // pairs: n * g of one kv head
+  // z: a share of the tiles, or (few tiles) a workgroup among several of every tile; pairs: n * g of one kv head
+  const int share = shares > 1 ? blockIdx.z : 0;
+  const int64_t vr0 = ((int64_t)(shares > 1 ? 0 : blockIdx.z) * gridDim.x + blockIdx.x) * 16;
   if (vr0 >= pairs) return;
   const int64_t vr = vr0 + l16;
   const bool ok = vr < pairs;
@@ -717,6 +791,29 @@ __global__ __launch_bounds__(64 * W) void attention_f32_tile_kernel(
   const int head = kvh * g + (int)((ok ? vr : pairs - 1) - row * g);
   const int my_start = row_kv_start[row], my_len = ok ? row_kv_len[row] : 0;
   const int64_t kv_row = (int64_t)Hkv * D;
+
+  // Rows of several requests: a run of equal first slots uses one of `runs` parts of the MFMAs, one run after the other.  Where that takes
+  // longer than the pairs one by one, shared out over the wavefronts of all workgroups of the tile, these do it.
+  const int next_start = __shfl(my_start, l16 < 15 ? l16 + 1 : l16);
+  const int runs = 1 + __builtin_popcountll(__ballot(lane < 15 && next_start != my_start));
+  if (runs > 1) {
+    const int top = __builtin_amdgcn_readfirstlane(wave_max(my_len));
+    const int tile_steps = runs * ((top + 32 * W - 1) / (32 * W));
+    const int pair_steps = (16 + shares * W - 1) / (shares * W) * ((top + 2048 / D - 1) / (2048 / D));
+    if (tile_steps * kF32RunSteps<D> > pair_steps) {
+      for (int i = share * W + wave; i < 16; i += shares * W) {
+        const int64_t v = vr0 + i;
+        if (v >= pairs) return;
+        const int64_t r = v / g;
+        const int h = kvh * g + (int)(v - r * g);
+        const int64_t at = (int64_t)row_kv_start[r] * kv_row + (int64_t)kvh * D + 4 * l16;
+        attend_pair_f32<D>(q + r * q_stride + (int64_t)h * D + 4 * l16, kc + at, vc + at, kv_row, row_kv_len[r], scale,
+                           out + (r * Hq + h) * D + 4 * l16);
+      }
+      return;                                       // the same for the whole workgroup
+    }
+  }
+  if (share) return;
   f32x4 qf[DS];
 #pragma unroll
   for (int s = 0; s < DS; ++s)
@@ -967,10 +1064,13 @@ int launch_attention(const void* q, int64_t q_stride, const void* k_cache, const
     const int64_t pairs = n * g, tiles = (pairs + 15) / 16;   // of one kv head
     // at most 2^32 - 1 threads along a grid dimension
     const int64_t slices = (tiles + (1 << 22) - 1) >> 22;
-    const dim3 grid((unsigned)((tiles + slices - 1) / slices), (unsigned)Hkv, (unsigned)slices);
+    // workgroups per tile: those past the first, which come last in the grid, are for tiles of many requests only and bring the chip to
+    // 2048 wavefronts
+    const int f32_shares = tiles * Hkv <= 128 ? 4 : (tiles * Hkv <= 256 ? 2 : 1);
+    const dim3 grid((unsigned)((tiles + slices - 1) / slices), (unsigned)Hkv, (unsigned)(f32_shares > 1 ? f32_shares : slices));
 #define VLC_LAUNCH_F32_TILE(D_, W_)                                                                                 \
   hipLaunchKernelGGL((attention_f32_tile_kernel<D_, W_>), grid, dim3(64 * W_), 0, st, (const float*)q, row_kv_len,  \
-                     row_kv_start, (const float*)k_cache, (const float*)v_cache, pairs, (int)q_stride, Hkv, g, scale, Hq, (float*)out)
+                     row_kv_start, (const float*)k_cache, (const float*)v_cache, pairs, (int)q_stride, Hkv, g, scale, Hq, (float*)out, f32_shares)
 #define VLC_LAUNCH_F32_PAIR(D_)                                                                                     \
   hipLaunchKernelGGL((attention_f32_pair_kernel<D_>), dim3((unsigned)n, (unsigned)Hq), dim3(1024), 0, st,           \
                      (const float*)q, row_kv_len, row_kv_start, (const float*)k_cache, (const float*)v_cache, (int)q_stride, \
