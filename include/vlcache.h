@@ -345,11 +345,14 @@ int vlc_layer_forward(const vlc_layer_shape* shape, const vlc_layer_weights* wei
  *   2 q|k|v projection                    3 RoPE of q,k + scatter of fresh k,v
  *   4 attention of the recomputed rows    5 output projection + residual
  *   6 post-attention RMSNorm              7 gate|up projection + SwiGLU     8 down projection + residual
- * fp32 layers of few rows and at most 512 columns take stages 1 and 3 inside the kernel of stage 2, and stage 6 inside that of
- * stage 7: these three are empty.
  * Everything else is identical to vlc_layer_forward.
+ * fp32 layers of few rows and at most 512 columns take stages 1 and 3 inside the kernel of stage 2, and stage 6 inside that of
+ * stage 7, each by the size of its own product: vlc_layer_empty_stages returns for a call of n_rows rows a mask with bit i set
+ * if stage i launches nothing (stage 0, which goes by the reuse list, is never named; n_rows == 0: all others), -1 for an
+ * invalid shape or n_rows < 0.
  */
 #define VLC_LAYER_STAGES 9
+int vlc_layer_empty_stages(const vlc_layer_shape* shape, int64_t n_rows);
 int vlc_layer_forward_timed(const vlc_layer_shape* shape, const vlc_layer_weights* weights,
                             const vlc_layer_plan* plan, const void* h_in, void* h_out, void* k_cache,
                             void* v_cache, void* workspace, int64_t workspace_bytes, void* stream,

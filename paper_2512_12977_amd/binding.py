@@ -79,6 +79,7 @@ def lib():
                                      C.c_int64, C.c_int, C.c_int, C.c_int, C.c_void_p]
         L.vlc_sparse_q_attention.argtypes = [C.c_void_p] * 5 + [C.c_int64, C.c_int, C.c_int, C.c_int, C.c_float,
                                                                 C.c_void_p, C.c_int, C.c_void_p]
+        L.vlc_layer_empty_stages.argtypes = [C.c_void_p, C.c_int64]
         L.vlc_layer_workspace_layout.argtypes = [C.c_void_p, C.c_int64, C.c_void_p]
         L.vlc_mean_squared_error_workspace_bytes.restype = C.c_int64
         L.vlc_mean_squared_error.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]
@@ -300,6 +301,14 @@ def vlc_layer_forward(shape: LayerShape, weights: LayerWeights, plan: LayerPlan,
 
 LAYER_STAGES = ("rope_shift", "rmsnorm1", "qkv_gemm", "rope_scatter", "attention", "o_gemm", "rmsnorm2",
                 "gate_up_swiglu_gemm", "down_gemm")
+
+
+def vlc_layer_empty_stages(shape: LayerShape, n_rows: int) -> int:
+    """Mask of the LAYER_STAGES that launch nothing in a call of n_rows rows (bit i: stage i)."""
+    m = lib().vlc_layer_empty_stages(C.addressof(shape), int(n_rows))
+    if m < 0:
+        raise VlcError(2, last_error())
+    return m
 
 
 def vlc_layer_forward_timed(shape: LayerShape, weights: LayerWeights, plan: LayerPlan, h_in, h_out, k_cache,

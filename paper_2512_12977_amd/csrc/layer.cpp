@@ -76,7 +76,27 @@ int check_shape(const vlc_layer_shape* s, const char* who) {
   return VLC_OK;
 }
 
+// Small fp32 layers: input norm, q|k|v product, rotation and scatter are one kernel; the norm after the attention goes with the
+// product that reads it (router or gate|up).  Each by its own product's size.
+bool f32_qkv_fused(const vlc_layer_shape& s, int64_t n) {
+  return s.dtype == VLC_F32 && vlc::gemm_f32_norms(n, (int64_t)(s.Hq + 2 * s.Hkv) * s.D, s.H, vlc::EPI_BIAS);
+}
+bool f32_norm2_fused(const vlc_layer_shape& s, int64_t n) {
+  return s.dtype == VLC_F32 && (s.n_experts > 0 ? vlc::gemm_f32_norms(n, s.n_experts, s.H, vlc::EPI_BIAS)
+                                                : vlc::gemm_f32_norms(n, s.I, s.H, vlc::EPI_SWIGLU));
+}
+
 }  // namespace
+
+extern "C" int vlc_layer_empty_stages(const vlc_layer_shape* shape, int64_t n_rows) {
+  if (check_shape(shape, "vlc_layer_empty_stages")) return -1;
+  if (n_rows < 0) {
+    fail(VLC_ERR_SHAPE, "vlc_layer_empty_stages: n_rows=%lld", (long long)n_rows);
+    return -1;
+  }
+  if (n_rows == 0) return (1 << VLC_LAYER_STAGES) - 2;
+  return (f32_qkv_fused(*shape, n_rows) ? 1 << 1 | 1 << 3 : 0) | (f32_norm2_fused(*shape, n_rows) ? 1 << 6 : 0);
+}
 
 extern "C" int64_t vlc_layer_workspace_bytes(const vlc_layer_shape* shape, int64_t n_rows_max) {
   if (check_shape(shape, "vlc_layer_workspace_bytes")) return 0;
@@ -177,14 +197,14 @@ static int layer_forward_impl(const vlc_layer_shape* shape, const vlc_layer_weig
   // x = h_in[map] is never materialised: the norm reads through the map, and so does the residual.
   // (a chained call finds the normed rows in the workspace: the layer above wrote them with its last kernel)
   VLC_MARK(1);
-  const bool f32_qkv = s.dtype == VLC_F32 && vlc::gemm_f32_norms(n, nqkv, H, vlc::EPI_BIAS);
+  const bool f32_qkv = f32_qkv_fused(s, n);
   if (!xn_ready && !f32_qkv) {
     rc = vlc::launch_rmsnorm(h_in, p->map, w->w_ln1, xn, n, s.H, s.eps, s.dtype, st);
     if (rc) return rc;
   }
   VLC_MARK(2);
   vlc::AttentionShares shares = {};
-  if (f32_qkv) {   // small fp32 layers: norm, projection, rotation and scatter in one kernel
+  if (f32_qkv) {
     rc = vlc::launch_qkv_rope_f32(xn_ready ? xn : h_in, xn_ready ? nullptr : p->map, xn_ready ? nullptr : w->w_ln1, w->w_qkv, w->b_qkv,
                                   n, H, s.eps, p->pos, mrope ? p->pos3 : nullptr, p->slot, s.Hq, s.Hkv, s.D, freq, w->w_qnorm,
                                   w->w_knorm, xn_ready ? nullptr : xn, qkv32, qrot, k_cache, v_cache, st);
@@ -213,9 +233,7 @@ static int layer_forward_impl(const vlc_layer_shape* shape, const vlc_layer_weig
                         s.dtype, skw, ws.splitk_bytes, st, &o_splits);
   if (rc) return rc;
   VLC_MARK(6);
-  // small fp32 layers: the norm goes with the product that reads it (router or gate|up)
-  const bool f32_n2 = s.dtype == VLC_F32 && vlc::gemm_f32_norms(n, s.n_experts > 0 ? s.n_experts : I, H,
-                                                                s.n_experts > 0 ? vlc::EPI_BIAS : vlc::EPI_SWIGLU);
+  const bool f32_n2 = f32_norm2_fused(s, n);
   if (f32_n2)
     rc = VLC_OK;
   else if (o_splits > 0)   // split-K partials: sum + residual -> h1 and the norm of h1 in one kernel

@@ -167,18 +167,25 @@ def chain_link(plans: DevicePlans, l: int):
     return links[l]
 
 
+def handed_norm(shape_rec, plans: DevicePlans, l: int):
+    """chain_link, but (False, None) where layer l + 1 norms its rows inside the product that reads them (small fp32 layers, by the
+    library's own condition): a norm handed on would be a launch more."""
+    link = chain_link(plans, l)
+    if link[0] and shape_rec.dtype == B.VLC_F32 and B.vlc_layer_empty_stages(shape_rec, plans.n_rows[l + 1]) >> 1 & 1:
+        return False, None
+    return link
+
+
 def run_layers(shape_rec, weights: Sequence[DeviceWeights], plans: DevicePlans, records: Sequence, h0, hbuf,
                k_cache, v_cache, ws: Workspace, stream=None, events=None, chain: bool = True):
     """All layers in order through vlc_layer_forward_chained: every layer hands its successor the input norm
-    (chain=False: every layer norms its own input).  h0 [n_in, H] is the first layer's input, hbuf two
+    where handed_norm says so (chain=False: every layer norms its own input).  h0 [n_in, H] is the first layer's input, hbuf two
     [n_max, H] buffers the layers alternate between; events: per-layer stage-event arrays or None.
     Returns the buffer that holds the last layer's output rows."""
-    # fp32 layers of up to 512 columns norm their rows inside the product that reads them: a norm handed on would be a launch more
-    chain = chain and not (shape_rec.dtype == B.VLC_F32 and shape_rec.H <= 512)
     h_in, ready = h0, False
     for l in range(plans.L):
         h_out = hbuf[l & 1]
-        linked, next_row = chain_link(plans, l) if chain else (False, None)
+        linked, next_row = handed_norm(shape_rec, plans, l) if chain else (False, None)
         B.vlc_layer_forward_chained(shape_rec, weights[l].rec, records[l], h_in, h_out, k_cache[l], v_cache[l], ws.t,
                                     ready, weights[l + 1].t["w_ln1"] if linked else None, next_row,
                                     None if events is None else events[l], stream)

@@ -1,0 +1,66 @@
+"""Which stages of small fp32 layers have no kernel of their own, and that run_layers asks the library which norms to hand on
+(host only)."""
+import types
+
+import pytest
+
+import vlc_synth as syn
+import paper_2512_12977_amd as vlc
+from paper_2512_12977_amd import runner as R
+
+STAGE = {name: i for i, name in enumerate(vlc.LAYER_STAGES)}
+# 96 tiles of 128 rows x 128 columns (SwiGLU: 64) is where the products begin to run on large tiles
+SHAPES = {
+    "wide gate|up": dict(H=256, Hq=1, Hkv=1, D=64, I=1024),              # q|k|v 192 columns: 2 tiles wide, gate|up 16
+    "narrow gate|up": dict(H=512, Hq=6, Hkv=3, D=128, I=64),             # 12 and 1
+    "experts": dict(H=256, Hq=6, Hkv=3, D=64, I=64, n_experts=8, top_k=2),   # 6, the router 1
+    "too wide": dict(H=576, Hq=4, Hkv=2, D=64, I=128),
+}
+
+
+def shape(name, dtype="f32"):
+    return syn.Shape(name, L=2, rope_base=1e4, dtype=dtype, qkv_bias=False, **SHAPES[name])
+
+
+def expected(name, n):
+    """(input norm and rotation inside q|k|v, second norm inside its product)"""
+    s = SHAPES[name]
+    tiles = lambda columns: -(-n // 128) * columns
+    qkv = -(-(s["Hq"] + 2 * s["Hkv"]) * s["D"] // 128)
+    second = 1 if "n_experts" in s else -(-s["I"] // 64)
+    return s["H"] <= 512 and tiles(qkv) < 96, s["H"] <= 512 and tiles(second) < 96
+
+
+@pytest.mark.parametrize("name", sorted(SHAPES))
+@pytest.mark.parametrize("n", [1, 128, 640, 641, 896, 897, 1920, 1921, 6016, 6017, 12160, 12161])
+def test_empty_stages(name, n):
+    qkv, second = expected(name, n)
+    want = (1 << STAGE["rmsnorm1"] | 1 << STAGE["rope_scatter"] if qkv else 0) | (1 << STAGE["rmsnorm2"] if second else 0)
+    assert vlc.vlc_layer_empty_stages(R.make_shape(shape(name)), n) == want
+
+
+def test_empty_stages_of_other_calls():
+    rec = R.make_shape(syn.SHAPES["tiny_bf16"])
+    assert vlc.vlc_layer_empty_stages(rec, 8) == 0
+    assert vlc.vlc_layer_empty_stages(rec, 0) == (1 << len(STAGE)) - 2
+    with pytest.raises(vlc.VlcError):
+        vlc.vlc_layer_empty_stages(rec, -1)
+    rec.D = 96
+    with pytest.raises(vlc.VlcError):
+        vlc.vlc_layer_empty_stages(rec, 8)
+
+
+def plans_of(rows):
+    return types.SimpleNamespace(L=2, n_rows=[rows, rows])
+
+
+@pytest.mark.parametrize("name,rows", [("experts", 1920), ("experts", 1921), ("wide gate|up", 6016), ("wide gate|up", 6017), ("too wide", 8)])
+def test_norms_are_handed_on_where_the_next_product_does_not_take_them(monkeypatch, name, rows):
+    """fp32 layers on large tiles (expert layers among them, whose weighted sum then takes the norm along) keep their link."""
+    calls = []
+    monkeypatch.setattr(R.B, "vlc_layer_forward_chained", lambda *a: calls.append(a))
+    weights = [types.SimpleNamespace(rec=None, t={"w_ln1": "norm %d" % l}) for l in range(2)]
+    R.run_layers(R.make_shape(shape(name)), weights, plans_of(rows), [None] * 2, None, [None] * 2, [None] * 2, [None] * 2,
+                 types.SimpleNamespace(t=None))
+    linked = not expected(name, rows)[0]
+    assert [(c[8], c[9]) for c in calls] == [(False, "norm 1" if linked else None), (linked, None)]
