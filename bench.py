@@ -113,6 +113,18 @@ def stage_work(sh, n, n_reuse, pairs):
     }
 
 
+def fused_stage_note(i, shape_rec, plans):
+    """What stands in place of a rate for stage i where layers take its work inside another stage's kernel (small fp32 layers),
+    so that the time between its events is no kernel's; None if no layer does."""
+    import paper_2512_12977_amd as vlc
+    rows = [n for n in plans.n_rows if n > 0]
+    empty = sum(vlc.vlc_layer_empty_stages(shape_rec, n) >> i & 1 for n in rows)
+    if not empty:
+        return None
+    kernel = "gate_up_swiglu_gemm" if vlc.LAYER_STAGES[i] == "rmsnorm2" else "qkv_gemm"
+    return "empty in %d of %d layers: part of their kernel counted under %s" % (empty, len(rows), kernel)
+
+
 def stage_bytes_of_gemm(sh, name, n):
     """Bytes a GEMM stage must move once: weights + input rows + output rows."""
     e = 2 if sh.dtype == "bf16" else 4
@@ -489,7 +501,7 @@ def main() -> int:
     pairs = np.asarray([float(plans.host["kv_len"][l, :plans.n_rows[l]].astype(np.float64).sum()) for l in range(L)])
     stage_avg_us = stage_ms.mean(axis=(0, 1)) * 1e3
     stages = {}
-    n_chained = 0 if args.no_chain else sum(R.chain_link(plans, l)[0] for l in range(L))
+    n_chained = 0 if args.no_chain else sum(R.handed_norm(rec, plans, l)[0] for l in range(L))
     for i, name in enumerate(vlc.LAYER_STAGES):
         fl = np.mean([stage_work(sh, plans.n_rows[l], plans.n_reuse[l], pairs[l])[name][0] for l in range(L)])
         by = np.mean([stage_work(sh, plans.n_rows[l], plans.n_reuse[l], pairs[l])[name][1] for l in range(L)])
@@ -497,6 +509,8 @@ def main() -> int:
         stages[name] = {"avg_us": round(us, 2), "share": round(float(stage_avg_us[i] / stage_avg_us.sum()), 4)}
         if name == "rope_shift" and shift_all_us is not None:
             stages[name]["note"] = "empty: the reused keys of all layers are moved by one launch per step"
+        elif fused_stage_note(i, rec, plans):
+            stages[name]["note"] = fused_stage_note(i, rec, plans)
         elif name == "rmsnorm1" and n_chained:
             stages[name]["note"] = ("%d of %d layers find their input norm in the workspace: the layer above took it in "
                                     "the kernel that sums its down projection (counted under down_gemm)" % (n_chained, L))

@@ -1,9 +1,10 @@
-"""Which stages of small fp32 layers have no kernel of their own, and that run_layers asks the library which norms to hand on
-(host only)."""
+"""Which stages of small fp32 layers have no kernel of their own, and that what goes by it - the norms that run_layers hands on,
+the stage table of the benchmark - asks the library (host only)."""
 import types
 
 import pytest
 
+import bench
 import vlc_synth as syn
 import paper_2512_12977_amd as vlc
 from paper_2512_12977_amd import runner as R
@@ -64,3 +65,12 @@ def test_norms_are_handed_on_where_the_next_product_does_not_take_them(monkeypat
                  types.SimpleNamespace(t=None))
     linked = not expected(name, rows)[0]
     assert [(c[8], c[9]) for c in calls] == [(False, "norm 1" if linked else None), (linked, None)]
+
+
+def test_the_stage_table_gives_no_rate_for_an_empty_stage():
+    rec, plans = R.make_shape(shape("experts")), types.SimpleNamespace(L=3, n_rows=[1921, 1920, 0])
+    notes = {name: bench.fused_stage_note(i, rec, plans) for name, i in STAGE.items()}
+    assert {name for name, note in notes.items() if note} == {"rmsnorm1", "rope_scatter", "rmsnorm2"}
+    assert notes["rmsnorm1"] == "empty in 1 of 2 layers: part of their kernel counted under qkv_gemm"
+    assert notes["rmsnorm2"] == "empty in 2 of 2 layers: part of their kernel counted under gate_up_swiglu_gemm"
+    assert not any(bench.fused_stage_note(i, R.make_shape(syn.SHAPES["7b"]), plans) for i in range(len(STAGE)))
