@@ -1655,3 +1655,7 @@ extern "C" int vlc_probe_gemm_stays(int epilogue, int64_t M, int64_t N, int64_t 
   const bool may = vlc::tile_may_stay(kStays[c.index], epilogue);
   return vlc::gemm_stays(may, tiles + (o[4] - 1) * (tiles % slots), (int)slots, (M + (epilogue == vlc::EPI_SWIGLU ? 2 : 1) * N) * K * 2);
 }
+
+extern "C" int vlc_probe_group_tile_rows(int64_t pairs, int n_experts, int dtype) {
+  return vlc::gemm_group_tile_rows(pairs, n_experts, dtype);
+}

@@ -200,5 +200,7 @@ int vlc_probe_gemm_choice(int epilogue, int64_t M, int64_t N, int64_t K, int scr
 int vlc_probe_gemm_waves(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred);
 // 1 if the workgroups of the same choice stay for several tiles
 int vlc_probe_gemm_stays(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred);
+// rows per tile of the experts' products of that many (row, expert) pairs
+int vlc_probe_group_tile_rows(int64_t pairs, int n_experts, int dtype);
 }
 #endif
