@@ -131,9 +131,11 @@ def _dtype_code(t) -> int:
 def _stream(stream) -> Optional[int]:
     import torch
     if stream is None:
-        # the handle alone: a Stream object costs 3 us per call, as much as a launch
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
+        # the handle alone: a Stream object costs 3 us per call, as much as a launch.  Not a public function of torch: without it
+        # the object's.
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None and torch.cuda.is_initialized():
+            return raw(torch.cuda.current_device()) or None
         return torch.cuda.current_stream().cuda_stream or None
     return getattr(stream, "cuda_stream", stream) or None
 

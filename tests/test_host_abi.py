@@ -338,6 +338,21 @@ def test_attention_key_shares(Hq, Hkv):
             assert f(n, Hq, Hkv, keys) <= max(1, -(-(-(-keys // 64)) // 4)), (pairs, keys)
 
 
+@pytest.mark.parametrize("raw", [True, False])
+def test_current_stream_with_and_without_the_raw_handle(monkeypatch, raw):
+    """The current stream's handle, from torch's function for the bare handle where this torch has it, else from the Stream object."""
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 77})())
+    if raw:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 70 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert vlc.binding._stream(None) == (73 if raw else 77)
+    assert vlc.binding._stream(12) == 12
+
+
 def test_header_is_plain_c_and_the_library_links_from_c(tmp_path):
     """include/vlcache.h compiles as C99 (-pedantic, warnings as errors) and a C program linked against the library
     gets the planner's result (host entry points only: no GPU needed)."""
