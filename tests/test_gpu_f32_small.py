@@ -8,6 +8,7 @@ import vlc_synth as syn
 import paper_2512_12977_amd as vlc
 from paper_2512_12977_amd import runner as R
 from test_gpu_layer import check_against_oracle
+from test_gpu_moe import stack_both_ways
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -39,3 +40,25 @@ def test_small_layers_around_the_tiles(H, Hq, Hkv, D, bias, norm, n_text):
         outs.append([h1, h2] + kc + vc)
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+# (query heads = kv heads, MLP width, experts, rows, stages inside another's kernel): 96 tiles of 128 rows x 128 columns (SwiGLU: 64)
+# are the line from which a product runs on large tiles and its norm apart.  q|k|v is 24 or 33 tiles wide, gate|up 32 or 1, the router 1.
+@pytest.mark.parametrize("heads,I,experts,rows,inside", [
+    (16, 2048, 0, 256, ("q|k|v", "gate|up")), (16, 2048, 0, 257, ("q|k|v",)), (16, 2048, 0, 384, ("q|k|v",)), (16, 2048, 0, 385, ()),
+    (22, 64, 0, 256, ("q|k|v", "gate|up")), (22, 64, 0, 257, ("gate|up",)),
+    (16, 64, 8, 384, ("q|k|v", "router")), (16, 64, 8, 385, ("router",))])
+def test_small_layers_around_the_large_tiles(heads, I, experts, rows, inside):
+    """Layers that norm in both, in one and in none of their products: two layers against the oracle, chained calls the same bits."""
+    more = dict(n_experts=experts, top_k=2, residual_proj_scale=0.01) if experts else {}
+    sh = syn.Shape("lines", L=2, H=64, Hq=heads, Hkv=heads, D=64, I=I, rope_base=1e4, dtype="f32", qkv_bias=not experts, qk_norm=True,
+                   text_scale=1.0, **more)
+    empty = vlc.vlc_layer_empty_stages(R.make_shape(sh), rows)
+    assert empty == (0b1010 if "q|k|v" in inside else 0) | (0b1000000 if inside and inside[-1] != "q|k|v" else 0)
+    wl = syn.Workload("lines", sh, [syn.Request([syn.Segment(0, rows, False)], 0)], 1, "static", static_k=0, seed=heads + rows)
+    check_against_oracle(wl, layers=2, teacher_forced=False, chain=True)
+    assert check_against_oracle.chained == 1
+    plain, chained, _ = stack_both_ways(wl, 2)
+    for l in range(2):
+        for a, b in zip(plain[l], chained[l]):
+            assert np.array_equal(a, b)
