@@ -281,7 +281,8 @@ def test_attention_unsorted_lengths_and_one_row(dtype):
 
 @pytest.mark.parametrize("D", [64, 128])
 def test_attention_f32_around_the_key_chunks(D):
-    """Key counts around a wavefront's 64 keys and the workgroup's chunk of 512, up to several chunks."""
+    """132 (row, head) pairs, one workgroup each: key counts around a wavefront's 32 keys and the workgroup's 512, up to several
+    of these."""
     slots = [-1, 0, 15, 16, 62, 63, 64, 126, 127, 128, 447, 448, 510, 511, 512, 513, 575, 576, 1022, 1023, 1024, 1299]
     attention_case("f32", 6, 2, D, [(1300, slots)], seed=31 + D)
 
@@ -336,8 +337,8 @@ def test_attention_f32_nan_scores_stay_visible(D):
 @pytest.mark.parametrize("Hq,n", [(1, 2047), (1, 2048), (7, 292), (7, 293), (16, 128), (16, 127)])
 @pytest.mark.parametrize("D", [64, 128])
 def test_attention_f32_around_the_workgroup_widths(D, Hq, n):
-    """(row, head) pairs on both sides of 2048, where the workgroup narrows from eight wavefronts to one; key counts around
-    the 64 keys of a wavefront."""
+    """Some 2048 (row, head) pairs of one kv head, 16 of them per workgroup of four wavefronts, the last workgroup full and not; one,
+    seven and sixteen heads per row of the group; key counts around multiples of a wavefront's 32."""
     some = [-1, 0, 1, 15, 16, 62, 63, 64, 127, 128, 190, 191, 299]
     attention_case("f32", Hq, 1, D, [(300, [some[i % len(some)] for i in range(n)])], seed=71 + n)
 

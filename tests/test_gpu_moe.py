@@ -169,7 +169,8 @@ def test_moe_mid_sized_groups_on_128_row_tiles(rows):
 
 @pytest.mark.parametrize("rows", [35, 36, 1279, 1280, 3072, 3073, 7171])
 def test_moe_lines_of_the_row_tiles_and_of_the_grouping(rows):
-    """Both sides of the line at 9 rows per expert (8 experts, 2 per token), more than any line (320), and both sides of the line from which slices of the pairs are grouped by workgroups of their own: 6144
+    """Both sides of the line at 9 rows per expert (8 experts, 2 per token), 319 and 320 rows per expert (tiles of 192 rows, between the
+    lines at 250 and 360), and both sides of the line from which slices of the pairs are grouped by workgroups of their own: 6144
     pairs (one workgroup), 6146 (6 slices of 1025, the last of 1021) and 14342 (14 slices).  Requests of at most 128 rows."""
     sh = syn.SHAPES["tiny_moe_bf16"]
     sizes = [min(128, rows - s) for s in range(0, rows, 128)]
@@ -240,7 +241,7 @@ def test_moe_more_pairs_than_2_gib_of_input_rows():
 @pytest.mark.parametrize("seed", range(12))
 def test_moe_random_expert_counts_widths_and_rows(seed):
     """Seeded random mixture-of-experts layers: 3-48 experts, 1-6 per token, expert widths 64-512, 5-1500 rows, fp32 and
-    bf16 in turn - expert groups from empty to several row tiles, on all three tile sizes of the grouped GEMMs."""
+    bf16 in turn - expert groups from empty to several row tiles, on tiles of different heights."""
     rng = np.random.default_rng(11000 + seed)
     bf16 = seed % 2 == 1
     D = 128 if bf16 else 64
@@ -263,7 +264,8 @@ def test_moe_random_expert_counts_widths_and_rows(seed):
 
 @pytest.mark.parametrize("rows", [3, 76, 80, 220, 224, 764, 768])
 def test_moe_rows_per_expert_around_the_tile_sizes(rows):
-    """Mean rows per expert just below and at the lines between the 32-, 64-, 128- and 256-row tiles (top 2 of 8)."""
+    """Mean rows per expert (top 2 of 8): none to one (tiles of 32 rows), 19 and 20 (64), just below and at the line at 56 (64 and 128);
+    191 and 192 lie on tiles of 256, around what a tile of 192 holds."""
     sh = syn.Shape("moe_tiles", L=1, H=256, Hq=4, Hkv=2, D=128, I=192, rope_base=1e4, dtype="bf16", qkv_bias=False,
                    qk_norm=True, mrope_section=(24, 20, 20), n_experts=8, top_k=2, text_scale=1.0, residual_proj_scale=0.01)
     req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
