@@ -346,8 +346,8 @@ int vlc_layer_forward(const vlc_layer_shape* shape, const vlc_layer_weights* wei
  *   4 attention of the recomputed rows    5 output projection + residual
  *   6 post-attention RMSNorm              7 gate|up projection + SwiGLU     8 down projection + residual
  * Everything else is identical to vlc_layer_forward.
- * fp32 layers of few rows and at most 512 columns take stages 1 and 3 inside the kernel of stage 2, and stage 6 inside that of
- * stage 7, each by the size of its own product: vlc_layer_empty_stages returns for a call of n_rows rows a mask with bit i set
+ * fp32 layers of at most 512 columns take stages 1 and 3 inside the kernel of stage 2, and stage 6 inside that of
+ * stage 7, where that is faster for the size of the product: vlc_layer_empty_stages returns for a call of n_rows rows a mask with bit i set
  * if stage i launches nothing (stage 0, which goes by the reuse list, is never named; n_rows == 0: all others), -1 for an
  * invalid shape or n_rows < 0.
  */

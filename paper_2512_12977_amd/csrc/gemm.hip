@@ -1457,6 +1457,19 @@ bool gemm_f32_norms(int64_t M, int64_t N, int64_t K, int epilogue) {
   return K % 16 == 0 && K <= kF32NormK && !f32_large_tiles(M, N, epilogue);
 }
 
+// q|k|v with rotation and scatter takes a head per workgroup, whose k-steps are those of four wavefronts in turn: at D = 128 eight column
+// tiles each.  With few workgroups that is longer than the three launches it saves: us per layer, one kernel | three | before both:
+//   columns x heads     512 x 8                             384 x 8             256 x 8             512 x 24
+//   rows    16    32.2 | 27.6 | 30.7    29.2 | 27.1 | 30.0  25.2 | 24.5 | 27.4  36.3 | 31.9 | 35.2
+//           64    33.5 | 29.3 | 35.3    30.8 | 28.6 | 34.2  25.9 | 25.4 | 30.9  39.7 | 39.2 | 42.4
+//          192    46.4 | 45.2 | 53.4    43.3 | 44.4 | 52.5  36.1 | 37.2 | 45.7  61.1 | 59.9 | 80.8
+//          512    64.7 | 71.5 | 141.6   58.8 | 68.1 | 139   50.2 | 55.6 | 127   113 | 113 | 265
+// The two are level at some 110 workgroups with 512 columns, 60 with 384, 30 with 256; with 128 columns, and at D = 64, the one is faster or level
+// (tiny_f32's shape 5 ... 15 %).
+bool qkv_rope_f32_pays(int64_t M, int heads, int D, int64_t K) {
+  return gemm_f32_norms(M, (int64_t)heads * D, K, EPI_BIAS) && (D == 64 || (M + 15) / 16 * heads >= (K - 192) / 3);
+}
+
 int launch_gemm_f32_normed(const void* x, const void* w_norm, const void* W, void* y, void* C, int64_t ldc, int64_t M, int64_t N,
                            int64_t K, float eps, int epilogue, hipStream_t st) {
   if (M <= 0 || N <= 0) return VLC_OK;

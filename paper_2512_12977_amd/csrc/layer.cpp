@@ -79,7 +79,7 @@ int check_shape(const vlc_layer_shape* s, const char* who) {
 // Small fp32 layers: input norm, q|k|v product, rotation and scatter are one kernel; the norm after the attention goes with the
 // product that reads it (router or gate|up).  Each by its own product's size.
 bool f32_qkv_fused(const vlc_layer_shape& s, int64_t n) {
-  return s.dtype == VLC_F32 && vlc::gemm_f32_norms(n, (int64_t)(s.Hq + 2 * s.Hkv) * s.D, s.H, vlc::EPI_BIAS);
+  return s.dtype == VLC_F32 && vlc::qkv_rope_f32_pays(n, s.Hq + 2 * s.Hkv, s.D, s.H);
 }
 bool f32_norm2_fused(const vlc_layer_shape& s, int64_t n) {
   return s.dtype == VLC_F32 && (s.n_experts > 0 ? vlc::gemm_f32_norms(n, s.n_experts, s.H, vlc::EPI_BIAS)

@@ -136,6 +136,8 @@ int64_t gemm_splitk_ws_bytes(int64_t n_rows, int64_t max_n);
 // f32: C = epilogue(RMSNorm(x) * w_norm * W^T) in one kernel for the sizes that gemm_f32_norms names; the normed rows are left in y
 // [M, K] as launch_rmsnorm leaves them.  Epilogues: EPI_BIAS without a bias, EPI_SWIGLU.
 bool gemm_f32_norms(int64_t M, int64_t N, int64_t K, int epilogue);
+// whether launch_qkv_rope_f32 is the faster way
+bool qkv_rope_f32_pays(int64_t M, int heads, int D, int64_t K);
 int launch_gemm_f32_normed(const void* x, const void* w_norm, const void* W, void* y, void* C, int64_t ldc, int64_t M, int64_t N,
                            int64_t K, float eps, int epilogue, hipStream_t st);
 // f32: launch_rmsnorm (through map, into y; skipped with w_norm = nullptr, x then holds the normed rows), the q|k|v product

@@ -29,11 +29,13 @@ def expected(name, n):
     tiles = lambda columns: -(-n // 128) * columns
     qkv = -(-(s["Hq"] + 2 * s["Hkv"]) * s["D"] // 128)
     second = 1 if "n_experts" in s else -(-s["I"] // 64)
-    return s["H"] <= 512 and tiles(qkv) < 96, s["H"] <= 512 and tiles(second) < 96
+    # with heads of 128 also: enough workgroups of 16 rows and one head
+    wide = s["D"] == 64 or -(-n // 16) * (s["Hq"] + 2 * s["Hkv"]) >= (s["H"] - 192) // 3
+    return s["H"] <= 512 and tiles(qkv) < 96 and wide, s["H"] <= 512 and tiles(second) < 96
 
 
 @pytest.mark.parametrize("name", sorted(SHAPES))
-@pytest.mark.parametrize("n", [1, 128, 640, 641, 896, 897, 1920, 1921, 6016, 6017, 12160, 12161])
+@pytest.mark.parametrize("n", [1, 128, 129, 640, 641, 896, 897, 1920, 1921, 6016, 6017, 12160, 12161])
 def test_empty_stages(name, n):
     qkv, second = expected(name, n)
     want = (1 << STAGE["rmsnorm1"] | 1 << STAGE["rope_scatter"] if qkv else 0) | (1 << STAGE["rmsnorm2"] if second else 0)

@@ -62,3 +62,15 @@ def test_small_layers_around_the_large_tiles(heads, I, experts, rows, inside):
     for l in range(2):
         for a, b in zip(plain[l], chained[l]):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("H,Hq,Hkv,bias,norm,rows,inside", [
+    (64, 2, 1, True, False, 8, True), (128, 4, 4, False, True, 23, True), (256, 4, 2, True, False, 32, False), (256, 4, 2, False, True, 33, True),
+    (320, 4, 2, True, True, 80, False), (320, 4, 2, True, True, 81, True), (512, 4, 2, True, False, 208, False), (512, 4, 2, False, True, 209, True),
+    (512, 8, 8, True, True, 64, False), (512, 8, 8, True, True, 65, True)])
+def test_small_layers_of_wide_heads(H, Hq, Hkv, bias, norm, rows, inside):
+    """Heads of 128 on both sides of the number of workgroups from which q|k|v takes norm, rotation and scatter along, and widths that always do."""
+    sh = syn.Shape("wide", L=1, H=H, Hq=Hq, Hkv=Hkv, D=128, I=128, rope_base=1e4, dtype="f32", qkv_bias=bias, qk_norm=norm)
+    assert bool(vlc.vlc_layer_empty_stages(R.make_shape(sh), rows) & 0b1010) == inside
+    test_small_layers_around_the_tiles(H, Hq, Hkv, 128, bias, norm, rows - 7)      # 4 of the image's and 3 of the last text's rows
+
