@@ -1525,17 +1525,28 @@ int64_t gemm_splitk_ws_bytes(int64_t n_rows, int64_t max_n) {
 //   rows per expert    9     37     56     81    106    138    175    219    269    325    394    469    562
 //   32              (579)
 //   64               581   (703)   793    944   1060
-//   128                     706  (767)  (847)   983   1157   1217   1387   1682   1886   2185   2508   2909
-//   192                     763    830    910  (970) (1019) (1178)  1481 (1586) (1750)  2110   2372   2734
+//   128                     706  (767)  (847)  (983)  1157   1217   1387   1682   1886   2185   2508   2909
+//   192                     763    830    910   970  (1019) (1178)  1481 (1586) (1750)  2110   2372   2734
 //   256                     816    857    963   1045   1061   1195 (1340)  1697   1885 (2030) (2288) (2819)
-// (Lines at 56, 140 and 320, for 128, 192 and 256 rows: 3 % slower than the best on average, 13 % at 138; these 0.3 %, 3 % at 562.)
-int gemm_group_tile_rows(int64_t rows, int n_groups, int dtype) {
+// (Lines at 56, 140 and 320, for 128, 192 and 256 rows: 3 % slower than the best on average, 13 % at 138; these 0.4 %, 3 % at 562.)
+// That is where the tiles are several rounds (128 experts x 6 column tiles of gate|up).  Where all of gate|up is within one, a product takes as long as one tile, and the smaller is the
+// faster: us of two layers, top 2 or 8, the smaller | the larger of two heights:
+//   experts x column tiles of gate|up     8 x 6           16 x 6        32 x 6        64 x 6        128 x 6       16 x 12       32 x 12
+//   128 | 192 rows, 105 on average        184 | 183       232 | 251     288 | 321     445 | 512     796 | 825     457 | 461     696 | 775
+//                   120                   187 | 211       249 | 257     316 | 325     490 | 519     841 | 845     491 | 470     763 | 787
+//                   135                   192 | 216       252 | 260     390 | 327     546 | 521     915 | 870     596 | 475     853 | 796
+//   192 | 256 rows, 220                   236 | 260       312 | 313     468 | 418     687 | 628     1255 | 1137   739 | 578     1129 | 966
+//                   245                   239 | 265       320 | 325     462 | 450     705 | 661     1254 | 1170   748 | 684     1146 | 1034
+//                   330                   253 | 279       350 | 373     526 | 554     771 | 844     1424 | 1565   769 | 887     1159 | 1360
+// The lines miss where one height just fills whole rounds: 32 and 64 experts x 4 column tiles are 4 and 9 % slower on 256 rows at 245, 11 and 6 % on
+// 192 at 355 (two tiles of each of 32 experts are the round of 256; a third starts another).
+int gemm_group_tile_rows(int64_t rows, int n_groups, int64_t width, int dtype) {
   if (dtype != VLC_BF16) return 64;
-  const int64_t mean = rows / (n_groups > 0 ? n_groups : 1);
+  const int64_t mean = rows / (n_groups > 0 ? n_groups : 1), columns = n_groups * ((2 * width + 255) / 256);
   if (mean < 56) return mean < 9 ? 32 : 64;
-  if (mean < 100) return 128;
+  if (mean < (columns >= 192 ? 128 : 140)) return 128;
   if (mean < 185) return 192;
-  if (mean < 250) return 256;
+  if (mean < 250) return columns >= 128 ? 256 : 192;
   return mean < 360 ? 192 : 256;
 }
 
@@ -1547,7 +1558,7 @@ int launch_gemm_grouped(const void* A, int64_t lda, const int32_t* amap, const v
   if (K <= 0 || n_groups <= 0) return fail(VLC_ERR_SHAPE, "grouped gemm: K=%lld groups=%d", (long long)K, n_groups);
   if (rows > INT32_MAX || N > INT32_MAX / 2 || K > INT32_MAX)
     return fail(VLC_ERR_SHAPE, "grouped gemm: dimension exceeds 32-bit tile indexing");
-  if (tile_rows != gemm_group_tile_rows(rows, n_groups, dtype))
+  if (tile_rows != gemm_group_tile_rows(rows, n_groups, epilogue == EPI_SWIGLU ? N : K, dtype))
     return fail(VLC_ERR_SHAPE, "grouped gemm: the tile table was built for %d rows per tile", tile_rows);
   const int max_tiles = (int)(rows / tile_rows) + n_groups;
   if (epilogue != EPI_BIAS && epilogue != EPI_SWIGLU)
@@ -1669,6 +1680,6 @@ extern "C" int vlc_probe_gemm_stays(int epilogue, int64_t M, int64_t N, int64_t 
   return vlc::gemm_stays(may, tiles + (o[4] - 1) * (tiles % slots), (int)slots, (M + (epilogue == vlc::EPI_SWIGLU ? 2 : 1) * N) * K * 2);
 }
 
-extern "C" int vlc_probe_group_tile_rows(int64_t pairs, int n_experts, int dtype) {
-  return vlc::gemm_group_tile_rows(pairs, n_experts, dtype);
+extern "C" int vlc_probe_group_tile_rows(int64_t pairs, int n_experts, int64_t width, int dtype) {
+  return vlc::gemm_group_tile_rows(pairs, n_experts, width, dtype);
 }

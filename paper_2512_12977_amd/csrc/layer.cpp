@@ -259,7 +259,7 @@ static int layer_forward_impl(const vlc_layer_shape* shape, const vlc_layer_weig
     ms.pair_row = reinterpret_cast<int32_t*>(base + ws.moe_row);
     ms.pair_pos = reinterpret_cast<int32_t*>(base + ws.moe_pos);
     void* y = base + ws.moe_y;
-    const int tile_rows = vlc::gemm_group_tile_rows(pairs, E, s.dtype);
+    const int tile_rows = vlc::gemm_group_tile_rows(pairs, E, I, s.dtype);
     int r_splits = 0;    // > 0: the scores are still split-K partials, summed by the choice kernel
     if (f32_n2)
       rc = vlc::launch_gemm_f32_normed(h1, w->w_ln2, w->w_router, n2, logits, E, n, E, H, s.eps, vlc::EPI_BIAS, st);

@@ -155,7 +155,7 @@ int launch_qkv_rope_f32(const void* x, const int32_t* map, const void* w_norm, c
 struct GroupTile {
   int32_t expert, m0, m_end, pad;
 };
-int gemm_group_tile_rows(int64_t rows, int n_groups, int dtype);
+int gemm_group_tile_rows(int64_t rows, int n_groups, int64_t width, int dtype);
 int launch_gemm_grouped(const void* A, int64_t lda, const int32_t* amap, const void* W, int64_t w_stride, void* C,
                         int64_t ldc, int64_t rows, int n_groups, int64_t N, int64_t K, int epilogue,
                         const GroupTile* tiles, const int32_t* n_tiles, int tile_rows, int dtype, hipStream_t st,
@@ -202,7 +202,7 @@ int vlc_probe_gemm_choice(int epilogue, int64_t M, int64_t N, int64_t K, int scr
 int vlc_probe_gemm_waves(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred);
 // 1 if the workgroups of the same choice stay for several tiles
 int vlc_probe_gemm_stays(int epilogue, int64_t M, int64_t N, int64_t K, int scratch, int deferred);
-// rows per tile of the experts' products of that many (row, expert) pairs
-int vlc_probe_group_tile_rows(int64_t pairs, int n_experts, int dtype);
+// rows per tile of the products of experts of that MLP width for that many (row, expert) pairs
+int vlc_probe_group_tile_rows(int64_t pairs, int n_experts, int64_t width, int dtype);
 }
 #endif

@@ -159,7 +159,7 @@ def test_moe_many_pairs_grouped_by_many_workgroups():
 @pytest.mark.parametrize("rows", [250, 420, 700])
 def test_moe_mid_sized_groups_on_128_row_tiles(rows):
     """62, 105 and 175 rows per expert on average (8 experts, 2 per token): the grouped GEMMs run on tiles of 128 rows
-    and, from 100 rows per expert on, of 192, with groups of one and of two row tiles, the last ragged."""
+    and, at 175, of 192, with groups of one and of two row tiles, the last ragged."""
     sh = syn.SHAPES["tiny_moe_bf16"]
     req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
     wl = syn.Workload("moe_mid_%d" % rows, sh, [req], 1, "static", static_k=0, seed=18)
@@ -265,7 +265,7 @@ def test_moe_random_expert_counts_widths_and_rows(seed):
 @pytest.mark.parametrize("rows", [3, 76, 80, 220, 224, 764, 768])
 def test_moe_rows_per_expert_around_the_tile_sizes(rows):
     """Mean rows per expert (top 2 of 8): none to one (tiles of 32 rows), 19 and 20 (64), just below and at the line at 56 (64 and 128);
-    191 and 192 lie on tiles of 256, around what a tile of 192 holds."""
+    191 and 192 lie on tiles of 192, around what one holds."""
     sh = syn.Shape("moe_tiles", L=1, H=256, Hq=4, Hkv=2, D=128, I=192, rope_base=1e4, dtype="bf16", qkv_bias=False,
                    qk_norm=True, mrope_section=(24, 20, 20), n_experts=8, top_k=2, text_scale=1.0, residual_proj_scale=0.01)
     req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
@@ -274,8 +274,19 @@ def test_moe_rows_per_expert_around_the_tile_sizes(rows):
 
 @pytest.mark.parametrize("rows", [396, 400, 736, 740, 996, 1000, 1436, 1440])
 def test_moe_rows_per_expert_around_the_upper_lines(rows):
-    """Mean rows per expert just below and at the lines at 100, 185, 250 and 360 (tiles of 128, 192, 256, 192 and 256 rows)."""
+    """99 and 100 mean rows per expert (tiles of 128 rows), 184, 185, 249 and 250 (192; few column tiles), just below and at the line at 360 (192
+    and 256)."""
     test_moe_rows_per_expert_around_the_tile_sizes(rows)
+
+
+@pytest.mark.parametrize("rows,I", [(508, 3072), (512, 3072), (556, 2944), (560, 2944), (736, 2048), (740, 2048), (996, 2048), (1000, 2048)])
+def test_moe_rows_per_expert_around_the_lines_of_many_columns(rows, I):
+    """The lines of experts with at least 192 (128) column tiles in all: just below and at 128 and, one column tile of each fewer, 140 rows
+    per expert (128 and 192 rows), 185 (192 and 256) and 250 (256 and 192)."""
+    sh = syn.Shape("moe_columns", L=1, H=64, Hq=4, Hkv=2, D=128, I=I, rope_base=1e4, dtype="bf16", qkv_bias=False,
+                   qk_norm=True, mrope_section=(24, 20, 20), n_experts=8, top_k=2, text_scale=1.0, residual_proj_scale=0.01)
+    req = syn.Request([syn.Segment(0, rows, False)], 0, 0, syn.grid_positions([("text", rows)]))
+    check_moe_layer(syn.Workload("moe_columns%d" % rows, sh, [req], 1, "static", static_k=0, seed=800 + rows), 0)
 
 
 @pytest.mark.parametrize("H,I", [(64, 64), (128, 320), (576, 128)])
